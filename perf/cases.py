@@ -60,7 +60,7 @@ def listed():
         # one served iteration of a small job, replayed from its captured graph
         dict(name="fb_512_graph", **_case("fb", 512, 512, 1, 20160, 8, cg_iters=20, graph=True)),
         # one iteration of a large multi-band job: 21 convolutions of 4 x 4096^2 pixels
-        dict(name="fb_4x4096_large", **_case("fb", 4096, 4096, 4, 16128, 16, cg_iters=20)),
+        dict(name="fb_4x4096_large", **_case("fb", 4096, 4096, 4, 16128, 16, uv_frac=0.2, cg_iters=20)),
         # the backward step with the wavelet prior at the usual size
         dict(name="prox_2048_wavelets", **_case("prox", 2048, 2048, 1, 60480, 16, pd_iters=10)),
         # whole exact-gradient iterations (gradient, CG, backward step) of a small two-band job
