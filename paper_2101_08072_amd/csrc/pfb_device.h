@@ -34,6 +34,8 @@ __device__ __forceinline__ float  dev_sqrt(float x)  { return sqrtf(x); }
 __device__ __forceinline__ double dev_sqrt(double x) { return sqrt(x); }
 __device__ __forceinline__ float  dev_floor(float x)  { return floorf(x); }
 __device__ __forceinline__ double dev_floor(double x) { return floor(x); }
+__device__ __forceinline__ float  dev_abs(float x)  { return __builtin_fabsf(x); }
+__device__ __forceinline__ double dev_abs(double x) { return __builtin_fabs(x); }
 __device__ __forceinline__ void dev_sincospi(float x, float *s, float *c) { sincospif(x, s, c); }
 __device__ __forceinline__ void dev_sincospi(double x, double *s, double *c) { sincospi(x, s, c); }
 

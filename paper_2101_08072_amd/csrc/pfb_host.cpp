@@ -909,7 +909,7 @@ pfb_status pfb_plan_create(pfb_plan **out, const pfb_problem *prob, const pfb_op
             return bail(PFB_EHIP);
         }
     }
-    double wlo = INFINITY, whi = -INFINITY;
+    double wlo = INFINITY, whi = -INFINITY, walo = INFINITY;   // walo: min |w|
     for (int64_t r = 0; r < pr.n_row; ++r) {
         for (int k = 0; k < 3; ++k)
             if (!std::isfinite(uvw[3 * r + k])) {
@@ -918,6 +918,7 @@ pfb_status pfb_plan_create(pfb_plan **out, const pfb_problem *prob, const pfb_op
             }
         wlo = std::min(wlo, uvw[3 * r + 2]);
         whi = std::max(whi, uvw[3 * r + 2]);
+        walo = std::min(walo, std::fabs(uvw[3 * r + 2]));
     }
     std::vector<double> fmin(pr.n_band, INFINITY), fmax(pr.n_band, 0.0);
     for (int64_t c = 0; c < pr.n_chan; ++c) {
@@ -943,13 +944,25 @@ pfb_status pfb_plan_create(pfb_plan **out, const pfb_problem *prob, const pfb_op
             bd.sc = 0.0;
             bd.nw = 1;
             bd.nj0 = 1;
+            bd.fold = 0;
         } else {
             const double s0 = fmin[b] / kC0, s1 = fmax[b] / kC0;
-            const double wmin = std::min({wlo * s0, wlo * s1, whi * s0, whi * s1});
-            const double wmax = std::max({wlo * s0, wlo * s1, whi * s0, whi * s1});
+            double wmin = std::min({wlo * s0, wlo * s1, whi * s0, whi * s1});
+            double wmax = std::max({wlo * s0, wlo * s1, whi * s0, whi * s1});
             // w oversampling 2: |dw (s - sc)| <= 1/4 over the pixels
             bd.dw = 1.0 / (2.0 * (P->s_max - P->s_min));
             bd.sc = 0.5 * (P->s_min + P->s_max);
+            // the image is real, so V(-u, -v, -w) = conj V(u, v, w): listing the
+            // visibilities with w < 0 at -(u, v, w), conjugated, leaves planes for the
+            // range of |w| only.  Done where that saves planes (their count sets the
+            // column and row passes' work); with w of one sign, or a range within one
+            // plane step, the listing stays as given.
+            const double amin = walo * s0, amax = std::max(std::fabs(wlo), std::fabs(whi)) * s1;
+            bd.fold = std::floor((amax - amin) / bd.dw) < std::floor((wmax - wmin) / bd.dw);
+            if (bd.fold) {
+                wmin = amin;
+                wmax = amax;
+            }
             const double D = (wmax - wmin) / bd.dw;
             bd.nj0 = (int)std::floor(D) + 2;
             bd.nw = bd.nj0 + opt.support - 1;
@@ -962,7 +975,7 @@ pfb_status pfb_plan_create(pfb_plan **out, const pfb_problem *prob, const pfb_op
     if (M.mfma) mfma_window(opt.support, &M.sort_rb, &M.sort_cb);
     GridderHost &Q = P->psf;
     Q.g = base_geom(*P, 2 * pr.nx, 2 * pr.ny, true);
-    Q.bands.assign(pr.n_band, BandDev{0.0, 1.0, 0.0, 1, 1});
+    Q.bands.assign(pr.n_band, BandDev{0.0, 1.0, 0.0, 1, 1, 0});
     Q.g.nj0max = 1;
     Q.g.nwmax = 1;
     Q.corr2d = false;

@@ -13,7 +13,9 @@ constexpr uint32_t kHomeBit = 0x80000000u;   // set in Rec::idx for the entry's 
 // One bucketed visibility: coordinates local to the tile it is listed under.
 //   fu, fv : grid coordinate minus the tile origin (cells); may lie outside [0, T)
 //            for copies listed under a neighbouring tile the kernel straddles
-//   fw     : absolute w-plane coordinate (t_w = (w - w0) / dw); 0 when flat
+//   fw     : absolute w-plane coordinate (t_w = (w - w0) / dw, > 0 since plane 0 lies
+//            (W - 1) / 2 planes below the lowest w); 0 when flat.  The sign bit marks an
+//            entry listed at -(u, v, w) (BandDev::fold), whose value is conjugated
 //   idx    : r * n_chan + c, plus kHomeBit on the copy in the tile holding (fu, fv)
 template <typename R> struct Rec {
     R fu, fv, fw;
@@ -27,6 +29,7 @@ struct BandDev {
     double sc;     // centre of n - 1 over the image (phase split point)
     int    nw;     // w-planes of this band
     int    nj0;    // base planes (nw - W + 1), 1 when flat
+    int    fold;   // 1: visibilities with w < 0 are listed at -(u, v, w), conjugated
 };
 
 // Spread work item: tile `tile` of band `band`, storing planes [p0, p1).

@@ -124,6 +124,13 @@ template <int NT = kThreads> __device__ double block_sum(double v, double *red) 
     return t;
 }
 
+// The value of an entry as its listing takes it: conjugated where the entry is
+// listed at -(u, v, w) (sign bit of fw).  Hessian values never need it: they are
+// degridded and gridded at the same listing.
+template <typename R> __device__ __forceinline__ cplx<R> entry_conj(const Rec<R> &rec, cplx<R> v) {
+    return cplx<R>{v.re, rec.fw < R(0) ? -v.im : v.im};
+}
+
 // ---------------------------------------------------------------------------
 // bucketing
 // ---------------------------------------------------------------------------
@@ -132,15 +139,24 @@ template <typename R>
 struct Keys {
     R fu, fv, fw;
     int tu, tv, j0, ou_lo, ou_hi, ov_lo, ov_hi;
+    bool conj;
 };
 
 // Grid coordinates of one visibility and the tiles its W x W footprint touches.
 // The local coordinates are rounded to R first so that the kernels, which
 // recompute the footprint from them, agree exactly with the bucket keys.
+// In a folded band an entry with w < 0 takes the keys of -(u, v, w): the image is
+// real, so V(-u, -v, -w) = conj V(u, v, w), and the planes only span |w|.
 template <typename R, bool FLAT>
 __device__ __forceinline__ bool vis_keys(const GeomDev &g, const BandDev &bd, double um, double vm,
                                          double wm, double f, Keys<R> &k) {
     const double s = f / kC0;
+    k.conj = !FLAT && bd.fold && wm < 0.0;
+    if (k.conj) {
+        um = -um;
+        vm = -vm;
+        wm = -wm;
+    }
     double tu = um * s * g.cellx * (double)g.gx;
     double tv = vm * s * g.celly * (double)g.gy;
     tu -= (double)g.gx * floor(tu / (double)g.gx);
@@ -239,7 +255,7 @@ __global__ __launch_bounds__(kThreads) void bucket_kernel(BucketArgs a) {
                     Rec<R> rec;
                     rec.fu = k.fu - (R)(ou * a.g.T);
                     rec.fv = k.fv - (R)(ov * a.g.T);
-                    rec.fw = k.fw;
+                    rec.fw = k.conj ? -k.fw : k.fw;
                     rec.idx = (uint32_t)e | ((ou == 0 && ov == 0) ? kHomeBit : 0u);
                     reinterpret_cast<Rec<R> *>(a.recs)[pos] = rec;
                     reinterpret_cast<R *>(a.omega)[pos] = w;
@@ -517,8 +533,8 @@ __global__ __launch_bounds__(kTileThreads) void spread_kernel(SpreadLaunch a) {
                 cplx<R> z;
                 if (VMODE == 0) {
                     const R om = omega[e];
-                    const cplx<R> v = vis[vid];
-                    z = v * cis_cycles<R>((w0 + rec.fw * dw) * sc) * om;
+                    const cplx<R> v = entry_conj(rec, vis[vid]);
+                    z = v * cis_cycles<R>((w0 + dev_abs(rec.fw) * dw) * sc) * om;
                 } else if (VMODE == 1) {
                     z = cplx<R>{omega[e], R(0)};
                 } else {
@@ -530,7 +546,7 @@ __global__ __launch_bounds__(kTileThreads) void spread_kernel(SpreadLaunch a) {
                 if (lane < W) {
                     pu = es_kernel<R>(R(i0 + lane) - rec.fu, beta, inv_hw);
                     pv = es_kernel<R>(R(j0 + lane) - rec.fv, beta, inv_hw);
-                    if (!FLAT) pw = es_kernel<R>(R(q + lane) - rec.fw, beta, inv_hw);
+                    if (!FLAT) pw = es_kernel<R>(R(q + lane) - dev_abs(rec.fw), beta, inv_hw);
                 }
                 R wu[W];
 #pragma unroll
@@ -730,7 +746,7 @@ __global__ __launch_bounds__(kTileThreads) void spread_run_kernel(SpreadLaunch a
                 cplx<R> v{R(0), R(0)};
                 if (eb < e_end) {
                     if (VMODE == 0) {
-                        v = vis[r.idx & ~kHomeBit] * (omega[eb] * fscale);
+                        v = entry_conj(r, vis[r.idx & ~kHomeBit]) * (omega[eb] * fscale);
                     } else if (VMODE == 1) {
                         v = cplx<R>{omega[eb] * fscale, R(0)};
                     } else {
@@ -757,10 +773,10 @@ __global__ __launch_bounds__(kTileThreads) void spread_run_kernel(SpreadLaunch a
                     if (lj < W) {
                         pu = es_kernel_fast(R(i0 + lj) - rec_c.fu, beta2, inv_hw);
                         pv = es_kernel_fast(R(j0 + lj) - rec_c.fv, beta2, inv_hw);
-                        if (!FLAT) pw = es_kernel_fast(R(q + lj) - rec_c.fw, beta2, inv_hw);
+                        if (!FLAT) pw = es_kernel_fast(R(q + lj) - dev_abs(rec_c.fw), beta2, inv_hw);
                     }
                     cplx<R> z = val_c;
-                    if (VMODE == 0) z = z * cis_cycles<R>((w0 + rec_c.fw * dw) * sc);
+                    if (VMODE == 0) z = z * cis_cycles<R>((w0 + dev_abs(rec_c.fw) * dw) * sc);
                     zr = z.re;
                     zi = z.im;
                 }
@@ -963,8 +979,8 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
         }
         return raw;
     };
-    auto make_val = [&](const RawVal &raw) {
-        if (VMODE == 0) return raw.z * raw.ph * (raw.om * fscale);
+    auto make_val = [&](const RawVal &raw, const Rec<R_> &rr) {
+        if (VMODE == 0) return entry_conj(rr, raw.z) * raw.ph * (raw.om * fscale);
         if (VMODE == 1) return cplx<R_>{raw.om * fscale, R_(0)};
         return raw.z * fscale;
     };
@@ -1050,7 +1066,7 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
                 const RawVal val_n = load_val(eb + lane, endb, rec_n, hp_n);
                 const Rec<R_> rec_nn = load_rec(ec + lane, endc);
                 const uint32_t hp_nn = load_hp(ec + lane, endc);
-                const cplx<R_> zc = make_val(val_c);
+                const cplx<R_> zc = make_val(val_c, rec_c);
                 const int nbatch = (int)min((int64_t)64, enda - ea);
                 // owner lane: window of its entry and the offsets of the window origin
                 int okey;
@@ -1062,7 +1078,7 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
                     okey = ((wa + 64) << 8) | (wb + 64);
                     odu = R_(wa * RB - (W - 1)) - rec_c.fu;     // row 0 of the window minus fu
                     odv = R_(wb * CB - (W - 1)) - rec_c.fv;
-                    odq = R_(q) - rec_c.fw;
+                    odq = R_(q) - dev_abs(rec_c.fw);
                 }
                 // operands of group 0 of the batch; each group fetches those of the next
                 // one before its matrix products, so the crossbar latency overlaps them
@@ -1423,7 +1439,7 @@ __global__ __launch_bounds__(kTileThreads) void interp_kernel(InterpLaunch a) {
             if (lane < W) {
                 pu = es_kernel<R>(R(i0 + lane) - rec.fu, beta, inv_hw);
                 pv = es_kernel<R>(R(j0 + lane) - rec.fv, beta, inv_hw);
-                if (!FLAT) pw = es_kernel<R>(R(q + lane) - rec.fw, beta, inv_hw);
+                if (!FLAT) pw = es_kernel<R>(R(q + lane) - dev_abs(rec.fw), beta, inv_hw);
             }
             R wu[W];
             R ww[WW];
@@ -1462,7 +1478,7 @@ __global__ __launch_bounds__(kTileThreads) void interp_kernel(InterpLaunch a) {
             if (lane == 0) {
                 const uint32_t vid = rec.idx & ~kHomeBit;
                 if (OMODE != 1) {
-                    cplx<R> out = FLAT ? acc : acc * conj(cis_cycles<R>((w0 + rec.fw * dw) * sc));
+                    cplx<R> out = FLAT ? acc : entry_conj(rec, acc * conj(cis_cycles<R>((w0 + dev_abs(rec.fw) * dw) * sc)));
                     cplx<R> *ov = reinterpret_cast<cplx<R> *>(a.out) + vid;
                     *ov = OMODE == 2 ? *ov + out : out;
                 } else {
@@ -1631,8 +1647,8 @@ __global__ __launch_bounds__(kTileThreads) void interp4_kernel(InterpLaunch a) {
             if constexpr (FLAT) {
                 ww[0] = R(1);
             } else {
-                const R pwa = es_kernel_fast(R(q + lq) - rec.fw, beta2, inv_hw);
-                const R pwb = es_kernel_fast(R(q + lq + 4) - rec.fw, beta2, inv_hw);
+                const R pwa = es_kernel_fast(R(q + lq) - dev_abs(rec.fw), beta2, inv_hw);
+                const R pwb = es_kernel_fast(R(q + lq + 4) - dev_abs(rec.fw), beta2, inv_hw);
                 quad_bcast_w<WW>(pwa, pwb, ww);
             }
             const int col = j0 + lq + H;
@@ -1662,7 +1678,8 @@ __global__ __launch_bounds__(kTileThreads) void interp4_kernel(InterpLaunch a) {
                 const uint32_t vid = rec.idx & ~kHomeBit;
                 if (OMODE != 1) {
                     cplx<R> out = acc;
-                    if (!FLAT) out = out * conj(a.use_phase ? ph : cis_cycles<R>((w0 + rec.fw * dw) * sc));
+                    if (!FLAT)
+                        out = entry_conj(rec, out * conj(a.use_phase ? ph : cis_cycles<R>((w0 + dev_abs(rec.fw) * dw) * sc)));
                     cplx<R> *ov = reinterpret_cast<cplx<R> *>(a.out) + vid;
                     *ov = OMODE == 2 ? *ov + out : out;
                 } else {

@@ -66,7 +66,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_gather_kernel(const Rec<R> 
             // centre; u l0 = t_u offx / g_x modulo whole turns, t_u = tile row * T + fu
             const int64_t bucket = (int64_t)(keys[i] >> sh_bucket);
             const BandDev bd = bands[bucket / bucket_per_band];
-            double t = (bd.w0 + (double)r.fw * bd.dw) * bd.sc;
+            double t = (bd.w0 + dev_abs((double)r.fw) * bd.dw) * bd.sc;
             if (geo.offx | geo.offy) {
                 const int tile = (int)((bucket % bucket_per_band) / geo.nj0max);
                 const double tu = (double)(tile / geo.nty) * geo.T + (double)r.fu;
