@@ -468,17 +468,21 @@ def main():
                     kernels[k]["frac_of_unpacked_fp32"] = round(ach / FP32_VECTOR_UNPACKED_TFLOPS, 4)
     log("kernels:", json.dumps(kernels))
 
-    # backward step: per-kernel ms per primal-dual iteration; the wavelet levels against
-    # HBM with algorithmic bytes = one read and one write of every level block, six
-    # wavelet bases, analysis and synthesis each
+    # backward step: per-kernel ms per primal-dual iteration against HBM.  Analysis with the
+    # dual update: u read once, the dual (seven bases) read and written, the low-pass blocks
+    # between levels written and read.  Finest synthesis level with the primal update: the
+    # dual's finest quadrants (and the low-pass block) read, x, z and the convolution read,
+    # x, u, d written.
     rsz = 4
-    blk = sum(prob.n_band * (prob.nx >> l) * (prob.ny >> l) for l in range(prox_levels))
-    level_bytes = 6 * 2 * blk * rsz
+    px = prob.n_band * prob.nx * prob.ny
+    low = sum(6 * prob.n_band * (prob.nx >> l) * (prob.ny >> l) for l in range(1, prox_levels))
+    prox_bytes = {"wavelet_analysis_kernel": (px + 14 * px + 2 * low) * rsz,
+                  "wavelet_finest_kernel": (7 * px + 6 * px) * rsz}
     prox_k = {k: {"launches_per_iteration": n / prox_iters, "ms_per_iteration": round(t / prox_iters, 4)}
               for k, (n, t) in sorted(prox_prof.items(), key=lambda kv: -kv[1][1])}
-    for k in ("wavelet_ana2_kernel", "wavelet_syn2_kernel"):
+    for k, nbytes in prox_bytes.items():
         if k in prox_k:
-            ach = level_bytes / (prox_k[k]["ms_per_iteration"] * 1e-3) / 1e9
+            ach = nbytes / (prox_k[k]["ms_per_iteration"] * 1e-3) / 1e9
             prox_k[k].update(bound="hbm", achieved_GBps=round(ach, 1), frac=round(ach / PEAK["hbm_GBps"], 4))
     prox_out = {"ms_per_iteration": round(breakdown["prox_iteration"], 4), "nbasis": 7, "levels": prox_levels,
                 "kernels": prox_k}

@@ -1592,47 +1592,15 @@ pfb_status wavelet_args_ok(const pfb_plan *P, int nbasis, int levels) {
     return PFB_OK;
 }
 
-// coef_k (k >= 1) = W_k^dagger src for every band, unscaled; the low-pass block
-// of every level but the last goes to buffer a or b (alternately)
-pfb_status analysis_bases(const pfb_plan *P, const void *src, char *coef, void *a, void *b, int nbasis, int levels,
-                          hipStream_t s) {
-    const bool d = P->dbl;
-    const int nx = P->prob.nx, ny = P->prob.ny, nb = P->prob.n_band;
-    const int64_t Pn = (int64_t)nx * ny;
-    const size_t img = (size_t)nb * Pn * P->rsz;
-    void *pp[2] = {a, b};
-    for (int k = 1; k < nbasis; ++k) {
-        const WaveletFilter f = db_filter(k);
-        void *ck = coef + (size_t)(k - 1) * img;
-        for (int l = 0; l < levels; ++l) {
-            const void *in = l == 0 ? src : pp[(l - 1) & 1];
-            void *ll = l == levels - 1 ? ck : pp[l & 1];
-            LAUNCH_OK(launch_wavelet_analysis_level(d, in, ck, ll, f, nx >> l, ny >> l, ny, Pn, nb, s));
-        }
-    }
-    return PFB_OK;
-}
-
-// out = v_0 + sum_{k >= 1} W_k v_k (unscaled); the low-pass block of every level
-// but the finest goes to buffer a or b (alternately)
-pfb_status synthesis_bases(const pfb_plan *P, const char *v, void *out, void *a, void *b, int nbasis, int levels,
-                           hipStream_t s) {
-    const bool d = P->dbl;
-    const int nx = P->prob.nx, ny = P->prob.ny, nb = P->prob.n_band;
-    const int64_t Pn = (int64_t)nx * ny;
-    const size_t img = (size_t)nb * Pn * P->rsz;
-    void *pp[2] = {a, b};
-    LAUNCH_OK(launch_wave_copy(d, v, out, (int64_t)nb * Pn, 1.0, s));
-    for (int k = 1; k < nbasis; ++k) {
-        const WaveletFilter f = db_filter(k);
-        const void *vk = v + (size_t)k * img;
-        for (int l = levels - 1; l >= 0; --l) {
-            const void *ll = l == levels - 1 ? vk : pp[(l + 1) & 1];
-            void *dst = l == 0 ? out : pp[l & 1];
-            LAUNCH_OK(launch_wavelet_synthesis_level(d, l == 0, ll, vk, dst, f, nx >> l, ny >> l, ny, Pn, nb, s));
-        }
-    }
-    return PFB_OK;
+WaveDict wave_dict(const pfb_plan *P, int nbasis, int levels) {
+    WaveDict D{};
+    D.nx = P->prob.nx;
+    D.ny = P->prob.ny;
+    D.n_band = P->prob.n_band;
+    D.nbasis = nbasis;
+    D.levels = levels;
+    for (int k = 1; k < nbasis; ++k) D.f[k] = db_filter(k);
+    return D;
 }
 
 }  // namespace
@@ -1656,13 +1624,8 @@ pfb_status pfb_wavelet_analysis(pfb_plan *P, const void *x, void *coeffs, void *
     const ProxLayout L = prox_layout(P, nbasis);
     if (ws_bytes < L.total) return fail(PFB_EINVAL, "workspace too small: %zu < %zu bytes", ws_bytes, L.total);
     const bool d = P->dbl;
-    const double scale = 1.0 / std::sqrt((double)nbasis);
-    char *c = reinterpret_cast<char *>(coeffs);
-    char *w = reinterpret_cast<char *>(ws);
-    const size_t img = (size_t)L.NP * P->rsz;
-    LAUNCH_OK(launch_wave_copy(d, x, c, L.NP, scale, s));
-    if ((st = analysis_bases(P, x, c + img, w + L.a, w + L.b, nbasis, levels, s))) return st;
-    if (nbasis > 1) LAUNCH_OK(launch_wave_copy(d, c + img, c + img, (int64_t)(nbasis - 1) * L.NP, scale, s));
+    LAUNCH_OK(launch_wavelet_analysis(d, wave_dict(P, nbasis, levels), x, coeffs, reinterpret_cast<char *>(ws) + L.a,
+                                      false, 1.0 / std::sqrt((double)nbasis), 0.0, s));
     return PFB_OK;
 }
 
@@ -1675,10 +1638,8 @@ pfb_status pfb_wavelet_synthesis(pfb_plan *P, const void *coeffs, void *x, void 
     if ((st = wavelet_args_ok(P, nbasis, levels))) return st;
     const ProxLayout L = prox_layout(P, nbasis);
     if (ws_bytes < L.total) return fail(PFB_EINVAL, "workspace too small: %zu < %zu bytes", ws_bytes, L.total);
-    char *w = reinterpret_cast<char *>(ws);
-    if ((st = synthesis_bases(P, reinterpret_cast<const char *>(coeffs), x, w + L.a, w + L.b, nbasis, levels, s)))
-        return st;
-    LAUNCH_OK(launch_wave_copy(P->dbl, x, x, L.NP, 1.0 / std::sqrt((double)nbasis), s));
+    LAUNCH_OK(launch_wavelet_synthesis(P->dbl, wave_dict(P, nbasis, levels), coeffs, x,
+                                       reinterpret_cast<char *>(ws) + L.a, nullptr, 1.0 / std::sqrt((double)nbasis), s));
     return PFB_OK;
 }
 
@@ -1699,24 +1660,22 @@ pfb_status pfb_prox_solve(pfb_plan *P, const void *z, void *x, void *ws, size_t 
     if (ws_bytes < L.total) return fail(PFB_EINVAL, "workspace too small: %zu < %zu bytes", ws_bytes, L.total);
     const bool d = P->dbl;
     char *w = reinterpret_cast<char *>(ws);
-    void *v = w + L.v, *coef = w + L.coef, *dd = w + L.d, *c = w + L.c, *u = w + L.u, *sv = w + L.sv;
+    void *v = w + L.v, *dd = w + L.d, *c = w + L.c, *u = w + L.u, *tmp = w + L.a;
     // Condat's iteration: F(x) = (x - z)^T U (x - z) / (2 gamma) with U = I^psf * + sigma Id,
     // G = positivity, H = lambda ||.||_{2,1} of L x = Psi^dagger x (||Psi^dagger|| = 1)
     const double beta = (unorm + sigma) / gamma;
     const double sigma_d = beta, tau = 0.99 / (0.5 * beta + sigma_d);
     const double psi_scale = 1.0 / std::sqrt((double)nbasis);
     const ConvArgs ca = conv_args(P);
-    if (!warm) LAUNCH_OK(launch_pd_dual(d, true, v, nullptr, nullptr, nbasis, P->prob.n_band,
-                                         (int64_t)P->prob.nx * P->prob.ny, 0.0, 0.0, 0.0, s));
-    LAUNCH_OK(launch_pd_primal(d, true, z, x, dd, nullptr, nullptr, nullptr, L.NP, 0.0, 1.0, 0.0, 0.0, warm, s));
+    const WaveDict D = wave_dict(P, nbasis, levels);
+    if (!warm) LAUNCH_OK(launch_pd_zero(d, v, (int64_t)nbasis * L.NP, s));
+    LAUNCH_OK(launch_pd_init(d, z, x, dd, L.NP, warm, s));
+    const PrimalArgs pa{z, c, x, dd, u, tau, gamma, sigma};
     for (int it = 0; it < iters; ++it) {
         LAUNCH_OK(launch_psf_conv(d, ca, dd, nullptr, c, nullptr, 0.0, CONV_IN_X, CONV_OUT_Y, s));
-        if ((st = synthesis_bases(P, reinterpret_cast<const char *>(v), sv, w + L.a, w + L.b, nbasis, levels, s)))
-            return st;
-        LAUNCH_OK(launch_pd_primal(d, false, z, x, dd, c, sv, u, L.NP, tau, gamma, sigma, psi_scale, warm, s));
-        if ((st = analysis_bases(P, u, reinterpret_cast<char *>(coef), w + L.a, w + L.b, nbasis, levels, s))) return st;
-        LAUNCH_OK(launch_pd_dual(d, false, v, u, coef, nbasis, P->prob.n_band, (int64_t)P->prob.nx * P->prob.ny,
-                                 sigma_d, psi_scale, lambda, s));
+        // x~, u = 2 x~ - x and the next d from Psi v; then v = P_lambda(v + sigma_d Psi^dagger u)
+        LAUNCH_OK(launch_wavelet_synthesis(d, D, v, nullptr, tmp, &pa, psi_scale, s));
+        LAUNCH_OK(launch_wavelet_analysis(d, D, u, v, tmp, true, sigma_d * psi_scale, lambda, s));
     }
     return PFB_OK;
 }

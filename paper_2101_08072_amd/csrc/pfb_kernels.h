@@ -208,22 +208,31 @@ struct WaveletFilter {
     double h[kMaxWaveletTaps];
     int len;
 };
-// One 2-D wavelet level (rows then columns) of the top-left nr x nc block in LDS
-// tiles: analysis writes LL to dst_ll and the three detail quadrants to
-// dst_detail; synthesis reads LL from src_ll and the details from src_detail
-// (acc: add into dst).  Source and destinations must not overlap.
-hipError_t launch_wavelet_analysis_level(bool dbl, const void *src, void *dst_detail, void *dst_ll,
-                                         const WaveletFilter &f, int nr, int nc, int ld, int64_t img, int n_img,
-                                         hipStream_t s);
-hipError_t launch_wavelet_synthesis_level(bool dbl, bool acc, const void *src_ll, const void *src_detail, void *dst,
-                                          const WaveletFilter &f, int nr, int nc, int ld, int64_t img, int n_img,
-                                          hipStream_t s);
-hipError_t launch_wave_copy(bool dbl, const void *src, void *dst, int64_t n, double scale, hipStream_t s);
+// The dictionary: Dirac (basis 0) and the filters f[1 .. nbasis - 1] (f[k].len = 2k),
+// `levels` levels of n_band images of nx x ny.
+struct WaveDict {
+    int nx, ny, n_band, nbasis, levels;
+    WaveletFilter f[kMaxWaveletTaps / 2 + 1];
+};
+// Analysis of src [n_band][nx][ny] into coef [nbasis][n_band][nx][ny]:
+// coef = scale a, or with `dual` coef = project(coef + scale a), where the bands of
+// every (basis, coefficient) are scaled onto the l2 ball of radius lam.  Synthesis
+// (the adjoint) of coef: dst = scale sum, or with `primal` the update below of
+// x, u and d from the sum (dst unused).  tmp: at least two images' worth of
+// [n_band][nx][ny] (low-pass blocks); it, src / dst and coef must not overlap.
+struct PrimalArgs {
+    const void *z, *conv;   // conv = I^psf * (x - z)
+    void *x, *d, *u;        // x~ = max(x - tau ((conv + sigma_u (x - z)) / gamma + scale sum), 0);
+                            // u = 2 x~ - x, x = x~, d = x~ - z
+    double tau, gamma, sigma_u;
+};
+hipError_t launch_wavelet_analysis(bool dbl, const WaveDict &D, const void *src, void *coef, void *tmp, bool dual,
+                                   double scale, double lam, hipStream_t s);
+hipError_t launch_wavelet_synthesis(bool dbl, const WaveDict &D, const void *coef, void *dst, void *tmp,
+                                    const PrimalArgs *primal, double scale, hipStream_t s);
 hipError_t launch_wave_axpy(bool dbl, const void *x, const void *y, void *z, int64_t n, double a, hipStream_t s);   // z = x + a y
-hipError_t launch_pd_primal(bool dbl, bool init, const void *z, void *x, void *d, const void *c, const void *sv,
-                            void *u, int64_t n, double tau, double gamma, double sigma_u, double psi_scale, int warm,
-                            hipStream_t s);
-hipError_t launch_pd_dual(bool dbl, bool zero, void *v, const void *u, const void *coef, int nbasis, int n_band,
-                          int64_t P, double sigma_d, double psi_scale, double lam, hipStream_t s);
+// start of the primal-dual iteration: x = max(z, 0) unless warm, d = x - z; and v = 0
+hipError_t launch_pd_init(bool dbl, const void *z, void *x, void *d, int64_t n, int warm, hipStream_t s);
+hipError_t launch_pd_zero(bool dbl, void *v, int64_t n, hipStream_t s);
 
 }  // namespace pfb

@@ -3006,173 +3006,487 @@ hipError_t launch_copy_scalar(int n_band, const double *scal, int slot, double *
 // Taps of one wavelet filter pair in the kernel's precision: low-pass h and
 // wavelet g[j] = (-1)^j h[2N-1-j].
 template <typename R> struct WaveletTaps {
-    R h[kMaxWaveletTaps], g[kMaxWaveletTaps];
+    R h[2 * kMaxWaveletTaps];   // h, then g
+    __device__ __host__ __forceinline__ R &g(int j) { return h[kMaxWaveletTaps + j]; }
+    __device__ __host__ __forceinline__ R g(int j) const { return h[kMaxWaveletTaps + j]; }
 };
+// basis N's taps from LDS into registers (as kernel arguments the taps of every basis
+// were loaded into scalar registers at the kernel's start and spilled: 520 of 4900
+// instructions)
+template <typename R, int N> __device__ __forceinline__ void wave_taps(const R *lds, WaveletTaps<R> &f) {
+#pragma unroll
+    for (int j = 0; j < 2 * N; ++j) {
+        f.h[j] = lds[j];
+        f.g(j) = lds[kMaxWaveletTaps + j];
+    }
+}
 static int64_t wave_blocks(int64_t total) {
     int64_t nb = (total + kThreads - 1) / kThreads;
     return nb < 1 ? 1 : (nb > 65536 ? 65536 : nb);
 }
 
-// One whole 2-D level per launch, in LDS tiles (rows pass, then columns pass,
-// the order of the level's definition), so a level reads its block once (plus a
-// halo of 2N - 2) and writes it once.  Analysis: a workgroup makes the four
-// coefficients (LL, LH, HL, HH) of kWaveTileR x kWaveTileC coefficient positions; LL goes
-// to dst_ll (the next level's input, or the coefficient array after the last
-// level), the details to dst_d at the level's quadrant positions.  Synthesis: a
-// workgroup makes 2 kWaveTileR x 2 kWaveTileC samples from the LL block (src_ll) and the
-// three detail quadrants (src_d), columns pass then rows pass (the adjoint order);
-// ACC adds into dst.  Rows `ld` apart, images `img` apart, periodic boundaries.
+// The dictionary's wavelet levels, one launch per level for all its bases.
+//
+// One 2-D level in LDS tiles (rows pass, then columns pass, the order of the
+// level's definition), so a level reads its block once (plus a halo of 2N - 2) and
+// writes it once.  Analysis: a workgroup makes the four coefficients (LL, LH, HL,
+// HH) of kWaveTileR x kWaveTileC coefficient positions of one basis; LL goes to
+// the next level's input (or the coefficients after the last level), the details
+// to the coefficients at the level's quadrant positions.  Synthesis: a workgroup
+// makes 2 kWaveTileR x 2 kWaveTileC samples, columns pass then rows pass (the
+// adjoint order).  Periodic boundaries.
+//
+// Launches and passes over memory bound these kernels: one launch per basis and
+// level with separate sums, dual and primal passes took 36 + 7 launches and 0.63 ms
+// per primal-dual iteration at 2048^2 (7 bases, 3 levels).  So all bases share a
+// level's launch (the finest level of the synthesis sums its bases in registers),
+// and what consumes the results is fused into the last step: the dual update
+// (projection onto the l2 ball over the bands) into the analysis, the primal update
+// into the synthesis: 9 launches and 0.26 ms (with the convolution's 0.09; 0.10 analysis
+// at 3.3 TB/s, 0.054 finest synthesis at 4.0 TB/s, 0.04 the coarser levels).  Blocks of
+// 256 threads on 16 x 32 positions: four to six of them share a CU's LDS, so that one's
+// loads overlap another's passes; the loads' window offsets come from LDS tables (the
+// wrap's modulo for every load took most of the time: finest level 0.26 -> 0.054 ms).
+// The Dirac basis (k = 0) is one more slice of the finest analysis level and the
+// start of the finest synthesis level's sum.
 constexpr int kWaveTileR = 16, kWaveTileC = 32;
-template <typename R, int N>
-__global__ __launch_bounds__(kThreads) void wavelet_ana2_kernel(const R *src, R *dst_d, R *dst_ll, WaveletTaps<R> f,
-                                                                int nr, int nc, int ld, int64_t img) {
+
+// The level's blocks: tiles of hr x hc coefficient positions, tile columns fastest,
+// then tile rows, then `slice` (counted from the longest filter, whose blocks take
+// longest).
+struct WaveTile {
+    int kr0, kc0, slice;
+};
+__device__ __forceinline__ WaveTile wave_tile(int hr, int hc) {
+    const int tc = (hc + kWaveTileC - 1) / kWaveTileC, tr = (hr + kWaveTileR - 1) / kWaveTileR;
+    const int t = (int)(blockIdx.x % (unsigned)tc), rest = (int)(blockIdx.x / (unsigned)tc);
+    return WaveTile{(rest % tr) * kWaveTileR, t * kWaveTileC, rest / tr};
+}
+static int64_t wave_tiles(int hr, int hc) {
+    return (int64_t)((hc + kWaveTileC - 1) / kWaveTileC) * ((hr + kWaveTileR - 1) / kWaveTileR);
+}
+
+template <typename R> struct WaveAna {
+    const R *src;                  // level input: image b of basis k at src + k src_basis + b src_img
+    int64_t src_basis, src_img;
+    R *ll;                         // low-pass output for the next level, likewise; null after the last level
+    int64_t ll_basis, ll_img;
+    R *coef;                       // [nbasis][n_band][P], Mallat layout
+    int64_t P;
+    int src_ld, ll_ld, ld;
+    int nr, nc, nbasis, n_band, first;   // bases first .. nbasis - 1 (first = 0: the finest level)
+    R scale;                       // coef = scale a, or (dual) v = project(v + scale a)
+    R lam;
+    WaveletTaps<R> f[kMaxWaveletTaps / 2];
+};
+// LDS values of a block, for the longest filter (N = 6)
+constexpr int kWaveLdsAna = (2 * kWaveTileR + 10) * (2 * kWaveTileC + 11) + (2 * kWaveTileR + 10) * (2 * kWaveTileC + 1);
+// element offsets of a tile's window rows and columns (wrapped round the block once per
+// tile, not once per load), after the values: analysis 42 + 74, synthesis 3 x 21 + 2 x 37
+constexpr int kWaveWinR = kWaveTileR + 5, kWaveWinC = kWaveTileC + 5;
+constexpr int kWaveTabAna = 2 * kWaveWinR + 2 * kWaveWinC, kWaveTabSyn = 3 * kWaveWinR + 2 * kWaveWinC;
+constexpr int kWaveYin = (2 * (kWaveTileR + 5)) * (2 * (kWaveTileC + 5) + 1);
+constexpr int kWaveLdsSyn = kWaveYin + (2 * kWaveTileR) * (2 * (kWaveTileC + 5) + 1);
+
+// What the analysis does with a coefficient a: store scale a, or update the dual of
+// one band (v = t min(1, lam / |t|), t = v + scale a) or of several bands: there t is
+// stored and its square summed, and wave_project scales the bands once the norm is
+// known (the stores are the thread's own).
+enum WaveMode { WAVE_STORE = 0, WAVE_DUAL1 = 1, WAVE_DUALN = 2 };
+template <typename R, int MODE>
+__device__ __forceinline__ R wave_value(R old, R add, R lam, double &nrm2) {
+    if constexpr (MODE == WAVE_STORE) return add;
+    const R t = old + add;
+    if constexpr (MODE == WAVE_DUAL1) {
+        const R n = dev_abs(t);
+        return n > lam ? t * (lam / n) : t;
+    }
+    nrm2 += (double)t * (double)t;
+    return t;
+}
+template <typename R>
+__device__ __forceinline__ void wave_project(R *v, int n_band, int64_t P, R lam, double nrm2) {
+    const double nrm = sqrt(nrm2);
+    if (!(nrm > (double)lam)) return;
+    const R sc = (R)((double)lam / nrm);
+    for (int b = 0; b < n_band; ++b) v[(size_t)b * P] *= sc;
+}
+
+// one tile of basis N >= 1 (N vanishing moments) of band b0, or of all bands (WAVE_DUALN);
+// tab: offsets of the window's rows, then columns
+template <typename R, int N, int MODE>
+__device__ __forceinline__ void wave_ana_tile(const WaveAna<R> &a, R *lds, const R *taps, const int *tab, const WaveTile &w, int b0) {
     constexpr int TR = kWaveTileR, TC = kWaveTileC;
     constexpr int IR = 2 * TR + 2 * N - 2, IC = 2 * TC + 2 * N - 2;
-    __shared__ R xin[IR][IC + 1];
-    __shared__ R trow[IR][2 * TC + 1];
-    const int hr = nr >> 1, hc = nc >> 1;
-    const int kr0 = blockIdx.y * TR, kc0 = blockIdx.x * TC;
-    const R *sp = src + (size_t)blockIdx.z * img;
-    // the tile wraps round the block only at its far edges (periodic boundaries)
-    const bool wrap = 2 * kr0 + IR > nr || 2 * kc0 + IC > nc;
-    for (int id = threadIdx.x; id < IR * IC; id += kThreads) {
-        const int r = id / IC, c = id - r * IC;
-        int gr = 2 * kr0 + r, gc = 2 * kc0 + c;
-        if (wrap) {
-            gr %= nr;
-            gc %= nc;
-        }
-        xin[r][c] = sp[(size_t)gr * ld + gc];
-    }
-    __syncthreads();
-    // rows: a thread makes KB consecutive (low, high) pairs from one window of
-    // 2N + 2KB - 2 samples held in registers
+    constexpr int XS = IC + 1, TS = 2 * TC + 1;
+    R *const xin = lds, *const trow = lds + IR * XS;
+    WaveletTaps<R> f;
+    wave_taps<R, N>(taps, f);
+    const int hr = a.nr >> 1, hc = a.nc >> 1;
     constexpr int KB = 4, WIN = 2 * N + 2 * KB - 2;
-    for (int id = threadIdx.x; id < IR * (TC / KB); id += kThreads) {
-        const int r = id / (TC / KB), k0 = (id - r * (TC / KB)) * KB;
-        R x[WIN];
+    static_assert((TR / KB) * 2 * TC == kThreads, "one column item per thread");
+    // column pass: the thread makes KB consecutive coefficient rows of column c; offsets
+    // within an image fit 32 bits
+    const int kb = threadIdx.x / (2 * TC), c = threadIdx.x % (2 * TC);
+    const bool chi = c >= TC;
+    const int kc = w.kc0 + (chi ? c - TC : c), kr = w.kr0 + kb * KB;
+    const int nk = kc < hc ? min(KB, hr - kr) : 0;         // rows inside the level (may be <= 0)
+    const bool lowpass = !chi && a.ll;                     // the low half goes to the next level
+    const int hi_off = hr * a.ld;
+    R *const coef = a.coef + (size_t)N * a.n_band * a.P;
+    const int at = kr * a.ld + (chi ? hc : 0) + kc;
+    double nlo[KB], nhi[KB];
 #pragma unroll
-        for (int t = 0; t < WIN; ++t) x[t] = xin[r][2 * k0 + t];
+    for (int u = 0; u < KB; ++u) nlo[u] = nhi[u] = 0.0;
+    const int nb = MODE == WAVE_DUALN ? a.n_band : 1;
+    for (int b = b0; b < b0 + nb; ++b) {
+        R *const ob = coef + (size_t)b * a.P;
+        // the dual's old values first (rows and columns clamped to the level): their
+        // latency is hidden by the passes
+        R vlo[KB], vhi[KB];
 #pragma unroll
         for (int u = 0; u < KB; ++u) {
-            R lo = R(0), hi = R(0);
-#pragma unroll
-            for (int j = 0; j < 2 * N; ++j) {
-                lo += f.h[j] * x[2 * u + j];
-                hi += f.g[j] * x[2 * u + j];
+            vlo[u] = vhi[u] = R(0);
+            if (MODE != WAVE_STORE) {
+                const int o = min(kr + u, hr - 1) * a.ld + (chi ? hc : 0) + min(kc, hc - 1);
+                vlo[u] = ob[o];
+                vhi[u] = ob[o + hi_off];
             }
-            trow[r][k0 + u] = lo;
-            trow[r][TC + k0 + u] = hi;
         }
-    }
-    __syncthreads();
-    R *dd = dst_d + (size_t)blockIdx.z * img;
-    R *dl = dst_ll + (size_t)blockIdx.z * img;
-    // columns: KB consecutive coefficient rows per thread, as above
-    for (int id = threadIdx.x; id < (TR / KB) * 2 * TC; id += kThreads) {
-        const int kb = id / (2 * TC), c = id - kb * (2 * TC);
-        const int kr0b = kb * KB;
-        const bool chi = c >= TC;
-        const int kc = chi ? c - TC : c;
-        if (kc0 + kc >= hc) continue;
+        const R *sp = a.src + (size_t)N * a.src_basis + (size_t)b * a.src_img;
+        constexpr int LI = (IR * IC + kThreads - 1) / kThreads;   // all loads of the thread before their LDS writes
+        R xv[LI];
+#pragma unroll
+        for (int v = 0; v < LI; ++v) {
+            const int id = min((int)threadIdx.x + v * kThreads, IR * IC - 1);
+            xv[v] = sp[tab[id / IC] + tab[2 * kWaveWinR + id % IC]];
+        }
+#pragma unroll
+        for (int v = 0; v < LI; ++v) {
+            const int id = min((int)threadIdx.x + v * kThreads, IR * IC - 1);
+            xin[id / IC * XS + id % IC] = xv[v];
+        }
+        __syncthreads();
+        // rows: a thread makes KB consecutive (low, high) pairs from one window of
+        // 2N + 2KB - 2 samples held in registers
+        for (int id = threadIdx.x; id < IR * (TC / KB); id += kThreads) {
+            const int r = id / (TC / KB), k0 = (id - r * (TC / KB)) * KB;
+            R x[WIN];
+#pragma unroll
+            for (int t = 0; t < WIN; ++t) x[t] = xin[r * XS + 2 * k0 + t];
+#pragma unroll
+            for (int u = 0; u < KB; ++u) {
+                R lo = R(0), hi = R(0);
+#pragma unroll
+                for (int j = 0; j < 2 * N; ++j) {
+                    lo += f.h[j] * x[2 * u + j];
+                    hi += f.g(j) * x[2 * u + j];
+                }
+                trow[r * TS + k0 + u] = lo;
+                trow[r * TS + TC + k0 + u] = hi;
+            }
+        }
+        __syncthreads();
+        // columns, as above (the next band's first barrier orders these reads before its row pass)
         R t[WIN];
 #pragma unroll
-        for (int v = 0; v < WIN; ++v) t[v] = trow[2 * kr0b + v][c];
-        const int col = (chi ? hc : 0) + kc0 + kc;
+        for (int v = 0; v < WIN; ++v) t[v] = trow[(2 * kb * KB + v) * TS + c];
+        R *const pl = lowpass ? a.ll + (size_t)N * a.ll_basis + (size_t)b * a.ll_img + (kr * a.ll_ld + kc) : ob + at;
+        const int sl = lowpass ? a.ll_ld : a.ld;
 #pragma unroll
         for (int u = 0; u < KB; ++u) {
-            const int kr = kr0b + u;
-            if (kr0 + kr >= hr) break;
             R lo = R(0), hi = R(0);
 #pragma unroll
             for (int j = 0; j < 2 * N; ++j) {
                 lo += f.h[j] * t[2 * u + j];
-                hi += f.g[j] * t[2 * u + j];
+                hi += f.g(j) * t[2 * u + j];
             }
-            if (chi) dd[(size_t)(kr0 + kr) * ld + col] = lo;
-            else dl[(size_t)(kr0 + kr) * ld + col] = lo;
-            dd[(size_t)(hr + kr0 + kr) * ld + col] = hi;
+            const R cl = wave_value<R, MODE>(vlo[u], a.scale * lo, a.lam, nlo[u]);
+            const R ch = wave_value<R, MODE>(vhi[u], a.scale * hi, a.lam, nhi[u]);
+            if (u < nk) {
+                pl[u * sl] = lowpass ? lo : cl;
+                ob[at + hi_off + u * a.ld] = ch;
+            }
+        }
+    }
+    if (MODE == WAVE_DUALN) {
+#pragma unroll
+        for (int u = 0; u < KB; ++u) {
+            if (u < nk) {
+                if (!lowpass) wave_project(coef + at + u * a.ld, a.n_band, a.P, a.lam, nlo[u]);
+                wave_project(coef + at + u * a.ld + hi_off, a.n_band, a.P, a.lam, nhi[u]);
+            }
         }
     }
 }
 
-template <typename R, int N, bool ACC>
-__global__ __launch_bounds__(kThreads) void wavelet_syn2_kernel(const R *src_ll, const R *src_d, R *dst,
-                                                                WaveletTaps<R> f, int nr, int nc, int ld, int64_t img) {
+// WAVE_DUALN: a block takes all bands of its tile (the norm runs over them), else one.
+template <typename R, int MODE>
+__global__ __launch_bounds__(kThreads) void wavelet_analysis_kernel(WaveAna<R> a) {
+    __shared__ R lds[kWaveLdsAna];
+    __shared__ __align__(16) R taps[2 * kMaxWaveletTaps];
+    __shared__ int tab[kWaveTabAna];
+    const WaveTile w = wave_tile(a.nr >> 1, a.nc >> 1);
+    const int k = a.nbasis - 1 - (MODE == WAVE_DUALN ? w.slice : w.slice / a.n_band);
+    const int b0 = MODE == WAVE_DUALN ? 0 : w.slice % a.n_band, nb = MODE == WAVE_DUALN ? a.n_band : 1;
+    if (k > 0 && threadIdx.x < 2 * kMaxWaveletTaps) taps[threadIdx.x] = a.f[k - 1].h[threadIdx.x];   // h, then g
+    for (int id = threadIdx.x; id < kWaveTabAna; id += kThreads)
+        tab[id] = id < 2 * kWaveWinR ? (2 * w.kr0 + id) % a.nr * a.src_ld : (2 * w.kc0 + id - 2 * kWaveWinR) % a.nc;
+    __syncthreads();
+    switch (k) {
+        case 1: wave_ana_tile<R, 1, MODE>(a, lds, taps, tab, w, b0); return;
+        case 2: wave_ana_tile<R, 2, MODE>(a, lds, taps, tab, w, b0); return;
+        case 3: wave_ana_tile<R, 3, MODE>(a, lds, taps, tab, w, b0); return;
+        case 4: wave_ana_tile<R, 4, MODE>(a, lds, taps, tab, w, b0); return;
+        case 5: wave_ana_tile<R, 5, MODE>(a, lds, taps, tab, w, b0); return;
+        case 6: wave_ana_tile<R, 6, MODE>(a, lds, taps, tab, w, b0); return;
+        default: break;
+    }
+    // the Dirac basis: the image itself (finest level only)
+    constexpr int TR = 2 * kWaveTileR, TC = 2 * kWaveTileC;
+    for (int id = threadIdx.x; id < TR * TC; id += kThreads) {
+        const int r = 2 * w.kr0 + id / TC, c = 2 * w.kc0 + id % TC;
+        if (r >= a.nr || c >= a.nc) continue;
+        R *const v = a.coef + (size_t)r * a.ld + c;
+        double nrm2 = 0.0;
+        for (int b = b0; b < b0 + nb; ++b) {
+            const R x = a.src[(size_t)b * a.src_img + (size_t)r * a.src_ld + c];
+            R *const vb = v + (size_t)b * a.P;
+            *vb = wave_value<R, MODE>(MODE == WAVE_STORE ? R(0) : *vb, a.scale * x, a.lam, nrm2);
+        }
+        if (MODE == WAVE_DUALN) wave_project(v, a.n_band, a.P, a.lam, nrm2);
+    }
+}
+
+template <typename R> struct WaveSyn {
+    const R *coef;                 // [nbasis][n_band][P], Mallat layout
+    const R *ll;                   // low-pass block from the coarser level (basis k, image b at
+    int64_t ll_basis, ll_img;      // ll + k ll_basis + b ll_img); null at the coarsest: in coef
+    R *dst;                        // the next finer level's low-pass block, likewise, or (FINEST) the image
+    int64_t dst_basis, dst_img;
+    int64_t P;
+    int ll_ld, dst_ld, ld;
+    int nr, nc, nbasis, n_band;
+    int vec;                       // FINEST: rows and pointers allow 16-byte accesses
+    R scale;                       // FINEST, store: dst = scale sum
+    // FINEST, primal update (conv = I^psf * (x - z)):
+    //   x~ = max(x - tau ((conv + sigma_u (x - z)) / gamma + scale sum), 0)
+    //   u = 2 x~ - x;  x = x~;  d = x~ - z
+    const R *z, *conv;
+    R *x, *d, *u;
+    R tau, inv_gamma, sigma_u;
+    WaveletTaps<R> f[kMaxWaveletTaps / 2];
+};
+
+// one tile of basis N: acc[2 u + e] += sample 2 (q0 + u) + e of the thread's row
+constexpr int kWavePB = 4;
+template <typename R, int N>
+__device__ __forceinline__ void wave_syn_tile(const WaveSyn<R> &a, R *lds, const R *taps, const int *tab, int b, R *acc) {
     constexpr int TR = kWaveTileR, TC = kWaveTileC;
     constexpr int YR = TR + N - 1, YC = TC + N - 1;   // coefficient rows / columns per half
-    __shared__ R yin[2 * YR][2 * YC + 1];
-    __shared__ R tcol[2 * TR][2 * YC + 1];
-    const int hr = nr >> 1, hc = nc >> 1;
-    const int kr0 = blockIdx.y * TR, kc0 = blockIdx.x * TC;
-    const R *sl = src_ll + (size_t)blockIdx.z * img;
-    const R *sd = src_d + (size_t)blockIdx.z * img;
-    // the coefficient window wraps only at the block's edges (periodic boundaries)
-    const bool wrap = kr0 < N - 1 || kc0 < N - 1 || kr0 + YR - (N - 1) > hr || kc0 + YC - (N - 1) > hc;
-    for (int id = threadIdx.x; id < 4 * YR * YC; id += kThreads) {
-        const int a = id / (2 * YC), b = id - a * (2 * YC);
-        const bool rhi = a >= YR, chi = b >= YC;
-        int pr = (rhi ? a - YR : a) + kr0 - (N - 1), pc = (chi ? b - YC : b) + kc0 - (N - 1);
-        if (wrap) {
-            while (pr < 0) pr += hr;
-            while (pc < 0) pc += hc;
-            pr %= hr;
-            pc %= hc;
-        }
-        const size_t off = (size_t)((rhi ? hr : 0) + pr) * ld + (chi ? hc : 0) + pc;
-        yin[a][b] = (!rhi && !chi) ? sl[off] : sd[off];
+    constexpr int YS = 2 * YC + 1;
+    // (fixed offset: the next basis fills yin while slower waves still read tcol)
+    R *const yin = lds, *const tcol = lds + kWaveYin;
+    WaveletTaps<R> f;
+    wave_taps<R, N>(taps + (N - 1) * 2 * kMaxWaveletTaps, f);
+    const R *sd = a.coef + ((size_t)N * a.n_band + b) * a.P;
+    const R *sl = a.ll ? a.ll + (size_t)N * a.ll_basis + (size_t)b * a.ll_img : sd;
+    // the table's window is the longest filter's: this one starts 6 - N later
+    const int *const rows = tab + 6 - N, *const cols = tab + 3 * kWaveWinR + 6 - N;
+    constexpr int LI = (4 * YR * YC + kThreads - 1) / kThreads;   // all loads of the thread before their LDS writes
+    R yv[LI];
+#pragma unroll
+    for (int v = 0; v < LI; ++v) {
+        const int id = min((int)threadIdx.x + v * kThreads, 4 * YR * YC - 1);
+        const int ra = id / (2 * YC), cb = id % (2 * YC);
+        const int rhi = ra >= YR, chi = cb >= YC;
+        // low rows: those of the low-pass block where the column is low too
+        const int ro = rows[ra + (rhi ? 2 * kWaveWinR - YR : (chi ? kWaveWinR : 0))];
+        const int co = cols[cb + (chi ? kWaveWinC - YC : 0)];
+        yv[v] = (rhi | chi ? sd : sl)[ro + co];
+    }
+#pragma unroll
+    for (int v = 0; v < LI; ++v) {
+        const int id = min((int)threadIdx.x + v * kThreads, 4 * YR * YC - 1);
+        yin[id / (2 * YC) * YS + id % (2 * YC)] = yv[v];
     }
     __syncthreads();
     // columns: sample rows 2p + e of the tile from coefficient rows p - i, i < N;
     // a thread makes PB consecutive p (both e) from PB + N - 1 low and high rows
-    constexpr int PB = 4, PW = PB + N - 1;
+    constexpr int PB = kWavePB, PW = PB + N - 1;
     for (int id = threadIdx.x; id < (TR / PB) * 2 * YC; id += kThreads) {
-        const int pb = id / (2 * YC), b = id - pb * (2 * YC);
+        const int pb = id / (2 * YC), cb = id - pb * (2 * YC);
         const int p0 = pb * PB;
         R lo[PW], hi[PW];
 #pragma unroll
         for (int t = 0; t < PW; ++t) {
-            lo[t] = yin[p0 + t][b];
-            hi[t] = yin[YR + p0 + t][b];
+            lo[t] = yin[(p0 + t) * YS + cb];
+            hi[t] = yin[(YR + p0 + t) * YS + cb];
         }
 #pragma unroll
         for (int u = 0; u < PB; ++u) {
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
-                R acc = R(0);
+                R s = R(0);
 #pragma unroll
-                for (int i = 0; i < N; ++i) acc += f.h[2 * i + e] * lo[u + N - 1 - i] + f.g[2 * i + e] * hi[u + N - 1 - i];
-                tcol[2 * (p0 + u) + e][b] = acc;
+                for (int i = 0; i < N; ++i) {
+                    s += f.h[2 * i + e] * lo[u + N - 1 - i];
+                    s += f.g(2 * i + e) * hi[u + N - 1 - i];
+                }
+                tcol[(2 * (p0 + u) + e) * YS + cb] = s;
             }
         }
     }
     __syncthreads();
-    R *dp = dst + (size_t)blockIdx.z * img;
-    // rows: PB consecutive q (both e) per thread, as above
-    for (int id = threadIdx.x; id < 2 * TR * (TC / PB); id += kThreads) {
-        const int mr = id / (TC / PB), q0 = (id - mr * (TC / PB)) * PB;
-        if (kr0 + (mr >> 1) >= hr) continue;
-        R lo[PW], hi[PW];
+    // rows: PB consecutive q (both e) per thread, as above (the next basis' first
+    // barrier orders these reads before its column pass)
+    static_assert(2 * TR * (TC / PB) == kThreads, "one row item per thread");
+    const int mr = threadIdx.x / (TC / PB), q0 = (threadIdx.x % (TC / PB)) * PB;
+    R lo[PW], hi[PW];
 #pragma unroll
-        for (int t = 0; t < PW; ++t) {
-            lo[t] = tcol[mr][q0 + t];
-            hi[t] = tcol[mr][YC + q0 + t];
-        }
-        R *orow = dp + (size_t)(2 * kr0 + mr) * ld + 2 * kc0;
+    for (int t = 0; t < PW; ++t) {
+        lo[t] = tcol[mr * YS + q0 + t];
+        hi[t] = tcol[mr * YS + YC + q0 + t];
+    }
 #pragma unroll
-        for (int u = 0; u < PB; ++u) {
-            if (kc0 + q0 + u >= hc) break;
+    for (int u = 0; u < PB; ++u) {
 #pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                R acc = R(0);
+        for (int e = 0; e < 2; ++e) {
+            R s = R(0);
 #pragma unroll
-                for (int i = 0; i < N; ++i) acc += f.h[2 * i + e] * lo[u + N - 1 - i] + f.g[2 * i + e] * hi[u + N - 1 - i];
-                R *o = orow + 2 * (q0 + u) + e;
-                if (ACC) *o += acc;
-                else *o = acc;
+            for (int i = 0; i < N; ++i) {
+                s += f.h[2 * i + e] * lo[u + N - 1 - i];
+                s += f.g(2 * i + e) * hi[u + N - 1 - i];
             }
+            acc[2 * u + e] += s;
         }
     }
+}
+// offsets of the window: rows in the low-pass block, low rows and high rows in the
+// coefficients, low columns, high columns
+template <typename R> __device__ __forceinline__ void wave_syn_table(const WaveSyn<R> &a, const WaveTile &w, R *taps, int *tab) {
+    const int hr = a.nr >> 1, hc = a.nc >> 1;
+    auto wrap = [](int i, int n) {
+        i %= n;
+        return i < 0 ? i + n : i;
+    };
+    for (int id = threadIdx.x; id < (a.nbasis - 1) * 2 * kMaxWaveletTaps; id += kThreads)
+        taps[id] = a.f[id / (2 * kMaxWaveletTaps)].h[id % (2 * kMaxWaveletTaps)];
+    for (int id = threadIdx.x; id < kWaveTabSyn; id += kThreads) {
+        const int part = id < 3 * kWaveWinR ? id / kWaveWinR : 3 + (id - 3 * kWaveWinR) / kWaveWinC;
+        const int i = part < 3 ? id - part * kWaveWinR : id - 3 * kWaveWinR - (part - 3) * kWaveWinC;
+        const int r = wrap(w.kr0 - 5 + i, hr), c = wrap(w.kc0 - 5 + i, hc);
+        tab[id] = part == 0 ? r * (a.ll ? a.ll_ld : a.ld)
+                            : (part == 1 ? r * a.ld : (part == 2 ? (hr + r) * a.ld : (part == 3 ? c : hc + c)));
+    }
+    __syncthreads();
+}
+
+// the 8 samples of a thread's row, as 16-byte accesses where rows and pointers allow
+// (VEC: then the row holds all 8 or none of each 16 bytes, nc being a multiple)
+template <typename R, bool VEC> __device__ __forceinline__ void wave_row_load(const R *p, int n, R *v) {
+    constexpr int E = 16 / (int)sizeof(R);
+    if constexpr (VEC) {
+        typedef R vecR __attribute__((ext_vector_type(E)));
+#pragma unroll
+        for (int q = 0; q < 2 * kWavePB; q += E) {
+            vecR t{};
+            if (q < n) t = *reinterpret_cast<const vecR *>(p + q);
+#pragma unroll
+            for (int j = 0; j < E; ++j) v[q + j] = t[j];
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < 2 * kWavePB; ++q) v[q] = q < n ? p[q] : R(0);
+    }
+}
+template <typename R, bool VEC> __device__ __forceinline__ void wave_row_store(R *p, int n, const R *v) {
+    constexpr int E = 16 / (int)sizeof(R);
+    if constexpr (VEC) {
+        typedef R vecR __attribute__((ext_vector_type(E)));
+#pragma unroll
+        for (int q = 0; q < 2 * kWavePB; q += E) {
+            vecR t;
+#pragma unroll
+            for (int j = 0; j < E; ++j) t[j] = v[q + j];
+            if (q < n) *reinterpret_cast<vecR *>(p + q) = t;
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < 2 * kWavePB; ++q)
+            if (q < n) p[q] = v[q];
+    }
+}
+
+// a level above the finest: each basis' samples are the next finer level's low-pass block
+template <typename R>
+__global__ __launch_bounds__(kThreads) void wavelet_synthesis_kernel(WaveSyn<R> a) {
+    __shared__ R lds[kWaveLdsSyn];
+    __shared__ __align__(16) R taps[kMaxWaveletTaps * kMaxWaveletTaps];   // of bases 1 .. 6
+    __shared__ int tab[kWaveTabSyn];
+    const WaveTile w = wave_tile(a.nr >> 1, a.nc >> 1);
+    const int k = a.nbasis - 1 - w.slice / a.n_band, b = w.slice % a.n_band;
+    wave_syn_table(a, w, taps, tab);
+    R acc[2 * kWavePB];
+#pragma unroll
+    for (int q = 0; q < 2 * kWavePB; ++q) acc[q] = R(0);
+    switch (k) {
+        case 1: wave_syn_tile<R, 1>(a, lds, taps, tab, b, acc); break;
+        case 2: wave_syn_tile<R, 2>(a, lds, taps, tab, b, acc); break;
+        case 3: wave_syn_tile<R, 3>(a, lds, taps, tab, b, acc); break;
+        case 4: wave_syn_tile<R, 4>(a, lds, taps, tab, b, acc); break;
+        case 5: wave_syn_tile<R, 5>(a, lds, taps, tab, b, acc); break;
+        default: wave_syn_tile<R, 6>(a, lds, taps, tab, b, acc); break;
+    }
+    const int mr = threadIdx.x / (kWaveTileC / kWavePB), q0 = (threadIdx.x % (kWaveTileC / kWavePB)) * kWavePB;
+    const int r = 2 * w.kr0 + mr, c = 2 * (w.kc0 + q0);
+    if (r < a.nr)
+        wave_row_store<R, false>(a.dst + (size_t)k * a.dst_basis + (size_t)b * a.dst_img + (size_t)r * a.dst_ld + c, a.nc - c,
+                                 acc);
+}
+
+// the finest level: the sum over all bases, then the scaled store or the primal update
+template <typename R, bool PRIMAL, bool VEC>
+__global__ __launch_bounds__(kThreads) void wavelet_finest_kernel(WaveSyn<R> a) {
+    __shared__ R lds[kWaveLdsSyn];
+    __shared__ __align__(16) R taps[kMaxWaveletTaps * kMaxWaveletTaps];   // of bases 1 .. 6
+    __shared__ int tab[kWaveTabSyn];
+    const WaveTile w = wave_tile(a.nr >> 1, a.nc >> 1);
+    const int b = w.slice;
+    wave_syn_table(a, w, taps, tab);
+    const int mr = threadIdx.x / (kWaveTileC / kWavePB), q0 = (threadIdx.x % (kWaveTileC / kWavePB)) * kWavePB;
+    const int r = 2 * w.kr0 + mr, c = 2 * (w.kc0 + q0);
+    const int n = r < a.nr ? a.nc - c : 0;                 // samples of the thread inside the image (any sign)
+    const size_t pix = (size_t)b * a.P + (size_t)r * a.ld + c;
+    R acc[2 * kWavePB];
+    wave_row_load<R, VEC>(a.coef + pix, n, acc);           // the Dirac basis
+    if (a.nbasis > 1) wave_syn_tile<R, 1>(a, lds, taps, tab, b, acc);
+    if (a.nbasis > 2) wave_syn_tile<R, 2>(a, lds, taps, tab, b, acc);
+    if (a.nbasis > 3) wave_syn_tile<R, 3>(a, lds, taps, tab, b, acc);
+    if (a.nbasis > 4) wave_syn_tile<R, 4>(a, lds, taps, tab, b, acc);
+    if (a.nbasis > 5) wave_syn_tile<R, 5>(a, lds, taps, tab, b, acc);
+    if (a.nbasis > 6) wave_syn_tile<R, 6>(a, lds, taps, tab, b, acc);
+    if (!PRIMAL) {
+#pragma unroll
+        for (int q = 0; q < 2 * kWavePB; ++q) acc[q] *= a.scale;
+        wave_row_store<R, VEC>(a.dst + pix, n, acc);
+        return;
+    }
+    R x[2 * kWavePB], z[2 * kWavePB], cv[2 * kWavePB], u[2 * kWavePB];
+    wave_row_load<R, VEC>(a.x + pix, n, x);
+    wave_row_load<R, VEC>(a.z + pix, n, z);
+    wave_row_load<R, VEC>(a.conv + pix, n, cv);
+#pragma unroll
+    for (int q = 0; q < 2 * kWavePB; ++q) {
+        const R grad = (cv[q] + a.sigma_u * (x[q] - z[q])) * a.inv_gamma;
+        const R xt = max(x[q] - a.tau * (grad + a.scale * acc[q]), R(0));
+        u[q] = R(2) * xt - x[q];
+        x[q] = xt;
+        z[q] = xt - z[q];
+    }
+    wave_row_store<R, VEC>(a.u + pix, n, u);
+    wave_row_store<R, VEC>(a.x + pix, n, x);
+    wave_row_store<R, VEC>(a.d + pix, n, z);
 }
 
 template <typename R>
@@ -3181,56 +3495,143 @@ static WaveletTaps<R> make_taps(const WaveletFilter &f) {
     const int L = f.len;
     for (int j = 0; j < L; ++j) {
         t.h[j] = (R)f.h[j];
-        t.g[j] = (R)((j & 1) ? -f.h[L - 1 - j] : f.h[L - 1 - j]);
+        t.g(j) = (R)((j & 1) ? -f.h[L - 1 - j] : f.h[L - 1 - j]);
     }
     return t;
 }
+// the taps of bases 1 .. nbasis - 1; basis k must have length 2k (its tile is compiled for it)
+template <typename R> static bool set_taps(WaveletTaps<R> *f, const WaveDict &D) {
+    if (D.nbasis < 1 || D.nbasis > kMaxWaveletTaps / 2 + 1) return false;
+    for (int k = 1; k < D.nbasis; ++k) {
+        if (D.f[k].len != 2 * k) return false;
+        f[k - 1] = make_taps<R>(D.f[k]);
+    }
+    return true;
+}
+
+// Low-pass blocks of level m (m = 1 .. levels - 1; (nx >> m) x (ny >> m), rows dense)
+// of the bases k >= 1: odd m at tmp, even m after the largest odd one (level 1: a
+// quarter of an image per basis, level 2: a sixteenth), so at most 15/8 images for six bases
+static int64_t wave_level_off(const WaveDict &D, int m) {
+    return (m & 1) ? 0 : (int64_t)(D.nbasis - 1) * D.n_band * (D.nx >> 1) * (D.ny >> 1);
+}
 
 template <typename R>
-static hipError_t wavelet_level_t(bool inv, bool acc, const void *a_src, const void *b_src, void *a_dst, void *b_dst,
-                                  const WaveletFilter &f, int nr, int nc, int ld, int64_t img, int n_img,
-                                  hipStream_t s) {
-    const int L = f.len;
-    if (L < 2 || L > kMaxWaveletTaps || (L & 1) || nr < 2 || nc < 2 || (nr & 1) || (nc & 1) || n_img > 65535)
-        return hipErrorInvalidValue;
-    const WaveletTaps<R> t = make_taps<R>(f);
-    const dim3 grid((nc / 2 + kWaveTileC - 1) / kWaveTileC, (nr / 2 + kWaveTileR - 1) / kWaveTileR, n_img);
-    if (grid.y > 65535) return hipErrorInvalidValue;
-    return dispatch_int<1, 6>(L / 2, [&](auto Nc) -> hipError_t {
-        constexpr int N = decltype(Nc)::value;
-        if (!inv) {
-            PFB_LAUNCH((wavelet_ana2_kernel<R, N>), grid, 0, s, (const R *)a_src, (R *)a_dst, (R *)b_dst, t, nr, nc,
-                       ld, img);
-        } else if (acc) {
-            PFB_LAUNCH((wavelet_syn2_kernel<R, N, true>), grid, 0, s, (const R *)a_src, (const R *)b_src, (R *)a_dst,
-                       t, nr, nc, ld, img);
-        } else {
-            PFB_LAUNCH((wavelet_syn2_kernel<R, N, false>), grid, 0, s, (const R *)a_src, (const R *)b_src, (R *)a_dst,
-                       t, nr, nc, ld, img);
+static hipError_t wavelet_analysis_t(const WaveDict &D, const void *src, void *coef, void *tmp, bool dual, double scale,
+                                     double lam, hipStream_t s) {
+    WaveAna<R> a{};
+    if (!set_taps(a.f, D)) return hipErrorInvalidValue;
+    const int64_t P = (int64_t)D.nx * D.ny;
+    a.coef = reinterpret_cast<R *>(coef);
+    a.P = P;
+    a.ld = D.ny;
+    a.nbasis = D.nbasis;
+    a.n_band = D.n_band;
+    a.scale = (R)scale;
+    a.lam = (R)lam;
+    for (int l = 0; l < D.levels; ++l) {
+        a.nr = D.nx >> l;
+        a.nc = D.ny >> l;
+        const int64_t Pl = (int64_t)a.nr * a.nc, Pn = Pl / 4;
+        a.first = l == 0 ? 0 : 1;
+        if (l == 0) {
+            a.src = reinterpret_cast<const R *>(src);
+            a.src_basis = 0;
+            a.src_img = P;
+            a.src_ld = D.ny;
+        } else {   // basis k at (k - 1) blocks
+            a.src = a.ll;
+            a.src_basis = a.ll_basis;
+            a.src_img = a.ll_img;
+            a.src_ld = a.ll_ld;
         }
-        return hipSuccess;
-    });
+        a.ll = nullptr;
+        if (l + 1 < D.levels) {
+            a.ll_img = Pn;
+            a.ll_basis = (int64_t)D.n_band * Pn;
+            a.ll_ld = a.nc / 2;
+            a.ll = reinterpret_cast<R *>(tmp) + wave_level_off(D, l + 1) - a.ll_basis;
+        }
+        const int64_t nb = wave_tiles(a.nr / 2, a.nc / 2) * (D.nbasis - a.first) * (dual ? 1 : D.n_band);
+        if (nb < 1) break;
+        if (nb > INT_MAX) return hipErrorInvalidValue;
+        if (!dual) PFB_LAUNCH((wavelet_analysis_kernel<R, WAVE_STORE>), (unsigned)nb, 0, s, a);
+        else if (D.n_band == 1) PFB_LAUNCH((wavelet_analysis_kernel<R, WAVE_DUAL1>), (unsigned)nb, 0, s, a);
+        else PFB_LAUNCH((wavelet_analysis_kernel<R, WAVE_DUALN>), (unsigned)nb, 0, s, a);
+    }
+    return hipSuccess;
 }
-
-hipError_t launch_wavelet_analysis_level(bool dbl, const void *src, void *dst_detail, void *dst_ll,
-                                         const WaveletFilter &f, int nr, int nc, int ld, int64_t img, int n_img,
-                                         hipStream_t s) {
-    if (dbl) return wavelet_level_t<double>(false, false, src, nullptr, dst_detail, dst_ll, f, nr, nc, ld, img, n_img, s);
-    return wavelet_level_t<float>(false, false, src, nullptr, dst_detail, dst_ll, f, nr, nc, ld, img, n_img, s);
-}
-
-hipError_t launch_wavelet_synthesis_level(bool dbl, bool acc, const void *src_ll, const void *src_detail, void *dst,
-                                          const WaveletFilter &f, int nr, int nc, int ld, int64_t img, int n_img,
-                                          hipStream_t s) {
-    if (dbl) return wavelet_level_t<double>(true, acc, src_ll, src_detail, dst, nullptr, f, nr, nc, ld, img, n_img, s);
-    return wavelet_level_t<float>(true, acc, src_ll, src_detail, dst, nullptr, f, nr, nc, ld, img, n_img, s);
+hipError_t launch_wavelet_analysis(bool dbl, const WaveDict &D, const void *src, void *coef, void *tmp, bool dual,
+                                   double scale, double lam, hipStream_t s) {
+    return dbl ? wavelet_analysis_t<double>(D, src, coef, tmp, dual, scale, lam, s)
+               : wavelet_analysis_t<float>(D, src, coef, tmp, dual, scale, lam, s);
 }
 
 template <typename R>
-__global__ __launch_bounds__(kThreads) void wave_copy_kernel(const R *src, R *dst, int64_t n, R scale) {
-    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads)
-        dst[i] = src[i] * scale;
+static hipError_t wavelet_synthesis_t(const WaveDict &D, const void *coef, void *dst, void *tmp, const PrimalArgs *p,
+                                      double scale, hipStream_t s) {
+    WaveSyn<R> a{};
+    if (!set_taps(a.f, D)) return hipErrorInvalidValue;
+    const int64_t P = (int64_t)D.nx * D.ny;
+    a.coef = reinterpret_cast<const R *>(coef);
+    a.P = P;
+    a.ld = D.ny;
+    a.nbasis = D.nbasis;
+    a.n_band = D.n_band;
+    a.scale = (R)scale;
+    if (p) {
+        a.z = reinterpret_cast<const R *>(p->z);
+        a.conv = reinterpret_cast<const R *>(p->conv);
+        a.x = reinterpret_cast<R *>(p->x);
+        a.d = reinterpret_cast<R *>(p->d);
+        a.u = reinterpret_cast<R *>(p->u);
+        a.tau = (R)p->tau;
+        a.inv_gamma = (R)(1.0 / p->gamma);
+        a.sigma_u = (R)p->sigma_u;
+    }
+    for (int l = D.levels - 1; l >= 0; --l) {
+        if (l > 0 && D.nbasis == 1) continue;
+        a.nr = D.nx >> l;
+        a.nc = D.ny >> l;
+        const int64_t Pl = (int64_t)a.nr * a.nc;
+        if (l + 1 < D.levels) {
+            a.ll = a.dst;
+            a.ll_basis = a.dst_basis;
+            a.ll_img = a.dst_img;
+            a.ll_ld = a.dst_ld;
+        }
+        if (l > 0) {
+            a.dst_img = Pl;
+            a.dst_basis = (int64_t)D.n_band * Pl;
+            a.dst_ld = a.nc;
+            a.dst = reinterpret_cast<R *>(tmp) + wave_level_off(D, l) - a.dst_basis;
+            const int64_t nb = wave_tiles(a.nr / 2, a.nc / 2) * (D.nbasis - 1) * D.n_band;
+            if (nb > INT_MAX) return hipErrorInvalidValue;
+            PFB_LAUNCH(wavelet_synthesis_kernel<R>, (unsigned)nb, 0, s, a);
+            continue;
+        }
+        a.dst = reinterpret_cast<R *>(dst);
+        // 16-byte accesses: every row of every image starts on 16 bytes
+        const uintptr_t bits = reinterpret_cast<uintptr_t>(coef) | reinterpret_cast<uintptr_t>(dst) |
+                               reinterpret_cast<uintptr_t>(a.z) | reinterpret_cast<uintptr_t>(a.conv) |
+                               reinterpret_cast<uintptr_t>(a.x) | reinterpret_cast<uintptr_t>(a.d) |
+                               reinterpret_cast<uintptr_t>(a.u) | ((uintptr_t)D.ny * sizeof(R));
+        const bool vec = (bits & 15) == 0;
+        const int64_t nb = wave_tiles(a.nr / 2, a.nc / 2) * D.n_band;
+        if (nb > INT_MAX) return hipErrorInvalidValue;
+        if (p && vec) PFB_LAUNCH((wavelet_finest_kernel<R, true, true>), (unsigned)nb, 0, s, a);
+        else if (p) PFB_LAUNCH((wavelet_finest_kernel<R, true, false>), (unsigned)nb, 0, s, a);
+        else if (vec) PFB_LAUNCH((wavelet_finest_kernel<R, false, true>), (unsigned)nb, 0, s, a);
+        else PFB_LAUNCH((wavelet_finest_kernel<R, false, false>), (unsigned)nb, 0, s, a);
+    }
+    return hipSuccess;
 }
+hipError_t launch_wavelet_synthesis(bool dbl, const WaveDict &D, const void *coef, void *dst, void *tmp,
+                                    const PrimalArgs *p, double scale, hipStream_t s) {
+    return dbl ? wavelet_synthesis_t<double>(D, coef, dst, tmp, p, scale, s)
+               : wavelet_synthesis_t<float>(D, coef, dst, tmp, p, scale, s);
+}
+
 template <typename R>
 __global__ __launch_bounds__(kThreads) void wave_axpy_kernel(const R *x, const R *y, R *z, int64_t n, R a) {
     for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads)
@@ -3245,106 +3646,29 @@ hipError_t launch_wave_axpy(bool dbl, const void *x, const void *y, void *z, int
     return hipSuccess;
 }
 
-hipError_t launch_wave_copy(bool dbl, const void *src, void *dst, int64_t n, double scale, hipStream_t s) {
-    const int64_t nb = wave_blocks(n);
-    if (dbl)
-        PFB_LAUNCH(wave_copy_kernel<double>, nb, 0, s, (const double *)src, (double *)dst, n, scale);
-    else
-        PFB_LAUNCH(wave_copy_kernel<float>, nb, 0, s, (const float *)src, (float *)dst, n, (float)scale);
-    return hipSuccess;
-}
-
-// Primal update of the primal-dual iteration, per pixel:
-//   x~ = max(x - tau ((c + sigma_u d) / gamma + psi_scale * s), 0),   d = x - z, c = I^psf * d
-//   u  = 2 x~ - x;  x = x~;  d = x~ - z
-// INIT (before the first iteration): x = max(z, 0) unless warm, d = x - z.
-template <typename R, bool INIT>
-__global__ __launch_bounds__(kThreads) void pd_primal_kernel(const R *z, R *x, R *d, const R *c, const R *sv, R *u,
-                                                             int64_t n, R tau, R inv_gamma, R sigma_u, R psi_scale,
-                                                             int warm) {
+// Start of the primal-dual iteration: x = max(z, 0) unless warm, d = x - z.
+template <typename R>
+__global__ __launch_bounds__(kThreads) void pd_init_kernel(const R *z, R *x, R *d, int64_t n, int warm) {
     for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads) {
-        if (INIT) {
-            const R xi = warm ? x[i] : max(z[i], R(0));
-            x[i] = xi;
-            d[i] = xi - z[i];
-        } else {
-            const R xi = x[i], di = d[i];
-            const R grad = (c[i] + sigma_u * di) * inv_gamma;
-            const R xt = max(xi - tau * (grad + psi_scale * sv[i]), R(0));
-            u[i] = R(2) * xt - xi;
-            x[i] = xt;
-            d[i] = xt - z[i];
-        }
+        const R xi = warm ? x[i] : max(z[i], R(0));
+        x[i] = xi;
+        d[i] = xi - z[i];
     }
 }
-
-// Dual update per (basis, coefficient): t_b = v_b + sigma_d psi_scale a_b over the
-// bands b, v = t min(1, lam / ||t||_2); basis 0 reads the image u (Dirac), basis
-// k >= 1 its analysis coefficients.  ZERO: v = 0.
-template <typename R, bool ZERO>
-__global__ __launch_bounds__(kThreads) void pd_dual_kernel(R *v, const R *u, const R *coef, int nbasis, int n_band,
-                                                           int64_t P, R sigma_d, R psi_scale, R lam) {
-    const int64_t total = (int64_t)nbasis * P;
-    for (int64_t id = (int64_t)blockIdx.x * kThreads + threadIdx.x; id < total;
-         id += (int64_t)gridDim.x * kThreads) {
-        const int k = (int)(id / P);
-        const int64_t p = id - (int64_t)k * P;
-        R *vk = v + (size_t)k * n_band * P + p;
-        if (ZERO) {
-            for (int b = 0; b < n_band; ++b) vk[(size_t)b * P] = R(0);
-            continue;
-        }
-        const R *ak = k == 0 ? u + p : coef + (size_t)(k - 1) * n_band * P + p;
-        double nrm2 = 0.0;
-        for (int b = 0; b < n_band; ++b) {
-            const R t = vk[(size_t)b * P] + sigma_d * psi_scale * ak[(size_t)b * P];
-            nrm2 += (double)t * (double)t;
-        }
-        const double nrm = sqrt(nrm2);
-        const R sc = nrm > (double)lam ? (R)((double)lam / nrm) : R(1);
-        for (int b = 0; b < n_band; ++b) {
-            const R t = vk[(size_t)b * P] + sigma_d * psi_scale * ak[(size_t)b * P];
-            vk[(size_t)b * P] = t * sc;
-        }
-    }
-}
-
-hipError_t launch_pd_primal(bool dbl, bool init, const void *z, void *x, void *d, const void *c, const void *sv,
-                            void *u, int64_t n, double tau, double gamma, double sigma_u, double psi_scale, int warm,
-                            hipStream_t s) {
+hipError_t launch_pd_init(bool dbl, const void *z, void *x, void *d, int64_t n, int warm, hipStream_t s) {
     const int64_t nb = wave_blocks(n);
-#define PDP(T)                                                                                                    \
-    if (init)                                                                                                     \
-        PFB_LAUNCH((pd_primal_kernel<T, true>), nb, 0, s, (const T *)z, (T *)x, (T *)d, (const T *)c,           \
-                   (const T *)sv, (T *)u, n, (T)tau, (T)(1.0 / gamma), (T)sigma_u, (T)psi_scale, warm);          \
-    else                                                                                                          \
-        PFB_LAUNCH((pd_primal_kernel<T, false>), nb, 0, s, (const T *)z, (T *)x, (T *)d, (const T *)c,          \
-                   (const T *)sv, (T *)u, n, (T)tau, (T)(1.0 / gamma), (T)sigma_u, (T)psi_scale, warm);
-    if (dbl) {
-        PDP(double)
-    } else {
-        PDP(float)
-    }
-#undef PDP
+    if (dbl) PFB_LAUNCH(pd_init_kernel<double>, nb, 0, s, (const double *)z, (double *)x, (double *)d, n, warm);
+    else PFB_LAUNCH(pd_init_kernel<float>, nb, 0, s, (const float *)z, (float *)x, (float *)d, n, warm);
     return hipSuccess;
 }
-
-hipError_t launch_pd_dual(bool dbl, bool zero, void *v, const void *u, const void *coef, int nbasis, int n_band,
-                          int64_t P, double sigma_d, double psi_scale, double lam, hipStream_t s) {
-    const int64_t nb = wave_blocks((int64_t)nbasis * P);
-#define PDD(T)                                                                                                  \
-    if (zero)                                                                                                   \
-        PFB_LAUNCH((pd_dual_kernel<T, true>), nb, 0, s, (T *)v, (const T *)u, (const T *)coef, nbasis, n_band, \
-                   P, (T)sigma_d, (T)psi_scale, (T)lam);                                                        \
-    else                                                                                                        \
-        PFB_LAUNCH((pd_dual_kernel<T, false>), nb, 0, s, (T *)v, (const T *)u, (const T *)coef, nbasis, n_band,\
-                   P, (T)sigma_d, (T)psi_scale, (T)lam);
-    if (dbl) {
-        PDD(double)
-    } else {
-        PDD(float)
-    }
-#undef PDD
+// v = 0, the cold dual variable
+template <typename R> __global__ __launch_bounds__(kThreads) void pd_zero_kernel(R *v, int64_t n) {
+    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads) v[i] = R(0);
+}
+hipError_t launch_pd_zero(bool dbl, void *v, int64_t n, hipStream_t s) {
+    const int64_t nb = wave_blocks(n);
+    if (dbl) PFB_LAUNCH(pd_zero_kernel<double>, nb, 0, s, (double *)v, n);
+    else PFB_LAUNCH(pd_zero_kernel<float>, nb, 0, s, (float *)v, n);
     return hipSuccess;
 }
 
