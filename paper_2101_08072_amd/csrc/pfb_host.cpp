@@ -222,7 +222,7 @@ struct pfb_plan {
     bool counted = false, ws_ready = false, psf_ready = false;
     size_t o_freq = 0, o_cb = 0, o_cheb = 0, o_tw = 0, o_flagged = 0, o_flagcur = 0;
     size_t o_planes = 0, o_t1 = 0, o_vals = 0, o_psfimg = 0;
-    size_t o_t1c = 0, o_psfhat = 0, o_vec = 0, o_partials = 0, o_scal = 0, o_absmax = 0;
+    size_t o_t1c = 0, o_psfhat = 0, o_vec = 0, o_partials = 0, o_scal = 0, o_ctr = 0, o_absmax = 0;
     size_t planes_bytes = 0, t_bytes = 0, vec_bytes = 0;
     size_t o_sorttmp = 0;   // scratch for the plan-time sort (aliases the w-plane area when it fits)
     Profiler prof;
@@ -484,15 +484,20 @@ pfb_status cg_solve(pfb_plan *P, const void *g, void *y, double sigma, int iters
     void *r = v, *p = v + P->vec_bytes, *ap = v + 2 * P->vec_bytes;
     const int vparts = vec_partials_per_band(Pn);
     const int cparts = conv_partials_per_band(d, ca);
+    // few blocks: the kernels reduce their own partials (no reduce launches)
+    unsigned *const ctr = reinterpret_cast<unsigned *>(P->p(P->o_ctr));
+    unsigned *const vctr = (int64_t)nb * vparts <= kFuseReduceBlocks ? ctr : nullptr;
+    ca.ctr = (int64_t)nb * cparts <= kFuseReduceBlocks ? ctr : nullptr;
+    ca.red_op = RED_ALPHA;
     LAUNCH_OK(launch_vec(d, VEC_CG_INIT, nb, Pn, ca.partials, ca.max_partials, ca.scal, const_cast<void *>(g), y, r,
-                         p, nullptr, 0, 0, s));
-    LAUNCH_OK(launch_reduce(RED_SET_RR, nb, ca.partials, vparts, ca.max_partials, ca.scal, s));
+                         p, nullptr, 0, 0, s, vctr, RED_SET_RR));
+    if (!vctr) LAUNCH_OK(launch_reduce(RED_SET_RR, nb, ca.partials, vparts, ca.max_partials, ca.scal, s));
     for (int it = 0; it < iters; ++it) {
         LAUNCH_OK(launch_psf_conv(d, ca, r, p, ap, p, sigma, CONV_IN_CG_P, CONV_OUT_CG, s));
-        LAUNCH_OK(launch_reduce(RED_ALPHA, nb, ca.partials, cparts, ca.max_partials, ca.scal, s));
+        if (!ca.ctr) LAUNCH_OK(launch_reduce(RED_ALPHA, nb, ca.partials, cparts, ca.max_partials, ca.scal, s));
         LAUNCH_OK(launch_vec(d, VEC_CG_UPDATE, nb, Pn, ca.partials, ca.max_partials, ca.scal, nullptr, y, r, p, ap,
-                             0, 0, s));
-        LAUNCH_OK(launch_reduce(RED_BETA, nb, ca.partials, vparts, ca.max_partials, ca.scal, s));
+                             0, 0, s, vctr, RED_BETA));
+        if (!vctr) LAUNCH_OK(launch_reduce(RED_BETA, nb, ca.partials, vparts, ca.max_partials, ca.scal, s));
         if (iters_done) *iters_done = it + 1;
         if (tol > 0.0) {
             std::vector<double> sc((size_t)nb * 8);
@@ -780,6 +785,7 @@ pfb_status count_and_layout(pfb_plan *P, char *tmp, hipStream_t stream) {
     P->o_vec = L.take(6 * P->vec_bytes);
     {
         ConvArgs ca{};
+        ca.n_band = nb;
         ca.nx = pr.nx;
         ca.ny = pr.ny;
         ca.lx = P->conv_lx;
@@ -788,6 +794,7 @@ pfb_status count_and_layout(pfb_plan *P, char *tmp, hipStream_t stream) {
     }
     P->o_partials = L.take((size_t)nb * P->max_partials * sizeof(double));
     P->o_scal = L.take((size_t)nb * 8 * sizeof(double));
+    P->o_ctr = L.take((size_t)nb * sizeof(unsigned));
     P->o_absmax = L.take((kAbsmaxBlocks + 64) * sizeof(float));
     P->ws_bytes = L.off;
     P->counted = true;
@@ -1182,6 +1189,7 @@ pfb_status pfb_plan_set_workspace(pfb_plan *P, void *dev, size_t bytes, hipStrea
         }
     }
     HIP_OK(hipMemsetAsync(P->p(P->o_scal), 0, (size_t)pr.n_band * 8 * sizeof(double), s));
+    HIP_OK(hipMemsetAsync(P->p(P->o_ctr), 0, (size_t)pr.n_band * sizeof(unsigned), s));   // zero between kernels
     // per-visibility Hessian values: keep entries that no band batch writes finite
     HIP_OK(hipMemsetAsync(P->p(P->o_vals), 0, (size_t)pr.n_row * pr.n_chan * 2 * P->rsz, s));
     P->ws_ready = true;

@@ -153,7 +153,12 @@ struct ConvArgs {
     double *partials;          // [n_band][max_partials]
     int max_partials;
     double *scal;              // [n_band][8] device scalars
+    unsigned *ctr;             // non-null: the partials' kernel reduces them itself (red_op)
+    int red_op;
 };
+// most blocks (over all bands) of a kernel that reduces its own partials: more than the
+// chip holds at once, and the counting at every block's end costs more than a launch
+constexpr int kFuseReduceBlocks = 1024;
 enum ConvIn { CONV_IN_X = 0, CONV_IN_CG_P = 1, CONV_IN_SCALED = 2 };
 enum ConvOut { CONV_OUT_Y = 0, CONV_OUT_SUB = 1, CONV_OUT_CG = 2, CONV_OUT_NORM = 3, CONV_OUT_DOT = 4 };
 // y = PSF * x with optional fused prologue / epilogue:
@@ -182,8 +187,8 @@ enum VecOp {
     VEC_NORM = 5,        // partial x.x
 };
 hipError_t launch_vec(bool dbl, int op, int n_band, int64_t P, double *partials, int max_partials,
-                      const double *scal, void *x, void *y, void *r, void *p, const void *ap,
-                      double gamma, double lam, hipStream_t s);
+                      double *scal, void *x, void *y, void *r, void *p, const void *ap,
+                      double gamma, double lam, hipStream_t s, unsigned *ctr = nullptr, int red_op = 0);
 int vec_partials_per_band(int64_t P);
 
 // scalar slots in scal[b*8 + k]

@@ -124,6 +124,69 @@ template <int NT = kThreads> __device__ double block_sum(double v, double *red) 
     return t;
 }
 
+// ---------------------------------------------------------------------------
+// device-side scalar reductions
+// ---------------------------------------------------------------------------
+// the update of a band's scalars sc from the sum t of its partials
+__device__ __forceinline__ void apply_reduce(int op, double t, double *sc) {
+    switch (op) {
+        case RED_SET_RR:
+            sc[S_RR] = t;
+            sc[S_RR0] = t;
+            sc[S_BETA] = 0.0;
+            break;
+        case RED_ALPHA:
+            sc[S_PAP] = t;
+            sc[S_ALPHA] = (t > 0.0 && sc[S_RR] > 0.0) ? sc[S_RR] / t : 0.0;
+            break;
+        case RED_BETA:
+            sc[S_BETA] = sc[S_RR] > 0.0 ? t / sc[S_RR] : 0.0;
+            sc[S_RR] = t;
+            break;
+        case RED_INV_SQRT:
+            sc[S_SCALE] = t > 0.0 ? 1.0 / sqrt(t) : 0.0;
+            break;
+        case RED_LAMBDA:
+            sc[S_LAMBDA] = t;
+            break;
+        default:
+            sc[S_TMP] = t;
+            break;
+    }
+}
+
+// The end of a block that adds a partial sum: without a counter the partial is stored
+// for reduce_kernel.  With one (few blocks, where a launch costs more than the tail of
+// a block), the band's last block sums the band's n_part partials in their fixed order
+// and updates the scalars, which the next kernel reads.  Partials and counter only move
+// through agent-scope atomics (coherent across the XCDs' L2s), each partial complete
+// before its block counts itself; the counter is zero again afterwards.
+template <int NT>
+__device__ __forceinline__ void finish_partial(double t, int k, int n_part, double *partials, double *sc, unsigned *ctr,
+                                               int op, double *red) {
+    if (!ctr) {
+        if (threadIdx.x == 0) partials[k] = t;
+        return;
+    }
+    __shared__ int last;
+    if (threadIdx.x == 0) {
+        __hip_atomic_store(partials + k, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_s_waitcnt(0);
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        last = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)n_part - 1u;
+    }
+    __syncthreads();
+    if (!last) return;
+    double v = 0.0;
+    for (int i = threadIdx.x; i < n_part; i += NT)
+        v += __hip_atomic_load(partials + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const double sum = block_sum<NT>(v, red);
+    if (threadIdx.x == 0) {
+        __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        apply_reduce(op, sum, sc);
+    }
+}
+
 // The value of an entry as its listing takes it: conjugated where the entry is
 // listed at -(u, v, w) (sign bit of fw).  Hessian values never need it: they are
 // degridded and gridded at the same listing.
@@ -1965,8 +2028,18 @@ __global__ __launch_bounds__(row_threads<LOG2L>(), row_min_waves<LOG2L>()) void 
 // planes in registers before the grid correction; the degrid pass keeps the
 // corrected image column in registers and writes, for every plane, only the
 // rows of tile rows the forward row pass reads.
-template <typename R, int LOG2N, int C> struct WCols {
+//
+// Few columns (PL): with the planes taken one after another, an image of 512 columns
+// ran on 64 blocks, 128 columns on 16.  There a block takes ONE column and C of its
+// planes at a time (the C vectors of the LDS buffer are planes, not columns); the grid
+// pass sums its C accumulators at the end.  Used below kColsFewBlocks blocks of the
+// column form (two 512-thread blocks for every CU): at 512^2, 9 planes, grid columns
+// 55 -> FIGG us, degrid columns 60 -> FIGD us; from there on the column form fills the
+// chip and reads whole 64-byte pieces per block.
+constexpr int kColsFewBlocks = 512;
+template <typename R, int LOG2N, int C, bool PL> struct WCols {
     static constexpr int N = 1 << LOG2N;
+    static constexpr int NPL = PL ? C : 1;   // planes of a round
     static constexpr int NT0 = C * N / 8;   // one radix-8 butterfly per thread and stage
     static constexpr int NT = NT0 < 64 ? 64 : NT0;
     static_assert(NT0 <= 1024, "at most 1024 threads per block");
@@ -1974,9 +2047,9 @@ template <typename R, int LOG2N, int C> struct WCols {
     static constexpr int ITER = (C * (N / R0) + NT - 1) / NT;   // innermost-stage items per thread
     // the transform buffer, the twiddle tables and two per-thread arrays of 8 values
     // that live across the plane loop (kept in LDS, not in registers)
-    // plus two buffers of a plane's tile-row flags (at most gx / 8 = N / 4 tile rows)
+    // plus two buffers of a round's tile-row flags (at most gx / 8 = N / 4 tile rows per plane)
     static constexpr size_t other =
-        (size_t)C * Lds<R, LOG2N>::ld * sizeof(cplx<R>) + 2 * 8 * (size_t)NT * sizeof(R) + 2 * (size_t)(N / 4);
+        (size_t)C * Lds<R, LOG2N>::ld * sizeof(cplx<R>) + 2 * 8 * (size_t)NT * sizeof(R) + 2 * (size_t)(NPL * (N / 4));
     static constexpr int SE = tw_stage_entries<R, LOG2N>(other);
     static constexpr size_t lds = other + (kTwEntries + SE) * sizeof(cplx<R>);
 };
@@ -2002,9 +2075,10 @@ template <int NSUB> __device__ __forceinline__ WColsBlock wcols_block(int n_bb, 
     return WColsBlock{gi % G, jb % NSUB, gi / G, gi < n_bb * G};
 }
 
-template <typename R, int LOG2N, int C>
-__global__ __launch_bounds__((WCols<R, LOG2N, C>::NT)) void wgrid_cols_kernel(XformArgs a) {
-    using K = WCols<R, LOG2N, C>;
+template <typename R, int LOG2N, int C, bool PL>
+__global__ __launch_bounds__((WCols<R, LOG2N, C, PL>::NT)) void wgrid_cols_kernel(XformArgs a) {
+    using K = WCols<R, LOG2N, C, PL>;
+    constexpr int NPL = K::NPL;
     using LD = Lds<R, LOG2N>;
     using P = FftPlan<LOG2N>;
     constexpr int N = K::N, NT = K::NT, S = P::NSTAGE, M = N / 8, R0 = K::R0, IT = K::ITER;
@@ -2016,12 +2090,13 @@ __global__ __launch_bounds__((WCols<R, LOG2N, C>::NT)) void wgrid_cols_kernel(Xf
     const TwTab<R> tt = tw_fill<R, NT, LOG2N, K::SE>(twl, reinterpret_cast<const cplx<R> *>(a.tw), a.log2_lmax);
     const int gx = a.g.gx, nx = a.g.nx, ny = a.g.ny, hx = nx / 2;
     const int G = (ny + CG - 1) / CG;
-    const WColsBlock wb = wcols_block<CG / C>(a.n_bb, G);
+    constexpr int CW = PL ? 1 : C;   // columns of a block
+    const WColsBlock wb = wcols_block<CG / CW>(a.n_bb, G);
     if (!wb.ok) return;
     const int b = a.band0 + wb.bb;
     const BandDev bd = a.bands[b];
     const int nw = a.g.flat ? 1 : bd.nw;
-    const int col0 = wb.g * CG + wb.sub * C;
+    const int col0 = wb.g * CG + wb.sub * CW;
     const int shg = a.log2_lmax - (LOG2N + 1), shn = a.log2_lmax - LOG2N;
     const int lgT = __builtin_ctz(a.g.T);
     // gx = 2 nx (power-of-two sides): G'[u] = G[u] (-i)^u, so the even half's
@@ -2032,7 +2107,8 @@ __global__ __launch_bounds__((WCols<R, LOG2N, C>::NT)) void wgrid_cols_kernel(Xf
     const int hs = qs ? N / 2 : 0;
     // first stage: thread (c, jr) owns the butterfly of rows u' = jr + t M (t < 8)
     const int c = threadIdx.x % C, jr = threadIdx.x / C;
-    const bool own = jr < M && col0 + c < ny;
+    const int vcol = PL ? 0 : c;   // column of vector c within the block
+    const bool own = jr < M && col0 + vcol < ny;
     // innermost stage: item (it, t) is position gq R0 + t of column cc, natural index i;
     // its n - 1 - sc and accumulator sit in LDS slot (it R0 + t) NT + thread
     cplx<R> ev[IT][R0];
@@ -2048,24 +2124,26 @@ __global__ __launch_bounds__((WCols<R, LOG2N, C>::NT)) void wgrid_cols_kernel(Xf
             const int i = dit_inv<LOG2N>(gq * R0 + t) ^ hs;
             const int sl = (it * R0 + t) * NT + threadIdx.x;
             accl[sl] = R(0);
-            svl[sl] = (!a.g.flat && id < C * (N / R0) && i < nx && col0 + cc < ny) ? pixel_sm1<R>(i, col0 + cc, a.g) - sc
-                                                                                    : R(0);
+            const int col = col0 + (PL ? 0 : cc);
+            svl[sl] = (!a.g.flat && id < C * (N / R0) && i < nx && col < ny) ? pixel_sm1<R>(i, col, a.g) - sc : R(0);
         }
     }
     uint8_t *const flb = reinterpret_cast<uint8_t *>(accl + 8 * NT);   // two buffers of ntx flags
-    for (int j = 0; j < nw; ++j) {
-        // the plane's tile-row flags go to LDS, so that the row loads do not wait on flag loads
-        const uint8_t *orow = a.occ_row + ((size_t)b * a.g.nwmax + j) * a.g.ntx;
-        uint8_t *const fl = flb + (j & 1) * (N / 4);
+    for (int j0 = 0; j0 < nw; j0 += NPL) {
+        // the planes' tile-row flags go to LDS, so that the row loads do not wait on flag loads
+        const uint8_t *orow = a.occ_row + ((size_t)b * a.g.nwmax + j0) * a.g.ntx;
+        uint8_t *const fls = flb + (j0 / NPL & 1) * (NPL * (N / 4));
+        const uint8_t *const fl = fls + (PL ? c * a.g.ntx : 0);   // vector c's plane
         int any = 0;
-        for (int k = threadIdx.x; k < a.g.ntx; k += NT) {
-            fl[k] = orow[k];
-            any |= orow[k];
+        const int nfl = min(NPL, nw - j0) * a.g.ntx;
+        for (int k = threadIdx.x; k < NPL * a.g.ntx; k += NT) {
+            const uint8_t f = k < nfl ? orow[k] : 0;
+            fls[k] = f;
+            any |= f;
         }
         if (!__syncthreads_or(any)) continue;   // (also orders the twiddle table and the last plane's LDS reads)
         const cplx<R> *T = reinterpret_cast<const cplx<R> *>(a.t1) +
-                           (((size_t)wb.bb * a.g.nwmax + j) * G + wb.g) * (size_t)gx * CG + wb.sub * C;
-        const R wj = (R)(bd.w0 + j * bd.dw);
+                           (((size_t)wb.bb * a.g.nwmax + j0 + (PL ? c : 0)) * G + wb.g) * (size_t)gx * CG + wb.sub * CW + vcol;
 #pragma unroll 1
         for (int p = 0; p < 2; ++p) {
             // inverse N-point DFT of the even (p = 0) or odd (p = 1) rows by decimation in
@@ -2076,7 +2154,7 @@ __global__ __launch_bounds__((WCols<R, LOG2N, C>::NT)) void wgrid_cols_kernel(Xf
                 for (int t = 0; t < 8; ++t) {   // all loads first
                     const int u = 2 * (jr + t * M) + p;
                     v[t] = cplx<R>{R(0), R(0)};
-                    if (fl[u >> lgT]) v[t] = T[(size_t)u * CG + c];
+                    if (fl[u >> lgT]) v[t] = T[(size_t)u * CG];
                 }
                 if (!qs) {
 #pragma unroll
@@ -2110,6 +2188,7 @@ __global__ __launch_bounds__((WCols<R, LOG2N, C>::NT)) void wgrid_cols_kernel(Xf
                 const int id = threadIdx.x + it * NT;
                 if (id >= C * (N / R0)) continue;
                 const int cc = id / (N / R0), gq = id - cc * (N / R0);
+                const R wj = (R)(bd.w0 + (j0 + (PL ? cc : 0)) * bd.dw);
                 const cplx<R> *vb = buf + cc * ld + LD::pad(gq * R0);
                 cplx<R> v[R0];
 #pragma unroll
@@ -2136,6 +2215,22 @@ __global__ __launch_bounds__((WCols<R, LOG2N, C>::NT)) void wgrid_cols_kernel(Xf
             if (p == 0) __syncthreads();   // the odd half overwrites the buffer
         }
     }
+    if constexpr (PL) {
+        // the sum over the C planes' accumulators of every row, at the first vector's slot
+        __syncthreads();
+        constexpr int V = N / R0;
+        for (int k = threadIdx.x; k < N; k += NT) {
+            const int gq = k / R0, t = k - gq * R0;
+            R sum = R(0);
+#pragma unroll
+            for (int cc = 0; cc < C; ++cc) {
+                const int id = cc * V + gq;
+                sum += accl[(id / NT * R0 + t) * NT + id % NT];
+            }
+            accl[(gq / NT * R0 + t) * NT + gq % NT] = sum;
+        }
+        __syncthreads();
+    }
     R *img = reinterpret_cast<R *>(a.image_out) + (size_t)b * nx * ny;
     const R *corr2d = reinterpret_cast<const R *>(a.corr2d);
 #pragma unroll
@@ -2143,7 +2238,7 @@ __global__ __launch_bounds__((WCols<R, LOG2N, C>::NT)) void wgrid_cols_kernel(Xf
         const int id = threadIdx.x + it * NT;
         const int cc = id / (N / R0), gq = id - cc * (N / R0);
         const int col = col0 + cc;
-        if (id >= C * (N / R0) || col >= ny) continue;
+        if (id >= CW * (N / R0) || col >= ny) continue;
         // the correction factors' loads first (corr2d, or corr_x[i] times corr_y[col])
         R cf[R0];
         const R cy = corr2d ? R(1) : reinterpret_cast<const R *>(a.corr_y)[col];
@@ -2165,9 +2260,10 @@ __global__ __launch_bounds__((WCols<R, LOG2N, C>::NT)) void wgrid_cols_kernel(Xf
     }
 }
 
-template <typename R, int LOG2N, int C>
-__global__ __launch_bounds__((WCols<R, LOG2N, C>::NT)) void wdegrid_cols_kernel(XformArgs a) {
-    using K = WCols<R, LOG2N, C>;
+template <typename R, int LOG2N, int C, bool PL>
+__global__ __launch_bounds__((WCols<R, LOG2N, C, PL>::NT)) void wdegrid_cols_kernel(XformArgs a) {
+    using K = WCols<R, LOG2N, C, PL>;
+    constexpr int NPL = K::NPL;
     using LD = Lds<R, LOG2N>;
     using P = FftPlan<LOG2N>;
     constexpr int N = K::N, NT = K::NT, S = P::NSTAGE, M = N / 8, R0 = K::R0, IT = K::ITER;
@@ -2179,12 +2275,13 @@ __global__ __launch_bounds__((WCols<R, LOG2N, C>::NT)) void wdegrid_cols_kernel(
     const TwTab<R> tt = tw_fill<R, NT, LOG2N, K::SE>(twl, reinterpret_cast<const cplx<R> *>(a.tw), a.log2_lmax);
     const int gx = a.g.gx, nx = a.g.nx, ny = a.g.ny, hx = nx / 2;
     const int G = (ny + CG - 1) / CG;
-    const WColsBlock wb = wcols_block<CG / C>(a.n_bb, G);
+    constexpr int CW = PL ? 1 : C;   // columns of a block
+    const WColsBlock wb = wcols_block<CG / CW>(a.n_bb, G);
     if (!wb.ok) return;
     const int b = a.band0 + wb.bb;
     const BandDev bd = a.bands[b];
     const int nw = a.g.flat ? 1 : bd.nw;
-    const int col0 = wb.g * CG + wb.sub * C;
+    const int col0 = wb.g * CG + wb.sub * CW;
     const int shg = a.log2_lmax - (LOG2N + 1), shn = a.log2_lmax - LOG2N;
     const int lgT = __builtin_ctz(a.g.T);
     // gx = 2 nx (power-of-two sides): w^(-u hx) = i^u = (-1)^k' i^p for u = 2k' + p,
@@ -2195,7 +2292,7 @@ __global__ __launch_bounds__((WCols<R, LOG2N, C>::NT)) void wdegrid_cols_kernel(
     // first stage: thread (c, jr) owns positions jr + t M (t < 8), image rows
     // (jr + t M) ^ hs, of column col
     const int c = threadIdx.x % C, jr = threadIdx.x / C;
-    const int col = col0 + c;
+    const int col = col0 + (PL ? 0 : c);
     const bool own = jr < M;
     // the corrected image value and n - 1 - sc of row t of the thread: LDS slot t NT + thread
     R *const xrl = reinterpret_cast<R *>(buf + C * ld);
@@ -2227,20 +2324,22 @@ __global__ __launch_bounds__((WCols<R, LOG2N, C>::NT)) void wdegrid_cols_kernel(
         }
     }
     uint8_t *const flb = reinterpret_cast<uint8_t *>(svl + 8 * NT);   // two buffers of ntx flags
-    for (int j = 0; j < nw; ++j) {
-        // the plane's tile-row flags go to LDS (two buffers: the last plane's stores may
+    for (int j0 = 0; j0 < nw; j0 += NPL) {
+        // the planes' tile-row flags go to LDS (two buffers: the last round's stores may
         // still read the other), so that the stores do not wait on flag loads
-        const uint8_t *nrow = a.need_row + ((size_t)b * a.g.nwmax + j) * a.g.ntx;
-        uint8_t *const fl = flb + (j & 1) * (N / 4);
+        const uint8_t *nrow = a.need_row + ((size_t)b * a.g.nwmax + j0) * a.g.ntx;
+        uint8_t *const fls = flb + (j0 / NPL & 1) * (NPL * (N / 4));
         int any = 0;
-        for (int k = threadIdx.x; k < a.g.ntx; k += NT) {
-            fl[k] = nrow[k];
-            any |= nrow[k];
+        const int nfl = min(NPL, nw - j0) * a.g.ntx;
+        for (int k = threadIdx.x; k < NPL * a.g.ntx; k += NT) {
+            const uint8_t f = k < nfl ? nrow[k] : 0;
+            fls[k] = f;
+            any |= f;
         }
         if (!__syncthreads_or(any)) continue;   // (also orders the twiddle table and the last plane's LDS reads)
         cplx<R> *T = reinterpret_cast<cplx<R> *>(a.t1) +
-                     (((size_t)wb.bb * a.g.nwmax + j) * G + wb.g) * (size_t)gx * CG + wb.sub * C;
-        const R wj = (R)(bd.w0 + j * bd.dw);
+                     (((size_t)wb.bb * a.g.nwmax + j0) * G + wb.g) * (size_t)gx * CG + wb.sub * CW;
+        const R wj = (R)(bd.w0 + (j0 + (PL ? c : 0)) * bd.dw);
         cplx<R> pv[8];   // x e^(-2 pi i w_j (n - 1 - sc))
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
@@ -2283,7 +2382,10 @@ __global__ __launch_bounds__((WCols<R, LOG2N, C>::NT)) void wdegrid_cols_kernel(
                 const int id = threadIdx.x + it * NT;
                 if (id >= C * (N / R0)) continue;
                 const int cc = id / (N / R0), gq = id - cc * (N / R0);
-                if (col0 + cc >= ny) continue;
+                if (col0 + (PL ? 0 : cc) >= ny) continue;
+                // PL: vector cc is plane j0 + cc of the one column (planes past nw have no set flags)
+                const uint8_t *const fl = fls + (PL ? cc * a.g.ntx : 0);
+                cplx<R> *const Tc = PL ? T + (size_t)cc * G * gx * CG : T + cc;
                 const cplx<R> *vb = buf + cc * ld + LD::pad(gq * R0);
                 cplx<R> v[R0];
 #pragma unroll
@@ -2293,7 +2395,7 @@ __global__ __launch_bounds__((WCols<R, LOG2N, C>::NT)) void wdegrid_cols_kernel(
                 for (int t = 0; t < R0; ++t) {
                     const int u = 2 * dit_inv<LOG2N>(gq * R0 + t) + p;
                     if (fl[u >> lgT])
-                        T[(size_t)u * CG + cc] = qs ? v[t] : v[t] * twiddle<R, true>(tt, ((u * hx) & (gx - 1)) << shg);
+                        Tc[(size_t)u * CG] = qs ? v[t] : v[t] * twiddle<R, true>(tt, ((u * hx) & (gx - 1)) << shg);
                 }
             }
             if (p == 0) __syncthreads();   // the odd half overwrites the buffer
@@ -2310,14 +2412,31 @@ static hipError_t wcols_launch(const XformArgs &a, hipStream_t s) {
         } else {
             constexpr int C = wcols_c<R, LG>();
             constexpr int CG = plane_cg<R>();
-            using K = WCols<R, LG, C>;
             const int G = (a.g.ny + CG - 1) / CG;
-            const int nb = ((a.n_bb * G + 7) / 8) * 8 * (CG / C);
-            if (GRID) PFB_LAUNCH_NT((wgrid_cols_kernel<R, LG, C>), nb, K::NT, K::lds, s, a);
-            else PFB_LAUNCH_NT((wdegrid_cols_kernel<R, LG, C>), nb, K::NT, K::lds, s, a);
+            const int rounds = ((a.n_bb * G + 7) / 8) * 8;   // column groups, padded to the XCDs
+            if constexpr (C > 1) {
+                if (!a.g.flat && rounds * (CG / C) < kColsFewBlocks) {
+                    using K = WCols<R, LG, C, true>;
+                    if (GRID) PFB_LAUNCH_NT((wgrid_cols_kernel<R, LG, C, true>), rounds * CG, K::NT, K::lds, s, a);
+                    else PFB_LAUNCH_NT((wdegrid_cols_kernel<R, LG, C, true>), rounds * CG, K::NT, K::lds, s, a);
+                    return hipSuccess;
+                }
+            }
+            using K = WCols<R, LG, C, false>;
+            const int nb = rounds * (CG / C);
+            if (GRID) PFB_LAUNCH_NT((wgrid_cols_kernel<R, LG, C, false>), nb, K::NT, K::lds, s, a);
+            else PFB_LAUNCH_NT((wdegrid_cols_kernel<R, LG, C, false>), nb, K::NT, K::lds, s, a);
             return hipSuccess;
         }
     });
+}
+
+// rows per block of the plane row passes: at most cmax, fewer where the listed tile rows
+// would not give every CU two blocks
+static int plane_rows_per_block(int cmax, int n_list, int T) {
+    int C = cmax;
+    while (C > 1 && (int64_t)n_list * (T / C) < 512) C /= 2;
+    return C;
 }
 
 template <typename R>
@@ -2325,7 +2444,7 @@ static hipError_t grid_xform_t(const XformArgs &a, hipStream_t s) {
     const int lgy = __builtin_ctz(a.g.gy);
     hipError_t e = dispatch_int<5, 14>(lgy, [&](auto Lc) -> hipError_t {
         constexpr int LG = decltype(Lc)::value;
-        const int C = std::min(rows_per_block<R, LG>(), a.g.T);
+        const int C = plane_rows_per_block(std::min(rows_per_block<R, LG>(), a.g.T), a.n_occ_list, a.g.T);
         const size_t lds = row_lds<R, LG>(C);
         const int64_t nb = (int64_t)a.n_occ_list * (a.g.T / C);
         if (nb > 0) PFB_LAUNCH_NT((g1_rows_kernel<R, LG>), nb, row_threads<LG>(), lds, s, a, C);
@@ -2342,7 +2461,7 @@ static hipError_t degrid_xform_t(const XformArgs &a, hipStream_t s) {
     const int lgy = __builtin_ctz(a.g.gy);
     return dispatch_int<5, 14>(lgy, [&](auto Lc) -> hipError_t {
         constexpr int LG = decltype(Lc)::value;
-        const int C2 = std::min(rows_per_block<R, LG>(), a.g.T);
+        const int C2 = plane_rows_per_block(std::min(rows_per_block<R, LG>(), a.g.T), a.n_need_list, a.g.T);
         const size_t lds = row_lds<R, LG>(C2);
         const int64_t nb = (int64_t)a.n_need_list * (a.g.T / C2);
         if (nb > 0) PFB_LAUNCH_NT((d3_rows_kernel<R, LG>), nb, row_threads<LG>(), lds, s, a, C2);
@@ -2675,6 +2794,11 @@ template <typename R, int LG> constexpr int conv_cgc() {
 template <typename R, int LG> constexpr int conv_layout_cg() {
     return conv_cgc<R, LG>() < 32 / (int)sizeof(cplx<R>) ? 32 / (int)sizeof(cplx<R>) : conv_cgc<R, LG>();
 }
+// columns per block where there are few: one wave of radix-8 butterflies, or one column
+template <typename R, int LG> constexpr int conv_few() {
+    constexpr int c = 512 >> LG;
+    return c < 1 ? 1 : (c < conv_cgc<R, LG>() ? c : conv_cgc<R, LG>());
+}
 int conv_group_cols(bool dbl, int nx) {
     int C = 1;
     (void)dispatch_int<4, 12>(__builtin_ctz(nx), [&](auto Lc) -> hipError_t {
@@ -2753,7 +2877,8 @@ __global__ __launch_bounds__(row_threads<LOG2L>(), row_min_waves<LOG2L>()) void 
         });
     if (OUT == CONV_OUT_CG || OUT == CONV_OUT_NORM || OUT == CONV_OUT_DOT) {
         const double t = block_sum<row_threads<LOG2L>()>(part, red);
-        if (threadIdx.x == 0) a.partials[(size_t)b * a.max_partials + ig] = t;
+        finish_partial<row_threads<LOG2L>()>(t, ig, ngrp, a.partials + (size_t)b * a.max_partials, a.scal + b * 8,
+                                             a.ctr ? a.ctr + b : nullptr, a.red_op, red);
     }
 }
 
@@ -2763,10 +2888,21 @@ static hipError_t conv_columns(const ConvArgs &a, int psf, hipStream_t s) {
         constexpr int LG = decltype(Lc)::value;
         constexpr int CG = conv_layout_cg<R, LG>();
         constexpr int CB = conv_cgc<R, LG>();   // columns per block
-        using K = ConvCols<R, LG, CB>;
         if (a.cgc != CG) return hipErrorInvalidValue;
         const int G = (a.ly / 2 + CG) / CG;
-        const int nb = ((a.n_band * G + 7) / 8) * 8 * (CG / CB);
+        const int rounds = ((a.n_band * G + 7) / 8) * 8;   // column groups, padded to the XCDs
+        // few columns: the fewest per block that still fill a wave (512^2, one band: 72
+        // blocks of 8 columns leave most CUs idle; FIGC us at one column per block)
+        constexpr int CS = conv_few<R, LG>();
+        if constexpr (CS < CB) {
+            if (!psf && rounds * (CG / CB) < kColsFewBlocks) {
+                using K = ConvCols<R, LG, CS>;
+                PFB_LAUNCH_NT((conv_cols_kernel<R, LG, CS, CG, false>), rounds * (CG / CS), K::NT, K::lds, s, a);
+                return hipSuccess;
+            }
+        }
+        using K = ConvCols<R, LG, CB>;
+        const int nb = rounds * (CG / CB);
         if (psf) PFB_LAUNCH_NT((conv_cols_kernel<R, LG, CB, CG, true>), nb, K::NT, K::lds, s, a);
         else PFB_LAUNCH_NT((conv_cols_kernel<R, LG, CB, CG, false>), nb, K::NT, K::lds, s, a);
         return hipSuccess;
@@ -2774,10 +2910,11 @@ static hipError_t conv_columns(const ConvArgs &a, int psf, hipStream_t s) {
 }
 
 // row pairs per block of the row passes: at most cmax, and a power of two that
-// divides the nx / 2 pairs of the image
-static int conv_row_pairs(int cmax, int nx) {
+// divides the nx / 2 pairs of the image; fewer where the bands' row pairs would not
+// give every CU a block
+static int conv_row_pairs(int cmax, int nx, int n_band) {
     int C = 1;
-    while (2 * C <= cmax && (nx / 2) % (2 * C) == 0) C *= 2;
+    while (2 * C <= cmax && (nx / 2) % (2 * C) == 0 && (int64_t)n_band * (nx / (4 * C)) >= 256) C *= 2;
     return C;
 }
 
@@ -2787,7 +2924,7 @@ static hipError_t psf_conv_t(const ConvArgs &a, const void *x, void *aux_in, voi
     const int lg = __builtin_ctz(a.ly);
     hipError_t e = dispatch_int<5, 14>(lg, [&](auto Lc) -> hipError_t {
         constexpr int LG = decltype(Lc)::value;
-        const int C = conv_row_pairs(rows_per_block<R, LG>(), a.nx);   // vectors = row pairs
+        const int C = conv_row_pairs(rows_per_block<R, LG>(), a.nx, a.n_band);   // vectors = row pairs
         const size_t lds = row_lds<R, LG>(C);
         const int nb = a.n_band * (a.nx / (2 * C));
         const R *xr = reinterpret_cast<const R *>(x);
@@ -2802,7 +2939,7 @@ static hipError_t psf_conv_t(const ConvArgs &a, const void *x, void *aux_in, voi
     if (e != hipSuccess) return e;
     return dispatch_int<5, 14>(lg, [&](auto Lc) -> hipError_t {
         constexpr int LG = decltype(Lc)::value;
-        const int C = conv_row_pairs(rows_per_block<R, LG>(), a.nx);   // vectors = row pairs
+        const int C = conv_row_pairs(rows_per_block<R, LG>(), a.nx, a.n_band);   // vectors = row pairs
         const size_t lds = row_lds<R, LG>(C);
         const int nb = a.n_band * (a.nx / (2 * C));
         R *yr = reinterpret_cast<R *>(y);
@@ -2834,7 +2971,7 @@ int conv_partials_per_band(bool dbl, const ConvArgs &a) {
         C = dbl ? rows_per_block<double, LG>() : rows_per_block<float, LG>();
         return hipSuccess;
     });
-    return a.nx / (2 * conv_row_pairs(C, a.nx));
+    return a.nx / (2 * conv_row_pairs(C, a.nx, a.n_band));
 }
 
 template <typename R>
@@ -2869,8 +3006,8 @@ int vec_partials_per_band(int64_t P) {
 
 template <typename R, int OP>
 __global__ __launch_bounds__(kThreads) void vec_kernel(int64_t P, int nblk, double *partials, int max_partials,
-                                                       const double *scal, R *x, R *y, R *r, R *p, const R *ap,
-                                                       R gamma, R lam) {
+                                                       double *scal, R *x, R *y, R *r, R *p, const R *ap, R gamma,
+                                                       R lam, unsigned *ctr, int red_op) {
     __shared__ double red[kThreads / 64];
     const int b = blockIdx.x / nblk;
     const int kb = blockIdx.x - b * nblk;
@@ -2905,19 +3042,20 @@ __global__ __launch_bounds__(kThreads) void vec_kernel(int64_t P, int nblk, doub
     }
     if (OP == VEC_CG_INIT || OP == VEC_CG_UPDATE || OP == VEC_DOT || OP == VEC_NORM) {
         const double t = block_sum(part, red);
-        if (threadIdx.x == 0) partials[(size_t)b * max_partials + kb] = t;
+        finish_partial<kThreads>(t, kb, nblk, partials + (size_t)b * max_partials, scal + b * 8, ctr ? ctr + b : nullptr,
+                                 red_op, red);
     }
 }
 
 hipError_t launch_vec(bool dbl, int op, int n_band, int64_t P, double *partials, int max_partials,
-                      const double *scal, void *x, void *y, void *r, void *p, const void *ap, double gamma,
-                      double lam, hipStream_t s) {
+                      double *scal, void *x, void *y, void *r, void *p, const void *ap, double gamma,
+                      double lam, hipStream_t s, unsigned *ctr, int red_op) {
     const int nblk = vec_partials_per_band(P);
     const int nb = n_band * nblk;
 #define VEC_CASE(T, OPV)                                                                                    \
     case OPV:                                                                                               \
         PFB_LAUNCH((vec_kernel<T, OPV>), nb, 0, s, P, nblk, partials, max_partials, scal, (T *)x, (T *)y, \
-                   (T *)r, (T *)p, (const T *)ap, (T)gamma, (T)lam);                                       \
+                   (T *)r, (T *)p, (const T *)ap, (T)gamma, (T)lam, ctr, red_op);                                       \
         break;
     if (dbl) {
         switch (op) {
@@ -2945,7 +3083,7 @@ hipError_t launch_vec(bool dbl, int op, int n_band, int64_t P, double *partials,
 }
 
 // One workgroup per band sums that band's partials (fixed order) and updates
-// the band's scalars.
+// the band's scalars (kernels of few blocks do this themselves: finish_partial).
 __global__ __launch_bounds__(kThreads) void reduce_kernel(int op, const double *partials, int n_part,
                                                           int max_partials, double *scal) {
     __shared__ double red[kThreads / 64];
@@ -2954,31 +3092,7 @@ __global__ __launch_bounds__(kThreads) void reduce_kernel(int op, const double *
     for (int k = threadIdx.x; k < n_part; k += kThreads) v += partials[(size_t)b * max_partials + k];
     const double t = block_sum(v, red);
     if (threadIdx.x != 0) return;
-    double *sc = scal + b * 8;
-    switch (op) {
-        case RED_SET_RR:
-            sc[S_RR] = t;
-            sc[S_RR0] = t;
-            sc[S_BETA] = 0.0;
-            break;
-        case RED_ALPHA:
-            sc[S_PAP] = t;
-            sc[S_ALPHA] = (t > 0.0 && sc[S_RR] > 0.0) ? sc[S_RR] / t : 0.0;
-            break;
-        case RED_BETA:
-            sc[S_BETA] = sc[S_RR] > 0.0 ? t / sc[S_RR] : 0.0;
-            sc[S_RR] = t;
-            break;
-        case RED_INV_SQRT:
-            sc[S_SCALE] = t > 0.0 ? 1.0 / sqrt(t) : 0.0;
-            break;
-        case RED_LAMBDA:
-            sc[S_LAMBDA] = t;
-            break;
-        default:
-            sc[S_TMP] = t;
-            break;
-    }
+    apply_reduce(op, t, scal + b * 8);
 }
 
 hipError_t launch_reduce(int op, int n_band, const double *partials, int n_part, int max_partials, double *scal,
