@@ -167,7 +167,7 @@ struct GridderHost {
     // band-major, with per-band starts (n_band + 1)
     std::vector<int32_t> occ_list, need_list;
     std::vector<int> occ_list_start, need_list_start;
-    bool mfma = false;                   // FP32 w-stacked: matrix-core spread (window sort, phase table)
+    bool mfma = false;                   // FP32 w-stacked gridder: phase table of the entries
     int sort_rb = 1, sort_cb = 1;        // sort blocks of base rows x columns
     int64_t n_entries = 0;
     size_t o_sortitems = 0;
@@ -433,6 +433,7 @@ SpreadLaunch spread_args(const pfb_plan *P, const GridderHost &G, int b0, int nb
     s.bands = G.d_bands;
     s.work = G.d_gwork + G.gband_start[b0];
     s.n_work = G.gband_start[b0 + nbb] - G.gband_start[b0];
+    s.n_entries = (G.offsets[(size_t)(b0 + nbb) * (G.keys() / G.g.n_band)] - G.offsets[(size_t)b0 * (G.keys() / G.g.n_band)]);
     s.offsets = G.d_offsets;
     s.recs = G.d_recs;
     s.omega = G.d_omega;
@@ -979,13 +980,14 @@ pfb_status pfb_plan_create(pfb_plan **out, const pfb_problem *prob, const pfb_op
         M.g.nwmax = std::max(M.g.nwmax, bd.nw);
     }
     M.mfma = !dbl && !opt.flat;
-    if (M.mfma) mfma_window(opt.support, &M.sort_rb, &M.sort_cb);
+    if (!dbl) mfma_window(opt.support, opt.flat != 0, &M.sort_rb, &M.sort_cb);
     GridderHost &Q = P->psf;
     Q.g = base_geom(*P, 2 * pr.nx, 2 * pr.ny, true);
     Q.bands.assign(pr.n_band, BandDev{0.0, 1.0, 0.0, 1, 1, 0});
     Q.g.nj0max = 1;
     Q.g.nwmax = 1;
     Q.corr2d = false;
+    if (!dbl) mfma_window(opt.support, true, &Q.sort_rb, &Q.sort_cb);
 
     *out = P;
     return PFB_OK;

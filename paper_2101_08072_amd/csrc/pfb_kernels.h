@@ -59,6 +59,7 @@ struct SpreadLaunch {
     const BandDev *bands;
     const GridWork *work;
     int n_work;
+    int64_t n_entries;    // entries of these bands
     const int64_t *offsets;
     const void *recs, *omega;
     const void *vis;      // VMODE 0: caller visibilities; VMODE 2: values in home-list order
@@ -66,12 +67,12 @@ struct SpreadLaunch {
     int band0;
     int vmode;            // 0 data, 1 unit visibilities, 2 precomputed values
     const float *absmax;  // FP32 path: device scalar, max |z| over active visibilities
-    const void *phase;    // FP32 w-stacked gridder: exp(2 pi i s_c w) per entry (selects the MFMA spread)
+    const void *phase;    // FP32 w-stacked gridder: exp(2 pi i s_c w) per entry
     const uint32_t *home_pos;  // VMODE 2: per entry, the home-list position of its visibility
 };
 // Window of the MFMA spread for support W (4..8): footprints whose base cells lie
 // in a block of rb rows x cb columns share one accumulator tile.
-void mfma_window(int W, int *rb, int *cb);
+void mfma_window(int W, bool flat, int *rb, int *cb);
 // LDS bytes per block of the spread and interpolation kernels (the larger)
 size_t gridder_lds_bytes(bool dbl, int W, int T, bool flat);
 constexpr size_t kMaxLdsBytes = 160 * 1024;

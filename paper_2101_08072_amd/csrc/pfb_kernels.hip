@@ -511,14 +511,12 @@ hipError_t launch_corr1d(bool dbl, int n, int gsize, const double *cheb, int nch
 // Its bucket lists every visibility whose footprint touches the core (copies
 // included), so every grid cell is accumulated by exactly one workgroup and
 // written to HBM once, coalesced, with no global atomics and no separate zero
-// fill.  A group of LPV lanes handles one visibility: lane j owns footprint
-// column j and loops over the W rows and the W planes.
+// fill.
 //
-// FP32 path: gfx950 LDS float atomics run at a small fraction of the integer
-// rate, so the ring accumulates 64-bit fixed point.  With S = 2^30 / max|z|
-// every contribution z phi_u phi_v phi_w (phi <= 1) becomes an exact int32 and
-// the int64 sums are exact; the store converts back with 1/S.
-// FP64 path: the ring holds doubles updated with LDS float atomics.
+// FP32 path (spread_mfma_kernel): gfx950 LDS float atomics run at a small fraction
+// of the integer rate, so the ring accumulates 64-bit fixed point scaled by
+// S / max|z|; the sums are exact and the store converts back.
+// FP64 path (spread64_kernel): lanes own cells and sum in registers.
 constexpr int kTileThreads = 1024;   // 16 waves share one tile's LDS ring
 
 // true for an infinite or NaN float (all exponent bits set); a bit test, so that no
@@ -545,20 +543,42 @@ __device__ __forceinline__ void fixed_point_scale(float am, float S, float &fsca
     }
 }
 
-template <typename R> struct SpreadAcc { using T = R; };
-template <> struct SpreadAcc<float> { using T = unsigned long long; };
+// FP64 spread: every lane of a wave owns one cell of an 8 x 8 block of the tile and
+// keeps its sums of the W planes q .. q + W - 1 in registers (no atomics: LDS FP64
+// atomics on the W x W x W cells of every entry bounded the kernel at 0.7 lane-adds per
+// cycle and CU: 4.8 ms, now 0.36 ms, for 3.6e5 visibilities at 1024^2, W = 13).  A wave takes its share of a bucket 64 entries at a time: a lane
+// loads one entry and forms its value, and the batch is staged in LDS; then, two entries
+// at a time, 8 + 8 + W lanes each evaluate one 1-D weight (the ES kernel's FP64 square
+// root and exponential are the costly part: once per weight, not once per lane and
+// weight), and every lane adds z U V P[k] to its planes.  After base plane q, plane q is
+// complete: the block's waves add up their sums in wave order (the results are bitwise
+// reproducible) and the first wave writes it.  Blocks of one wave where buckets are
+// short, more where one wave's serial pass would be the launch's tail.
+constexpr int kSpread64Long = 512;   // entries per work item (on average) from which a block has four waves
+template <int W, bool FLAT> struct Spread64 {
+    static constexpr int WW = FLAT ? 1 : W;
+    static constexpr int ENT = 5;                        // fu, fv, fw, Re z, Im z
+    static constexpr int WAVE = 64 * ENT + 2 * 32;       // doubles of a wave: batch, weights of two entries
+    static constexpr size_t lds(int waves) { return (size_t)waves * (WAVE + (waves > 1 ? 128 : 0)) * sizeof(double); }
+};
+// LDS writes of this wave's lanes are seen by its other lanes' later reads
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
-template <typename R, int W, int LPV, bool FLAT, int VMODE>
-__global__ __launch_bounds__(kTileThreads) void spread_kernel(SpreadLaunch a) {
-    using A = typename SpreadAcc<R>::T;
-    constexpr bool FIX = std::is_same<R, float>::value;
-    constexpr int WW = FLAT ? 1 : W;
-    constexpr int NT = kTileThreads;
-    constexpr int NGRP = NT / LPV;
+template <int W, bool FLAT, int VMODE>
+__global__ __launch_bounds__(256, 4) void spread64_kernel(SpreadLaunch a) {
+    using K = Spread64<W, FLAT>;
+    using R = double;
+    constexpr int WW = K::WW, ENT = K::ENT;
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    const int T = a.g.T, TT = T * T;
-    A *sre = reinterpret_cast<A *>(smem_raw);
-    A *sim = sre + WW * TT;
+    const int lane = threadIdx.x & 63, nwave = blockDim.x >> 6;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    R *const ent = reinterpret_cast<R *>(smem_raw) + wv * K::WAVE, *const wgt = ent + 64 * ENT;
+    cplx<R> *const sums = reinterpret_cast<cplx<R> *>(reinterpret_cast<R *>(smem_raw) + nwave * K::WAVE);
+    const int T = a.g.T, nsub = T / 8;                   // 8 x 8 blocks per tile side
     const GridWork wk = a.work[blockIdx.x];
     const BandDev bd = a.bands[wk.band];
     const int ntiles = a.g.ntx * a.g.nty;
@@ -568,133 +588,114 @@ __global__ __launch_bounds__(kTileThreads) void spread_kernel(SpreadLaunch a) {
     const R *omega = reinterpret_cast<const R *>(a.omega);
     const cplx<R> *vis = reinterpret_cast<const cplx<R> *>(a.vis);
     cplx<R> *planes = reinterpret_cast<cplx<R> *>(a.planes);
-    // fixed-point scale (FP32 path)
-    R fscale = R(1), finv = R(1);
-    if constexpr (FIX) fixed_point_scale(*a.absmax, 1073741824.0f, fscale, finv);   // 2^30 / max|z|
-
-    for (int k = threadIdx.x; k < 2 * WW * TT; k += NT) sre[k] = A(0);
-    __syncthreads();
-
-    const int lane = threadIdx.x % LPV;
-    const int grp = threadIdx.x / LPV;
-    const R beta = (R)a.g.beta, inv_hw = R(2) / R(W), hw = R(0.5) * R(W);
-    const R w0 = (R)bd.w0, dw = (R)bd.dw, sc = (R)bd.sc;
+    const R beta = a.g.beta, inv_hw = R(2) / R(W), hw = R(0.5) * R(W);
     const int64_t keybase = ((int64_t)wk.band * ntiles + wk.tile) * a.g.nj0max;
-    const int qstart = FLAT ? 0 : max(0, wk.p0 - W + 1);
+    const int qstart = max(0, wk.p0 - WW + 1);
     const size_t plane_sz = (size_t)a.g.gx * a.g.gy;
+    // weight evaluated by this lane for entry lane / 32 of a pair: rows 0-7, columns 0-7, planes
+    const int wi = lane & 31, wsel = wi < 8 ? 0 : (wi < 16 ? 1 : 2);
+    const int crow = lane >> 3, ccol = lane & 7;
 
-    for (int q = qstart; q < wk.p1; ++q) {
-        if (q < bd.nj0) {
-            // each lane group takes a contiguous run of the bucket, so the groups
-            // working at the same time sit far apart in it (different baselines)
-            const int64_t b0 = a.offsets[keybase + q], n = a.offsets[keybase + q + 1] - b0;
-            const int64_t per = (n + NGRP - 1) / NGRP;
-            const int64_t e_beg = b0 + min(n, grp * per), e_end = b0 + min(n, (grp + 1) * per);
-            for (int64_t e = e_beg; e < e_end; ++e) {
+    for (int sub = 0; sub < nsub * nsub; ++sub) {
+        const int r0 = (sub / nsub) * 8, c0 = (sub % nsub) * 8;
+        R are[WW], aim[WW];
+#pragma unroll
+        for (int k = 0; k < WW; ++k) are[k] = aim[k] = R(0);
+        unsigned live = 0;    // bit k: base plane q - k has entries in this bucket
+        for (int q = qstart; q < wk.p1; ++q) {
+            int64_t b0 = 0, n = 0;
+            if (q < bd.nj0) {
+                b0 = a.offsets[keybase + q];
+                n = a.offsets[keybase + q + 1] - b0;
+            }
+            const int64_t per = (n + nwave - 1) / nwave;
+            const int64_t e_beg = b0 + min(n, wv * per), e_end = b0 + min(n, (wv + 1) * per);
+            const R wbase = wsel == 0 ? R(r0 + wi) : (wsel == 1 ? R(c0 + wi - 8) : R(q + wi - 16));
+            for (int64_t e0 = e_beg; e0 < e_end; e0 += 64) {
+                const int64_t e = min(e0 + lane, e_end - 1);
                 const Rec<R> rec = recs[e];
                 const uint32_t vid = rec.idx & ~kHomeBit;
+                const R fw = dev_abs(rec.fw);
                 cplx<R> z;
                 if (VMODE == 0) {
-                    const R om = omega[e];
-                    const cplx<R> v = entry_conj(rec, vis[vid]);
-                    z = v * cis_cycles<R>((w0 + dev_abs(rec.fw) * dw) * sc) * om;
+                    z = entry_conj(rec, vis[vid]) * omega[e];
+                    if (!FLAT) z = z * cis_cycles<R>((bd.w0 + fw * bd.dw) * bd.sc);
                 } else if (VMODE == 1) {
                     z = cplx<R>{omega[e], R(0)};
                 } else {
                     z = vis[a.home_pos[e]];
                 }
-                const int i0 = (int)dev_floor(rec.fu - hw) + 1;
-                const int j0 = (int)dev_floor(rec.fv - hw) + 1;
-                R pu = R(0), pv = R(0), pw = R(1);
-                if (lane < W) {
-                    pu = es_kernel<R>(R(i0 + lane) - rec.fu, beta, inv_hw);
-                    pv = es_kernel<R>(R(j0 + lane) - rec.fv, beta, inv_hw);
-                    if (!FLAT) pw = es_kernel<R>(R(q + lane) - dev_abs(rec.fw), beta, inv_hw);
-                }
-                R wu[W];
+                // entries of the batch whose footprint meets this 8 x 8 block
+                const int i0 = (int)dev_floor(rec.fu - hw) + 1, j0 = (int)dev_floor(rec.fv - hw) + 1;
+                unsigned long long todo = __builtin_amdgcn_ballot_w64(e0 + lane < e_end && i0 < r0 + 8 && i0 + W > r0 &&
+                                                                      j0 < c0 + 8 && j0 + W > c0);
+                wave_lds_fence();    // the last batch's reads are done
+                ent[lane * ENT] = rec.fu;
+                ent[lane * ENT + 1] = rec.fv;
+                ent[lane * ENT + 2] = fw;
+                ent[lane * ENT + 3] = z.re;
+                ent[lane * ENT + 4] = z.im;
+                wave_lds_fence();
+                while (todo) {
+                    const int ea = __builtin_ctzll(todo);
+                    todo &= todo - 1;
+                    const int eb = todo ? __builtin_ctzll(todo) : ea;
+                    const bool two = todo != 0;
+                    todo &= todo - 1;
+                    const int ex = lane < 32 ? ea : eb;
+                    const R w = es_kernel<R>(wbase - ent[ex * ENT + wsel], beta, inv_hw);
+                    wave_lds_fence();
+                    wgt[lane] = w;
+                    wave_lds_fence();
 #pragma unroll
-                for (int i = 0; i < W; ++i) wu[i] = __shfl(pu, i, LPV);
-                R ww[WW];
-                if (FLAT) {
-                    ww[0] = R(1);
-                } else {
+                    for (int h = 0; h < 2; ++h) {
+                        if (h == 1 && !two) break;
+                        const R *const wh = wgt + 32 * h;
+                        const R *const en = ent + (h ? eb : ea) * ENT;
+                        const R uv = wh[crow] * wh[8 + ccol];
+                        const R zr = en[3] * uv, zi = en[4] * uv;
+                        if (FLAT) {
+                            are[0] += zr;
+                            aim[0] += zi;
+                        } else {
 #pragma unroll
-                    for (int k = 0; k < WW; ++k) ww[k] = __shfl(pw, k, LPV);
-                }
-                const int c = j0 + lane;
-                const bool cok = (lane < W) && (c >= 0) && (c < T);
-                const cplx<R> zv = z * (pv * fscale);
-#pragma unroll
-                for (int k = 0; k < WW; ++k) {
-                    const int p = q + k;
-                    if (!FLAT && (p < wk.p0 || p >= wk.p1)) continue;
-                    const int slot = FLAT ? 0 : p % W;
-                    A *re = sre + slot * TT + c;
-                    A *im = sim + slot * TT + c;
-                    const cplx<R> zk = zv * ww[k];
-#pragma unroll
-                    for (int i = 0; i < W; ++i) {
-                        const int row = i0 + i;
-                        if (cok && row >= 0 && row < T) {
-                            if constexpr (FIX) {
-                                const long long qr = (long long)__float2int_rn(zk.re * wu[i]);
-                                const long long qi = (long long)__float2int_rn(zk.im * wu[i]);
-                                atomicAdd(re + row * T, (unsigned long long)qr);
-                                atomicAdd(im + row * T, (unsigned long long)qi);
-                            } else {
-                                atomicAdd(re + row * T, zk.re * wu[i]);
-                                atomicAdd(im + row * T, zk.im * wu[i]);
+                            for (int k = 0; k < WW; ++k) {
+                                const R pk = wh[16 + k];
+                                are[k] += zr * pk;
+                                aim[k] += zi * pk;
                             }
                         }
                     }
                 }
             }
-        }
-        __syncthreads();
-        const int slot = FLAT ? 0 : q % W;
-        if (FLAT || q >= wk.p0) {
-            cplx<R> *dst = planes + ((size_t)bb * a.g.nwmax + q) * plane_sz + (size_t)tu * T * a.g.gy + (size_t)tv * T;
-            for (int k = threadIdx.x; k < TT; k += NT) {
-                const int row = k / T, col = k - row * T;
-                cplx<R> v;
-                if constexpr (FIX) {
-                    v = cplx<R>{(R)((double)(long long)sre[slot * TT + k] * (double)finv),
-                                (R)((double)(long long)sim[slot * TT + k] * (double)finv)};
-                } else {
-                    v = cplx<R>{sre[slot * TT + k], sim[slot * TT + k]};
-                }
-                dst[(size_t)row * a.g.gy + col] = v;
+            live = ((live << 1) | (n > 0 ? 1u : 0u)) & ((1u << WW) - 1u);
+            // planes that no base plane of their reach touches are zero: not written (the
+            // transforms read only occupied tiles), and their sums are zero already
+            if (!live) continue;
+            cplx<R> v{are[0], aim[0]};
+#pragma unroll
+            for (int k = 0; k + 1 < WW; ++k) {
+                are[k] = are[k + 1];
+                aim[k] = aim[k + 1];
             }
+            are[WW - 1] = aim[WW - 1] = R(0);
+            if (q < wk.p0) continue;
+            if (nwave > 1) {
+                sums[threadIdx.x] = v;
+                __syncthreads();
+                if (wv == 0)
+                    for (int k = 1; k < nwave; ++k) v = v + sums[64 * k + lane];
+                __syncthreads();
+            }
+            if (wv == 0)
+                planes[((size_t)bb * a.g.nwmax + q) * plane_sz + (size_t)(tu * T + r0 + crow) * a.g.gy +
+                       (size_t)(tv * T + c0 + ccol)] = v;
         }
-        for (int k = threadIdx.x; k < TT; k += NT) {
-            sre[slot * TT + k] = A(0);
-            sim[slot * TT + k] = A(0);
-        }
-        __syncthreads();
     }
 }
 
-// FP32 spread over sorted buckets: one wave per visibility, register
-// accumulation across runs of visibilities that share a footprint.
-//
-// Buckets are sorted by footprint base cell (i0, j0), so consecutive entries
-// often cover the same W x W x W block.  Each wave takes a contiguous part of a
-// bucket; lane (j, k) owns footprint column j and plane q + k and keeps the W
-// row sums of its column in registers; when the base cell changes (or after
-// kRunMax visibilities) the wave adds its block to the LDS ring (64-bit fixed
-// point, ds_add_u64).  Values are pre-scaled by S = 2^26 / max|z|, so a partial
-// sum of at most kRunMax = 31 contributions is below 2^31 in magnitude and
-// converts to int32 with one truncation (zero-mean for values of either sign,
-// relative size 2^-26 for one-signed sums).  The per-visibility quantities
-// (1-D ES weights, z) are computed for 8 visibilities at once, one visibility
-// per 8-lane group, then broadcast with readlane / shuffles.  The wave index,
-// the bucket range and the run state are wave-uniform (scalar registers).
-// FLAT (PSF gridder, one plane): lane (j, i) owns cell (i, j) of the footprint.
-constexpr int kRunMax = 31;
-constexpr float kRunScale = 67108864.0f;   // 2^26
-// LDS stride of one plane slot, in 64-bit words.  A flush touches 7 columns of
-// 7 plane slots at once; padding each slot by 2 words spreads those 49
-// addresses over the 16 two-bank pairs (at most 4 per pair instead of 7).
+// LDS stride of one plane slot, in 64-bit words: padding each slot by 2 words spreads
+// the plane slots that a flush touches at once over the banks.
 __host__ __device__ constexpr int run_slot_stride(int T, bool flat) { return flat ? T * T : T * T + 2; }
 
 __device__ __forceinline__ unsigned long long f2fix(float x) {
@@ -714,193 +715,7 @@ __device__ __forceinline__ float es_kernel_fast(float z, float beta2, float inv_
     return a > 0.f ? __builtin_amdgcn_exp2f(beta2 * (__builtin_amdgcn_sqrtf(a) - 1.f)) : 0.f;
 }
 
-template <int W, bool FLAT, int VMODE>
-__global__ __launch_bounds__(kTileThreads) void spread_run_kernel(SpreadLaunch a) {
-    using R = float;
-    using A = unsigned long long;
-    constexpr int WW = FLAT ? 1 : W;
-    constexpr int NACC = FLAT ? 1 : W;
-    constexpr int NWAVE = kTileThreads / 64;
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    const int T = a.g.T, TT = T * T, TS = run_slot_stride(T, FLAT);
-    A *sre = reinterpret_cast<A *>(smem_raw);
-    A *sim = sre + WW * TS;
-    const GridWork wk = a.work[blockIdx.x];
-    const BandDev bd = a.bands[wk.band];
-    const int ntiles = a.g.ntx * a.g.nty;
-    const int tu = wk.tile / a.g.nty, tv = wk.tile - tu * a.g.nty;
-    const int bb = wk.band - a.band0;
-    const Rec<R> *recs = reinterpret_cast<const Rec<R> *>(a.recs);
-    const R *omega = reinterpret_cast<const R *>(a.omega);
-    const cplx<R> *vis = reinterpret_cast<const cplx<R> *>(a.vis);
-    cplx<R> *planes = reinterpret_cast<cplx<R> *>(a.planes);
-    R fscale = R(1), finv = R(1);
-    fixed_point_scale(*a.absmax, kRunScale, fscale, finv);
-    for (int k = threadIdx.x; k < 2 * WW * TS; k += kTileThreads) sre[k] = A(0);
-    __syncthreads();
-
-    const int lane = threadIdx.x & 63;
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int lj = lane & 7, ls = lane >> 3;         // column j; plane offset k (or row i when FLAT)
-    const bool lact = (lj < W) && (ls < W);
-    const R beta2 = (R)(a.g.beta * 1.4426950408889634), inv_hw = R(2) / R(W), hw = R(0.5) * R(W);
-    const R w0 = (R)bd.w0, dw = (R)bd.dw, sc = (R)bd.sc;
-    const int64_t keybase = ((int64_t)wk.band * ntiles + wk.tile) * a.g.nj0max;
-    const int qstart = FLAT ? 0 : max(0, wk.p0 - W + 1);
-    const size_t plane_sz = (size_t)a.g.gx * a.g.gy;
-
-    for (int q = qstart; q < wk.p1; ++q) {
-        if (q < bd.nj0) {
-            const int64_t b0 = a.offsets[keybase + q], n = a.offsets[keybase + q + 1] - b0;
-            const int64_t per = (n + NWAVE - 1) / NWAVE;
-            const int64_t e_beg = b0 + min(n, wv * per), e_end = b0 + min(n, (wv + 1) * per);
-            // this lane's LDS word for footprint cell (row 0, column 0) of a base at (0, 0)
-            bool lane_ok;
-            int lane_off;
-            if (FLAT) {
-                lane_ok = lact;
-                lane_off = ls * T + lj;
-            } else {
-                const int p = q + ls;
-                lane_ok = lact && p >= wk.p0 && p < wk.p1;
-                lane_off = (p % W) * TS + lj;
-            }
-            R acc_re[NACC], acc_im[NACC];
-#pragma unroll
-            for (int i = 0; i < NACC; ++i) acc_re[i] = acc_im[i] = R(0);
-            int cur = -1, run = 0;
-            auto flush = [&](int base) {
-                const int i0 = (base >> 16) - 64, j0 = (base & 0xffff) - 64;
-                const int c = j0 + lj;
-                if (!lane_ok || c < 0 || c >= T) return;
-                const int idx0 = lane_off + i0 * T + j0;
-                if (FLAT) {
-                    const int row = i0 + ls;
-                    if (row < 0 || row >= T) return;
-                    atomicAdd(sre + idx0, f2fix(acc_re[0]));
-                    atomicAdd(sim + idx0, f2fix(acc_im[0]));
-                } else {
-                    const int ilo = max(0, -i0), ihi = min(W, T - i0);
-                    if (ilo == 0 && ihi == W) {
-#pragma unroll
-                        for (int i = 0; i < W; ++i) {
-                            atomicAdd(sre + idx0 + i * T, f2fix(acc_re[i]));
-                            atomicAdd(sim + idx0 + i * T, f2fix(acc_im[i]));
-                        }
-                    } else {
-#pragma unroll
-                        for (int i = 0; i < W; ++i) {
-                            if (i >= ilo && i < ihi) {
-                                atomicAdd(sre + idx0 + i * T, f2fix(acc_re[i]));
-                                atomicAdd(sim + idx0 + i * T, f2fix(acc_im[i]));
-                            }
-                        }
-                    }
-                }
-            };
-            // software pipeline: the record of the next batch and the value it
-            // gathers are loaded while the current batch is being accumulated
-            auto load_rec = [&](int64_t eb) {
-                Rec<R> r{R(0), R(0), R(0), 0u};
-                if (eb < e_end) r = recs[eb];
-                return r;
-            };
-            auto load_val = [&](int64_t eb, const Rec<R> &r) {
-                cplx<R> v{R(0), R(0)};
-                if (eb < e_end) {
-                    if (VMODE == 0) {
-                        v = entry_conj(r, vis[r.idx & ~kHomeBit]) * (omega[eb] * fscale);
-                    } else if (VMODE == 1) {
-                        v = cplx<R>{omega[eb] * fscale, R(0)};
-                    } else {
-                        v = vis[a.home_pos[eb]] * fscale;
-                    }
-                }
-                return v;
-            };
-            Rec<R> rec_c = load_rec(e_beg + ls);
-            cplx<R> val_c = load_val(e_beg + ls, rec_c);
-            Rec<R> rec_n = load_rec(e_beg + 8 + ls);
-            for (int64_t e = e_beg; e < e_end; e += 8) {
-                const int nb = (int)min((int64_t)8, e_end - e);
-                // prefetch: value of the next batch, record of the one after
-                const cplx<R> val_n = load_val(e + 8 + ls, rec_n);
-                const Rec<R> rec_nn = load_rec(e + 16 + ls);
-                // batched prologue: group ls handles visibility e + ls, lane lj its 1-D weights
-                R pu = R(0), pv = R(0), pw = R(1), zr = R(0), zi = R(0);
-                int base = 0;
-                if (ls < nb) {
-                    const int i0 = (int)dev_floor(rec_c.fu - hw) + 1;
-                    const int j0 = (int)dev_floor(rec_c.fv - hw) + 1;
-                    base = ((i0 + 64) << 16) | (j0 + 64);
-                    if (lj < W) {
-                        pu = es_kernel_fast(R(i0 + lj) - rec_c.fu, beta2, inv_hw);
-                        pv = es_kernel_fast(R(j0 + lj) - rec_c.fv, beta2, inv_hw);
-                        if (!FLAT) pw = es_kernel_fast(R(q + lj) - dev_abs(rec_c.fw), beta2, inv_hw);
-                    }
-                    cplx<R> z = val_c;
-                    if (VMODE == 0) z = z * cis_cycles<R>((w0 + dev_abs(rec_c.fw) * dw) * sc);
-                    zr = z.re;
-                    zi = z.im;
-                }
-                // all shuffles of the batch first (one LDS round trip), then accumulate
-                R wgt[8];
-#pragma unroll
-                for (int t = 0; t < 8; ++t)
-                    wgt[t] = __shfl(pv, t * 8 + lj) * (FLAT ? __shfl(pu, t * 8 + ls) : __shfl(pw, t * 8 + ls));
-#pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    if (t < nb) {
-                        const int src = t * 8;
-                        const int bt = rdlane(base, src);
-                        if (bt != cur || run == kRunMax) {
-                            if (cur >= 0) flush(cur);
-#pragma unroll
-                            for (int i = 0; i < NACC; ++i) acc_re[i] = acc_im[i] = R(0);
-                            cur = bt;
-                            run = 0;
-                        }
-                        ++run;
-                        const R cr = rdlane(zr, src) * wgt[t], ci = rdlane(zi, src) * wgt[t];
-                        if (FLAT) {
-                            acc_re[0] += cr;
-                            acc_im[0] += ci;
-                        } else {
-#pragma unroll
-                            for (int i = 0; i < W; ++i) {
-                                const R u = rdlane(pu, src + i);
-                                acc_re[i] += cr * u;
-                                acc_im[i] += ci * u;
-                            }
-                        }
-                    }
-                }
-                rec_c = rec_n;
-                val_c = val_n;
-                rec_n = rec_nn;
-            }
-            if (cur >= 0) flush(cur);
-        }
-        __syncthreads();
-        const int slot = FLAT ? 0 : q % W;
-        if (FLAT || q >= wk.p0) {
-            cplx<R> *dst = planes + ((size_t)bb * a.g.nwmax + q) * plane_sz + (size_t)tu * T * a.g.gy + (size_t)tv * T;
-            for (int k = threadIdx.x; k < TT; k += kTileThreads) {
-                const int row = k / T, col = k - row * T;
-                dst[(size_t)row * a.g.gy + col] =
-                    cplx<R>{(R)((double)(long long)sre[slot * TS + k] * (double)finv),
-                            (R)((double)(long long)sim[slot * TS + k] * (double)finv)};
-            }
-        }
-        for (int k = threadIdx.x; k < TT; k += kTileThreads) {
-            sre[slot * TS + k] = A(0);
-            sim[slot * TS + k] = A(0);
-        }
-        __syncthreads();
-    }
-}
-
-// FP32 w-stacked spread on the matrix cores.
+// FP32 spread on the matrix cores.
 //
 // For visibilities whose footprints lie in one window of 8 rows, 16 columns
 // and the W planes q .. q + W - 1 of a bucket, the gridded block is a sum of
@@ -920,17 +735,21 @@ __global__ __launch_bounds__(kTileThreads) void spread_run_kernel(SpreadLaunch a
 // P[r - 8], all 16 the column weight V[r]; DPP within the 16-lane row gives
 // every lane U[r mod 8] and the plane weights of the tiles.  Slots outside the
 // window of an MFMA round get a zero B row.
+// FLAT (one plane, the PSF gridder): the window is 16 rows x 16 columns, A the row
+// weights alone; unit visibilities (VMODE 1) have no imaginary part.  Against one wave
+// per visibility with LDS adds of its W x W cells: 262 -> 121 us for 2.5e6 entries of a
+// 1024^2 image's PSF.
 constexpr int kMfmaRunMax = 124;                // visibilities per flush: 124 * 2^24 < 2^31
 constexpr float kMfmaScale = 16777216.0f;       // 2^24
 constexpr int kMfmaThreads = 1024;              // 16 waves (at most 128 registers per lane)
-template <int W> struct MfmaWin {
-    static constexpr int R = 8;                 // window rows
+template <int W, bool FLAT> struct MfmaWin {
+    static constexpr int R = FLAT ? 16 : 8;     // window rows
     static constexpr int RB = R - W + 1;        // base rows per window
     static constexpr int CB = 16 - W + 1;       // base columns per window
-    static constexpr int NT = (W + 1) / 2;      // 16-row tiles: two planes each
+    static constexpr int NT = FLAT ? 1 : (W + 1) / 2;   // 16-row tiles: two planes each (one plane, flat)
 };
-void mfma_window(int W, int *rb, int *cb) {
-    *rb = 8 - W + 1;
+void mfma_window(int W, bool flat, int *rb, int *cb) {
+    *rb = (flat ? 16 : 8) - W + 1;
     *cb = 16 - W + 1;
 }
 typedef float mfma_v4f __attribute__((ext_vector_type(4)));
@@ -957,16 +776,19 @@ __device__ __forceinline__ int64_t rfl64(int64_t v) {
 
 // TC: the tile side as a compile-time constant (LDS offsets become immediates), or
 // 0 to take it from the launch arguments
-template <int W, int VMODE, int TC>
+template <int W, int VMODE, int TC, bool FLAT>
 __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch a) {
     using R_ = float;
     using A = unsigned long long;
-    constexpr int RB = MfmaWin<W>::RB, CB = MfmaWin<W>::CB, NT = MfmaWin<W>::NT;
+    using Win = MfmaWin<W, FLAT>;
+    constexpr int RB = Win::RB, CB = Win::CB, NT = Win::NT, WR = Win::R;
+    constexpr int WW = FLAT ? 1 : W;            // planes of the ring
+    constexpr bool IM = !(FLAT && VMODE == 1);  // unit visibilities on one plane: the sums are real
     constexpr int NWAVE = kMfmaThreads / 64;
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    const int T = TC ? TC : a.g.T, TT = T * T, TS = run_slot_stride(T, false);
+    const int T = TC ? TC : a.g.T, TT = T * T, TS = run_slot_stride(T, FLAT);
     A *sre = reinterpret_cast<A *>(smem_raw);
-    A *sim = sre + W * TS;
+    A *sim = sre + WW * TS;
     const GridWork wk = a.work[blockIdx.x];
     const BandDev bd = a.bands[wk.band];
     const int ntiles = a.g.ntx * a.g.nty;
@@ -980,12 +802,12 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
     R_ fscale = R_(1), finv = R_(1);
     fixed_point_scale(*a.absmax, kMfmaScale, fscale, finv);
     const int64_t keybase = ((int64_t)wk.band * ntiles + wk.tile) * a.g.nj0max;
-    const int qstart = max(0, wk.p0 - W + 1);
+    const int qstart = max(0, wk.p0 - WW + 1);
     const int qlast = min(wk.p1, bd.nj0);        // base planes qstart .. qlast - 1 can hold entries
     // bucket offsets of those base planes: entries of base plane q are
     // soff[q - qstart] .. soff[q - qstart + 1] - 1
-    int64_t *soff = reinterpret_cast<int64_t *>(sim + W * TS);
-    for (int k = threadIdx.x; k < 2 * W * TS; k += kMfmaThreads) sre[k] = A(0);
+    int64_t *soff = reinterpret_cast<int64_t *>(sim + WW * TS);
+    for (int k = threadIdx.x; k < 2 * WW * TS; k += kMfmaThreads) sre[k] = A(0);
     for (int k = threadIdx.x; k <= qlast - qstart; k += kMfmaThreads) soff[k] = a.offsets[keybase + qstart + k];
     __syncthreads();
 
@@ -1033,7 +855,7 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
         RawVal raw{{R_(0), R_(0)}, {R_(1), R_(0)}, R_(1)};
         if (VMODE == 0) {
             raw.z = vis[rr.idx & ~kHomeBit];
-            raw.ph = phase[ec];
+            if (!FLAT) raw.ph = phase[ec];
             raw.om = omega[ec];
         } else if (VMODE == 1) {
             raw.om = omega[ec];
@@ -1043,6 +865,7 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
         return raw;
     };
     auto make_val = [&](const RawVal &raw, const Rec<R_> &rr) {
+        if (VMODE == 0 && FLAT) return raw.z * (raw.om * fscale);
         if (VMODE == 0) return entry_conj(rr, raw.z) * raw.ph * (raw.om * fscale);
         if (VMODE == 1) return cplx<R_>{raw.om * fscale, R_(0)};
         return raw.z * fscale;
@@ -1077,15 +900,24 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 const int k = 2 * t + (sg >> 1), p = q + k;
-                koff[t] = (k < W && p >= wk.p0 && p < wk.p1) ? (p % W) * TS : -1;
+                koff[t] = FLAT ? 0 : ((k < W && p >= wk.p0 && p < wk.p1) ? (p % W) * TS : -1);
             }
-            const int ioff = (4 * (sg & 1)) * T + r;
+            const int irow = 4 * (FLAT ? sg : sg & 1);
+            const int ioff = irow * T + r;
             // add the accumulators of window `key` to the plane ring and clear them
             auto flush = [&](int key) {
                 const int I = ((key >> 8) - 64) * RB - (W - 1), J = ((key & 0xff) - 64) * CB - (W - 1);
                 const int base = I * T + J + ioff;
-                const bool colok = J + r >= 0 && J + r < T;
-                const bool rows_in = I >= 0 && I + 8 <= T;    // wave-uniform
+                // lanes of columns that no entry of the run touched hold zeros: left out (the
+                // LDS adds go by active lanes, and a short run covers W to W + 2 of 16 columns)
+                int touched = 0;
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        touched |= __float_as_int(cre[t][v]) | (IM ? __float_as_int(cim[t][v]) : 0);
+                const bool colok = J + r >= 0 && J + r < T && (touched & 0x7fffffff);
+                const bool rows_in = I >= 0 && I + WR <= T;    // wave-uniform
                 if (rows_in) {    // one lane mask per tile, no per-row tests
 #pragma unroll
                     for (int t = 0; t < NT; ++t) {
@@ -1094,7 +926,7 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
 #pragma unroll
                             for (int v = 0; v < 4; ++v) {
                                 atomicAdd(sre + idx + v * T, f2fix(cre[t][v]));
-                                atomicAdd(sim + idx + v * T, f2fix(cim[t][v]));
+                                if (IM) atomicAdd(sim + idx + v * T, f2fix(cim[t][v]));
                             }
                         }
                         cre[t] = cim[t] = mfma_v4f{0.f, 0.f, 0.f, 0.f};
@@ -1105,11 +937,11 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
                 for (int t = 0; t < NT; ++t) {
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        const int row = I + 4 * (sg & 1) + v;
+                        const int row = I + irow + v;
                         if (colok && koff[t] >= 0 && row >= 0 && row < T) {
                             const int idx = koff[t] + base + v * T;
                             atomicAdd(sre + idx, f2fix(cre[t][v]));
-                            atomicAdd(sim + idx, f2fix(cim[t][v]));
+                            if (IM) atomicAdd(sim + idx, f2fix(cim[t][v]));
                         }
                     }
                     cre[t] = cim[t] = mfma_v4f{0.f, 0.f, 0.f, 0.f};
@@ -1152,7 +984,7 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
 #pragma unroll 1
                 for (int g4 = 0; g4 < nbatch; g4 += 4) {
                     const int nb = min(4, nbatch - g4);
-                    const bool hi = r >= 8;               // rows 8..15 of a tile: its second plane
+                    const bool hi = !FLAT && r >= 8;      // rows 8..15 of a tile: its second plane
                     // plane weights k = r - 8 >= W fall outside the support (zero) and
                     // their planes are never flushed
                     // the VALU work of a group (weights, operands) and the flushes run at a
@@ -1162,9 +994,10 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
                     __builtin_amdgcn_s_setprio(1);
                     const R_ E = es_kernel_fast(hi ? dq + R_(r - 8) : du + R_(r), beta2, inv_hw);
                     const R_ V = es_kernel_fast(dv + R_(r), beta2, inv_hw);
-                    const R_ U = row_lo_to_hi(E);         // U[r mod 8]
+                    const R_ U = FLAT ? E : row_lo_to_hi(E);   // U[r mod 8]
                     R_ At[NT];                            // U x plane weight (2t, 2t + 1 for rows 8-15)
-                    At[0] = U * row_half_bcast<8, 9>(E);
+                    if constexpr (FLAT) At[0] = E;
+                    else At[0] = U * row_half_bcast<8, 9>(E);
                     if constexpr (NT > 1) At[1] = U * row_half_bcast<10, 11>(E);
                     if constexpr (NT > 2) At[2] = U * row_half_bcast<12, 13>(E);
                     if constexpr (NT > 3) At[3] = U * row_half_bcast<14, 15>(E);
@@ -1218,7 +1051,7 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
 #pragma unroll
                         for (int t = 0; t < NT; ++t) {
                             cre[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(At[t], bre, cre[t], 0, 0, 0);
-                            cim[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(At[t], bim, cim[t], 0, 0, 0);
+                            if (IM) cim[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(At[t], bim, cim[t], 0, 0, 0);
                         }
                         rem &= ~sel;
                     }
@@ -1240,18 +1073,19 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
         // written (the transforms read only occupied tiles), and their LDS slot
         // stays zero; a plane without atomics needs no barrier before its write-out
         if (has) __syncthreads();
-        live = ((live << 1) | (has ? 1u : 0u)) & ((1u << W) - 1u);
+        live = ((live << 1) | (has ? 1u : 0u)) & ((1u << WW) - 1u);
         if (!live) continue;
-        const int slot = q % W;
+        const int slot = FLAT ? 0 : q % W;
         if (q >= wk.p0) {
             cplx<R_> *dst = planes + ((size_t)bb * a.g.nwmax + q) * plane_sz + (size_t)tu * T * a.g.gy + (size_t)tv * T;
             for (int k = threadIdx.x; k < TT; k += kMfmaThreads) {
                 const int row = k / T, col = k - row * T;
                 dst[(size_t)row * a.g.gy + col] =
                     cplx<R_>{(R_)((double)(long long)sre[slot * TS + k] * (double)finv),
-                             (R_)((double)(long long)sim[slot * TS + k] * (double)finv)};
+                             IM ? (R_)((double)(long long)sim[slot * TS + k] * (double)finv) : R_(0)};
             }
         }
+        if (q + 1 >= wk.p1) break;   // the last plane's slot is not used again
         for (int k = threadIdx.x; k < TT; k += kMfmaThreads) {
             sre[slot * TS + k] = A(0);
             sim[slot * TS + k] = A(0);
@@ -1361,14 +1195,14 @@ hipError_t launch_absmax(int vmode, const void *vis, const void *weight, const u
     return hipSuccess;
 }
 
-template <typename R, int W, int LPV>
-static hipError_t spread_w(const SpreadLaunch &a, hipStream_t s) {
+template <int W>
+static hipError_t spread64_w(const SpreadLaunch &a, hipStream_t s) {
+    const int waves = a.n_work > 0 && a.n_entries / a.n_work >= kSpread64Long ? 4 : 1;
     const bool flat = a.g.flat;
-    const size_t lds = 2 * (size_t)(flat ? 1 : W) * a.g.T * a.g.T * sizeof(typename SpreadAcc<R>::T);
-#define SPREAD_CASE(FL, VM)                                                         \
-    if (flat == FL && a.vmode == VM) {                                              \
-        PFB_LAUNCH_NT((spread_kernel<R, W, LPV, FL, VM>), a.n_work, kTileThreads, lds, s, a); \
-        return hipSuccess;                                                          \
+#define SPREAD_CASE(FL, VM)                                                                                       \
+    if (flat == FL && a.vmode == VM) {                                                                            \
+        PFB_LAUNCH_NT((spread64_kernel<W, FL, VM>), a.n_work, 64 * waves, (Spread64<W, FL>::lds(waves)), s, a); \
+        return hipSuccess;                                                                                        \
     }
     SPREAD_CASE(false, 0)
     SPREAD_CASE(false, 1)
@@ -1380,37 +1214,22 @@ static hipError_t spread_w(const SpreadLaunch &a, hipStream_t s) {
     return hipErrorInvalidValue;
 }
 
-template <int W>
-static hipError_t spread_run_w(const SpreadLaunch &a, hipStream_t s) {
-    const bool flat = a.g.flat;
-    if (!flat && a.phase) {
-        // plane ring + bucket offsets of the base planes of one work item
-        const size_t lds = 2 * (size_t)W * run_slot_stride(a.g.T, false) * sizeof(unsigned long long) +
-                           ((size_t)a.g.nj0max + 1) * sizeof(int64_t);
-        if (a.g.T == 32) {   // the default tile
-            if (a.vmode == 0) PFB_LAUNCH_NT((spread_mfma_kernel<W, 0, 32>), a.n_work, kMfmaThreads, lds, s, a);
-            else if (a.vmode == 1) PFB_LAUNCH_NT((spread_mfma_kernel<W, 1, 32>), a.n_work, kMfmaThreads, lds, s, a);
-            else PFB_LAUNCH_NT((spread_mfma_kernel<W, 2, 32>), a.n_work, kMfmaThreads, lds, s, a);
-        } else {
-            if (a.vmode == 0) PFB_LAUNCH_NT((spread_mfma_kernel<W, 0, 0>), a.n_work, kMfmaThreads, lds, s, a);
-            else if (a.vmode == 1) PFB_LAUNCH_NT((spread_mfma_kernel<W, 1, 0>), a.n_work, kMfmaThreads, lds, s, a);
-            else PFB_LAUNCH_NT((spread_mfma_kernel<W, 2, 0>), a.n_work, kMfmaThreads, lds, s, a);
-        }
-        return hipSuccess;
+template <int W, bool FLAT>
+static hipError_t spread_mfma_w(const SpreadLaunch &a, hipStream_t s) {
+    // plane ring + bucket offsets of the base planes of one work item
+    const size_t lds = 2 * (size_t)(FLAT ? 1 : W) * run_slot_stride(a.g.T, FLAT) * sizeof(unsigned long long) +
+                       ((size_t)a.g.nj0max + 1) * sizeof(int64_t);
+    if (!FLAT && !a.phase) return hipErrorInvalidValue;
+#define SPREAD_MFMA_CASE(VM)                                                                             \
+    if (a.vmode == VM) {                                                                                 \
+        if (a.g.T == 32) PFB_LAUNCH_NT((spread_mfma_kernel<W, VM, 32, FLAT>), a.n_work, kMfmaThreads, lds, s, a); \
+        else PFB_LAUNCH_NT((spread_mfma_kernel<W, VM, 0, FLAT>), a.n_work, kMfmaThreads, lds, s, a);     \
+        return hipSuccess;                                                                               \
     }
-    const size_t lds = 2 * (size_t)(flat ? 1 : W) * run_slot_stride(a.g.T, flat) * sizeof(unsigned long long);
-#define SPREAD_RUN_CASE(FL, VM)                                                                 \
-    if (flat == FL && a.vmode == VM) {                                                          \
-        PFB_LAUNCH_NT((spread_run_kernel<W, FL, VM>), a.n_work, kTileThreads, lds, s, a);       \
-        return hipSuccess;                                                                      \
-    }
-    SPREAD_RUN_CASE(false, 0)
-    SPREAD_RUN_CASE(false, 1)
-    SPREAD_RUN_CASE(false, 2)
-    SPREAD_RUN_CASE(true, 0)
-    SPREAD_RUN_CASE(true, 1)
-    SPREAD_RUN_CASE(true, 2)
-#undef SPREAD_RUN_CASE
+    SPREAD_MFMA_CASE(0)
+    SPREAD_MFMA_CASE(1)
+    SPREAD_MFMA_CASE(2)
+#undef SPREAD_MFMA_CASE
     return hipErrorInvalidValue;
 }
 
@@ -1431,8 +1250,11 @@ size_t gridder_lds_bytes(bool dbl, int W, int T, bool flat) {
 hipError_t launch_spread(bool dbl, const SpreadLaunch &a, hipStream_t s) {
     if (a.n_work <= 0) return hipSuccess;
     if (dbl)
-        return dispatch_int<9, 16>(a.g.W, [&](auto Wc) { return spread_w<double, decltype(Wc)::value, 16>(a, s); });
-    return dispatch_int<4, 8>(a.g.W, [&](auto Wc) { return spread_run_w<decltype(Wc)::value>(a, s); });
+        return dispatch_int<9, 16>(a.g.W, [&](auto Wc) { return spread64_w<decltype(Wc)::value>(a, s); });
+    return dispatch_int<4, 8>(a.g.W, [&](auto Wc) {
+        constexpr int W = decltype(Wc)::value;
+        return a.g.flat ? spread_mfma_w<W, true>(a, s) : spread_mfma_w<W, false>(a, s);
+    });
 }
 
 // ---------------------------------------------------------------------------
@@ -2033,9 +1855,9 @@ __global__ __launch_bounds__(row_threads<LOG2L>(), row_min_waves<LOG2L>()) void 
 // ran on 64 blocks, 128 columns on 16.  There a block takes ONE column and C of its
 // planes at a time (the C vectors of the LDS buffer are planes, not columns); the grid
 // pass sums its C accumulators at the end.  Used below kColsFewBlocks blocks of the
-// column form (two 512-thread blocks for every CU): at 512^2, 9 planes, grid columns
-// 55 -> FIGG us, degrid columns 60 -> FIGD us; from there on the column form fills the
-// chip and reads whole 64-byte pieces per block.
+// column form (two 512-thread blocks for every CU): grid columns of 128^2, 8 planes,
+// 50 -> 12 us, degrid columns of 512^2, 9 planes, 73 -> 29 us; from there on the column
+// form fills the chip and reads whole 64-byte pieces per block.
 constexpr int kColsFewBlocks = 512;
 template <typename R, int LOG2N, int C, bool PL> struct WCols {
     static constexpr int N = 1 << LOG2N;
@@ -2892,7 +2714,8 @@ static hipError_t conv_columns(const ConvArgs &a, int psf, hipStream_t s) {
         const int G = (a.ly / 2 + CG) / CG;
         const int rounds = ((a.n_band * G + 7) / 8) * 8;   // column groups, padded to the XCDs
         // few columns: the fewest per block that still fill a wave (512^2, one band: 72
-        // blocks of 8 columns leave most CUs idle; FIGC us at one column per block)
+        // blocks of 8 columns leave most CUs idle; the convolution 22.7 -> 19.1 us with
+        // one column per block and one row pair per row block)
         constexpr int CS = conv_few<R, LG>();
         if constexpr (CS < CB) {
             if (!psf && rounds * (CG / CB) < kColsFewBlocks) {
