@@ -169,6 +169,7 @@ struct GridderHost {
     std::vector<int> occ_list_start, need_list_start;
     bool mfma = false;                   // FP32 w-stacked gridder: phase table of the entries
     int sort_rb = 1, sort_cb = 1;        // sort blocks of base rows x columns
+    bool parts = false;                  // some spread item owns a part of its tile
     int64_t n_entries = 0;
     size_t o_sortitems = 0;
     // workspace offsets
@@ -254,13 +255,17 @@ GeomDev base_geom(const pfb_plan &P, int nx, int ny, bool flat) {
     return g;
 }
 
-// Work lists from the per-(band, tile, base plane) counts.
-void build_work(GridderHost &G, const std::vector<unsigned> &counts, const std::vector<unsigned> &hcounts, int chunk) {
+// Work lists from the per-(band, tile, base plane) counts: spread items of at most
+// `chunk` entries, interpolation items of at most `ichunk` home entries.  share > 0
+// (FP32, 32-cell tiles): tiles of more than two such shares of the entries are split into parts.
+void build_work(GridderHost &G, const std::vector<unsigned> &counts, const std::vector<unsigned> &hcounts, int chunk,
+                int ichunk, int64_t share) {
     const GeomDev &g = G.g;
     const int ntiles = g.ntx * g.nty;
     const int W = g.flat ? 1 : g.W;
     G.gwork.clear();
     G.iwork.clear();
+    G.parts = false;
     G.gband_start.assign(g.n_band + 1, 0);
     G.iband_start.assign(g.n_band + 1, 0);
     std::vector<std::pair<int64_t, GridWork>> gw;
@@ -283,22 +288,34 @@ void build_work(GridderHost &G, const std::vector<unsigned> &counts, const std::
                 if (c[q])   // base plane q reaches planes q .. q + W - 1
                     for (int p = q; p < std::min(q + W, bd.nw); ++p) G.occ[((size_t)b * g.nwmax + p) * ntiles + t] = 1;
             }
-            // spread items: split the plane range so each item sees <= chunk entries;
-            // tiles without entries get none (the row transforms read them as zero)
+            // spread items: tiles without entries get none (the row transforms read them
+            // as zero).  uv tracks crowd the centre: in a job of few tiles the densest one
+            // held its compute unit long after the others were done (128^2, 7e3
+            // visibilities: a quarter of the entries in one tile), so a tile of more than
+            // two (eight) units' shares goes to 2 x 2 (4 x 4) items that own a part of its
+            // cells each and take the entries that reach them: ((T / 2 + W - 1) /
+            // (T + W - 1))^2 = a third of the entries each (a seventh), not a quarter
+            // (a sixteenth).  Then the plane range is split so that an item sees <= chunk.
             const int nw = tot ? bd.nw : 0;
+            int split = 1;
+            if (share > 0)
+                while (split < 4 && tot > 2 * share * split * split) split *= 2;
+            G.parts = G.parts || split > 1;
+            const double reach = (double)(g.T / split + g.W - 1) / (g.T + g.W - 1), frac = reach * reach;
             int p0 = 0;
             while (p0 < nw) {
                 int p1 = p0 + 1;
                 auto cost = [&](int a0, int a1) {
                     int64_t s = 0;
                     for (int q = std::max(0, a0 - W + 1); q < std::min(a1, bd.nj0); ++q) s += c[q];
-                    return s;
+                    return (int64_t)(s * frac);
                 };
                 while (p1 < nw && cost(p0, p1 + 1) <= chunk) ++p1;
-                gw.push_back({cost(p0, p1) * (int64_t)W + 1, GridWork{b, t, p0, p1}});
+                for (int part = 0; part < split * split; ++part)
+                    gw.push_back({cost(p0, p1) * (int64_t)W + 1, GridWork{b, t, p0, p1, split, part}});
                 p0 = p1;
             }
-            // interpolation items: runs of <= chunk home entries
+            // interpolation items: runs of <= ichunk home entries
             const unsigned *hc = hcounts.data() + kb;
             int64_t htot = 0;
             for (int q2 = 0; q2 < bd.nj0; ++q2) htot += hc[q2];
@@ -308,7 +325,7 @@ void build_work(GridderHost &G, const std::vector<unsigned> &counts, const std::
             int64_t qend = G.hoffsets[kb] + hc[0];
             while (e < eend) {
                 while (e >= qend) qend += hc[++q];
-                const int64_t e1 = std::min(eend, e + chunk);
+                const int64_t e1 = std::min(eend, e + ichunk);
                 int q1 = q;
                 int64_t qe = qend;
                 while (e1 > qe) qe += hc[++q1];
@@ -434,6 +451,7 @@ SpreadLaunch spread_args(const pfb_plan *P, const GridderHost &G, int b0, int nb
     s.work = G.d_gwork + G.gband_start[b0];
     s.n_work = G.gband_start[b0 + nbb] - G.gband_start[b0];
     s.n_entries = (G.offsets[(size_t)(b0 + nbb) * (G.keys() / G.g.n_band)] - G.offsets[(size_t)b0 * (G.keys() / G.g.n_band)]);
+    s.parts = G.parts;
     s.offsets = G.d_offsets;
     s.recs = G.d_recs;
     s.omega = G.d_omega;
@@ -673,7 +691,21 @@ pfb_status count_and_layout(pfb_plan *P, char *tmp, hipStream_t stream) {
             n_cu = 256;
         const int chunk = opt.chunk ? opt.chunk
                                     : (int)std::min<int64_t>(std::max<int64_t>(4096, acc / n_cu), 1 << 24);
-        build_work(*G, cnt, hcnt, chunk);
+        // a unit's share of the work: the entries, and per item about what 1500 entries
+        // cost (filling or clearing the plane ring, the steps over its planes).  Where that
+        // is small, the densest tiles are split (FP32, 32-cell tiles; a given chunk is kept): spread
+        // tiles into parts, interpolation items, which only read, at a third of a share
+        // (>= 1024 entries).
+        int64_t tiles = 0;   // (band, tile)s with entries
+        for (size_t k2 = 0; k2 < cnt.size(); k2 += G->g.nj0max) {
+            bool any = false;
+            for (int q = 0; q < G->g.nj0max; ++q) any = any || cnt[k2 + q];
+            tiles += any;
+        }
+        const int64_t unit = (acc + 1500 * tiles) / n_cu;
+        const int ichunk = opt.chunk ? opt.chunk : (int)std::min<int64_t>(std::max<int64_t>(1024, unit / 3), chunk);
+        const int64_t share = dbl || opt.chunk || opt.tile != 32 ? 0 : std::max<int64_t>(256, unit);
+        build_work(*G, cnt, hcnt, chunk, ichunk, share);
         G->sort_items.clear();
         for (size_t k2 = 0; k2 < cnt.size(); ++k2)
             if (cnt[k2]) {

@@ -32,9 +32,11 @@ struct BandDev {
     int    fold;   // 1: visibilities with w < 0 are listed at -(u, v, w), conjugated
 };
 
-// Spread work item: tile `tile` of band `band`, storing planes [p0, p1).
+// Spread work item: tile `tile` of band `band`, storing planes [p0, p1) of part `part`
+// of its `split` x `split` equal parts (1: the whole tile; row part / split, column
+// part mod split).
 struct GridWork {
-    int band, tile, p0, p1;
+    int band, tile, p0, p1, split, part;
 };
 // Interpolation work item: positions [e0, e1) of one tile's home-entry list, base planes [q0, q1].
 struct InterpWork {

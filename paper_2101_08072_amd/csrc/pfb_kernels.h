@@ -60,6 +60,7 @@ struct SpreadLaunch {
     const GridWork *work;
     int n_work;
     int64_t n_entries;    // entries of these bands
+    int parts;            // the list holds items of parts of tiles (FP32, T = 32)
     const int64_t *offsets;
     const void *recs, *omega;
     const void *vis;      // VMODE 0: caller visibilities; VMODE 2: values in home-list order

@@ -111,6 +111,15 @@ __device__ __forceinline__ int wrapi(int a, int n) {
     return a < 0 ? a + n : a;
 }
 
+// k / n for 0 <= k < 2^16 and a divisor 0 < n < 2^16 that is not known at compile time:
+// with m = floor((2^32 - 1) / n) + 1 = (2^32 + r) / n, 0 < r <= n, the product k m / 2^32
+// exceeds k / n by k r / (n 2^32) < 2^-16, less than the 1 / n to the next integer
+struct SmallDiv {
+    unsigned m;
+    __device__ __forceinline__ explicit SmallDiv(int n) : m(0xffffffffu / (unsigned)n + 1u) {}
+    __device__ __forceinline__ int operator()(int k) const { return (int)__umulhi((unsigned)k, m); }
+};
+
 // block-wide FP64 sum over NT threads; result valid in thread 0
 template <int NT = kThreads> __device__ double block_sum(double v, double *red) {
     for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
@@ -775,8 +784,9 @@ __device__ __forceinline__ int64_t rfl64(int64_t v) {
 }
 
 // TC: the tile side as a compile-time constant (LDS offsets become immediates), or
-// 0 to take it from the launch arguments
-template <int W, int VMODE, int TC, bool FLAT>
+// 0 to take it from the launch arguments.  PARTS: the work list holds items of parts of
+// tiles (with the test in the one kernel, short buckets of whole tiles took 8 % longer)
+template <int W, int VMODE, int TC, bool FLAT, bool PARTS>
 __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch a) {
     using R_ = float;
     using A = unsigned long long;
@@ -801,6 +811,10 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
     cplx<R_> *planes = reinterpret_cast<cplx<R_> *>(a.planes);
     R_ fscale = R_(1), finv = R_(1);
     fixed_point_scale(*a.absmax, kMfmaScale, fscale, finv);
+    // the cells of this item: rows [rlo, rhi), columns [clo, chi) of the tile
+    const int part_t = PARTS ? T / wk.split : T;
+    const int rlo = PARTS ? wk.part / wk.split * part_t : 0, rhi = rlo + part_t;
+    const int clo = PARTS ? wk.part % wk.split * part_t : 0, chi = clo + part_t;
     const int64_t keybase = ((int64_t)wk.band * ntiles + wk.tile) * a.g.nj0max;
     const int qstart = max(0, wk.p0 - WW + 1);
     const int qlast = min(wk.p1, bd.nj0);        // base planes qstart .. qlast - 1 can hold entries
@@ -916,8 +930,8 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
                         touched |= __float_as_int(cre[t][v]) | (IM ? __float_as_int(cim[t][v]) : 0);
-                const bool colok = J + r >= 0 && J + r < T && (touched & 0x7fffffff);
-                const bool rows_in = I >= 0 && I + WR <= T;    // wave-uniform
+                const bool colok = J + r >= clo && J + r < chi && (touched & 0x7fffffff);
+                const bool rows_in = I >= rlo && I + WR <= rhi;    // wave-uniform
                 if (rows_in) {    // one lane mask per tile, no per-row tests
 #pragma unroll
                     for (int t = 0; t < NT; ++t) {
@@ -938,7 +952,7 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         const int row = I + irow + v;
-                        if (colok && koff[t] >= 0 && row >= 0 && row < T) {
+                        if (colok && koff[t] >= 0 && row >= rlo && row < rhi) {
                             const int idx = koff[t] + base + v * T;
                             atomicAdd(sre + idx, f2fix(cre[t][v]));
                             if (IM) atomicAdd(sim + idx, f2fix(cim[t][v]));
@@ -961,8 +975,8 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
                 const RawVal val_n = load_val(eb + lane, endb, rec_n, hp_n);
                 const Rec<R_> rec_nn = load_rec(ec + lane, endc);
                 const uint32_t hp_nn = load_hp(ec + lane, endc);
-                const cplx<R_> zc = make_val(val_c, rec_c);
-                const int nbatch = (int)min((int64_t)64, enda - ea);
+                cplx<R_> zc = make_val(val_c, rec_c);
+                int nbatch = (int)min((int64_t)64, enda - ea);
                 // owner lane: window of its entry and the offsets of the window origin
                 int okey;
                 R_ odu, odv, odq;
@@ -974,6 +988,23 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
                     odu = R_(wa * RB - (W - 1)) - rec_c.fu;     // row 0 of the window minus fu
                     odv = R_(wb * CB - (W - 1)) - rec_c.fv;
                     odq = R_(q) - dev_abs(rec_c.fw);
+                    if (PARTS && wk.split > 1) {
+                        // only the entries whose footprint reaches this part: lane k takes the
+                        // k-th of them (the batch stays in order)
+                        const bool on = lane < nbatch && i0 < rhi && i0 + W > rlo && j0 < chi && j0 + W > clo;
+                        const unsigned long long m = __builtin_amdgcn_ballot_w64(on);
+                        const int rank = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0));
+                        nbatch = __builtin_popcountll(m);
+                        // (lanes that are off go to the slots behind, so that every slot has one source)
+                        const int to = on ? rank : nbatch + (lane - rank);
+                        const int from = 4 * __builtin_amdgcn_ds_permute(4 * to, lane);
+                        odu = bperm_f(from, odu);
+                        odv = bperm_f(from, odv);
+                        odq = bperm_f(from, odq);
+                        zc.re = bperm_f(from, zc.re);
+                        zc.im = bperm_f(from, zc.im);
+                        okey = __builtin_amdgcn_ds_bpermute(from, okey);
+                    }
                 }
                 // operands of group 0 of the batch; each group fetches those of the next
                 // one before its matrix products, so the crossbar latency overlaps them
@@ -1076,20 +1107,31 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
         live = ((live << 1) | (has ? 1u : 0u)) & ((1u << WW) - 1u);
         if (!live) continue;
         const int slot = FLAT ? 0 : q % W;
-        if (q >= wk.p0) {
-            cplx<R_> *dst = planes + ((size_t)bb * a.g.nwmax + q) * plane_sz + (size_t)tu * T * a.g.gy + (size_t)tv * T;
-            for (int k = threadIdx.x; k < TT; k += kMfmaThreads) {
-                const int row = k / T, col = k - row * T;
-                dst[(size_t)row * a.g.gy + col] =
-                    cplx<R_>{(R_)((double)(long long)sre[slot * TS + k] * (double)finv),
-                             IM ? (R_)((double)(long long)sim[slot * TS + k] * (double)finv) : R_(0)};
+        cplx<R_> *dst = planes + ((size_t)bb * a.g.nwmax + q) * plane_sz + (size_t)tu * T * a.g.gy + (size_t)tv * T;
+        auto write_cell = [&](int row, int col) {
+            const int c = slot * TS + row * T + col;
+            dst[(size_t)row * a.g.gy + col] = cplx<R_>{(R_)((double)(long long)sre[c] * (double)finv),
+                                                       IM ? (R_)((double)(long long)sim[c] * (double)finv) : R_(0)};
+        };
+        auto clear_cell = [&](int row, int col) {
+            const int c = slot * TS + row * T + col;
+            sre[c] = A(0);
+            if (IM) sim[c] = A(0);
+        };
+        if (!PARTS || wk.split == 1) {
+            if (q >= wk.p0)
+                for (int k = threadIdx.x; k < TT; k += kMfmaThreads) write_cell(k / T, k - k / T * T);
+            if (q + 1 >= wk.p1) break;   // the last plane's slot is not used again
+            for (int k = threadIdx.x; k < TT; k += kMfmaThreads) clear_cell(0, k);
+        } else {   // the part's cells (its side is a power of two)
+            const int lgp = __builtin_ctz(part_t);
+            for (int k = threadIdx.x; k < part_t * part_t; k += kMfmaThreads) {
+                const int row = rlo + (k >> lgp), col = clo + (k & (part_t - 1));
+                if (q >= wk.p0) write_cell(row, col);
+                clear_cell(row, col);
             }
         }
         if (q + 1 >= wk.p1) break;   // the last plane's slot is not used again
-        for (int k = threadIdx.x; k < TT; k += kMfmaThreads) {
-            sre[slot * TS + k] = A(0);
-            sim[slot * TS + k] = A(0);
-        }
         __syncthreads();
     }
 }
@@ -1219,11 +1261,12 @@ static hipError_t spread_mfma_w(const SpreadLaunch &a, hipStream_t s) {
     // plane ring + bucket offsets of the base planes of one work item
     const size_t lds = 2 * (size_t)(FLAT ? 1 : W) * run_slot_stride(a.g.T, FLAT) * sizeof(unsigned long long) +
                        ((size_t)a.g.nj0max + 1) * sizeof(int64_t);
-    if (!FLAT && !a.phase) return hipErrorInvalidValue;
+    if ((!FLAT && !a.phase) || (a.parts && a.g.T != 32)) return hipErrorInvalidValue;
 #define SPREAD_MFMA_CASE(VM)                                                                             \
     if (a.vmode == VM) {                                                                                 \
-        if (a.g.T == 32) PFB_LAUNCH_NT((spread_mfma_kernel<W, VM, 32, FLAT>), a.n_work, kMfmaThreads, lds, s, a); \
-        else PFB_LAUNCH_NT((spread_mfma_kernel<W, VM, 0, FLAT>), a.n_work, kMfmaThreads, lds, s, a);     \
+        if (a.parts) PFB_LAUNCH_NT((spread_mfma_kernel<W, VM, 32, FLAT, true>), a.n_work, kMfmaThreads, lds, s, a); \
+        else if (a.g.T == 32) PFB_LAUNCH_NT((spread_mfma_kernel<W, VM, 32, FLAT, false>), a.n_work, kMfmaThreads, lds, s, a); \
+        else PFB_LAUNCH_NT((spread_mfma_kernel<W, VM, 0, FLAT, false>), a.n_work, kMfmaThreads, lds, s, a); \
         return hipSuccess;                                                                               \
     }
     SPREAD_MFMA_CASE(0)
@@ -1288,12 +1331,13 @@ __global__ __launch_bounds__(kTileThreads) void interp_kernel(InterpLaunch a) {
     const int gx = a.g.gx, gy = a.g.gy;
     const int ox = tu * T - H, oy = tv * T - H;
 
+    const SmallDiv by_s(S);
     auto load_plane = [&](int p, int slot) {
         const cplx<R> *P = pbase + (size_t)p * plane_sz;
         cplx<R> *dst = ring + slot * SS;
         for (int k = threadIdx.x; k < SS; k += NT) {
-            const int aa = k / S, cc = k - aa * S;
-            const int gi = wrapi(ox + aa, gx), gj = wrapi(oy + cc, gy);
+            const int aa = by_s(k), cc = k - aa * S;
+            const int gi = (ox + aa) & (gx - 1), gj = (oy + cc) & (gy - 1);   // grids are powers of two
             dst[k] = P[(size_t)gi * gy + gj];
         }
     };
@@ -1428,12 +1472,16 @@ __global__ __launch_bounds__(kTileThreads) void interp4_kernel(InterpLaunch a) {
     const int ox = tu * T - H, oy = tv * T - H;
 
     // value k of the E x E footprint of plane p (row k / E, column k mod E, wrapped)
+    // (the grids are powers of two; divisions and remainders by runtime values took most
+    // of a short item's time: 68 -> 44 us with the smaller items for 2.9e5 visibilities at
+    // 512^2; 4.3 -> 3.95 ms for 5.8e7 in four bands of 4096^2)
+    const SmallDiv by_e(E), by_per(E * E);
     auto fetch = [&](int p, int k) {
-        const int aa = k / E, cc = k - aa * E;
-        return pbase[(size_t)p * plane_sz + (size_t)wrapi(ox + aa, gx) * gy + wrapi(oy + cc, gy)];
+        const int aa = by_e(k), cc = k - aa * E;
+        return pbase[(size_t)p * plane_sz + (size_t)(((ox + aa) & (gx - 1)) * gy + ((oy + cc) & (gy - 1)))];
     };
     auto put = [&](int p, int k, const cplx<R> &v) {
-        const int aa = k / E;
+        const int aa = by_e(k);
         ring[(p % WW) * SS + aa * S + k - aa * E] = v;
     };
     // the footprints of planes pa .. pb - 1 into their ring slots, eight loads per
@@ -1445,12 +1493,12 @@ __global__ __launch_bounds__(kTileThreads) void interp4_kernel(InterpLaunch a) {
             cplx<R> v[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int k = k0 + u * NT, pl = k / per;
+                const int k = k0 + u * NT, pl = by_per(k);
                 if (k < total) v[u] = fetch(pa + pl, k - pl * per);
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int k = k0 + u * NT, pl = k / per;
+                const int k = k0 + u * NT, pl = by_per(k);
                 if (k < total) put(pa + pl, k - pl * per, v[u]);
             }
         }
@@ -1461,6 +1509,23 @@ __global__ __launch_bounds__(kTileThreads) void interp4_kernel(InterpLaunch a) {
             const int r = k / kInterp4ColPad, c = k - r * kInterp4ColPad;
             ring[r * S + E + c] = cplx<R>{R(0), R(0)};
         }
+    const int lq = threadIdx.x & 3;
+    const int grp = threadIdx.x >> 2;
+    const int64_t keybase = ((int64_t)wk.band * ntiles + wk.tile) * a.g.nj0max;
+    // A group's first entry of base plane q (list position, entry, then its record, stored
+    // phase and weight) is loaded while the ring is filled (the first base plane) or while
+    // the one before it is processed: three dependent loads that every base plane of a
+    // short item waited for.  Indices are clamped to the item's last entry.
+    constexpr bool PH = OMODE != 1 && !FLAT;
+    const cplx<R> *phs = reinterpret_cast<const cplx<R> *>(a.phase);
+    const int64_t hlast = wk.e1 - 1;
+    int64_t off_lo = a.hoffsets[keybase + wk.q0], off_hi = a.hoffsets[keybase + wk.q0 + 1];
+    int64_t e_first = a.hidx[min(max((int64_t)wk.e0, off_lo) + grp, hlast)];
+    Rec<R> rec_first = recs[e_first];
+    cplx<R> ph_first{R(1), R(0)};
+    R om_first = R(0);
+    if (PH && a.use_phase) ph_first = phs[e_first];
+    if (OMODE == 1) om_first = omega[e_first];
     load_planes(wk.q0, min(wk.q0 + WW, FLAT ? 1 : bd.nw));
     __syncthreads();
     // the plane that replaces plane q in the ring is loaded into registers before
@@ -1468,12 +1533,9 @@ __global__ __launch_bounds__(kTileThreads) void interp4_kernel(InterpLaunch a) {
     constexpr int kPre = 2;
     const bool pre_ok = E * E <= kPre * NT;
 
-    const int lq = threadIdx.x & 3;
-    const int grp = threadIdx.x >> 2;
     const R inv_hw = R(2) / R(W), hw = R(0.5) * R(W);
     const float beta2 = (float)(a.g.beta * 1.4426950408889634);
     const R w0 = (R)bd.w0, dw = (R)bd.dw, sc = (R)bd.sc;
-    const int64_t keybase = ((int64_t)wk.band * ntiles + wk.tile) * a.g.nj0max;
 
     // OMODE 1: largest |Re| and |Im| of the values written (scale of the FP32 spread
     // that follows); vbad: some value is NaN or infinite
@@ -1489,28 +1551,22 @@ __global__ __launch_bounds__(kTileThreads) void interp4_kernel(InterpLaunch a) {
                 if (k < E * E) pre[u] = fetch(q + W, k);
             }
         }
-        const int64_t lo = max((int64_t)wk.e0, a.hoffsets[keybase + q]);
-        const int64_t hi = min((int64_t)wk.e1, a.hoffsets[keybase + q + 1]);
+        const int64_t lo = max((int64_t)wk.e0, off_lo);
+        const int64_t hi = min((int64_t)wk.e1, off_hi);
         const int64_t n = max(hi - lo, (int64_t)0);
         const int64_t e_end = lo + n;
         int64_t h = lo + grp;
-        int64_t e_n = 0, e_nn = 0;
-        Rec<R> rec_n{R(0), R(0), R(0), 0u};
-        // the stored phase of the next entry (degridding with stored phases), loaded with its record
-        constexpr bool PH = OMODE != 1 && !FLAT;
-        const cplx<R> *phs = reinterpret_cast<const cplx<R> *>(a.phase);
-        cplx<R> ph_n{R(1), R(0)};
-        R om_n = R(0);   // the weight of the next entry (OMODE 1)
         // the loads of the next two entries run ahead of this one's arithmetic; their
         // indices are clamped to the last entry instead of tested, so that no branch
         // joins a load's value before it is used (that would wait for every load in flight)
-        if (h < e_end) {
-            e_n = a.hidx[h];
-            rec_n = recs[e_n];
-            if (PH && a.use_phase) ph_n = phs[e_n];
-            if (OMODE == 1) om_n = omega[e_n];
-            e_nn = a.hidx[min(h + NGRP, e_end - 1)];
-        }
+        int64_t e_nn = a.hidx[min(h + NGRP, hlast)];
+        Rec<R> rec_n = rec_first;
+        cplx<R> ph_n = ph_first;   // the stored phase of the next entry (degridding with stored phases)
+        R om_n = om_first;         // the weight of the next entry (OMODE 1)
+        int64_t e_n;
+        // the next base plane's bounds and first entry
+        const int64_t off_nx = q < wk.q1 ? a.hoffsets[keybase + q + 2] : off_hi;
+        e_first = a.hidx[min(max((int64_t)wk.e0, off_hi) + grp, hlast)];
         for (; h < e_end; h += NGRP) {
             const Rec<R> rec = rec_n;
             const cplx<R> ph = ph_n;
@@ -1519,7 +1575,7 @@ __global__ __launch_bounds__(kTileThreads) void interp4_kernel(InterpLaunch a) {
             rec_n = recs[e_n];
             if (PH && a.use_phase) ph_n = phs[e_n];
             if (OMODE == 1) om_n = omega[e_n];
-            e_nn = a.hidx[min(h + 2 * NGRP, e_end - 1)];
+            e_nn = a.hidx[min(h + 2 * NGRP, hlast)];
             const int i0 = (int)dev_floor(rec.fu - hw) + 1;
             const int j0 = (int)dev_floor(rec.fv - hw) + 1;
             const R pv0 = es_kernel_fast(R(j0 + lq) - rec.fv, beta2, inv_hw);
@@ -1576,6 +1632,11 @@ __global__ __launch_bounds__(kTileThreads) void interp4_kernel(InterpLaunch a) {
                 }
             }
         }
+        off_lo = off_hi;
+        off_hi = off_nx;
+        rec_first = recs[e_first];
+        if (PH && a.use_phase) ph_first = phs[e_first];
+        if (OMODE == 1) om_first = omega[e_first];
         __syncthreads();
         if (refill) {
             if (pre_ok) {

@@ -63,3 +63,51 @@ def test_fp32_supports_flat_and_sparse(support, tol):
              rel(host(plan.make_psf()), psf_ref))
         say(f"fp32 W={support} rows={n_row}: {e}")
         assert max(e) < tol
+
+
+@pytest.mark.parametrize("support", [4, 7, 8])
+@pytest.mark.parametrize("tile", [16, 32])
+@pytest.mark.parametrize("kind", ["centre", "corner", "edge"])
+def test_dense_tiles_split_into_parts(kind, tile, support):
+    """Most visibilities in one uv tile (its centre, a corner, across the periodic edge):
+    the tile goes to 2 x 2 or 4 x 4 items that own parts of its cells.  A given chunk
+    keeps whole tiles: the same sums, exact in fixed point, so nearly the same image."""
+    import torch
+    prob, vis, x = _case(3000, nx=64, ny=64, seed=345)
+    rng = np.random.default_rng(346)
+    lam = synth.C_LIGHT / prob.freq[0]
+    at = {"centre": (48.0, 48.0), "corner": (32.0, 64.0), "edge": (0.0, 0.0)}[kind]
+    spread = 6.0 if kind == "centre" else 3.0
+    for k, (n, cell) in enumerate(((128, prob.cellx), (128, prob.celly))):
+        prob.uvw[300:, k] = (at[k] + rng.normal(0, spread, prob.n_row - 300)) / (cell * n) * lam
+    e = []
+    for flat in (False, True):
+        parts = make_plan(prob, "fp32", support=support, tile=tile, flat=flat)
+        whole = make_plan(prob, "fp32", support=support, tile=tile, flat=flat, chunk=1 << 20)
+        got = [host(p.grid(to_dev(vis, torch.complex64))).copy() for p in (parts, whole, parts)]
+        hx = [host(p.hessian(to_dev(x, torch.float32))) for p in (parts, whole)]
+        tol = {4: 5e-3, 7: 1e-5, 8: 1e-5}[support]
+        e += [rel(got[0], oracle.grid(prob, vis, flat=flat)), rel(hx[0], oracle.hessian(prob, x, flat=flat))]
+        # flush order differs (runs of a window end elsewhere): 2^-24 of the largest value each
+        assert rel(got[0], got[1]) < 1e-6 and rel(hx[0], hx[1]) < 1e-6
+        assert np.array_equal(got[0], got[2])
+    say(f"parts {kind} W={support} T={tile}: {e}")
+    assert max(e) < tol
+
+
+@pytest.mark.parametrize("support", [4, 7, 8])
+def test_w_planes_with_gaps_between_their_entries(support):
+    """Entries in a few w clusters more than a support apart: planes without entries in
+    reach lie between them, so ring slots are cleared, skipped and used again."""
+    import torch
+    prob, vis, x = _case(400, nx=64, ny=64, seed=345)
+    rng = np.random.default_rng(346)
+    step = 1.0 / (2.0 * 2.7e-4)                    # about one plane step at this field
+    prob.uvw[:, 2] = (rng.choice([0, 9, 10, 21, 40], prob.n_row) + rng.uniform(0, 0.2, prob.n_row)) * step * 0.3
+    plan = make_plan(prob, "fp32", support=support)
+    tol = {4: 5e-3, 7: 1e-5, 8: 1e-5}[support]
+    got = [host(plan.grid(to_dev(vis, torch.complex64))).copy() for _ in range(3)]
+    e = rel(got[0], oracle.grid(prob, vis)), rel(host(plan.hessian(to_dev(x, torch.float32))), oracle.hessian(prob, x))
+    say(f"w gaps W={support}: planes {plan.info()['n_wplanes_max']}, {e}")
+    assert max(e) < tol
+    assert np.array_equal(got[0], got[1]) and np.array_equal(got[0], got[2])
