@@ -85,8 +85,12 @@ hipError_t launch_absmax_clear(float *absmax, hipStream_t s);
 hipError_t launch_absmax(int vmode, const void *vis, const void *weight, const uint8_t *flag, int64_t n,
                          float *partials, float *absmax, hipStream_t s);
 
+// Interpolation of tiles with few entries (w-stacked): items of at most kStreamEntries
+// home entries of one tile, any base planes.
+template <typename R> constexpr int kStreamEntries = sizeof(R) == 4 ? 64 : 32;
 struct InterpLaunch {
     GeomDev g;
+    int stream;           // the items are those of the kernel for tiles with few entries
     const BandDev *bands;
     const InterpWork *work;
     int n_work;

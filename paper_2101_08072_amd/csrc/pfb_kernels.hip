@@ -1303,124 +1303,75 @@ hipError_t launch_spread(bool dbl, const SpreadLaunch &a, hipStream_t s) {
 // ---------------------------------------------------------------------------
 // degridding: halo subgrid of W w-planes in an LDS ring
 // ---------------------------------------------------------------------------
-// A work item covers a run of entries of one tile sorted by base plane; it
-// keeps the (T+W) x (T+W) halo region of W consecutive w-planes in LDS and
-// slides one plane at a time.  Each visibility is computed once, from its home
-// tile; lanes of a group own footprint columns and the partial sums are
-// reduced across the group with lane shuffles.
-// FP64 mode: `interp_kernel` (LPV lanes per visibility, lane shuffles); FP32:
-// `interp4_kernel` below.
-template <typename R, int W, int LPV, bool FLAT, int OMODE>
-__global__ __launch_bounds__(kTileThreads) void interp_kernel(InterpLaunch a) {
-    constexpr int WW = FLAT ? 1 : W;
+// Each visibility is computed once, from its home tile.  `interp4_kernel` (FP32) covers a
+// run of entries of one tile sorted by base plane; it keeps the (T+W) x (T+W) halo
+// region of W consecutive w-planes in LDS and slides one plane at a time.
+// `interp_stream_kernel` (w-stacked FP64, and FP32 tiles with few entries) passes over the
+// planes with a block's entries in registers.  FP64 flat: `interp_flat_kernel`, one plane
+// in LDS, LPV lanes per visibility (a lane owns a footprint column; the partial sums are
+// reduced across the group with lane shuffles).
+template <int W, int LPV, int OMODE>
+__global__ __launch_bounds__(kTileThreads) void interp_flat_kernel(InterpLaunch a) {
+    using R = double;
     constexpr int NT = kTileThreads;
     constexpr int NGRP = NT / LPV;
     constexpr int H = (W - 1) / 2;
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    cplx<R> *ring = reinterpret_cast<cplx<R> *>(smem_raw);
+    cplx<R> *halo = reinterpret_cast<cplx<R> *>(smem_raw);
     const int T = a.g.T, S = T + W, SS = S * S;
     const InterpWork wk = a.work[blockIdx.x];
-    const BandDev bd = a.bands[wk.band];
-    const int ntiles = a.g.ntx * a.g.nty;
     const int tu = wk.tile / a.g.nty, tv = wk.tile - tu * a.g.nty;
-    const int bb = wk.band - a.band0;
     const Rec<R> *recs = reinterpret_cast<const Rec<R> *>(a.recs);
     const R *omega = reinterpret_cast<const R *>(a.omega);
-    const size_t plane_sz = (size_t)a.g.gx * a.g.gy;
-    const cplx<R> *pbase = reinterpret_cast<const cplx<R> *>(a.planes) + (size_t)bb * a.g.nwmax * plane_sz;
     const int gx = a.g.gx, gy = a.g.gy;
+    const cplx<R> *plane = reinterpret_cast<const cplx<R> *>(a.planes) + (size_t)(wk.band - a.band0) * a.g.nwmax * gx * gy;
     const int ox = tu * T - H, oy = tv * T - H;
-
     const SmallDiv by_s(S);
-    auto load_plane = [&](int p, int slot) {
-        const cplx<R> *P = pbase + (size_t)p * plane_sz;
-        cplx<R> *dst = ring + slot * SS;
-        for (int k = threadIdx.x; k < SS; k += NT) {
-            const int aa = by_s(k), cc = k - aa * S;
-            const int gi = (ox + aa) & (gx - 1), gj = (oy + cc) & (gy - 1);   // grids are powers of two
-            dst[k] = P[(size_t)gi * gy + gj];
-        }
-    };
-
-    for (int k = 0; k < WW; ++k)
-        if (wk.q0 + k < (FLAT ? 1 : bd.nw)) load_plane(wk.q0 + k, (wk.q0 + k) % WW);
+    for (int k = threadIdx.x; k < SS; k += NT) {
+        const int aa = by_s(k), cc = k - aa * S;
+        halo[k] = plane[(size_t)((ox + aa) & (gx - 1)) * gy + ((oy + cc) & (gy - 1))];   // grids are powers of two
+    }
     __syncthreads();
-
     const int lane = threadIdx.x % LPV;
-    const int grp = threadIdx.x / LPV;
     const R beta = (R)a.g.beta, inv_hw = R(2) / R(W), hw = R(0.5) * R(W);
-    const R w0 = (R)bd.w0, dw = (R)bd.dw, sc = (R)bd.sc;
-    const int64_t keybase = ((int64_t)wk.band * ntiles + wk.tile) * a.g.nj0max;
-
-    for (int q = wk.q0; q <= wk.q1; ++q) {
-        const int64_t lo = max((int64_t)wk.e0, a.hoffsets[keybase + q]);
-        const int64_t hi = min((int64_t)wk.e1, a.hoffsets[keybase + q + 1]);
-        // group grp takes entries lo + grp, lo + grp + NGRP, ...: the groups of a
-        // wave read neighbouring footprints (same window)
-        const int64_t n = max(hi - lo, (int64_t)0);
-        const int64_t e_end = lo + n;
-        for (int64_t h = lo + grp; h < e_end; h += NGRP) {
-            const int64_t e = a.hidx[h];        // entry listed under its own tile
-            const Rec<R> rec = recs[e];
-            const int i0 = (int)dev_floor(rec.fu - hw) + 1;
-            const int j0 = (int)dev_floor(rec.fv - hw) + 1;
-            R pu = R(0), pv = R(0), pw = R(1);
-            if (lane < W) {
-                pu = es_kernel<R>(R(i0 + lane) - rec.fu, beta, inv_hw);
-                pv = es_kernel<R>(R(j0 + lane) - rec.fv, beta, inv_hw);
-                if (!FLAT) pw = es_kernel<R>(R(q + lane) - dev_abs(rec.fw), beta, inv_hw);
-            }
-            R wu[W];
-            R ww[WW];
+    for (int64_t h = (int64_t)wk.e0 + threadIdx.x / LPV; h < wk.e1; h += NGRP) {
+        const int64_t e = a.hidx[h];        // entry listed under its own tile
+        const Rec<R> rec = recs[e];
+        const int i0 = (int)dev_floor(rec.fu - hw) + 1;
+        const int j0 = (int)dev_floor(rec.fv - hw) + 1;
+        R pu = R(0), pv = R(0);
+        if (lane < W) {
+            pu = es_kernel<R>(R(i0 + lane) - rec.fu, beta, inv_hw);
+            pv = es_kernel<R>(R(j0 + lane) - rec.fv, beta, inv_hw);
+        }
+        R wu[W];
 #pragma unroll
-            for (int i = 0; i < W; ++i) wu[i] = __shfl(pu, i, LPV);
-            if (FLAT) {
-                ww[0] = R(1);
+        for (int i = 0; i < W; ++i) wu[i] = __shfl(pu, i, LPV);
+        cplx<R> acc{R(0), R(0)};
+        if (lane < W) {
+            const cplx<R> *base = halo + j0 + lane + H;
+#pragma unroll
+            for (int i = 0; i < W; ++i) {
+                const cplx<R> g = base[(i0 + i + H) * S];
+                acc.re += wu[i] * g.re;
+                acc.im += wu[i] * g.im;
+            }
+            acc.re *= pv;
+            acc.im *= pv;
+        }
+#pragma unroll
+        for (int off = LPV / 2; off >= 1; off >>= 1) {
+            acc.re += __shfl_xor(acc.re, off, LPV);
+            acc.im += __shfl_xor(acc.im, off, LPV);
+        }
+        if (lane == 0) {
+            if (OMODE != 1) {
+                cplx<R> *ov = reinterpret_cast<cplx<R> *>(a.out) + (rec.idx & ~kHomeBit);
+                *ov = OMODE == 2 ? *ov + acc : acc;
             } else {
-#pragma unroll
-                for (int k = 0; k < WW; ++k) ww[k] = __shfl(pw, k, LPV);
-            }
-            cplx<R> acc{R(0), R(0)};
-            if (lane < W) {
-                const int col = j0 + lane + H;
-#pragma unroll
-                for (int k = 0; k < WW; ++k) {
-                    const cplx<R> *base = ring + ((q + k) % WW) * SS + col;
-                    cplx<R> ak{R(0), R(0)};
-#pragma unroll
-                    for (int i = 0; i < W; ++i) {
-                        const cplx<R> g = base[(i0 + i + H) * S];
-                        ak.re += wu[i] * g.re;
-                        ak.im += wu[i] * g.im;
-                    }
-                    acc.re += ww[k] * ak.re;
-                    acc.im += ww[k] * ak.im;
-                }
-                acc.re *= pv;
-                acc.im *= pv;
-            }
-#pragma unroll
-            for (int off = LPV / 2; off >= 1; off >>= 1) {
-                acc.re += __shfl_xor(acc.re, off, LPV);
-                acc.im += __shfl_xor(acc.im, off, LPV);
-            }
-            if (lane == 0) {
-                const uint32_t vid = rec.idx & ~kHomeBit;
-                if (OMODE != 1) {
-                    cplx<R> out = FLAT ? acc : entry_conj(rec, acc * conj(cis_cycles<R>((w0 + dev_abs(rec.fw) * dw) * sc)));
-                    cplx<R> *ov = reinterpret_cast<cplx<R> *>(a.out) + vid;
-                    *ov = OMODE == 2 ? *ov + out : out;
-                } else {
-                    const cplx<R> o = acc * omega[e];
-                    reinterpret_cast<cplx<R> *>(a.out)[h] = o;   // home-list order
-                }
+                reinterpret_cast<cplx<R> *>(a.out)[h] = acc * omega[e];   // home-list order
             }
         }
-        __syncthreads();
-        if (!FLAT && q < wk.q1 && q + W < bd.nw) {
-            load_plane(q + W, q % W);
-        }
-        __syncthreads();
     }
 }
 
@@ -1663,30 +1614,182 @@ __global__ __launch_bounds__(kTileThreads) void interp4_kernel(InterpLaunch a) {
     }
 }
 
-template <typename R, int W, int LPV>
-static hipError_t interp_w(const InterpLaunch &a, hipStream_t s) {
-    const bool flat = a.g.flat;
-    const int S = a.g.T + W;
-    const size_t lds = (size_t)(flat ? 1 : W) * S * S * sizeof(cplx<R>);
-#define INTERP_CASE(FL, OM)                                                         \
-    if (flat == FL && a.omode == OM) {                                              \
-        PFB_LAUNCH_NT((interp_kernel<R, W, LPV, FL, OM>), a.n_work, kTileThreads, lds, s, a); \
-        return hipSuccess;                                                          \
+// Interpolation of tiles with few entries, plane by plane.  The ring kernels hold W planes
+// of a tile's halo in LDS (one block per CU) and step over base planes; with few entries
+// per tile their time was latency: filling the ring, then a step per base plane.  Here a
+// block takes up to NV home entries of a tile (one per group of LPV lanes, whatever their
+// base planes), keeps each one's weights and sums in registers and passes over the planes
+// they reach with two single-plane buffers: the next plane is loaded while this one is
+// used, one barrier per plane, and five or more blocks share a CU.  A lane owns footprint
+// columns l and l + LPV (a column past the support reads the last one with weight zero).
+// The planes are read once per block instead of once per tile, so FP32 tiles with many
+// entries stay with the ring.  FP32, ring -> stream: 1.5e5 visibilities at 2048^2 (35 per
+// tile) 288 -> 147 us, at 512^2 (390 per tile) 34 -> 31, 1.5e6 at 1024^2 (1030 per tile)
+// 168 -> 232.  FP64, where a lane's sums cost more than the planes' reads, against a
+// ring: 1.5e5 at 1024^2 1.54 -> 0.42 ms, 1.5e6 at 128^2 (2900 per tile) 1.99 -> 0.91.
+template <typename R> struct Stream {
+    static constexpr int LPV = sizeof(R) == 4 ? 4 : 8;   // lanes per visibility: 2 LPV >= W columns
+    static constexpr int NT = 256, NV = kStreamEntries<R>;
+    static_assert(NV * LPV == NT, "one entry per group");
+};
+template <typename R, int W, int OMODE>
+__global__ __launch_bounds__(256) void interp_stream_kernel(InterpLaunch a) {
+    constexpr int LPV = Stream<R>::LPV, NT = Stream<R>::NT;
+    static_assert(W <= 2 * LPV, "two columns per lane");
+    constexpr int H = (W - 1) / 2;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int T = a.g.T, E = T + W, S = E + 1, SS = E * S;   // rows padded by one value
+    cplx<R> *const buf = reinterpret_cast<cplx<R> *>(smem_raw);
+    const InterpWork wk = a.work[blockIdx.x];
+    const BandDev bd = a.bands[wk.band];
+    const int tu = wk.tile / a.g.nty, tv = wk.tile - tu * a.g.nty;
+    const int bb = wk.band - a.band0;
+    const int gx = a.g.gx, gy = a.g.gy;
+    const size_t plane_sz = (size_t)gx * gy;
+    const cplx<R> *pbase = reinterpret_cast<const cplx<R> *>(a.planes) + (size_t)bb * a.g.nwmax * plane_sz;
+    const int ox = tu * T - H, oy = tv * T - H;
+    const SmallDiv by_e(E);
+    // the entry of this group (groups past the item's end repeat its last one and store nothing)
+    const int l = threadIdx.x & (LPV - 1);
+    const int64_t h = (int64_t)wk.e0 + threadIdx.x / LPV;
+    const bool on = h < wk.e1;
+    const int64_t e = a.hidx[min(h, (int64_t)wk.e1 - 1)];
+    const Rec<R> rec = reinterpret_cast<const Rec<R> *>(a.recs)[e];
+    // values of a plane per thread in flight: a whole plane with the default tiles (39^2, 21^2)
+    constexpr int PF = sizeof(R) == 4 ? 6 : 2;
+    const int per = E * E, p_end = min(wk.q1 + W, bd.nw);
+    auto fetch = [&](int p, int k) {
+        const int aa = by_e(k), cc = k - aa * E;
+        return pbase[(size_t)p * plane_sz + (size_t)(((ox + aa) & (gx - 1)) * gy + ((oy + cc) & (gy - 1)))];
+    };
+    auto put = [&](int p, int k, const cplx<R> &v) {
+        const int aa = by_e(k);
+        buf[(p & 1) * SS + aa * S + k - aa * E] = v;
+    };
+    cplx<R> pre[PF];
+    auto load = [&](int p, int k0) {
+#pragma unroll
+        for (int u = 0; u < PF; ++u) pre[u] = fetch(p, min(k0 + u * NT, per - 1));
+    };
+    auto store = [&](int p, int k0) {
+#pragma unroll
+        for (int u = 0; u < PF; ++u)
+            if (k0 + u * NT < per) put(p, k0 + u * NT, pre[u]);
+    };
+    load(wk.q0, threadIdx.x);
+    const R hw = R(0.5) * R(W), inv_hw = R(2) / R(W), fw = dev_abs(rec.fw);
+    const R bt = sizeof(R) == 4 ? (R)(a.g.beta * 1.4426950408889634) : (R)a.g.beta;
+    auto es = [&](R z) -> R {
+        if constexpr (sizeof(R) == 4) return es_kernel_fast(z, bt, inv_hw);
+        else return es_kernel<R>(z, bt, inv_hw);
+    };
+    const int i0 = (int)dev_floor(rec.fu - hw) + 1, j0 = (int)dev_floor(rec.fv - hw) + 1;
+    const int q = (int)dev_floor(fw - hw) + 1;             // the entry's base plane
+    const R pv0 = es(R(j0 + l) - rec.fv), pv1 = l + LPV < W ? es(R(j0 + l + LPV) - rec.fv) : R(0);
+    const R pua = es(R(i0 + l) - rec.fu), pub = es(R(i0 + l + LPV) - rec.fu);
+    const R pwa = es(R(q + l) - fw), pwb = es(R(q + l + LPV) - fw);
+    R wu[W];
+    if constexpr (sizeof(R) == 4) {
+        quad_bcast_w<W>(pua, pub, wu);
+    } else {
+#pragma unroll
+        for (int i = 0; i < W; ++i) wu[i] = __shfl(i < LPV ? pua : pub, i & (LPV - 1), LPV);
     }
-    INTERP_CASE(false, 0)
-    INTERP_CASE(false, 1)
-    INTERP_CASE(false, 2)
-    INTERP_CASE(true, 0)
-    INTERP_CASE(true, 1)
-    INTERP_CASE(true, 2)
-#undef INTERP_CASE
-    return hipErrorInvalidValue;
+    const int at = (i0 + H) * S + j0 + l + H, second = min(l + LPV, W - 1) - l;
+    cplx<R> A0{R(0), R(0)}, A1{R(0), R(0)};
+    store(wk.q0, threadIdx.x);
+    for (int k0 = threadIdx.x + PF * NT; k0 < per; k0 += PF * NT) {
+        load(wk.q0, k0);
+        store(wk.q0, k0);
+    }
+    __syncthreads();
+    for (int p = wk.q0; p < p_end; ++p) {
+        const bool more = p + 1 < p_end;
+        if (more) load(p + 1, threadIdx.x);
+        const int k = p - q;
+        const R ka = __shfl(pwa, k & (LPV - 1), LPV), kb = __shfl(pwb, k & (LPV - 1), LPV);
+        if (k >= 0 && k < W) {
+            const cplx<R> *base = buf + (p & 1) * SS + at;
+            const R ww = k < LPV ? ka : kb;
+            cplx<R> a0{R(0), R(0)}, a1{R(0), R(0)};
+#pragma unroll
+            for (int i = 0; i < W; ++i) {
+                const cplx<R> g0 = base[i * S], g1 = base[i * S + second];
+                a0.re += wu[i] * g0.re;
+                a0.im += wu[i] * g0.im;
+                a1.re += wu[i] * g1.re;
+                a1.im += wu[i] * g1.im;
+            }
+            A0.re += ww * a0.re;
+            A0.im += ww * a0.im;
+            A1.re += ww * a1.re;
+            A1.im += ww * a1.im;
+        }
+        if (more) {
+            store(p + 1, threadIdx.x);
+            for (int k0 = threadIdx.x + PF * NT; k0 < per; k0 += PF * NT) {
+                load(p + 1, k0);
+                store(p + 1, k0);
+            }
+        }
+        __syncthreads();
+    }
+    cplx<R> acc{pv0 * A0.re + pv1 * A1.re, pv0 * A0.im + pv1 * A1.im};
+#pragma unroll
+    for (int off = LPV / 2; off >= 1; off >>= 1) {
+        acc.re += __shfl_xor(acc.re, off, LPV);
+        acc.im += __shfl_xor(acc.im, off, LPV);
+    }
+    float vm = 0.f;
+    if (l == 0 && on) {
+        if (OMODE != 1) {
+            const cplx<R> ph = a.use_phase ? reinterpret_cast<const cplx<R> *>(a.phase)[e]
+                                           : cis_cycles<R>(((R)bd.w0 + fw * (R)bd.dw) * (R)bd.sc);
+            const cplx<R> out = entry_conj(rec, acc * conj(ph));
+            cplx<R> *ov = reinterpret_cast<cplx<R> *>(a.out) + (rec.idx & ~kHomeBit);
+            *ov = OMODE == 2 ? *ov + out : out;
+        } else {
+            const cplx<R> o = acc * reinterpret_cast<const R *>(a.omega)[e];
+            reinterpret_cast<cplx<R> *>(a.out)[h] = o;   // home-list order
+            if (sizeof(R) == 4)   // (as in interp4_kernel: the scale of the FP32 spread that follows)
+                vm = not_finite((float)o.re) || not_finite((float)o.im)
+                         ? INFINITY
+                         : (float)sqrt((double)o.re * (double)o.re + (double)o.im * (double)o.im);
+        }
+    }
+    if (OMODE == 1 && sizeof(R) == 4 && a.absmax) {
+        for (int off = 32; off >= 1; off >>= 1) vm = fmaxf(vm, __shfl_xor(vm, off, 64));
+        if ((threadIdx.x & 63) == 0 && vm > 0.f)
+            atomicMax(reinterpret_cast<unsigned *>(a.absmax), __float_as_uint(vm * 1.0001f));
+    }
+}
+template <typename R, int W> static hipError_t interp_stream_w(const InterpLaunch &a, hipStream_t s) {
+    const size_t lds = 2 * (size_t)(a.g.T + W) * (a.g.T + W + 1) * sizeof(cplx<R>);
+    if (a.g.flat) return hipErrorInvalidValue;
+    if (a.omode == 0) PFB_LAUNCH_NT((interp_stream_kernel<R, W, 0>), a.n_work, 256, lds, s, a);
+    else if (a.omode == 1) PFB_LAUNCH_NT((interp_stream_kernel<R, W, 1>), a.n_work, 256, lds, s, a);
+    else PFB_LAUNCH_NT((interp_stream_kernel<R, W, 2>), a.n_work, 256, lds, s, a);
+    return hipSuccess;
+}
+
+template <int W> static hipError_t interp_flat_w(const InterpLaunch &a, hipStream_t s) {
+    const int S = a.g.T + W;
+    const size_t lds = (size_t)S * S * sizeof(cplx<double>);
+    if (!a.g.flat) return hipErrorInvalidValue;
+    if (a.omode == 0) PFB_LAUNCH_NT((interp_flat_kernel<W, 16, 0>), a.n_work, kTileThreads, lds, s, a);
+    else if (a.omode == 1) PFB_LAUNCH_NT((interp_flat_kernel<W, 16, 1>), a.n_work, kTileThreads, lds, s, a);
+    else PFB_LAUNCH_NT((interp_flat_kernel<W, 16, 2>), a.n_work, kTileThreads, lds, s, a);
+    return hipSuccess;
 }
 
 hipError_t launch_interp(bool dbl, const InterpLaunch &a, hipStream_t s) {
     if (a.n_work <= 0) return hipSuccess;
+    if (a.stream) {
+        if (dbl) return dispatch_int<9, 16>(a.g.W, [&](auto Wc) { return interp_stream_w<double, decltype(Wc)::value>(a, s); });
+        return dispatch_int<4, 8>(a.g.W, [&](auto Wc) { return interp_stream_w<float, decltype(Wc)::value>(a, s); });
+    }
     if (dbl)
-        return dispatch_int<9, 16>(a.g.W, [&](auto Wc) { return interp_w<double, decltype(Wc)::value, 16>(a, s); });
+        return dispatch_int<9, 16>(a.g.W, [&](auto Wc) { return interp_flat_w<decltype(Wc)::value>(a, s); });
     return dispatch_int<4, 8>(a.g.W, [&](auto Wc) {
         constexpr int W = decltype(Wc)::value;
         const bool flat = a.g.flat;
