@@ -170,7 +170,10 @@ struct GridderHost {
     bool mfma = false;                   // FP32 w-stacked gridder: phase table of the entries
     int sort_rb = 1, sort_cb = 1;        // sort blocks of base rows x columns
     bool istream = false;                // interpolation items of the kernel for few entries per tile
-    bool parts = false;                  // some spread item owns a part of its tile
+    std::vector<SharedTile> shared;      // tiles whose entries several spread items share
+    std::vector<int> shared_start;       // per band first of them (n_band + 1)
+    int n_scratch = 0;                   // scratch tiles they need
+    size_t scratch_bytes = 0;
     int64_t n_entries = 0;
     size_t o_sortitems = 0;
     // workspace offsets
@@ -184,7 +187,10 @@ struct GridderHost {
     unsigned long long *d_cursor = nullptr;
     GridWork *d_gwork = nullptr;
     InterpWork *d_iwork = nullptr;
+    SharedTile *d_shared = nullptr;
+    void *d_scratch = nullptr;
     void *d_recs = nullptr, *d_omega = nullptr, *d_corr2d = nullptr, *d_corrx = nullptr, *d_corry = nullptr;
+    size_t o_shared = 0, o_scratch = 0;
     size_t o_phase = 0;
     void *d_phase = nullptr;
     size_t o_hidx = 0, o_hoffsets = 0;
@@ -261,16 +267,19 @@ GeomDev base_geom(const pfb_plan &P, int nx, int ny, bool flat) {
 constexpr int64_t kStreamPerTile = 400;
 
 // Work lists from the per-(band, tile, base plane) counts: spread items of at most
-// `chunk` entries, interpolation items of at most `ichunk` home entries.  share > 0
-// (FP32, 32-cell tiles): tiles of more than two such shares of the entries are split into parts.
+// `chunk` entries, interpolation items of at most `ichunk` home entries.  share > 0: tiles
+// of more than two such shares of entries go to several items that share them instead,
+// with one scratch tile each (per_share) or one together.
 void build_work(GridderHost &G, const std::vector<unsigned> &counts, const std::vector<unsigned> &hcounts, int chunk,
-                int ichunk, int64_t share) {
+                int ichunk, int64_t share, bool per_share) {
     const GeomDev &g = G.g;
     const int ntiles = g.ntx * g.nty;
     const int W = g.flat ? 1 : g.W;
     G.gwork.clear();
     G.iwork.clear();
-    G.parts = false;
+    G.shared.clear();
+    G.shared_start.assign(g.n_band + 1, 0);
+    G.n_scratch = 0;
     G.gband_start.assign(g.n_band + 1, 0);
     G.iband_start.assign(g.n_band + 1, 0);
     std::vector<std::pair<int64_t, GridWork>> gw;
@@ -295,30 +304,31 @@ void build_work(GridderHost &G, const std::vector<unsigned> &counts, const std::
             }
             // spread items: tiles without entries get none (the row transforms read them
             // as zero).  uv tracks crowd the centre: in a job of few tiles the densest one
-            // held its compute unit long after the others were done (128^2, 7e3
-            // visibilities: a quarter of the entries in one tile), so a tile of more than
-            // two (eight) units' shares goes to 2 x 2 (4 x 4) items that own a part of its
-            // cells each and take the entries that reach them: ((T / 2 + W - 1) /
-            // (T + W - 1))^2 = a third of the entries each (a seventh), not a quarter
-            // (a sixteenth).  Then the plane range is split so that an item sees <= chunk.
+            // held its compute unit long after the others were done (128^2: a quarter of
+            // the entries in one tile), and a split of its plane range re-reads nearly
+            // every entry (W planes each of hardly more than W); so a dense tile's buckets
+            // are shared between items, whose sums meet in a scratch tile.  With a given
+            // chunk the plane range is split so that an item sees <= chunk.
             const int nw = tot ? bd.nw : 0;
-            int split = 1;
-            if (share > 0)
-                while (split < 4 && tot > 2 * share * split * split) split *= 2;
-            G.parts = G.parts || split > 1;
-            const double reach = (double)(g.T / split + g.W - 1) / (g.T + g.W - 1), frac = reach * reach;
-            int p0 = 0;
-            while (p0 < nw) {
-                int p1 = p0 + 1;
-                auto cost = [&](int a0, int a1) {
-                    int64_t s = 0;
-                    for (int q = std::max(0, a0 - W + 1); q < std::min(a1, bd.nj0); ++q) s += c[q];
-                    return (int64_t)(s * frac);
-                };
-                while (p1 < nw && cost(p0, p1 + 1) <= chunk) ++p1;
-                for (int part = 0; part < split * split; ++part)
-                    gw.push_back({cost(p0, p1) * (int64_t)W + 1, GridWork{b, t, p0, p1, split, part}});
-                p0 = p1;
+            auto cost = [&](int a0, int a1) {
+                int64_t s = 0;
+                for (int q = std::max(0, a0 - W + 1); q < std::min(a1, bd.nj0); ++q) s += c[q];
+                return s;
+            };
+            if (share > 0 && tot > 2 * share) {
+                const int ns = (int)((tot + share - 1) / share);
+                G.shared.push_back(SharedTile{b, t, G.n_scratch, ns});
+                for (int k = 0; k < ns; ++k)
+                    gw.push_back({tot / ns * (int64_t)W + 1, GridWork{b, t, 0, nw, k, ns, G.n_scratch}});
+                G.n_scratch += per_share ? ns : 1;
+            } else {
+                int p0 = 0;
+                while (p0 < nw) {
+                    int p1 = share > 0 ? nw : p0 + 1;
+                    while (p1 < nw && cost(p0, p1 + 1) <= chunk) ++p1;
+                    gw.push_back({cost(p0, p1) * (int64_t)W + 1, GridWork{b, t, p0, p1, 0, 1, 0}});
+                    p0 = p1;
+                }
             }
             // interpolation items: runs of <= ichunk home entries
             const unsigned *hc = hcounts.data() + kb;
@@ -363,6 +373,7 @@ void build_work(GridderHost &G, const std::vector<unsigned> &counts, const std::
         for (auto &x : iw) G.iwork.push_back(x.second);
         G.gband_start[b + 1] = (int)G.gwork.size();
         G.iband_start[b + 1] = (int)G.iwork.size();
+        G.shared_start[b + 1] = (int)G.shared.size();
     }
     G.occ_list.clear();
     G.need_list.clear();
@@ -455,8 +466,10 @@ SpreadLaunch spread_args(const pfb_plan *P, const GridderHost &G, int b0, int nb
     s.bands = G.d_bands;
     s.work = G.d_gwork + G.gband_start[b0];
     s.n_work = G.gband_start[b0 + nbb] - G.gband_start[b0];
-    s.n_entries = (G.offsets[(size_t)(b0 + nbb) * (G.keys() / G.g.n_band)] - G.offsets[(size_t)b0 * (G.keys() / G.g.n_band)]);
-    s.parts = G.parts;
+    s.shared = G.d_shared + G.shared_start[b0];
+    s.n_shared = G.shared_start[b0 + nbb] - G.shared_start[b0];
+    s.scratch = G.d_scratch;
+    s.occ = G.d_occ;
     s.offsets = G.d_offsets;
     s.recs = G.d_recs;
     s.omega = G.d_omega;
@@ -698,10 +711,9 @@ pfb_status count_and_layout(pfb_plan *P, char *tmp, hipStream_t stream) {
         const int chunk = opt.chunk ? opt.chunk
                                     : (int)std::min<int64_t>(std::max<int64_t>(4096, acc / n_cu), 1 << 24);
         // a unit's share of the work: the entries, and per item about what 1500 entries
-        // cost (filling or clearing the plane ring, the steps over its planes).  Where that
-        // is small, the densest tiles are split (FP32, 32-cell tiles; a given chunk is kept): spread
-        // tiles into parts, interpolation items, which only read, at a third of a share
-        // (>= 1024 entries).
+        // cost (filling or clearing the plane ring, the steps over its planes).  Spread tiles
+        // of more than two such shares are shared between items, interpolation items, which
+        // only read, are split at a third of a share (>= 1024 entries); a given chunk is kept.
         int64_t tiles = 0;   // (band, tile)s with entries
         for (size_t k2 = 0; k2 < cnt.size(); k2 += G->g.nj0max) {
             bool any = false;
@@ -712,8 +724,12 @@ pfb_status count_and_layout(pfb_plan *P, char *tmp, hipStream_t stream) {
         // w-stacked FP64, and FP32 with few entries per tile: the plane-by-plane interpolation
         G->istream = !G->g.flat && (dbl || (!opt.chunk && hacc < kStreamPerTile * tiles));
         const int ichunk = G->istream ? (dbl ? kStreamEntries<double> : kStreamEntries<float>) : opt.chunk ? opt.chunk : (int)std::min<int64_t>(std::max<int64_t>(1024, unit / 3), chunk);
-        const int64_t share = dbl || opt.chunk || opt.tile != 32 ? 0 : std::max<int64_t>(256, unit);
-        build_work(*G, cnt, hcnt, chunk, ichunk, share);
+        // (FP64 items are single waves, of which a unit holds sixteen: half their share, so
+        // that the densest unshared tile is no tail)
+        const int64_t share = opt.chunk ? 0
+                              : dbl     ? std::max<int64_t>(64, acc / (32 * (int64_t)n_cu))
+                                        : std::max<int64_t>(256, unit);
+        build_work(*G, cnt, hcnt, chunk, ichunk, share, dbl);
         G->sort_items.clear();
         for (size_t k2 = 0; k2 < cnt.size(); ++k2)
             if (cnt[k2]) {
@@ -779,6 +795,9 @@ pfb_status count_and_layout(pfb_plan *P, char *tmp, hipStream_t stream) {
         G->o_cursor = L.take((G->offsets.size()) * sizeof(unsigned long long));
         G->o_gwork = L.take(std::max<size_t>(G->gwork.size(), 1) * sizeof(GridWork));
         G->o_iwork = L.take(std::max<size_t>(G->iwork.size(), 1) * sizeof(InterpWork));
+        G->o_shared = L.take(std::max<size_t>(G->shared.size(), 1) * sizeof(SharedTile));
+        G->scratch_bytes = (size_t)G->n_scratch * G->g.nwmax * G->g.T * G->g.T * 16;
+        G->o_scratch = L.take(std::max<size_t>(G->scratch_bytes, 1));
         G->o_sortitems = L.take(std::max<size_t>(G->sort_items.size(), 4) * sizeof(int64_t));
         G->o_recs = L.take(std::max<int64_t>(G->n_entries, 1) * (dbl ? sizeof(Rec<double>) : sizeof(Rec<float>)));
         G->o_omega = L.take(std::max<int64_t>(G->n_entries, 1) * P->rsz);
@@ -1142,6 +1161,13 @@ pfb_status pfb_plan_set_workspace(pfb_plan *P, void *dev, size_t bytes, hipStrea
         G->d_cursor = reinterpret_cast<unsigned long long *>(P->p(G->o_cursor));
         G->d_gwork = reinterpret_cast<GridWork *>(P->p(G->o_gwork));
         G->d_iwork = reinterpret_cast<InterpWork *>(P->p(G->o_iwork));
+        G->d_shared = reinterpret_cast<SharedTile *>(P->p(G->o_shared));
+        G->d_scratch = P->p(G->o_scratch);
+        if (!G->shared.empty()) {
+            HIP_OK(hipMemcpyAsync(G->d_shared, G->shared.data(), G->shared.size() * sizeof(SharedTile),
+                                  hipMemcpyHostToDevice, s));
+            HIP_OK(hipMemsetAsync(G->d_scratch, 0, G->scratch_bytes, s));   // zero between launches
+        }
         G->d_recs = P->p(G->o_recs);
         G->d_omega = P->p(G->o_omega);
         G->d_phase = G->mfma ? P->p(G->o_phase) : nullptr;

@@ -32,11 +32,16 @@ struct BandDev {
     int    fold;   // 1: visibilities with w < 0 are listed at -(u, v, w), conjugated
 };
 
-// Spread work item: tile `tile` of band `band`, storing planes [p0, p1) of part `part`
-// of its `split` x `split` equal parts (1: the whole tile; row part / split, column
-// part mod split).
+// Spread work item: tile `tile` of band `band`, storing planes [p0, p1).  nshare > 1: the
+// item takes the share-th of nshare equal runs of every bucket, and its sums go to the
+// scratch tile `slot` (see SpreadLaunch::shares).
 struct GridWork {
-    int band, tile, p0, p1, split, part;
+    int band, tile, p0, p1, share, nshare, slot;
+};
+// A tile whose entries are shared between items: scratch tiles slot (FP32) or slot ..
+// slot + nshare - 1 (FP64) hold its planes until they are summed up.
+struct SharedTile {
+    int band, tile, slot, nshare;
 };
 // Interpolation work item: positions [e0, e1) of one tile's home-entry list, base planes [q0, q1].
 struct InterpWork {

@@ -59,8 +59,15 @@ struct SpreadLaunch {
     const BandDev *bands;
     const GridWork *work;
     int n_work;
-    int64_t n_entries;    // entries of these bands
-    int parts;            // the list holds items of parts of tiles (FP32, T = 32)
+    // tiles whose entries several items share (a dense tile would hold one compute unit
+    // long after the others are done): scratch tile k holds planes [nwmax][T T] of 64-bit
+    // fixed-point (re, im) pairs that the items add to (FP32: exact, in any order; zero
+    // between launches), or of complex values stored by one share (FP64); a kernel after
+    // the spread sums them into the planes
+    const SharedTile *shared;
+    int n_shared;
+    void *scratch;
+    const uint8_t *occ;   // as XformArgs::occ: planes of a tile that the spread writes
     const int64_t *offsets;
     const void *recs, *omega;
     const void *vis;      // VMODE 0: caller visibilities; VMODE 2: values in home-list order

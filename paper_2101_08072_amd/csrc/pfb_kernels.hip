@@ -560,15 +560,13 @@ __device__ __forceinline__ void fixed_point_scale(float am, float S, float &fsca
 // at a time, 8 + 8 + W lanes each evaluate one 1-D weight (the ES kernel's FP64 square
 // root and exponential are the costly part: once per weight, not once per lane and
 // weight), and every lane adds z U V P[k] to its planes.  After base plane q, plane q is
-// complete: the block's waves add up their sums in wave order (the results are bitwise
-// reproducible) and the first wave writes it.  Blocks of one wave where buckets are
-// short, more where one wave's serial pass would be the launch's tail.
-constexpr int kSpread64Long = 512;   // entries per work item (on average) from which a block has four waves
+// complete and is written.  A block is one wave; dense tiles are shared between items,
+// whose planes are summed in the order of the shares (bitwise reproducible).
 template <int W, bool FLAT> struct Spread64 {
     static constexpr int WW = FLAT ? 1 : W;
     static constexpr int ENT = 5;                        // fu, fv, fw, Re z, Im z
     static constexpr int WAVE = 64 * ENT + 2 * 32;       // doubles of a wave: batch, weights of two entries
-    static constexpr size_t lds(int waves) { return (size_t)waves * (WAVE + (waves > 1 ? 128 : 0)) * sizeof(double); }
+    static constexpr size_t lds = (size_t)WAVE * sizeof(double);
 };
 // LDS writes of this wave's lanes are seen by its other lanes' later reads
 __device__ __forceinline__ void wave_lds_fence() {
@@ -578,15 +576,13 @@ __device__ __forceinline__ void wave_lds_fence() {
 }
 
 template <int W, bool FLAT, int VMODE>
-__global__ __launch_bounds__(256, 4) void spread64_kernel(SpreadLaunch a) {
+__global__ __launch_bounds__(64, 4) void spread64_kernel(SpreadLaunch a) {
     using K = Spread64<W, FLAT>;
     using R = double;
     constexpr int WW = K::WW, ENT = K::ENT;
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    const int lane = threadIdx.x & 63, nwave = blockDim.x >> 6;
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    R *const ent = reinterpret_cast<R *>(smem_raw) + wv * K::WAVE, *const wgt = ent + 64 * ENT;
-    cplx<R> *const sums = reinterpret_cast<cplx<R> *>(reinterpret_cast<R *>(smem_raw) + nwave * K::WAVE);
+    const int lane = threadIdx.x;
+    R *const ent = reinterpret_cast<R *>(smem_raw), *const wgt = ent + 64 * ENT;
     const int T = a.g.T, nsub = T / 8;                   // 8 x 8 blocks per tile side
     const GridWork wk = a.work[blockIdx.x];
     const BandDev bd = a.bands[wk.band];
@@ -617,8 +613,7 @@ __global__ __launch_bounds__(256, 4) void spread64_kernel(SpreadLaunch a) {
                 b0 = a.offsets[keybase + q];
                 n = a.offsets[keybase + q + 1] - b0;
             }
-            const int64_t per = (n + nwave - 1) / nwave;
-            const int64_t e_beg = b0 + min(n, wv * per), e_end = b0 + min(n, (wv + 1) * per);
+            const int64_t e_beg = b0 + n * wk.share / wk.nshare, e_end = b0 + n * (wk.share + 1) / wk.nshare;
             const R wbase = wsel == 0 ? R(r0 + wi) : (wsel == 1 ? R(c0 + wi - 8) : R(q + wi - 16));
             for (int64_t e0 = e_beg; e0 < e_end; e0 += 64) {
                 const int64_t e = min(e0 + lane, e_end - 1);
@@ -689,18 +684,46 @@ __global__ __launch_bounds__(256, 4) void spread64_kernel(SpreadLaunch a) {
             }
             are[WW - 1] = aim[WW - 1] = R(0);
             if (q < wk.p0) continue;
-            if (nwave > 1) {
-                sums[threadIdx.x] = v;
-                __syncthreads();
-                if (wv == 0)
-                    for (int k = 1; k < nwave; ++k) v = v + sums[64 * k + lane];
-                __syncthreads();
-            }
-            if (wv == 0)
+            if (wk.nshare > 1)
+                reinterpret_cast<cplx<R> *>(a.scratch)[((size_t)(wk.slot + wk.share) * a.g.nwmax + q) * T * T +
+                                                       (r0 + crow) * T + c0 + ccol] = v;
+            else
                 planes[((size_t)bb * a.g.nwmax + q) * plane_sz + (size_t)(tu * T + r0 + crow) * a.g.gy +
                        (size_t)(tv * T + c0 + ccol)] = v;
         }
     }
+}
+
+// The planes of shared tiles from their scratch tiles: FP32 converts the fixed-point sums
+// and clears them for the next launch, FP64 adds the shares in order.  One block per
+// (shared tile, plane); planes the spread did not touch are left alone.
+template <typename R>
+__global__ __launch_bounds__(kThreads) void shared_tiles_kernel(SpreadLaunch a, float S) {
+    const SharedTile st = a.shared[blockIdx.x / a.g.nwmax];
+    const int p = blockIdx.x % a.g.nwmax;
+    const int T = a.g.T, TT = T * T, lgT = __builtin_ctz(T);
+    const int tu = st.tile / a.g.nty, tv = st.tile - tu * a.g.nty;
+    if (!a.occ[((size_t)st.band * a.g.nwmax + p) * a.g.ntx * a.g.nty + st.tile]) return;
+    cplx<R> *dst = reinterpret_cast<cplx<R> *>(a.planes) +
+                   ((size_t)(st.band - a.band0) * a.g.nwmax + p) * a.g.gx * a.g.gy + (size_t)tu * T * a.g.gy + (size_t)tv * T;
+    float fscale = 1.f, finv = 1.f;
+    if constexpr (sizeof(R) == 4) fixed_point_scale(*a.absmax, S, fscale, finv);
+    for (int k = threadIdx.x; k < TT; k += kThreads) {
+        cplx<R> v{R(0), R(0)};
+        if constexpr (sizeof(R) == 4) {
+            long long *const c = reinterpret_cast<long long *>(a.scratch) + 2 * (((size_t)st.slot * a.g.nwmax + p) * TT + k);
+            v = cplx<R>{(R)((double)c[0] * (double)finv), (R)((double)c[1] * (double)finv)};
+            c[0] = c[1] = 0;
+        } else {
+            const cplx<R> *c = reinterpret_cast<const cplx<R> *>(a.scratch) + ((size_t)st.slot * a.g.nwmax + p) * TT + k;
+            for (int i = 0; i < st.nshare; ++i) v = v + c[(size_t)i * a.g.nwmax * TT];
+        }
+        dst[(size_t)(k >> lgT) * a.g.gy + (k & (T - 1))] = v;
+    }
+}
+template <typename R> static hipError_t sum_shared_tiles(const SpreadLaunch &a, float S, hipStream_t s) {
+    if (a.n_shared > 0) PFB_LAUNCH(shared_tiles_kernel<R>, (unsigned)((int64_t)a.n_shared * a.g.nwmax), 0, s, a, S);
+    return hipSuccess;
 }
 
 // LDS stride of one plane slot, in 64-bit words: padding each slot by 2 words spreads
@@ -784,9 +807,10 @@ __device__ __forceinline__ int64_t rfl64(int64_t v) {
 }
 
 // TC: the tile side as a compile-time constant (LDS offsets become immediates), or
-// 0 to take it from the launch arguments.  PARTS: the work list holds items of parts of
-// tiles (with the test in the one kernel, short buckets of whole tiles took 8 % longer)
-template <int W, int VMODE, int TC, bool FLAT, bool PARTS>
+// 0 to take it from the launch arguments.  SHARES: the work list holds tiles shared
+// between items (a kernel of its own: tests of the item's kind inside this one made
+// short buckets of whole tiles take 8 % longer)
+template <int W, int VMODE, int TC, bool FLAT, bool SHARES>
 __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch a) {
     using R_ = float;
     using A = unsigned long long;
@@ -811,10 +835,6 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
     cplx<R_> *planes = reinterpret_cast<cplx<R_> *>(a.planes);
     R_ fscale = R_(1), finv = R_(1);
     fixed_point_scale(*a.absmax, kMfmaScale, fscale, finv);
-    // the cells of this item: rows [rlo, rhi), columns [clo, chi) of the tile
-    const int part_t = PARTS ? T / wk.split : T;
-    const int rlo = PARTS ? wk.part / wk.split * part_t : 0, rhi = rlo + part_t;
-    const int clo = PARTS ? wk.part % wk.split * part_t : 0, chi = clo + part_t;
     const int64_t keybase = ((int64_t)wk.band * ntiles + wk.tile) * a.g.nj0max;
     const int qstart = max(0, wk.p0 - WW + 1);
     const int qlast = min(wk.p1, bd.nj0);        // base planes qstart .. qlast - 1 can hold entries
@@ -844,7 +864,12 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
         be += 64;
         if (be < bend) return;
         for (++bq; bq < qlast; ++bq) {
-            const int64_t b0 = soff_at(bq - qstart), n = soff_at(bq - qstart + 1) - b0;
+            int64_t b0 = soff_at(bq - qstart), n = soff_at(bq - qstart + 1) - b0;
+            if (SHARES) {   // this item's run of the bucket
+                const int64_t s0 = n * wk.share / wk.nshare, s1 = n * (wk.share + 1) / wk.nshare;
+                b0 += s0;
+                n = s1 - s0;
+            }
             const int64_t per = (n + NWAVE - 1) / NWAVE;
             be = b0 + min(n, wv * per);
             bend = b0 + min(n, (wv + 1) * per);
@@ -930,8 +955,8 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
                         touched |= __float_as_int(cre[t][v]) | (IM ? __float_as_int(cim[t][v]) : 0);
-                const bool colok = J + r >= clo && J + r < chi && (touched & 0x7fffffff);
-                const bool rows_in = I >= rlo && I + WR <= rhi;    // wave-uniform
+                const bool colok = J + r >= 0 && J + r < T && (touched & 0x7fffffff);
+                const bool rows_in = I >= 0 && I + WR <= T;    // wave-uniform
                 if (rows_in) {    // one lane mask per tile, no per-row tests
 #pragma unroll
                     for (int t = 0; t < NT; ++t) {
@@ -952,7 +977,7 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         const int row = I + irow + v;
-                        if (colok && koff[t] >= 0 && row >= rlo && row < rhi) {
+                        if (colok && koff[t] >= 0 && row >= 0 && row < T) {
                             const int idx = koff[t] + base + v * T;
                             atomicAdd(sre + idx, f2fix(cre[t][v]));
                             if (IM) atomicAdd(sim + idx, f2fix(cim[t][v]));
@@ -975,8 +1000,8 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
                 const RawVal val_n = load_val(eb + lane, endb, rec_n, hp_n);
                 const Rec<R_> rec_nn = load_rec(ec + lane, endc);
                 const uint32_t hp_nn = load_hp(ec + lane, endc);
-                cplx<R_> zc = make_val(val_c, rec_c);
-                int nbatch = (int)min((int64_t)64, enda - ea);
+                const cplx<R_> zc = make_val(val_c, rec_c);
+                const int nbatch = (int)min((int64_t)64, enda - ea);
                 // owner lane: window of its entry and the offsets of the window origin
                 int okey;
                 R_ odu, odv, odq;
@@ -988,23 +1013,6 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
                     odu = R_(wa * RB - (W - 1)) - rec_c.fu;     // row 0 of the window minus fu
                     odv = R_(wb * CB - (W - 1)) - rec_c.fv;
                     odq = R_(q) - dev_abs(rec_c.fw);
-                    if (PARTS && wk.split > 1) {
-                        // only the entries whose footprint reaches this part: lane k takes the
-                        // k-th of them (the batch stays in order)
-                        const bool on = lane < nbatch && i0 < rhi && i0 + W > rlo && j0 < chi && j0 + W > clo;
-                        const unsigned long long m = __builtin_amdgcn_ballot_w64(on);
-                        const int rank = __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0));
-                        nbatch = __builtin_popcountll(m);
-                        // (lanes that are off go to the slots behind, so that every slot has one source)
-                        const int to = on ? rank : nbatch + (lane - rank);
-                        const int from = 4 * __builtin_amdgcn_ds_permute(4 * to, lane);
-                        odu = bperm_f(from, odu);
-                        odv = bperm_f(from, odv);
-                        odq = bperm_f(from, odq);
-                        zc.re = bperm_f(from, zc.re);
-                        zc.im = bperm_f(from, zc.im);
-                        okey = __builtin_amdgcn_ds_bpermute(from, okey);
-                    }
                 }
                 // operands of group 0 of the batch; each group fetches those of the next
                 // one before its matrix products, so the crossbar latency overlaps them
@@ -1113,25 +1121,24 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
             dst[(size_t)row * a.g.gy + col] = cplx<R_>{(R_)((double)(long long)sre[c] * (double)finv),
                                                        IM ? (R_)((double)(long long)sim[c] * (double)finv) : R_(0)};
         };
-        auto clear_cell = [&](int row, int col) {
-            const int c = slot * TS + row * T + col;
-            sre[c] = A(0);
-            if (IM) sim[c] = A(0);
+        auto clear_cell = [&](int k) {
+            sre[slot * TS + k] = A(0);
+            if (IM) sim[slot * TS + k] = A(0);
         };
-        if (!PARTS || wk.split == 1) {
+        if (SHARES && wk.nshare > 1) {
+            // this share's sums to the tile's scratch planes: integers, so their order is free
+            A *const sc = reinterpret_cast<A *>(a.scratch) + 2 * ((size_t)wk.slot * a.g.nwmax + q) * TT;
             if (q >= wk.p0)
-                for (int k = threadIdx.x; k < TT; k += kMfmaThreads) write_cell(k / T, k - k / T * T);
-            if (q + 1 >= wk.p1) break;   // the last plane's slot is not used again
-            for (int k = threadIdx.x; k < TT; k += kMfmaThreads) clear_cell(0, k);
-        } else {   // the part's cells (its side is a power of two)
-            const int lgp = __builtin_ctz(part_t);
-            for (int k = threadIdx.x; k < part_t * part_t; k += kMfmaThreads) {
-                const int row = rlo + (k >> lgp), col = clo + (k & (part_t - 1));
-                if (q >= wk.p0) write_cell(row, col);
-                clear_cell(row, col);
-            }
+                for (int k = threadIdx.x; k < TT; k += kMfmaThreads) {
+                    const A re = sre[slot * TS + k], im = IM ? sim[slot * TS + k] : A(0);
+                    if (re) atomicAdd(sc + 2 * k, re);
+                    if (im) atomicAdd(sc + 2 * k + 1, im);
+                }
+        } else if (q >= wk.p0) {
+            for (int k = threadIdx.x; k < TT; k += kMfmaThreads) write_cell(k / T, k - k / T * T);
         }
         if (q + 1 >= wk.p1) break;   // the last plane's slot is not used again
+        for (int k = threadIdx.x; k < TT; k += kMfmaThreads) clear_cell(k);
         __syncthreads();
     }
 }
@@ -1239,12 +1246,11 @@ hipError_t launch_absmax(int vmode, const void *vis, const void *weight, const u
 
 template <int W>
 static hipError_t spread64_w(const SpreadLaunch &a, hipStream_t s) {
-    const int waves = a.n_work > 0 && a.n_entries / a.n_work >= kSpread64Long ? 4 : 1;
     const bool flat = a.g.flat;
 #define SPREAD_CASE(FL, VM)                                                                                       \
     if (flat == FL && a.vmode == VM) {                                                                            \
-        PFB_LAUNCH_NT((spread64_kernel<W, FL, VM>), a.n_work, 64 * waves, (Spread64<W, FL>::lds(waves)), s, a); \
-        return hipSuccess;                                                                                        \
+        PFB_LAUNCH_NT((spread64_kernel<W, FL, VM>), a.n_work, 64, (Spread64<W, FL>::lds), s, a); \
+        return sum_shared_tiles<double>(a, 1.f, s);                                                                                        \
     }
     SPREAD_CASE(false, 0)
     SPREAD_CASE(false, 1)
@@ -1261,11 +1267,15 @@ static hipError_t spread_mfma_w(const SpreadLaunch &a, hipStream_t s) {
     // plane ring + bucket offsets of the base planes of one work item
     const size_t lds = 2 * (size_t)(FLAT ? 1 : W) * run_slot_stride(a.g.T, FLAT) * sizeof(unsigned long long) +
                        ((size_t)a.g.nj0max + 1) * sizeof(int64_t);
-    if ((!FLAT && !a.phase) || (a.parts && a.g.T != 32)) return hipErrorInvalidValue;
+    if (!FLAT && !a.phase) return hipErrorInvalidValue;
 #define SPREAD_MFMA_CASE(VM)                                                                             \
     if (a.vmode == VM) {                                                                                 \
-        if (a.parts) PFB_LAUNCH_NT((spread_mfma_kernel<W, VM, 32, FLAT, true>), a.n_work, kMfmaThreads, lds, s, a); \
-        else if (a.g.T == 32) PFB_LAUNCH_NT((spread_mfma_kernel<W, VM, 32, FLAT, false>), a.n_work, kMfmaThreads, lds, s, a); \
+        if (a.n_shared > 0) {                                                                            \
+            if (a.g.T == 32) PFB_LAUNCH_NT((spread_mfma_kernel<W, VM, 32, FLAT, true>), a.n_work, kMfmaThreads, lds, s, a); \
+            else PFB_LAUNCH_NT((spread_mfma_kernel<W, VM, 0, FLAT, true>), a.n_work, kMfmaThreads, lds, s, a); \
+            return sum_shared_tiles<float>(a, kMfmaScale, s);                                            \
+        }                                                                                                \
+        if (a.g.T == 32) PFB_LAUNCH_NT((spread_mfma_kernel<W, VM, 32, FLAT, false>), a.n_work, kMfmaThreads, lds, s, a); \
         else PFB_LAUNCH_NT((spread_mfma_kernel<W, VM, 0, FLAT, false>), a.n_work, kMfmaThreads, lds, s, a); \
         return hipSuccess;                                                                               \
     }

@@ -68,10 +68,10 @@ def test_fp32_supports_flat_and_sparse(support, tol):
 @pytest.mark.parametrize("support", [4, 7, 8])
 @pytest.mark.parametrize("tile", [16, 32])
 @pytest.mark.parametrize("kind", ["centre", "corner", "edge"])
-def test_dense_tiles_split_into_parts(kind, tile, support):
+def test_dense_tiles_shared_between_items(kind, tile, support):
     """Most visibilities in one uv tile (its centre, a corner, across the periodic edge):
-    the tile goes to 2 x 2 or 4 x 4 items that own parts of its cells.  A given chunk
-    keeps whole tiles: the same sums, exact in fixed point, so nearly the same image."""
+    several items share the tile's entries and their sums meet in a scratch tile.  A given
+    chunk keeps one item per tile: the same sums but for where runs are cut."""
     import torch
     prob, vis, x = _case(3000, nx=64, ny=64, seed=345)
     rng = np.random.default_rng(346)
@@ -91,7 +91,7 @@ def test_dense_tiles_split_into_parts(kind, tile, support):
         # flush order differs (runs of a window end elsewhere): 2^-24 of the largest value each
         assert rel(got[0], got[1]) < 1e-6 and rel(hx[0], hx[1]) < 1e-6
         assert np.array_equal(got[0], got[2])
-    say(f"parts {kind} W={support} T={tile}: {e}")
+    say(f"shares {kind} W={support} T={tile}: {e}")
     assert max(e) < tol
 
 
@@ -111,3 +111,49 @@ def test_w_planes_with_gaps_between_their_entries(support):
     say(f"w gaps W={support}: planes {plan.info()['n_wplanes_max']}, {e}")
     assert max(e) < tol
     assert np.array_equal(got[0], got[1]) and np.array_equal(got[0], got[2])
+
+
+@pytest.mark.parametrize("support,tile", [(13, 8), (9, 16), (16, 8)])
+def test_fp64_dense_tiles_shared_between_items(support, tile):
+    import torch
+    prob, vis, x = _case(6000, nx=64, ny=64, seed=347)
+    prob.uvw[:, :2] *= 0.15                        # a handful of tiles around the centre
+    tol = 1e-7 if support == 9 else 1e-10
+    for flat in (False, True):
+        plan = make_plan(prob, "fp64", support=support, tile=tile, flat=flat)
+        got = [host(plan.grid(to_dev(vis, torch.complex128))).copy() for _ in range(3)]
+        one = host(make_plan(prob, "fp64", support=support, tile=tile, flat=flat, chunk=1 << 20)
+                   .grid(to_dev(vis, torch.complex128)))
+        assert rel(got[0], oracle.grid(prob, vis, flat=flat)) < tol
+        assert rel(got[0], one) < 1e-13
+        assert np.array_equal(got[0], got[1]) and np.array_equal(got[0], got[2])
+        assert rel(host(plan.hessian(to_dev(x, torch.float64))), oracle.hessian(prob, x, flat=flat)) < tol
+    psf = host(plan.make_psf())
+    assert rel(psf, oracle.psf(prob)) < tol
+
+
+def test_shared_tiles_with_bands_in_batches():
+    """Shared tiles of several bands, all at once and one band at a time; replays of a
+    captured graph of the gridding give the eager result (the scratch is zero again)."""
+    import torch
+    prob = synth.tiny_problem(seed=348, nx=64, ny=64, n_row=5000, freqs=(1.0e9, 1.1e9, 1.2e9), cell_arcsec=60.0,
+                              n_band=3, w_frac=1.0)
+    prob.uvw[:, :2] *= 0.3
+    vis = to_dev(np.random.default_rng(349).normal(size=(5000, 3)) + 0.5j, torch.complex64)
+    one, every = make_plan(prob, band_batch=1), make_plan(prob)
+    a, b = one.grid(vis), every.grid(vis)
+    assert torch.equal(a, b)
+    assert rel(host(a), oracle.grid(prob, host(vis))) < TOL["fp32"]
+    out = torch.empty_like(a)
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        every.grid(vis, out=out)
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, a)
+        every.grid(vis)
+        torch.cuda.synchronize()
