@@ -170,6 +170,8 @@ struct GridderHost {
     bool mfma = false;                   // FP32 w-stacked gridder: phase table of the entries
     int sort_rb = 1, sort_cb = 1;        // sort blocks of base rows x columns
     bool istream = false;                // interpolation items of the kernel for few entries per tile
+    std::vector<GridWork> cwork;         // FP32: tiles of few entries, for the spread whose lanes own cells
+    std::vector<int> cband_start;        // per band first of them (n_band + 1)
     std::vector<SharedTile> shared;      // tiles whose entries several spread items share
     std::vector<int> shared_start;       // per band first of them (n_band + 1)
     int n_scratch = 0;                   // scratch tiles they need
@@ -188,9 +190,10 @@ struct GridderHost {
     GridWork *d_gwork = nullptr;
     InterpWork *d_iwork = nullptr;
     SharedTile *d_shared = nullptr;
+    GridWork *d_cwork = nullptr;
     void *d_scratch = nullptr;
     void *d_recs = nullptr, *d_omega = nullptr, *d_corr2d = nullptr, *d_corrx = nullptr, *d_corry = nullptr;
-    size_t o_shared = 0, o_scratch = 0;
+    size_t o_shared = 0, o_scratch = 0, o_cwork = 0;
     size_t o_phase = 0;
     void *d_phase = nullptr;
     size_t o_hidx = 0, o_hoffsets = 0;
@@ -269,20 +272,23 @@ constexpr int64_t kStreamPerTile = 400;
 // Work lists from the per-(band, tile, base plane) counts: spread items of at most
 // `chunk` entries, interpolation items of at most `ichunk` home entries.  share > 0: tiles
 // of more than two such shares of entries go to several items that share them instead,
-// with one scratch tile each (per_share) or one together.
+// with one scratch tile each (per_share) or one together.  Tiles of at most `cells`
+// entries go to the list of the kernel whose lanes own cells.
 void build_work(GridderHost &G, const std::vector<unsigned> &counts, const std::vector<unsigned> &hcounts, int chunk,
-                int ichunk, int64_t share, bool per_share) {
+                int ichunk, int64_t share, bool per_share, int64_t cells) {
     const GeomDev &g = G.g;
     const int ntiles = g.ntx * g.nty;
     const int W = g.flat ? 1 : g.W;
     G.gwork.clear();
     G.iwork.clear();
+    G.cwork.clear();
+    G.cband_start.assign(g.n_band + 1, 0);
     G.shared.clear();
     G.shared_start.assign(g.n_band + 1, 0);
     G.n_scratch = 0;
     G.gband_start.assign(g.n_band + 1, 0);
     G.iband_start.assign(g.n_band + 1, 0);
-    std::vector<std::pair<int64_t, GridWork>> gw;
+    std::vector<std::pair<int64_t, GridWork>> gw, cw;
     std::vector<std::pair<int64_t, InterpWork>> iw;
     const size_t nflag = (size_t)g.n_band * g.nwmax * ntiles;
     G.occ.assign(nflag, 0);
@@ -292,6 +298,7 @@ void build_work(GridderHost &G, const std::vector<unsigned> &counts, const std::
     for (int b = 0; b < g.n_band; ++b) {
         const BandDev &bd = G.bands[b];
         gw.clear();
+        cw.clear();
         iw.clear();
         for (int t = 0; t < ntiles; ++t) {
             const int64_t kb = ((int64_t)b * ntiles + t) * g.nj0max;
@@ -315,7 +322,9 @@ void build_work(GridderHost &G, const std::vector<unsigned> &counts, const std::
                 for (int q = std::max(0, a0 - W + 1); q < std::min(a1, bd.nj0); ++q) s += c[q];
                 return s;
             };
-            if (share > 0 && tot > 2 * share) {
+            if (tot > 0 && tot <= cells) {
+                cw.push_back({tot, GridWork{b, t, 0, nw, 0, 1, 0}});
+            } else if (share > 0 && tot > 2 * share) {
                 const int ns = (int)((tot + share - 1) / share);
                 G.shared.push_back(SharedTile{b, t, G.n_scratch, ns});
                 for (int k = 0; k < ns; ++k)
@@ -369,11 +378,14 @@ void build_work(GridderHost &G, const std::vector<unsigned> &counts, const std::
         }
         std::stable_sort(gw.begin(), gw.end(), [](auto &a, auto &b) { return a.first > b.first; });
         std::stable_sort(iw.begin(), iw.end(), [](auto &a, auto &b) { return a.first > b.first; });
+        std::stable_sort(cw.begin(), cw.end(), [](auto &a, auto &b) { return a.first > b.first; });
         for (auto &x : gw) G.gwork.push_back(x.second);
+        for (auto &x : cw) G.cwork.push_back(x.second);
         for (auto &x : iw) G.iwork.push_back(x.second);
         G.gband_start[b + 1] = (int)G.gwork.size();
         G.iband_start[b + 1] = (int)G.iwork.size();
         G.shared_start[b + 1] = (int)G.shared.size();
+        G.cband_start[b + 1] = (int)G.cwork.size();
     }
     G.occ_list.clear();
     G.need_list.clear();
@@ -466,6 +478,8 @@ SpreadLaunch spread_args(const pfb_plan *P, const GridderHost &G, int b0, int nb
     s.bands = G.d_bands;
     s.work = G.d_gwork + G.gband_start[b0];
     s.n_work = G.gband_start[b0 + nbb] - G.gband_start[b0];
+    s.cwork = G.d_cwork + G.cband_start[b0];
+    s.n_cwork = G.cband_start[b0 + nbb] - G.cband_start[b0];
     s.shared = G.d_shared + G.shared_start[b0];
     s.n_shared = G.shared_start[b0 + nbb] - G.shared_start[b0];
     s.scratch = G.d_scratch;
@@ -714,12 +728,20 @@ pfb_status count_and_layout(pfb_plan *P, char *tmp, hipStream_t stream) {
         // cost (filling or clearing the plane ring, the steps over its planes).  Spread tiles
         // of more than two such shares are shared between items, interpolation items, which
         // only read, are split at a third of a share (>= 1024 entries); a given chunk is kept.
-        int64_t tiles = 0;   // (band, tile)s with entries
+        int64_t tiles = 0, sparse = 0;   // (band, tile)s with entries, with few
         for (size_t k2 = 0; k2 < cnt.size(); k2 += G->g.nj0max) {
-            bool any = false;
-            for (int q = 0; q < G->g.nj0max; ++q) any = any || cnt[k2 + q];
-            tiles += any;
+            int64_t tot = 0;
+            for (int q = 0; q < G->g.nj0max; ++q) tot += cnt[k2 + q];
+            tiles += tot > 0;
+            sparse += tot > 0 && tot <= kCellsMax;
         }
+        // tiles of few entries go to the kernel whose lanes own cells, where all do or enough
+        // to fill the device twice (beside a few dense tiles, whose launch takes its time
+        // anyway, a second launch cost more than it saved: 512^2, 1.5e5 visibilities, 68
+        // against 24 + 66 us)
+        const bool own = sparse == tiles || sparse >= 2 * n_cu;
+        const int64_t cells = !dbl && !G->g.flat && !opt.chunk && G->g.T <= 32 && G->g.nj0max <= kCellsMaxPlanes && own
+                                  ? kCellsMax : 0;
         const int64_t unit = (acc + 1500 * tiles) / n_cu;
         // w-stacked FP64, and FP32 with few entries per tile: the plane-by-plane interpolation
         G->istream = !G->g.flat && (dbl || (!opt.chunk && hacc < kStreamPerTile * tiles));
@@ -729,7 +751,7 @@ pfb_status count_and_layout(pfb_plan *P, char *tmp, hipStream_t stream) {
         const int64_t share = opt.chunk ? 0
                               : dbl     ? std::max<int64_t>(64, acc / (32 * (int64_t)n_cu))
                                         : std::max<int64_t>(256, unit);
-        build_work(*G, cnt, hcnt, chunk, ichunk, share, dbl);
+        build_work(*G, cnt, hcnt, chunk, ichunk, share, dbl, cells);
         G->sort_items.clear();
         for (size_t k2 = 0; k2 < cnt.size(); ++k2)
             if (cnt[k2]) {
@@ -795,6 +817,7 @@ pfb_status count_and_layout(pfb_plan *P, char *tmp, hipStream_t stream) {
         G->o_cursor = L.take((G->offsets.size()) * sizeof(unsigned long long));
         G->o_gwork = L.take(std::max<size_t>(G->gwork.size(), 1) * sizeof(GridWork));
         G->o_iwork = L.take(std::max<size_t>(G->iwork.size(), 1) * sizeof(InterpWork));
+        G->o_cwork = L.take(std::max<size_t>(G->cwork.size(), 1) * sizeof(GridWork));
         G->o_shared = L.take(std::max<size_t>(G->shared.size(), 1) * sizeof(SharedTile));
         G->scratch_bytes = (size_t)G->n_scratch * G->g.nwmax * G->g.T * G->g.T * 16;
         G->o_scratch = L.take(std::max<size_t>(G->scratch_bytes, 1));
@@ -1161,6 +1184,10 @@ pfb_status pfb_plan_set_workspace(pfb_plan *P, void *dev, size_t bytes, hipStrea
         G->d_cursor = reinterpret_cast<unsigned long long *>(P->p(G->o_cursor));
         G->d_gwork = reinterpret_cast<GridWork *>(P->p(G->o_gwork));
         G->d_iwork = reinterpret_cast<InterpWork *>(P->p(G->o_iwork));
+        G->d_cwork = reinterpret_cast<GridWork *>(P->p(G->o_cwork));
+        if (!G->cwork.empty())
+            HIP_OK(hipMemcpyAsync(G->d_cwork, G->cwork.data(), G->cwork.size() * sizeof(GridWork),
+                                  hipMemcpyHostToDevice, s));
         G->d_shared = reinterpret_cast<SharedTile *>(P->p(G->o_shared));
         G->d_scratch = P->p(G->o_scratch);
         if (!G->shared.empty()) {

@@ -54,6 +54,8 @@ hipError_t launch_corr2d(bool dbl, const GeomDev &g, const BandDev *bands, const
 hipError_t launch_corr1d(bool dbl, int n, int gsize, const double *cheb, int ncheb, double xi_max,
                          void *corr, hipStream_t s);
 
+constexpr int kCellsMax = 384;          // entries of a tile
+constexpr int kCellsMaxPlanes = 1024;   // base planes (their offsets sit in LDS)
 struct SpreadLaunch {
     GeomDev g;
     const BandDev *bands;
@@ -64,6 +66,8 @@ struct SpreadLaunch {
     // fixed-point (re, im) pairs that the items add to (FP32: exact, in any order; zero
     // between launches), or of complex values stored by one share (FP64); a kernel after
     // the spread sums them into the planes
+    const GridWork *cwork;  // FP32 w-stacked: tiles of at most kCellsMax entries, whole, for the
+    int n_cwork;            // kernel whose lanes own cells
     const SharedTile *shared;
     int n_shared;
     void *scratch;

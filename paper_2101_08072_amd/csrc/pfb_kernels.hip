@@ -1143,6 +1143,129 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
     }
 }
 
+// FP32 spread of tiles with few entries: every lane of a wave owns one cell of an 8 x 8
+// block of the tile and keeps its sums of the planes q .. q + W - 1 in registers, as
+// spread64_kernel does.  The matrix-core kernel's LDS ring leaves one block per CU, which
+// takes about 16 us per tile however few entries it holds: barriers and write-outs plane
+// by plane, and flushes of whole windows for one or two entries.  Here a block of (T / 8)^2
+// waves stages the tile's entries (all base planes) in LDS once; then its waves go through
+// the base planes on their own, take the entries that reach their 8 x 8 block and store
+// their own cells of every finished plane, without barriers, and two blocks share a CU.  An entry costs about 2.7 times what it costs in a
+// dense window product, so tiles of more than kCellsMax entries stay there:
+// 1728 x 1200, two bands, 4.3e5 visibilities 657 -> 222 + 33 us; 1.5e5 at 2048^2 375 ->
+// 128; 7.2e6 there 1434 -> 94 + 1160.
+// Values are scaled by 1 / max |z| (sums of order one; a bad maximum gives NaN cells).
+template <int W, int VMODE>
+__global__ __launch_bounds__(1024, 8) void spread_cells_kernel(SpreadLaunch a) {
+    using R = float;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int T = a.g.T, nsub = T / 8, nthr = 64 * nsub * nsub;
+    R *const efu = reinterpret_cast<R *>(smem_raw), *const efv = efu + kCellsMax, *const efw = efv + kCellsMax;
+    cplx<R> *const ez = reinterpret_cast<cplx<R> *>(efw + kCellsMax);
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    R *const wgt = reinterpret_cast<R *>(ez + kCellsMax) + 64 * wv;          // weights of two entries
+    int *const soff = reinterpret_cast<int *>(reinterpret_cast<R *>(ez + kCellsMax) + nthr);
+    const GridWork wk = a.cwork[blockIdx.x];
+    const BandDev bd = a.bands[wk.band];
+    const int ntiles = a.g.ntx * a.g.nty;
+    const int tu = wk.tile / a.g.nty, tv = wk.tile - tu * a.g.nty;
+    const int bb = wk.band - a.band0;
+    const Rec<R> *recs = reinterpret_cast<const Rec<R> *>(a.recs);
+    const R *omega = reinterpret_cast<const R *>(a.omega);
+    const cplx<R> *phase = reinterpret_cast<const cplx<R> *>(a.phase);
+    const cplx<R> *vis = reinterpret_cast<const cplx<R> *>(a.vis);
+    cplx<R> *planes = reinterpret_cast<cplx<R> *>(a.planes);
+    R fscale = R(1), finv = R(1);
+    fixed_point_scale(*a.absmax, 1.0f, fscale, finv);
+    // the tile's entries: base plane q at ebase + soff[q] .. soff[q + 1] - 1
+    const int64_t keybase = ((int64_t)wk.band * ntiles + wk.tile) * a.g.nj0max;
+    const int64_t ebase = a.offsets[keybase];
+    for (int k = threadIdx.x; k <= bd.nj0; k += nthr) soff[k] = (int)(a.offsets[keybase + k] - ebase);
+    __syncthreads();
+    const int n_all = __builtin_amdgcn_readfirstlane(soff[bd.nj0]);
+    const R beta2 = (R)(a.g.beta * 1.4426950408889634), inv_hw = R(2) / R(W), hw = R(0.5) * R(W);
+    const size_t plane_sz = (size_t)a.g.gx * a.g.gy;
+    const int r0 = wv / nsub * 8, c0 = wv % nsub * 8;
+    const int crow = lane >> 3, ccol = lane & 7;
+    cplx<R> *const dst = planes + (size_t)bb * a.g.nwmax * plane_sz + (size_t)(tu * T + r0 + crow) * a.g.gy +
+                         (size_t)(tv * T + c0 + ccol);
+    // weight evaluated by this lane for entry lane / 32 of a pair: rows 0-7, columns 0-7, planes
+    const int wi = lane & 31;
+    const R *const ecoord = wi < 8 ? efu : (wi < 16 ? efv : efw);
+    const R wpos = wi < 8 ? R(r0 + wi) : (wi < 16 ? R(c0 + wi - 8) : R(wi - 16));
+    R are[W], aim[W];
+#pragma unroll
+    for (int k = 0; k < W; ++k) are[k] = aim[k] = R(0);
+    unsigned live = 0;    // bit k: base plane q - k has entries
+    for (int k = threadIdx.x; k < n_all; k += nthr) {
+        const int64_t e = ebase + k;
+        const Rec<R> rec = recs[e];
+        cplx<R> z;
+        if (VMODE == 0) z = entry_conj(rec, vis[rec.idx & ~kHomeBit]) * phase[e] * (omega[e] * fscale);
+        else if (VMODE == 1) z = cplx<R>{omega[e] * fscale, R(0)};
+        else z = vis[a.home_pos[e]] * fscale;
+        efu[k] = rec.fu;
+        efv[k] = rec.fv;
+        efw[k] = dev_abs(rec.fw);
+        ez[k] = z;
+    }
+    __syncthreads();
+    for (int q = 0; q < bd.nw; ++q) {
+        const int qb = q < bd.nj0 ? __builtin_amdgcn_readfirstlane(soff[q]) : n_all;
+        const int qe = q < bd.nj0 ? __builtin_amdgcn_readfirstlane(soff[q + 1]) : n_all;
+        const R wbase = wi < 16 ? wpos : wpos + R(q);
+        for (int k0 = qb; k0 < qe; k0 += 64) {
+            const int k = min(k0 + lane, qe - 1);
+            const int i0 = (int)dev_floor(efu[k] - hw) + 1, j0 = (int)dev_floor(efv[k] - hw) + 1;
+            unsigned long long todo = __builtin_amdgcn_ballot_w64(k0 + lane < qe && i0 < r0 + 8 && i0 + W > r0 &&
+                                                                  j0 < c0 + 8 && j0 + W > c0);
+            while (todo) {
+                const int ea = k0 + __builtin_ctzll(todo);
+                todo &= todo - 1;
+                const bool two = todo != 0;
+                const int eb = two ? k0 + __builtin_ctzll(todo) : ea;
+                todo &= todo - 1;
+                const R w = es_kernel_fast(wbase - ecoord[lane < 32 ? ea : eb], beta2, inv_hw);
+                wave_lds_fence();
+                wgt[lane] = w;
+                wave_lds_fence();
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    if (h == 1 && !two) break;
+                    const R *const wh = wgt + 32 * h;
+                    const cplx<R> z = ez[h ? eb : ea];
+                    const R uv = wh[crow] * wh[8 + ccol];
+                    const R zr = z.re * uv, zi = z.im * uv;
+#pragma unroll
+                    for (int p = 0; p < W; ++p) {
+                        are[p] += zr * wh[16 + p];
+                        aim[p] += zi * wh[16 + p];
+                    }
+                }
+            }
+        }
+        live = ((live << 1) | (qe > qb ? 1u : 0u)) & ((1u << W) - 1u);
+        if (!live) continue;  // zero sums; the transforms do not read this plane of the tile
+        dst[(size_t)q * plane_sz] = cplx<R>{are[0] * finv, aim[0] * finv};
+#pragma unroll
+        for (int k = 0; k + 1 < W; ++k) {
+            are[k] = are[k + 1];
+            aim[k] = aim[k + 1];
+        }
+        are[W - 1] = aim[W - 1] = R(0);
+    }
+}
+template <int W> static hipError_t spread_cells_w(const SpreadLaunch &a, hipStream_t s) {
+    if (a.g.flat || !a.phase || a.g.T > 32 || a.g.nj0max > kCellsMaxPlanes) return hipErrorInvalidValue;
+    const int nthr = a.g.T * a.g.T;   // 64 threads per 8 x 8 block
+    const size_t lds = (size_t)kCellsMax * 20 + (size_t)nthr * sizeof(float) + ((size_t)a.g.nj0max + 1) * sizeof(int);
+    if (a.vmode == 0) PFB_LAUNCH_NT((spread_cells_kernel<W, 0>), a.n_cwork, nthr, lds, s, a);
+    else if (a.vmode == 1) PFB_LAUNCH_NT((spread_cells_kernel<W, 1>), a.n_cwork, nthr, lds, s, a);
+    else PFB_LAUNCH_NT((spread_cells_kernel<W, 2>), a.n_cwork, nthr, lds, s, a);
+    return hipSuccess;
+}
+
 // max |z| over active visibilities (FP32 path): per-block maxima, then one block
 __global__ __launch_bounds__(kThreads) void absmax_blocks_kernel(int vmode, const cplx<float> *vis,
                                                                  const float *weight, const uint8_t *flag,
@@ -1301,6 +1424,11 @@ size_t gridder_lds_bytes(bool dbl, int W, int T, bool flat) {
 }
 
 hipError_t launch_spread(bool dbl, const SpreadLaunch &a, hipStream_t s) {
+    if (a.n_cwork > 0) {
+        if (dbl) return hipErrorInvalidValue;
+        const hipError_t e = dispatch_int<4, 8>(a.g.W, [&](auto Wc) { return spread_cells_w<decltype(Wc)::value>(a, s); });
+        if (e != hipSuccess) return e;
+    }
     if (a.n_work <= 0) return hipSuccess;
     if (dbl)
         return dispatch_int<9, 16>(a.g.W, [&](auto Wc) { return spread64_w<decltype(Wc)::value>(a, s); });

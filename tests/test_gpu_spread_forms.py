@@ -157,3 +157,46 @@ def test_shared_tiles_with_bands_in_batches():
         assert torch.equal(out, a)
         every.grid(vis)
         torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("support,tile,tol", [(4, 32, 5e-3), (7, 32, 1e-5), (8, 32, 1e-5), (7, 16, 1e-5), (7, 8, 1e-5)])
+@pytest.mark.parametrize("n_row", [3000, 40000])
+def test_fp32_tiles_of_few_entries(support, tile, tol, n_row):
+    """Many tiles of few entries (lanes own cells), some of them denser than that kernel
+    takes (n_row = 40000); w of several planes with gaps."""
+    import torch
+    prob = synth.tiny_problem(seed=350, nx=512, ny=400, n_row=n_row, freqs=(1.3e9,), cell_arcsec=60.0, w_frac=0.3,
+                              flag_frac=0.1)
+    rng = np.random.default_rng(351)
+    prob.uvw[n_row // 2:, :2] *= 0.2               # half of them in a few tiles
+    prob.uvw[: n_row // 3, 2] += 4.0 * np.abs(prob.uvw[:, 2]).max()
+    vis = rng.normal(size=(n_row, 1)) + 1j * rng.normal(size=(n_row, 1))
+    plan = make_plan(prob, "fp32", support=support, tile=tile)
+    got = [host(plan.grid(to_dev(vis, torch.complex64))).copy() for _ in range(2)]
+    pix = rng.choice(512 * 400, 60, replace=False)
+    x = np.zeros((1, 512, 400))
+    x[0, rng.integers(0, 512, 50), rng.integers(0, 400, 50)] = rng.uniform(0.1, 1.0, 50)
+    pix_h = np.concatenate([np.flatnonzero(x), pix])
+    h = host(plan.hessian(to_dev(x, torch.float32)))
+    e = rel(got[0].ravel()[pix], oracle.grid(prob, vis, pix=pix)), rel(h.ravel()[pix_h], oracle.hessian(prob, x, pix=pix_h))
+    say(f"cells W={support} T={tile} rows={n_row}: planes {plan.info()['n_wplanes_max']}, {e}")
+    assert max(e) < tol
+    assert np.array_equal(got[0], got[1])
+
+
+def test_fp32_tiles_of_few_entries_extreme_scales():
+    """The scaled sums keep the range that the fixed-point kernel has; a NaN or infinite
+    visibility is loud in every pixel."""
+    import torch
+    prob = synth.tiny_problem(seed=352, nx=512, ny=512, n_row=3000, freqs=(1.3e9,), cell_arcsec=60.0)
+    rng = np.random.default_rng(353)
+    vis = rng.normal(size=(3000, 1)) + 1j * rng.normal(size=(3000, 1))
+    plan = make_plan(prob, "fp32")
+    ref = host(plan.grid(to_dev(vis, torch.complex64))).astype(np.float64)
+    for scale in (1e-20, 1e18):
+        assert rel(host(plan.grid(to_dev(vis * scale, torch.complex64))).astype(np.float64) / scale, ref) < 1e-6
+    for bad in (np.nan, np.inf):
+        vis2 = vis.copy()
+        vis2[7] = bad
+        assert np.isnan(host(plan.grid(to_dev(vis2, torch.complex64)))).all()
+    assert np.all(host(plan.grid(to_dev(0 * vis, torch.complex64))) == 0)
