@@ -211,6 +211,26 @@ template <typename R, bool INV> __device__ __forceinline__ void stage_twiddles_t
     }
 }
 
+// v[t] *= w^(t e) for t = 1 .. 7 from w^e, w^2e, w^4e (forward), which a thread of an
+// outermost stage keeps: its e is the same for every transform of the block
+template <typename R> struct OuterTw {
+    cplx<R> w1, w2, w4;
+};
+template <typename R> __device__ __forceinline__ OuterTw<R> outer_twiddles(const TwTab<R> &tw, int e) {
+    return OuterTw<R>{tw.get(e), tw.get(2 * e), tw.get(4 * e)};
+}
+template <typename R, bool INV> __device__ __forceinline__ void stage_twiddles_kept(cplx<R> *v, const OuterTw<R> &o) {
+    const cplx<R> w1 = INV ? conj(o.w1) : o.w1, w2 = INV ? conj(o.w2) : o.w2, w4 = INV ? conj(o.w4) : o.w4;
+    const cplx<R> w3 = w1 * w2;
+    v[1] = v[1] * w1;
+    v[2] = v[2] * w2;
+    v[3] = v[3] * w3;
+    v[4] = v[4] * w4;
+    v[5] = v[5] * (w1 * w4);
+    v[6] = v[6] * (w2 * w4);
+    v[7] = v[7] * (w3 * w4);
+}
+
 // v[t] *= w^(t e) for t = 1 .. RAD - 1
 template <typename R, bool INV, int RAD>
 __device__ __forceinline__ void stage_twiddles(cplx<R> *v, const TwTab<R> &tw, int e) {

@@ -196,6 +196,32 @@ __device__ __forceinline__ void finish_partial(double t, int k, int n_part, doub
     }
 }
 
+// exp(2 pi i t) of the w-plane phases.  FP32: reduced to |f| <= 1 / 8 of a turn around the
+// nearest quarter turn, exactly, then sin and cos(2 pi f) by polynomials fitted to minimax
+// (errors against 64 bits at most 5.9e-8, as the library's sincospif has); 25
+// vector instructions where the library call took 41, of about 140 per value in the
+// column passes.
+template <typename R> __device__ __forceinline__ cplx<R> cis_plane(R t) {
+    if constexpr (sizeof(R) == 8) {
+        return cis_cycles<R>(t);
+    } else {
+        const float r = t - __builtin_rintf(t), q = __builtin_rintf(4.f * r), f = __builtin_fmaf(q, -0.25f, r);
+        const float f2 = f * f;
+        float p = __builtin_fmaf(f2, -75.36964124f, 81.59198331f);
+        p = __builtin_fmaf(p, f2, -41.34166256f);
+        p = __builtin_fmaf(p, f2, -1.7484556e-7f);          // 2 pi less its FP32 value
+        const float sn = __builtin_fmaf(f, 6.2831855f, f * p);
+        float c = __builtin_fmaf(f2, 59.24596098f, -85.44374163f);
+        c = __builtin_fmaf(c, f2, 64.93932647f);
+        c = __builtin_fmaf(c, f2, -19.73920869f);
+        const float cs = __builtin_fmaf(c, f2, 1.f);
+        const int k = (int)q;
+        const float a = (k & 1) ? sn : cs, b = (k & 1) ? cs : sn;
+        return cplx<float>{__uint_as_float(__float_as_uint(a) ^ ((unsigned)(k + 1) << 30 & 0x80000000u)),
+                           __uint_as_float(__float_as_uint(b) ^ ((unsigned)k << 30 & 0x80000000u))};
+    }
+}
+
 // The value of an entry as its listing takes it: conjugated where the entry is
 // listed at -(u, v, w) (sign bit of fw).  Hessian values never need it: they are
 // degridded and gridded at the same listing.
@@ -2253,6 +2279,12 @@ __global__ __launch_bounds__((WCols<R, LOG2N, C, PL>::NT)) void wgrid_cols_kerne
         }
     }
     uint8_t *const flb = reinterpret_cast<uint8_t *>(accl + 8 * NT);   // two buffers of ntx flags
+    // the outermost stage's twiddles, kept over the planes where registers allow (FP32, up to
+    // 8192-row grids)
+    constexpr bool KEEP = sizeof(R) == 4 && LOG2N <= 12;
+    __syncthreads();   // twiddle table
+    OuterTw<R> otw{};
+    if (KEEP && jr < M) otw = outer_twiddles(tt, jr << shn);
     for (int j0 = 0; j0 < nw; j0 += NPL) {
         // the planes' tile-row flags go to LDS, so that the row loads do not wait on flag loads
         const uint8_t *orow = a.occ_row + ((size_t)b * a.g.nwmax + j0) * a.g.ntx;
@@ -2288,7 +2320,8 @@ __global__ __launch_bounds__((WCols<R, LOG2N, C, PL>::NT)) void wgrid_cols_kerne
                     }
                 }
                 dft_small<R, true, 8>(v);
-                stage_twiddles<R, true, 8>(v, tt, jr << shn);
+                if constexpr (KEEP) stage_twiddles_kept<R, true>(v, otw);
+                else stage_twiddles<R, true, 8>(v, tt, jr << shn);
                 cplx<R> *vb = buf + c * ld + LD::pad(jr);
 #pragma unroll
                 for (int t = 0; t < 8; ++t) vb[LD::pad(t * M)] = v[t];
@@ -2330,7 +2363,7 @@ __global__ __launch_bounds__((WCols<R, LOG2N, C, PL>::NT)) void wgrid_cols_kerne
                         if (a.g.flat) {
                             accl[sl] += y.re;
                         } else {
-                            const cplx<R> ph = cis_cycles<R>(wj * svl[sl]);
+                            const cplx<R> ph = cis_plane<R>(wj * svl[sl]);
                             accl[sl] += y.re * ph.re - y.im * ph.im;
                         }
                     }
@@ -2448,6 +2481,12 @@ __global__ __launch_bounds__((WCols<R, LOG2N, C, PL>::NT)) void wdegrid_cols_ker
         }
     }
     uint8_t *const flb = reinterpret_cast<uint8_t *>(svl + 8 * NT);   // two buffers of ntx flags
+    // the outermost stage's twiddles, kept over the planes where registers allow (FP32, up to
+    // 8192-row grids)
+    constexpr bool KEEP = sizeof(R) == 4 && LOG2N <= 12;
+    __syncthreads();   // twiddle table
+    OuterTw<R> otw{};
+    if (KEEP && jr < M) otw = outer_twiddles(tt, jr << shn);
     for (int j0 = 0; j0 < nw; j0 += NPL) {
         // the planes' tile-row flags go to LDS (two buffers: the last round's stores may
         // still read the other), so that the stores do not wait on flag loads
@@ -2468,7 +2507,7 @@ __global__ __launch_bounds__((WCols<R, LOG2N, C, PL>::NT)) void wdegrid_cols_ker
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
             const R xv = xrl[t * NT + threadIdx.x];
-            pv[t] = a.g.flat ? cplx<R>{xv, R(0)} : conj(cis_cycles<R>(wj * svl[t * NT + threadIdx.x])) * xv;
+            pv[t] = a.g.flat ? cplx<R>{xv, R(0)} : conj(cis_plane<R>(wj * svl[t * NT + threadIdx.x])) * xv;
         }
 #pragma unroll 1
         for (int p = 0; p < 2; ++p) {
@@ -2486,7 +2525,8 @@ __global__ __launch_bounds__((WCols<R, LOG2N, C, PL>::NT)) void wdegrid_cols_ker
                     v[t] = p == 0 ? pv[t] : pv[t] * f;
                 }
                 dft_small<R, false, 8>(v);
-                stage_twiddles<R, false, 8>(v, tt, jr << shn);
+                if constexpr (KEEP) stage_twiddles_kept<R, false>(v, otw);
+                else stage_twiddles<R, false, 8>(v, tt, jr << shn);
                 cplx<R> *vb = buf + c * ld + LD::pad(jr);
 #pragma unroll
                 for (int t = 0; t < 8; ++t) vb[LD::pad(t * M)] = v[t];
@@ -2730,6 +2770,10 @@ template <typename R, int LOG2N, int C> struct ConvCols {
     static constexpr int NT0 = C * N / 8;   // one radix-8 butterfly per thread and stage
     static constexpr int NT = NT0 < 64 ? 64 : NT0;
     static_assert(NT0 <= 1024, "at most 1024 threads per block");
+    // outermost twiddles kept in registers: at 4096 points (13.5 -> 13.1 ms for 21
+    // convolutions of 4 x 4096^2, three blocks per CU at 80 registers) and in small blocks;
+    // the 512-thread blocks of 512 to 2048 points would spill (7 % slower)
+    static constexpr bool KEEP = sizeof(R) == 4 && (LOG2N == 12 || NT < 512);
     static constexpr int SE = tw_stage_entries<R, LOG2N>((size_t)C * Lds<R, LOG2N>::ld * sizeof(cplx<R>));
     static constexpr size_t lds = (size_t)C * Lds<R, LOG2N>::ld * sizeof(cplx<R>) + (kTwEntries + SE) * sizeof(cplx<R>);
 };
@@ -2740,7 +2784,8 @@ template <typename R, int LOG2N, int C> struct ConvCols {
 // there: they run at the same time on one XCD and read the group's rows through
 // its L2 (each block reads C of every CG contiguous values).
 template <typename R, int LOG2N, int C, int CG, bool PSF>
-__global__ __launch_bounds__((ConvCols<R, LOG2N, C>::NT)) void conv_cols_kernel(ConvArgs a) {
+__global__ __launch_bounds__((ConvCols<R, LOG2N, C>::NT), (ConvCols<R, LOG2N, C>::KEEP && LOG2N == 12 ? 6 : 1))
+void conv_cols_kernel(ConvArgs a) {
     using K = ConvCols<R, LOG2N, C>;
     using LD = Lds<R, LOG2N>;
     using P = FftPlan<LOG2N>;
@@ -2786,6 +2831,10 @@ __global__ __launch_bounds__((ConvCols<R, LOG2N, C>::NT)) void conv_cols_kernel(
     }
     __syncthreads();   // twiddle table
     const cplx<R> wj = twiddle<R, false>(tt, j << sh2n);
+    // the outermost stages' twiddles, the same in all four transforms
+    constexpr bool KEEP = K::KEEP;
+    OuterTw<R> otw{};
+    if (KEEP && own) otw = outer_twiddles(tt, j << shn);
     // image mode: the PSF spectrum at the thread's innermost-stage outputs of a half
     // (8 / R0 items of R0 values), loaded before the middle stages that hide its latency
     // where that measured faster (N <= 2048: 0.101 -> 0.092 ms at 2048^2; at N = 4096 the
@@ -2824,7 +2873,8 @@ __global__ __launch_bounds__((ConvCols<R, LOG2N, C>::NT)) void conv_cols_kernel(
                 v[t] = p == 0 ? x : x * (wj * root16<R>(t));   // w^r = w^j exp(-2 pi i t / 16)
             }
             dft_small<R, false, 8>(v);
-            stage_twiddles<R, false, 8>(v, tt, (j * (N / (8 * M))) << shn);
+            if constexpr (KEEP) stage_twiddles_kept<R, false>(v, otw);
+            else stage_twiddles<R, false, 8>(v, tt, j << shn);
             cplx<R> *vb = buf + c * ld + LD::pad(j);
 #pragma unroll
             for (int t = 0; t < 8; ++t) vb[LD::pad(t * M)] = v[t];
@@ -2888,7 +2938,8 @@ __global__ __launch_bounds__((ConvCols<R, LOG2N, C>::NT)) void conv_cols_kernel(
             cplx<R> v[8];
 #pragma unroll
             for (int t = 0; t < 8; ++t) v[t] = vb[LD::pad(t * M)];
-            stage_twiddles<R, true, 8>(v, tt, j << shn);
+            if constexpr (KEEP) stage_twiddles_kept<R, true>(v, otw);
+            else stage_twiddles<R, true, 8>(v, tt, j << shn);
             dft_small<R, true, 8>(v);
 #pragma unroll
             for (int t = 0; t < 8; ++t) {
@@ -3121,7 +3172,12 @@ hipError_t launch_psfhat(bool dbl, const ConvArgs &a, const void *psf_img, hipSt
 // ---------------------------------------------------------------------------
 // vector kernels and device-side scalar reductions
 // ---------------------------------------------------------------------------
-constexpr int kVecPerThread = 8;
+// Elements per thread of a small image: one 16-byte access per array.  One element at a
+// time, a thread's eight loads each waited for the store before them (the arrays may
+// alias for the compiler): a forward-backward step of 512^2 707 -> 659 us.  Large images
+// keep one element per access, which streams better there (4 x 4096^2: 6.2 against
+// 6.9 ms for 22 updates).
+constexpr int kVecPerThread = 4;
 
 int vec_partials_per_band(int64_t P) {
     const int64_t per = (int64_t)kThreads * kVecPerThread;
@@ -3129,11 +3185,39 @@ int vec_partials_per_band(int64_t P) {
     return (int)std::min<int64_t>(n, 4096);
 }
 
-template <typename R, int OP>
+// V elements at a time: 16-byte accesses where every array and band start on 16 bytes, or one
+template <typename R, int V> struct VecOf {
+    R v[V];
+    __device__ __forceinline__ static VecOf load(const R *p) {
+        VecOf o;
+        if constexpr (V == 1) {
+            o.v[0] = *p;
+        } else {
+            typedef R vecR __attribute__((ext_vector_type(V)));
+            const vecR t = *reinterpret_cast<const vecR *>(p);
+#pragma unroll
+            for (int i = 0; i < V; ++i) o.v[i] = t[i];
+        }
+        return o;
+    }
+    __device__ __forceinline__ void store(R *p) const {
+        if constexpr (V == 1) {
+            *p = v[0];
+        } else {
+            typedef R vecR __attribute__((ext_vector_type(V)));
+            vecR t;
+#pragma unroll
+            for (int i = 0; i < V; ++i) t[i] = v[i];
+            *reinterpret_cast<vecR *>(p) = t;
+        }
+    }
+};
+template <typename R, int OP, int V>
 __global__ __launch_bounds__(kThreads) void vec_kernel(int64_t P, int nblk, double *partials, int max_partials,
                                                        double *scal, R *x, R *y, R *r, R *p, const R *ap, R gamma,
                                                        R lam, unsigned *ctr, int red_op) {
     __shared__ double red[kThreads / 64];
+    using T = VecOf<R, V>;
     const int b = blockIdx.x / nblk;
     const int kb = blockIdx.x - b * nblk;
     const size_t off = (size_t)b * P;
@@ -3141,28 +3225,53 @@ __global__ __launch_bounds__(kThreads) void vec_kernel(int64_t P, int nblk, doub
     double part = 0.0;
     const R alpha = (OP == VEC_CG_UPDATE) ? (R)sc[S_ALPHA] : R(0);
     const R scale = (OP == VEC_SCALE_COPY) ? (R)sc[S_SCALE] : R(1);
-    for (int64_t k = (int64_t)kb * kThreads + threadIdx.x; k < P; k += (int64_t)nblk * kThreads) {
-        const size_t e = off + k;
-        if (OP == VEC_CG_INIT) {
-            const R g = x[e];
-            y[e] = R(0);
-            r[e] = g;
-            p[e] = R(0);
-            part += (double)g * (double)g;
-        } else if (OP == VEC_CG_UPDATE) {
+    for (int64_t k = (int64_t)kb * kThreads + threadIdx.x; k < P / V; k += (int64_t)nblk * kThreads) {
+        const size_t e = off + (size_t)k * V;
+        if constexpr (V == 1 && OP == VEC_CG_UPDATE) {   // y's store before r's loads streams 6 % better
             y[e] += alpha * p[e];
             const R rn = r[e] - alpha * ap[e];
             r[e] = rn;
             part += (double)rn * (double)rn;
+            continue;
+        }
+        // all loads before the stores
+        constexpr bool RX = OP != VEC_CG_UPDATE, RY = OP == VEC_CG_UPDATE || OP == VEC_DOT || OP == VEC_FB_PROX;
+        T tx{}, ty{}, tr{}, tp{}, ta{};
+        if (RX) tx = T::load(x + e);
+        if (RY) ty = T::load(y + e);
+        if (OP == VEC_CG_UPDATE) {
+            tr = T::load(r + e);
+            tp = T::load(p + e);
+            ta = T::load(ap + e);
+        }
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+            if (OP == VEC_CG_INIT || OP == VEC_NORM) {
+                part += (double)tx.v[i] * (double)tx.v[i];
+            } else if (OP == VEC_CG_UPDATE) {
+                ty.v[i] += alpha * tp.v[i];
+                tr.v[i] -= alpha * ta.v[i];
+                part += (double)tr.v[i] * (double)tr.v[i];
+            } else if (OP == VEC_SCALE_COPY) {
+                ty.v[i] = tx.v[i] * scale;
+            } else if (OP == VEC_DOT) {
+                part += (double)tx.v[i] * (double)ty.v[i];
+            } else if (OP == VEC_FB_PROX) {
+                const R v = tx.v[i] - gamma * ty.v[i] - gamma * lam;
+                tx.v[i] = v > R(0) ? v : R(0);
+            }
+        }
+        if (OP == VEC_CG_INIT) {
+            T{}.store(y + e);
+            tx.store(r + e);
+            T{}.store(p + e);
+        } else if (OP == VEC_CG_UPDATE) {
+            ty.store(y + e);
+            tr.store(r + e);
         } else if (OP == VEC_SCALE_COPY) {
-            y[e] = x[e] * scale;
-        } else if (OP == VEC_DOT) {
-            part += (double)x[e] * (double)y[e];
+            ty.store(y + e);
         } else if (OP == VEC_FB_PROX) {
-            const R v = x[e] - gamma * y[e] - gamma * lam;
-            x[e] = v > R(0) ? v : R(0);
-        } else if (OP == VEC_NORM) {
-            part += (double)x[e] * (double)x[e];
+            tx.store(x + e);
         }
     }
     if (OP == VEC_CG_INIT || OP == VEC_CG_UPDATE || OP == VEC_DOT || OP == VEC_NORM) {
@@ -3177,10 +3286,19 @@ hipError_t launch_vec(bool dbl, int op, int n_band, int64_t P, double *partials,
                       double lam, hipStream_t s, unsigned *ctr, int red_op) {
     const int nblk = vec_partials_per_band(P);
     const int nb = n_band * nblk;
+    // 16-byte accesses: the arrays that the operation has, and every band of them
+    const uintptr_t bits = reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(y) |
+                           reinterpret_cast<uintptr_t>(r) | reinterpret_cast<uintptr_t>(p) |
+                           reinterpret_cast<uintptr_t>(ap) | ((uintptr_t)P * (dbl ? 8 : 4));
+    const bool vec = (bits & 15) == 0 && nb <= kFuseReduceBlocks;
 #define VEC_CASE(T, OPV)                                                                                    \
     case OPV:                                                                                               \
-        PFB_LAUNCH((vec_kernel<T, OPV>), nb, 0, s, P, nblk, partials, max_partials, scal, (T *)x, (T *)y, \
-                   (T *)r, (T *)p, (const T *)ap, (T)gamma, (T)lam, ctr, red_op);                                       \
+        if (vec)                                                                                            \
+            PFB_LAUNCH((vec_kernel<T, OPV, 16 / sizeof(T)>), nb, 0, s, P, nblk, partials, max_partials, scal, (T *)x, \
+                       (T *)y, (T *)r, (T *)p, (const T *)ap, (T)gamma, (T)lam, ctr, red_op);               \
+        else                                                                                                \
+            PFB_LAUNCH((vec_kernel<T, OPV, 1>), nb, 0, s, P, nblk, partials, max_partials, scal, (T *)x, (T *)y, \
+                       (T *)r, (T *)p, (const T *)ap, (T)gamma, (T)lam, ctr, red_op);                       \
         break;
     if (dbl) {
         switch (op) {
