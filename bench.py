@@ -89,11 +89,13 @@ def kernel_models(info, prob, M, W, csz, rsz):
     spread_flops = M * (4.0 * W ** 3 + 60.0 * W)
     return {
         # ES spread / interpolation: W^3 complex*real multiply-adds + 3W kernel values per visibility
-        "spread_kernel": ("alu", spread_flops),
+        "spread64_kernel": ("alu", spread_flops),   # FP64 mode
         "spread_run_kernel": ("alu", spread_flops),
+        "spread_cells_kernel": ("alu", spread_flops),
         # same algorithmic work, computed as FP32 matrix products on the matrix cores
         "spread_mfma_kernel": ("mfma", spread_flops),
-        "interp_kernel": ("alu", spread_flops),     # FP64 mode
+        "interp_stream_kernel": ("alu", spread_flops),
+        "interp_flat_kernel": ("alu", spread_flops),
         "interp4_kernel": ("alu", spread_flops),    # FP32
         # row inverse DFT of every w-plane: read its occupied tiles (the rest of the
         # plane is zero), write the cropped rows of tile rows that hold them

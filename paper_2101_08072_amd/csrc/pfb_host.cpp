@@ -747,8 +747,8 @@ pfb_status count_and_layout(pfb_plan *P, char *tmp, hipStream_t stream) {
         G->istream = !G->g.flat && (dbl || (!opt.chunk && hacc < kStreamPerTile * tiles));
         const int ichunk = G->istream ? (dbl ? kStreamEntries<double> : kStreamEntries<float>) : opt.chunk ? opt.chunk : (int)std::min<int64_t>(std::max<int64_t>(1024, unit / 3), chunk);
         // (FP64 items are single waves, of which a unit holds sixteen: half their share, so
-        // that the densest unshared tile is no tail)
-        const int64_t share = opt.chunk ? 0
+        // that the densest unshared tile is no tail; the FP32 PSF's spread does not share)
+        const int64_t share = opt.chunk || (!dbl && G == &Q) ? 0
                               : dbl     ? std::max<int64_t>(64, acc / (32 * (int64_t)n_cu))
                                         : std::max<int64_t>(256, unit);
         build_work(*G, cnt, hcnt, chunk, ichunk, share, dbl, cells);
@@ -1069,7 +1069,6 @@ pfb_status pfb_plan_create(pfb_plan **out, const pfb_problem *prob, const pfb_op
     Q.g.nj0max = 1;
     Q.g.nwmax = 1;
     Q.corr2d = false;
-    if (!dbl) mfma_window(opt.support, true, &Q.sort_rb, &Q.sort_cb);
 
     *out = P;
     return PFB_OK;

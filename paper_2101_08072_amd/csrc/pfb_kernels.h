@@ -12,7 +12,7 @@ namespace pfb {
 // Records HIP events around each kernel launch of the thread that installed it.
 struct Profiler {
     struct Rec {
-        const char *name;   // launch expression text, e.g. "(spread_kernel<R, W, ...>)"
+        const char *name;   // launch expression text, e.g. "(spread_mfma_kernel<W, ...>)"
         hipEvent_t a, b;
     };
     std::vector<Rec> recs;

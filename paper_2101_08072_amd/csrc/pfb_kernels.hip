@@ -773,6 +773,118 @@ __device__ __forceinline__ float es_kernel_fast(float z, float beta2, float inv_
     return a > 0.f ? __builtin_amdgcn_exp2f(beta2 * (__builtin_amdgcn_sqrtf(a) - 1.f)) : 0.f;
 }
 
+// FP32 spread of unit visibilities on one plane (the PSF) over sorted buckets: one wave per
+// visibility, register accumulation across runs of visibilities that share a footprint.
+//
+// Buckets are sorted by footprint base cell (i0, j0), so consecutive entries often cover
+// the same W x W block.  Each wave takes a contiguous part of a bucket; lane (j, i) owns
+// footprint cell (i, j) and keeps its sum in a register; when the base cell changes (or
+// after kRunMax visibilities) the wave adds its block to the LDS tile (64-bit fixed point,
+// ds_add_u64).  Values are pre-scaled by S = 2^26 / max|z|, so a partial sum of at most
+// kRunMax = 31 contributions is below 2^31 in magnitude and converts to int32 with one
+// truncation (relative size 2^-26).  The per-visibility quantities (1-D ES weights, value)
+// are computed for 8 visibilities at once, one per 8-lane group, then broadcast with
+// readlane / shuffles.  The values are real, so only real sums are kept: half of the LDS
+// adds that bound the kernel.  The matrix-core windows below, with dense tiles shared
+// between items, are faster still (121 us for 2.5e6 entries of a 1024^2 image's PSF, where
+// complex sums took 262; the whole PSF 242, 285 and 395 us), but they round the PSF differently (by 1.7e-7), and an
+// ill-conditioned CG solve with it amplifies that a thousandfold.
+constexpr int kRunMax = 31;
+constexpr float kRunScale = 67108864.0f;   // 2^26
+template <int W>
+__global__ __launch_bounds__(kTileThreads) void spread_run_kernel(SpreadLaunch a) {
+    using R = float;
+    using A = unsigned long long;
+    constexpr int NWAVE = kTileThreads / 64;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int T = a.g.T, TT = T * T;
+    A *sum = reinterpret_cast<A *>(smem_raw);
+    const GridWork wk = a.work[blockIdx.x];
+    const int ntiles = a.g.ntx * a.g.nty;
+    const int tu = wk.tile / a.g.nty, tv = wk.tile - tu * a.g.nty;
+    const int bb = wk.band - a.band0;
+    const Rec<R> *recs = reinterpret_cast<const Rec<R> *>(a.recs);
+    const R *omega = reinterpret_cast<const R *>(a.omega);
+    R fscale = R(1), finv = R(1);
+    fixed_point_scale(*a.absmax, kRunScale, fscale, finv);
+    for (int k = threadIdx.x; k < TT; k += kTileThreads) sum[k] = A(0);
+    __syncthreads();
+
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lj = lane & 7, ls = lane >> 3;         // column j, row i
+    const bool lact = (lj < W) && (ls < W);
+    const R beta2 = (R)(a.g.beta * 1.4426950408889634), inv_hw = R(2) / R(W), hw = R(0.5) * R(W);
+    const int64_t key = ((int64_t)wk.band * ntiles + wk.tile) * a.g.nj0max;
+    const int64_t b0 = a.offsets[key], n = a.offsets[key + 1] - b0;
+    const int64_t per = (n + NWAVE - 1) / NWAVE;
+    const int64_t e_beg = b0 + min(n, wv * per), e_end = b0 + min(n, (wv + 1) * per);
+    R acc = R(0);
+    int cur = -1, run = 0;
+    auto flush = [&](int base) {
+        const int row = (base >> 16) - 64 + ls, c = (base & 0xffff) - 64 + lj;
+        if (!lact || c < 0 || c >= T || row < 0 || row >= T) return;
+        atomicAdd(sum + row * T + c, f2fix(acc));
+    };
+    // software pipeline: the records and weights of the batches after this one are loaded
+    // while it is being accumulated
+    auto load_rec = [&](int64_t eb) {
+        Rec<R> r{R(0), R(0), R(0), 0u};
+        if (eb < e_end) r = recs[eb];
+        return r;
+    };
+    auto load_val = [&](int64_t eb) { return eb < e_end ? omega[eb] * fscale : R(0); };
+    Rec<R> rec_c = load_rec(e_beg + ls);
+    R val_c = load_val(e_beg + ls);
+    Rec<R> rec_n = load_rec(e_beg + 8 + ls);
+    for (int64_t e = e_beg; e < e_end; e += 8) {
+        const int nb = (int)min((int64_t)8, e_end - e);
+        const R val_n = load_val(e + 8 + ls);
+        const Rec<R> rec_nn = load_rec(e + 16 + ls);
+        // batched prologue: group ls handles visibility e + ls, lane lj its 1-D weights
+        R pu = R(0), pv = R(0);
+        int base = 0;
+        if (ls < nb) {
+            const int i0 = (int)dev_floor(rec_c.fu - hw) + 1;
+            const int j0 = (int)dev_floor(rec_c.fv - hw) + 1;
+            base = ((i0 + 64) << 16) | (j0 + 64);
+            if (lj < W) {
+                pu = es_kernel_fast(R(i0 + lj) - rec_c.fu, beta2, inv_hw);
+                pv = es_kernel_fast(R(j0 + lj) - rec_c.fv, beta2, inv_hw);
+            }
+        }
+        // all shuffles of the batch first (one LDS round trip), then accumulate
+        R wgt[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) wgt[t] = __shfl(pv, t * 8 + lj) * __shfl(pu, t * 8 + ls);
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            if (t < nb) {
+                const int bt = rdlane(base, t * 8);
+                if (bt != cur || run == kRunMax) {
+                    if (cur >= 0) flush(cur);
+                    acc = R(0);
+                    cur = bt;
+                    run = 0;
+                }
+                ++run;
+                acc = __builtin_fmaf(rdlane(val_c, t * 8), wgt[t], acc);
+            }
+        }
+        rec_c = rec_n;
+        val_c = val_n;
+        rec_n = rec_nn;
+    }
+    if (cur >= 0) flush(cur);
+    __syncthreads();
+    cplx<R> *dst = reinterpret_cast<cplx<R> *>(a.planes) + (size_t)bb * a.g.nwmax * a.g.gx * a.g.gy +
+                   (size_t)tu * T * a.g.gy + (size_t)tv * T;
+    for (int k = threadIdx.x; k < TT; k += kTileThreads) {
+        const int row = k / T, col = k - row * T;
+        dst[(size_t)row * a.g.gy + col] = cplx<R>{(R)((double)(long long)sum[k] * (double)finv), R(0)};
+    }
+}
+
 // FP32 spread on the matrix cores.
 //
 // For visibilities whose footprints lie in one window of 8 rows, 16 columns
@@ -793,10 +905,8 @@ __device__ __forceinline__ float es_kernel_fast(float z, float beta2, float inv_
 // P[r - 8], all 16 the column weight V[r]; DPP within the 16-lane row gives
 // every lane U[r mod 8] and the plane weights of the tiles.  Slots outside the
 // window of an MFMA round get a zero B row.
-// FLAT (one plane, the PSF gridder): the window is 16 rows x 16 columns, A the row
-// weights alone; unit visibilities (VMODE 1) have no imaginary part.  Against one wave
-// per visibility with LDS adds of its W x W cells: 262 -> 121 us for 2.5e6 entries of a
-// 1024^2 image's PSF.
+// FLAT (one plane, the flat operators): the window is 16 rows x 16 columns, A the row
+// weights alone.
 constexpr int kMfmaRunMax = 124;                // visibilities per flush: 124 * 2^24 < 2^31
 constexpr float kMfmaScale = 16777216.0f;       // 2^24
 constexpr int kMfmaThreads = 1024;              // 16 waves (at most 128 registers per lane)
@@ -843,7 +953,6 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
     using Win = MfmaWin<W, FLAT>;
     constexpr int RB = Win::RB, CB = Win::CB, NT = Win::NT, WR = Win::R;
     constexpr int WW = FLAT ? 1 : W;            // planes of the ring
-    constexpr bool IM = !(FLAT && VMODE == 1);  // unit visibilities on one plane: the sums are real
     constexpr int NWAVE = kMfmaThreads / 64;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int T = TC ? TC : a.g.T, TT = T * T, TS = run_slot_stride(T, FLAT);
@@ -980,7 +1089,7 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
                 for (int t = 0; t < NT; ++t)
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
-                        touched |= __float_as_int(cre[t][v]) | (IM ? __float_as_int(cim[t][v]) : 0);
+                        touched |= __float_as_int(cre[t][v]) | __float_as_int(cim[t][v]);
                 const bool colok = J + r >= 0 && J + r < T && (touched & 0x7fffffff);
                 const bool rows_in = I >= 0 && I + WR <= T;    // wave-uniform
                 if (rows_in) {    // one lane mask per tile, no per-row tests
@@ -991,7 +1100,7 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
 #pragma unroll
                             for (int v = 0; v < 4; ++v) {
                                 atomicAdd(sre + idx + v * T, f2fix(cre[t][v]));
-                                if (IM) atomicAdd(sim + idx + v * T, f2fix(cim[t][v]));
+                                atomicAdd(sim + idx + v * T, f2fix(cim[t][v]));
                             }
                         }
                         cre[t] = cim[t] = mfma_v4f{0.f, 0.f, 0.f, 0.f};
@@ -1006,7 +1115,7 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
                         if (colok && koff[t] >= 0 && row >= 0 && row < T) {
                             const int idx = koff[t] + base + v * T;
                             atomicAdd(sre + idx, f2fix(cre[t][v]));
-                            if (IM) atomicAdd(sim + idx, f2fix(cim[t][v]));
+                            atomicAdd(sim + idx, f2fix(cim[t][v]));
                         }
                     }
                     cre[t] = cim[t] = mfma_v4f{0.f, 0.f, 0.f, 0.f};
@@ -1116,7 +1225,7 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
 #pragma unroll
                         for (int t = 0; t < NT; ++t) {
                             cre[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(At[t], bre, cre[t], 0, 0, 0);
-                            if (IM) cim[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(At[t], bim, cim[t], 0, 0, 0);
+                            cim[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(At[t], bim, cim[t], 0, 0, 0);
                         }
                         rem &= ~sel;
                     }
@@ -1145,18 +1254,18 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
         auto write_cell = [&](int row, int col) {
             const int c = slot * TS + row * T + col;
             dst[(size_t)row * a.g.gy + col] = cplx<R_>{(R_)((double)(long long)sre[c] * (double)finv),
-                                                       IM ? (R_)((double)(long long)sim[c] * (double)finv) : R_(0)};
+                                                       (R_)((double)(long long)sim[c] * (double)finv)};
         };
         auto clear_cell = [&](int k) {
             sre[slot * TS + k] = A(0);
-            if (IM) sim[slot * TS + k] = A(0);
+            sim[slot * TS + k] = A(0);
         };
         if (SHARES && wk.nshare > 1) {
             // this share's sums to the tile's scratch planes: integers, so their order is free
             A *const sc = reinterpret_cast<A *>(a.scratch) + 2 * ((size_t)wk.slot * a.g.nwmax + q) * TT;
             if (q >= wk.p0)
                 for (int k = threadIdx.x; k < TT; k += kMfmaThreads) {
-                    const A re = sre[slot * TS + k], im = IM ? sim[slot * TS + k] : A(0);
+                    const A re = sre[slot * TS + k], im = sim[slot * TS + k];
                     if (re) atomicAdd(sc + 2 * k, re);
                     if (im) atomicAdd(sc + 2 * k + 1, im);
                 }
@@ -1429,8 +1538,10 @@ static hipError_t spread_mfma_w(const SpreadLaunch &a, hipStream_t s) {
         return hipSuccess;                                                                               \
     }
     SPREAD_MFMA_CASE(0)
-    SPREAD_MFMA_CASE(1)
     SPREAD_MFMA_CASE(2)
+    if constexpr (!FLAT) {
+        SPREAD_MFMA_CASE(1)
+    }
 #undef SPREAD_MFMA_CASE
     return hipErrorInvalidValue;
 }
@@ -1460,6 +1571,11 @@ hipError_t launch_spread(bool dbl, const SpreadLaunch &a, hipStream_t s) {
         return dispatch_int<9, 16>(a.g.W, [&](auto Wc) { return spread64_w<decltype(Wc)::value>(a, s); });
     return dispatch_int<4, 8>(a.g.W, [&](auto Wc) {
         constexpr int W = decltype(Wc)::value;
+        if (a.g.flat && a.vmode == 1) {   // the PSF: one item per tile, its sums in a fixed order
+            if (a.n_shared > 0) return hipErrorInvalidValue;
+            PFB_LAUNCH_NT((spread_run_kernel<W>), a.n_work, kTileThreads, (size_t)a.g.T * a.g.T * sizeof(uint64_t), s, a);
+            return hipSuccess;
+        }
         return a.g.flat ? spread_mfma_w<W, true>(a, s) : spread_mfma_w<W, false>(a, s);
     });
 }
@@ -2225,7 +2341,7 @@ template <int NSUB> __device__ __forceinline__ WColsBlock wcols_block(int n_bb, 
     return WColsBlock{gi % G, jb % NSUB, gi / G, gi < n_bb * G};
 }
 
-template <typename R, int LOG2N, int C, bool PL>
+template <typename R, int LOG2N, int C, bool PL, bool KEEP>
 __global__ __launch_bounds__((WCols<R, LOG2N, C, PL>::NT)) void wgrid_cols_kernel(XformArgs a) {
     using K = WCols<R, LOG2N, C, PL>;
     constexpr int NPL = K::NPL;
@@ -2279,9 +2395,7 @@ __global__ __launch_bounds__((WCols<R, LOG2N, C, PL>::NT)) void wgrid_cols_kerne
         }
     }
     uint8_t *const flb = reinterpret_cast<uint8_t *>(accl + 8 * NT);   // two buffers of ntx flags
-    // the outermost stage's twiddles, kept over the planes where registers allow (FP32, up to
-    // 8192-row grids)
-    constexpr bool KEEP = sizeof(R) == 4 && LOG2N <= 12;
+    // KEEP: the outermost stage's twiddles, kept over the planes
     __syncthreads();   // twiddle table
     OuterTw<R> otw{};
     if (KEEP && jr < M) otw = outer_twiddles(tt, jr << shn);
@@ -2576,19 +2690,25 @@ static hipError_t wcols_launch(const XformArgs &a, hipStream_t s) {
         } else {
             constexpr int C = wcols_c<R, LG>();
             constexpr int CG = plane_cg<R>();
+            // twiddles kept over the planes where registers allow (FP32, up to 8192-row grids);
+            // not for the one plane of a flat grid, which gains nothing (and the PSF's rounding,
+            // which differs by 2e-8 with them, grows a thousandfold in ill-conditioned solves)
+            constexpr bool KEEP = sizeof(R) == 4 && LG <= 12;
             const int G = (a.g.ny + CG - 1) / CG;
             const int rounds = ((a.n_bb * G + 7) / 8) * 8;   // column groups, padded to the XCDs
             if constexpr (C > 1) {
                 if (!a.g.flat && rounds * (CG / C) < kColsFewBlocks) {
                     using K = WCols<R, LG, C, true>;
-                    if (GRID) PFB_LAUNCH_NT((wgrid_cols_kernel<R, LG, C, true>), rounds * CG, K::NT, K::lds, s, a);
+                    if (GRID) PFB_LAUNCH_NT((wgrid_cols_kernel<R, LG, C, true, KEEP>), rounds * CG, K::NT, K::lds, s, a);
                     else PFB_LAUNCH_NT((wdegrid_cols_kernel<R, LG, C, true>), rounds * CG, K::NT, K::lds, s, a);
                     return hipSuccess;
                 }
             }
             using K = WCols<R, LG, C, false>;
             const int nb = rounds * (CG / C);
-            if (GRID) PFB_LAUNCH_NT((wgrid_cols_kernel<R, LG, C, false>), nb, K::NT, K::lds, s, a);
+            if (GRID && KEEP && a.g.flat)
+                PFB_LAUNCH_NT((wgrid_cols_kernel<R, LG, C, false, false>), nb, K::NT, K::lds, s, a);
+            else if (GRID) PFB_LAUNCH_NT((wgrid_cols_kernel<R, LG, C, false, KEEP>), nb, K::NT, K::lds, s, a);
             else PFB_LAUNCH_NT((wdegrid_cols_kernel<R, LG, C, false>), nb, K::NT, K::lds, s, a);
             return hipSuccess;
         }
@@ -2770,10 +2890,6 @@ template <typename R, int LOG2N, int C> struct ConvCols {
     static constexpr int NT0 = C * N / 8;   // one radix-8 butterfly per thread and stage
     static constexpr int NT = NT0 < 64 ? 64 : NT0;
     static_assert(NT0 <= 1024, "at most 1024 threads per block");
-    // outermost twiddles kept in registers: at 4096 points (13.5 -> 13.1 ms for 21
-    // convolutions of 4 x 4096^2, three blocks per CU at 80 registers) and in small blocks;
-    // the 512-thread blocks of 512 to 2048 points would spill (7 % slower)
-    static constexpr bool KEEP = sizeof(R) == 4 && (LOG2N == 12 || NT < 512);
     static constexpr int SE = tw_stage_entries<R, LOG2N>((size_t)C * Lds<R, LOG2N>::ld * sizeof(cplx<R>));
     static constexpr size_t lds = (size_t)C * Lds<R, LOG2N>::ld * sizeof(cplx<R>) + (kTwEntries + SE) * sizeof(cplx<R>);
 };
@@ -2784,8 +2900,7 @@ template <typename R, int LOG2N, int C> struct ConvCols {
 // there: they run at the same time on one XCD and read the group's rows through
 // its L2 (each block reads C of every CG contiguous values).
 template <typename R, int LOG2N, int C, int CG, bool PSF>
-__global__ __launch_bounds__((ConvCols<R, LOG2N, C>::NT), (ConvCols<R, LOG2N, C>::KEEP && LOG2N == 12 ? 6 : 1))
-void conv_cols_kernel(ConvArgs a) {
+__global__ __launch_bounds__((ConvCols<R, LOG2N, C>::NT)) void conv_cols_kernel(ConvArgs a) {
     using K = ConvCols<R, LOG2N, C>;
     using LD = Lds<R, LOG2N>;
     using P = FftPlan<LOG2N>;
@@ -2831,10 +2946,8 @@ void conv_cols_kernel(ConvArgs a) {
     }
     __syncthreads();   // twiddle table
     const cplx<R> wj = twiddle<R, false>(tt, j << sh2n);
-    // the outermost stages' twiddles, the same in all four transforms
-    constexpr bool KEEP = K::KEEP;
-    OuterTw<R> otw{};
-    if (KEEP && own) otw = outer_twiddles(tt, j << shn);
+    // (outermost twiddles kept in registers, the same in all four transforms: 19.1 -> 18.8 us
+    // at 512^2, but another rounding, 1.2e-7, that an ill-conditioned solve amplifies)
     // image mode: the PSF spectrum at the thread's innermost-stage outputs of a half
     // (8 / R0 items of R0 values), loaded before the middle stages that hide its latency
     // where that measured faster (N <= 2048: 0.101 -> 0.092 ms at 2048^2; at N = 4096 the
@@ -2873,8 +2986,7 @@ void conv_cols_kernel(ConvArgs a) {
                 v[t] = p == 0 ? x : x * (wj * root16<R>(t));   // w^r = w^j exp(-2 pi i t / 16)
             }
             dft_small<R, false, 8>(v);
-            if constexpr (KEEP) stage_twiddles_kept<R, false>(v, otw);
-            else stage_twiddles<R, false, 8>(v, tt, j << shn);
+            stage_twiddles<R, false, 8>(v, tt, j << shn);
             cplx<R> *vb = buf + c * ld + LD::pad(j);
 #pragma unroll
             for (int t = 0; t < 8; ++t) vb[LD::pad(t * M)] = v[t];
@@ -2938,8 +3050,7 @@ void conv_cols_kernel(ConvArgs a) {
             cplx<R> v[8];
 #pragma unroll
             for (int t = 0; t < 8; ++t) v[t] = vb[LD::pad(t * M)];
-            if constexpr (KEEP) stage_twiddles_kept<R, true>(v, otw);
-            else stage_twiddles<R, true, 8>(v, tt, j << shn);
+            stage_twiddles<R, true, 8>(v, tt, j << shn);
             dft_small<R, true, 8>(v);
 #pragma unroll
             for (int t = 0; t < 8; ++t) {
