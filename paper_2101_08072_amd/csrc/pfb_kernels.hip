@@ -785,9 +785,8 @@ __device__ __forceinline__ float es_kernel_fast(float z, float beta2, float inv_
 // truncation (relative size 2^-26).  The per-visibility quantities (1-D ES weights, value)
 // are computed for 8 visibilities at once, one per 8-lane group, then broadcast with
 // readlane / shuffles.  The values are real, so only real sums are kept: half of the LDS
-// adds that bound the kernel.  The matrix-core windows below, with dense tiles shared
-// between items, are faster still (121 us for 2.5e6 entries of a 1024^2 image's PSF, where
-// complex sums took 262; the whole PSF 242, 285 and 395 us), but they round the PSF differently (by 1.7e-7), and an
+// adds that bound the kernel (262 -> 162 us for 2.5e6 entries of a 1024^2 image's PSF).  The matrix-core windows below, with dense tiles shared
+// between items, are faster still (121 us; the whole PSF 242 us against 285, and 395 before), but they round the PSF differently (by 1.7e-7), and an
 // ill-conditioned CG solve with it amplifies that a thousandfold.
 constexpr int kRunMax = 31;
 constexpr float kRunScale = 67108864.0f;   // 2^26
