@@ -164,16 +164,18 @@ __device__ __forceinline__ void apply_reduce(int op, double t, double *sc) {
     }
 }
 
-// The end of a block that adds a partial sum: without a counter the partial is stored
-// for reduce_kernel.  With one (few blocks, where a launch costs more than the tail of
-// a block), the band's last block sums the band's n_part partials in their fixed order
-// and updates the scalars, which the next kernel reads.  Partials and counter only move
-// through agent-scope atomics (coherent across the XCDs' L2s), each partial complete
-// before its block counts itself; the counter is zero again afterwards.
-template <int NT>
+// The end of a block that adds a partial sum.  FUSE (few blocks, where a launch costs
+// more than the tail of a block): the band's last block sums the band's n_part partials
+// in their fixed order and updates the scalars, which the next kernel reads.  Partials
+// and counter only move through agent-scope atomics (coherent across the XCDs' L2s),
+// each partial complete before its block counts itself; the counter is zero again
+// afterwards.  Otherwise the partial is stored for reduce_kernel, by a kernel that does
+// not hold the tail's code (with it, unused, s3_kernel took 329.0 instead of 326.2 us at
+// 4 x 4096^2, all buffers at the same addresses).
+template <int NT, bool FUSE>
 __device__ __forceinline__ void finish_partial(double t, int k, int n_part, double *partials, double *sc, unsigned *ctr,
                                                int op, double *red) {
-    if (!ctr) {
+    if constexpr (!FUSE) {
         if (threadIdx.x == 0) partials[k] = t;
         return;
     }
@@ -3099,7 +3101,7 @@ int conv_group_cols(bool dbl, int nx) {
 // Inverse of s1's pairing: rows 2c and 2c + 1 have Hermitian half spectra X_a,
 // X_b; Z = X_a + i X_b transforms to row a in the real part and row b in the
 // imaginary part.  C vectors (2C rows) per block.
-template <typename R, int LOG2L, int OUT>
+template <typename R, int LOG2L, int OUT, bool FUSE>
 __global__ __launch_bounds__(row_threads<LOG2L>(), row_min_waves<LOG2L>()) void s3_kernel(ConvArgs a, R *y, const R *aux, R sigma, int C) {
     constexpr int L = 1 << LOG2L;
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -3162,8 +3164,8 @@ __global__ __launch_bounds__(row_threads<LOG2L>(), row_min_waves<LOG2L>()) void 
         });
     if (OUT == CONV_OUT_CG || OUT == CONV_OUT_NORM || OUT == CONV_OUT_DOT) {
         const double t = block_sum<row_threads<LOG2L>()>(part, red);
-        finish_partial<row_threads<LOG2L>()>(t, ig, ngrp, a.partials + (size_t)b * a.max_partials, a.scal + b * 8,
-                                             a.ctr ? a.ctr + b : nullptr, a.red_op, red);
+        finish_partial<row_threads<LOG2L>(), FUSE>(t, ig, ngrp, a.partials + (size_t)b * a.max_partials, a.scal + b * 8,
+                                                   a.ctr + b, a.red_op, red);
     }
 }
 
@@ -3231,13 +3233,19 @@ static hipError_t psf_conv_t(const ConvArgs &a, const void *x, void *aux_in, voi
         R *yr = reinterpret_cast<R *>(y);
         const R *ax = reinterpret_cast<const R *>(aux_out);
         const R sg = (R)sigma;
+#define S3_LAUNCH(OUT, FUSE) PFB_LAUNCH_NT((s3_kernel<R, LG, OUT, FUSE>), nb, row_threads<LG>(), lds, s, a, yr, ax, sg, C)
+        if (a.ctr && out_mode != CONV_OUT_CG) return hipErrorInvalidValue;   // only CG's sums are reduced in the kernel
         switch (out_mode) {
-            case CONV_OUT_Y: PFB_LAUNCH_NT((s3_kernel<R, LG, CONV_OUT_Y>), nb, row_threads<LG>(), lds, s, a, yr, ax, sg, C); break;
-            case CONV_OUT_SUB: PFB_LAUNCH_NT((s3_kernel<R, LG, CONV_OUT_SUB>), nb, row_threads<LG>(), lds, s, a, yr, ax, sg, C); break;
-            case CONV_OUT_CG: PFB_LAUNCH_NT((s3_kernel<R, LG, CONV_OUT_CG>), nb, row_threads<LG>(), lds, s, a, yr, ax, sg, C); break;
-            case CONV_OUT_NORM: PFB_LAUNCH_NT((s3_kernel<R, LG, CONV_OUT_NORM>), nb, row_threads<LG>(), lds, s, a, yr, ax, sg, C); break;
-            default: PFB_LAUNCH_NT((s3_kernel<R, LG, CONV_OUT_DOT>), nb, row_threads<LG>(), lds, s, a, yr, ax, sg, C); break;
+            case CONV_OUT_Y: S3_LAUNCH(CONV_OUT_Y, false); break;
+            case CONV_OUT_SUB: S3_LAUNCH(CONV_OUT_SUB, false); break;
+            case CONV_OUT_CG:
+                if (a.ctr) S3_LAUNCH(CONV_OUT_CG, true);
+                else S3_LAUNCH(CONV_OUT_CG, false);
+                break;
+            case CONV_OUT_NORM: S3_LAUNCH(CONV_OUT_NORM, false); break;
+            default: S3_LAUNCH(CONV_OUT_DOT, false); break;
         }
+#undef S3_LAUNCH
         return hipSuccess;
     });
 }
@@ -3322,7 +3330,7 @@ template <typename R, int V> struct VecOf {
         }
     }
 };
-template <typename R, int OP, int V>
+template <typename R, int OP, int V, bool FUSE>
 __global__ __launch_bounds__(kThreads) void vec_kernel(int64_t P, int nblk, double *partials, int max_partials,
                                                        double *scal, R *x, R *y, R *r, R *p, const R *ap, R gamma,
                                                        R lam, unsigned *ctr, int red_op) {
@@ -3386,8 +3394,7 @@ __global__ __launch_bounds__(kThreads) void vec_kernel(int64_t P, int nblk, doub
     }
     if (OP == VEC_CG_INIT || OP == VEC_CG_UPDATE || OP == VEC_DOT || OP == VEC_NORM) {
         const double t = block_sum(part, red);
-        finish_partial<kThreads>(t, kb, nblk, partials + (size_t)b * max_partials, scal + b * 8, ctr ? ctr + b : nullptr,
-                                 red_op, red);
+        finish_partial<kThreads, FUSE>(t, kb, nblk, partials + (size_t)b * max_partials, scal + b * 8, ctr + b, red_op, red);
     }
 }
 
@@ -3401,15 +3408,19 @@ hipError_t launch_vec(bool dbl, int op, int n_band, int64_t P, double *partials,
                            reinterpret_cast<uintptr_t>(r) | reinterpret_cast<uintptr_t>(p) |
                            reinterpret_cast<uintptr_t>(ap) | ((uintptr_t)P * (dbl ? 8 : 4));
     const bool vec = (bits & 15) == 0 && nb <= kFuseReduceBlocks;
+#define VEC_LAUNCH(T, OPV, V, FUSE)                                                                         \
+    PFB_LAUNCH((vec_kernel<T, OPV, V, FUSE>), nb, 0, s, P, nblk, partials, max_partials, scal, (T *)x, (T *)y, (T *)r, \
+               (T *)p, (const T *)ap, (T)gamma, (T)lam, ctr, red_op)
 #define VEC_CASE(T, OPV)                                                                                    \
-    case OPV:                                                                                               \
-        if (vec)                                                                                            \
-            PFB_LAUNCH((vec_kernel<T, OPV, 16 / sizeof(T)>), nb, 0, s, P, nblk, partials, max_partials, scal, (T *)x, \
-                       (T *)y, (T *)r, (T *)p, (const T *)ap, (T)gamma, (T)lam, ctr, red_op);               \
-        else                                                                                                \
-            PFB_LAUNCH((vec_kernel<T, OPV, 1>), nb, 0, s, P, nblk, partials, max_partials, scal, (T *)x, (T *)y, \
-                       (T *)r, (T *)p, (const T *)ap, (T)gamma, (T)lam, ctr, red_op);                       \
-        break;
+    case OPV: {                                                                                             \
+        constexpr bool SUM = OPV == VEC_CG_INIT || OPV == VEC_CG_UPDATE;   /* CG's sums */                  \
+        if (ctr && !SUM) return hipErrorInvalidValue;                                                       \
+        if (ctr && vec) VEC_LAUNCH(T, OPV, 16 / sizeof(T), SUM);                                            \
+        else if (ctr) VEC_LAUNCH(T, OPV, 1, SUM);                                                           \
+        else if (vec) VEC_LAUNCH(T, OPV, 16 / sizeof(T), false);                                            \
+        else VEC_LAUNCH(T, OPV, 1, false);                                                                  \
+        break;                                                                                              \
+    }
     if (dbl) {
         switch (op) {
             VEC_CASE(double, VEC_CG_INIT)
@@ -3432,6 +3443,7 @@ hipError_t launch_vec(bool dbl, int op, int n_band, int64_t P, double *partials,
         }
     }
 #undef VEC_CASE
+#undef VEC_LAUNCH
     return hipSuccess;
 }
 
