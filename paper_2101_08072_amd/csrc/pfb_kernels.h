@@ -54,6 +54,9 @@ hipError_t launch_corr2d(bool dbl, const GeomDev &g, const BandDev *bands, const
 hipError_t launch_corr1d(bool dbl, int n, int gsize, const double *cheb, int ncheb, double xi_max,
                          void *corr, hipStream_t s);
 
+// FP32 additions into one partial sum of the w-stacked spread, on the matrix cores
+// (visibilities per flush: 124 * 2^24 < 2^31) or in the registers of a cell's lane
+constexpr int kSumMax = 124;
 constexpr int kCellsMax = 384;          // entries of a tile
 constexpr int kCellsMaxPlanes = 1024;   // base planes (their offsets sit in LDS)
 struct SpreadLaunch {

@@ -914,7 +914,7 @@ __global__ __launch_bounds__(kTileThreads) void spread_run_kernel(SpreadLaunch a
 // the run of spread_run_kernel: visibilities 1e-5 of the largest lose 0.25 % of their
 // image to truncation there, 0.94 % at the w-stacked step, which costs a tenth less time
 // (1.6e6 visibilities at 1024^2: dirty image 144 against 134 us).
-template <bool FLAT> constexpr int kMfmaRunMax = FLAT ? 28 : 124;
+template <bool FLAT> constexpr int kMfmaRunMax = FLAT ? 28 : kSumMax;
 template <bool FLAT> constexpr float kMfmaScale = FLAT ? 67108864.0f : 16777216.0f;
 constexpr int kMfmaThreads = 1024;              // 16 waves (at most 128 registers per lane)
 template <int W, bool FLAT> struct MfmaWin {
@@ -1297,6 +1297,12 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
 // 1728 x 1200, two bands, 4.3e5 visibilities 657 -> 222 + 33 us; 1.5e5 at 2048^2 375 ->
 // 128; 7.2e6 there 1434 -> 94 + 1160.
 // Values are scaled by 1 / max |z| (sums of order one; a bad maximum gives NaN cells).
+// No FP32 sum takes more than kSumMax values, as in the matrix-core kernel: then the
+// wave's sums go to a second set in LDS, and the rounding errors of those additions
+// (two-sum) stay in the registers as the next sums' start.  Without it a run of 384
+// values rounded up to three times as much.  Rare, and in code of its own for tiles of
+// more than kSumMax entries: in the one loop its tests took 10 % of every tile's time.
+// Its LDS still leaves two blocks per CU.
 template <int W, int VMODE>
 __global__ __launch_bounds__(1024, 8) void spread_cells_kernel(SpreadLaunch a) {
     using R = float;
@@ -1307,7 +1313,8 @@ __global__ __launch_bounds__(1024, 8) void spread_cells_kernel(SpreadLaunch a) {
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     R *const wgt = reinterpret_cast<R *>(ez + kCellsMax) + 64 * wv;          // weights of two entries
-    int *const soff = reinterpret_cast<int *>(reinterpret_cast<R *>(ez + kCellsMax) + nthr);
+    cplx<R> *const high = reinterpret_cast<cplx<R> *>(reinterpret_cast<R *>(ez + kCellsMax) + nthr) + threadIdx.x;
+    int *const soff = reinterpret_cast<int *>(high - threadIdx.x + W * nthr);
     const GridWork wk = a.cwork[blockIdx.x];
     const BandDev bd = a.bands[wk.band];
     const int ntiles = a.g.ntx * a.g.nty;
@@ -1353,55 +1360,85 @@ __global__ __launch_bounds__(1024, 8) void spread_cells_kernel(SpreadLaunch a) {
         ez[k] = z;
     }
     __syncthreads();
-    for (int q = 0; q < bd.nw; ++q) {
-        const int qb = q < bd.nj0 ? __builtin_amdgcn_readfirstlane(soff[q]) : n_all;
-        const int qe = q < bd.nj0 ? __builtin_amdgcn_readfirstlane(soff[q + 1]) : n_all;
-        const R wbase = wi < 16 ? wpos : wpos + R(q);
-        for (int k0 = qb; k0 < qe; k0 += 64) {
-            const int k = min(k0 + lane, qe - 1);
-            const int i0 = (int)dev_floor(efu[k] - hw) + 1, j0 = (int)dev_floor(efv[k] - hw) + 1;
-            unsigned long long todo = __builtin_amdgcn_ballot_w64(k0 + lane < qe && i0 < r0 + 8 && i0 + W > r0 &&
-                                                                  j0 < c0 + 8 && j0 + W > c0);
-            while (todo) {
-                const int ea = k0 + __builtin_ctzll(todo);
-                todo &= todo - 1;
-                const bool two = todo != 0;
-                const int eb = two ? k0 + __builtin_ctzll(todo) : ea;
-                todo &= todo - 1;
-                const R w = es_kernel_fast(wbase - ecoord[lane < 32 ? ea : eb], beta2, inv_hw);
-                wave_lds_fence();
-                wgt[lane] = w;
-                wave_lds_fence();
+    auto planes_of = [&](auto MOVE) {   // MOVE: the tile holds more than kSumMax entries
+        constexpr bool kMove = decltype(MOVE)::value;
+        unsigned hset = 0;    // bit k: plane q + k has a part in high[plane mod W]
+        int run = 0;          // entries added since the sums started or were moved there
+        for (int q = 0; q < bd.nw; ++q) {
+            const int qb = q < bd.nj0 ? __builtin_amdgcn_readfirstlane(soff[q]) : n_all;
+            const int qe = q < bd.nj0 ? __builtin_amdgcn_readfirstlane(soff[q + 1]) : n_all;
+            const R wbase = wi < 16 ? wpos : wpos + R(q);
+            for (int k0 = qb; k0 < qe; k0 += 64) {
+                const int k = min(k0 + lane, qe - 1);
+                const int i0 = (int)dev_floor(efu[k] - hw) + 1, j0 = (int)dev_floor(efv[k] - hw) + 1;
+                unsigned long long todo = __builtin_amdgcn_ballot_w64(k0 + lane < qe && i0 < r0 + 8 && i0 + W > r0 &&
+                                                                      j0 < c0 + 8 && j0 + W > c0);
+                while (todo) {
+                    const int ea = k0 + __builtin_ctzll(todo);
+                    todo &= todo - 1;
+                    const bool two = todo != 0;
+                    const int eb = two ? k0 + __builtin_ctzll(todo) : ea;
+                    todo &= todo - 1;
+                    if (kMove && run > kSumMax - 2) {
+                        run = 0;
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    if (h == 1 && !two) break;
-                    const R *const wh = wgt + 32 * h;
-                    const cplx<R> z = ez[h ? eb : ea];
-                    const R uv = wh[crow] * wh[8 + ccol];
-                    const R zr = z.re * uv, zi = z.im * uv;
+                        for (int p = 0; p < W; ++p) {
+                            cplx<R> *const hp = high + (q + p) % W * nthr;
+                            cplx<R> h{R(0), R(0)};
+                            if (hset >> p & 1u) h = *hp;
+                            const R sr = h.re + are[p], si = h.im + aim[p], tr = sr - h.re, ti = si - h.im;
+                            are[p] = (h.re - (sr - tr)) + (are[p] - tr);
+                            aim[p] = (h.im - (si - ti)) + (aim[p] - ti);
+                            *hp = cplx<R>{sr, si};
+                        }
+                        hset = (1u << W) - 1u;
+                    }
+                    run += 2;
+                    const R w = es_kernel_fast(wbase - ecoord[lane < 32 ? ea : eb], beta2, inv_hw);
+                    wave_lds_fence();
+                    wgt[lane] = w;
+                    wave_lds_fence();
 #pragma unroll
-                    for (int p = 0; p < W; ++p) {
-                        are[p] += zr * wh[16 + p];
-                        aim[p] += zi * wh[16 + p];
+                    for (int h = 0; h < 2; ++h) {
+                        if (h == 1 && !two) break;
+                        const R *const wh = wgt + 32 * h;
+                        const cplx<R> z = ez[h ? eb : ea];
+                        const R uv = wh[crow] * wh[8 + ccol];
+                        const R zr = z.re * uv, zi = z.im * uv;
+#pragma unroll
+                        for (int p = 0; p < W; ++p) {
+                            are[p] += zr * wh[16 + p];
+                            aim[p] += zi * wh[16 + p];
+                        }
                     }
                 }
             }
-        }
-        live = ((live << 1) | (qe > qb ? 1u : 0u)) & ((1u << W) - 1u);
-        if (!live) continue;  // zero sums; the transforms do not read this plane of the tile
-        dst[(size_t)q * plane_sz] = cplx<R>{are[0] * finv, aim[0] * finv};
+            live = ((live << 1) | (qe > qb ? 1u : 0u)) & ((1u << W) - 1u);
+            const bool moved = hset & 1u;
+            hset >>= 1;
+            if (!live) continue;  // zero sums; the transforms do not read this plane of the tile
+            if (kMove && moved) {
+                const cplx<R> h = high[q % W * nthr];
+                are[0] += h.re;
+                aim[0] += h.im;
+            }
+            dst[(size_t)q * plane_sz] = cplx<R>{are[0] * finv, aim[0] * finv};
 #pragma unroll
-        for (int k = 0; k + 1 < W; ++k) {
-            are[k] = are[k + 1];
-            aim[k] = aim[k + 1];
+            for (int k = 0; k + 1 < W; ++k) {
+                are[k] = are[k + 1];
+                aim[k] = aim[k + 1];
+            }
+            are[W - 1] = aim[W - 1] = R(0);
         }
-        are[W - 1] = aim[W - 1] = R(0);
-    }
+    };
+    if (n_all <= kSumMax) planes_of(std::false_type{});
+    else planes_of(std::true_type{});
 }
 template <int W> static hipError_t spread_cells_w(const SpreadLaunch &a, hipStream_t s) {
     if (a.g.flat || !a.phase || a.g.T > 32 || a.g.nj0max > kCellsMaxPlanes) return hipErrorInvalidValue;
     const int nthr = a.g.T * a.g.T;   // 64 threads per 8 x 8 block
-    const size_t lds = (size_t)kCellsMax * 20 + (size_t)nthr * sizeof(float) + ((size_t)a.g.nj0max + 1) * sizeof(int);
+    const size_t lds = (size_t)kCellsMax * 20 + (size_t)nthr * (sizeof(float) + W * sizeof(cplx<float>)) +
+                       ((size_t)a.g.nj0max + 1) * sizeof(int);
     if (a.vmode == 0) PFB_LAUNCH_NT((spread_cells_kernel<W, 0>), a.n_cwork, nthr, lds, s, a);
     else if (a.vmode == 1) PFB_LAUNCH_NT((spread_cells_kernel<W, 1>), a.n_cwork, nthr, lds, s, a);
     else PFB_LAUNCH_NT((spread_cells_kernel<W, 2>), a.n_cwork, nthr, lds, s, a);
