@@ -746,10 +746,13 @@ pfb_status count_and_layout(pfb_plan *P, char *tmp, hipStream_t stream) {
         // w-stacked FP64, and FP32 with few entries per tile: the plane-by-plane interpolation
         G->istream = !G->g.flat && (dbl || (!opt.chunk && hacc < kStreamPerTile * tiles));
         const int ichunk = G->istream ? (dbl ? kStreamEntries<double> : kStreamEntries<float>) : opt.chunk ? opt.chunk : (int)std::min<int64_t>(std::max<int64_t>(1024, unit / 3), chunk);
-        // (FP64 items are single waves, of which a unit holds sixteen: half their share, so
-        // that the densest unshared tile is no tail; the FP32 PSF's spread does not share)
+        // (FP64 items are single waves for each 8 x 8 block of the tile, of which a unit
+        // holds sixteen: half their share, so that the densest unshared tile is no tail, and
+        // at least a batch of 64 entries; in a tile of several blocks a wave takes about
+        // one entry of n_sub; the FP32 PSF's spread does not share)
+        const int64_t n_sub = (int64_t)(G->g.T + G->g.W - 1) * (G->g.T + G->g.W - 1) / ((7 + G->g.W) * (7 + G->g.W));
         const int64_t share = opt.chunk || (!dbl && G == &Q) ? 0
-                              : dbl     ? std::max<int64_t>(64, acc / (32 * (int64_t)n_cu))
+                              : dbl     ? n_sub * std::max<int64_t>(64, acc / (32 * (int64_t)n_cu))
                                         : std::max<int64_t>(256, unit);
         build_work(*G, cnt, hcnt, chunk, ichunk, share, dbl, cells);
         G->sort_items.clear();

@@ -585,15 +585,20 @@ __device__ __forceinline__ void fixed_point_scale(float am, float S, float &fsca
 // atomics on the W x W x W cells of every entry bounded the kernel at 0.7 lane-adds per
 // cycle and CU: 4.8 ms, now 0.36 ms, for 3.6e5 visibilities at 1024^2, W = 13).  A wave takes its share of a bucket 64 entries at a time: a lane
 // loads one entry and forms its value, and the batch is staged in LDS; then, two entries
-// at a time, 8 + 8 + W lanes each evaluate one 1-D weight (the ES kernel's FP64 square
-// root and exponential are the costly part: once per weight, not once per lane and
-// weight), and every lane adds z U V P[k] to its planes.  After base plane q, plane q is
-// complete and is written.  A block is one wave; dense tiles are shared between items,
-// whose planes are summed in the order of the shares (bitwise reproducible).
+// at a time (four where there is one plane), 8 + 8 + W lanes each (8 + 8) evaluate one
+// 1-D weight (the ES kernel's FP64 square root and exponential are the costly part: once
+// per weight, not once per lane and weight), and every lane adds z U V P[k] to its planes.  After base plane q, plane q is
+// complete and is written.  A block is one wave: one 8 x 8 block of an item's tile
+// (larger tiles than the default of 8 have several, whose waves each read the item's
+// entries and skip the batches that do not reach them; one wave going through a tile's
+// blocks took 2960 us for 3.2e5 visibilities at 512^2, flat, T = 64, these 230).  Dense
+// tiles are shared between items, whose planes are summed in a fixed order (bitwise
+// reproducible).
 template <int W, bool FLAT> struct Spread64 {
     static constexpr int WW = FLAT ? 1 : W;
     static constexpr int ENT = 5;                        // fu, fv, fw, Re z, Im z
-    static constexpr int WAVE = 64 * ENT + 2 * 32;       // doubles of a wave: batch, weights of two entries
+    static constexpr int PER = FLAT ? 4 : 2;             // entries whose weights the lanes evaluate together
+    static constexpr int WAVE = 64 * ENT + 64;           // doubles of a wave: batch, those weights
     static constexpr size_t lds = (size_t)WAVE * sizeof(double);
 };
 // LDS writes of this wave's lanes are seen by its other lanes' later reads
@@ -607,12 +612,13 @@ template <int W, bool FLAT, int VMODE>
 __global__ __launch_bounds__(64, 4) void spread64_kernel(SpreadLaunch a) {
     using K = Spread64<W, FLAT>;
     using R = double;
-    constexpr int WW = K::WW, ENT = K::ENT;
+    constexpr int WW = K::WW, ENT = K::ENT, PER = K::PER, LPE = 64 / PER;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int lane = threadIdx.x;
     R *const ent = reinterpret_cast<R *>(smem_raw), *const wgt = ent + 64 * ENT;
     const int T = a.g.T, nsub = T / 8;                   // 8 x 8 blocks per tile side
-    const GridWork wk = a.work[blockIdx.x];
+    const int sub = blockIdx.x % (nsub * nsub);
+    const GridWork wk = a.work[blockIdx.x / (nsub * nsub)];
     const BandDev bd = a.bands[wk.band];
     const int ntiles = a.g.ntx * a.g.nty;
     const int tu = wk.tile / a.g.nty, tv = wk.tile - tu * a.g.nty;
@@ -625,132 +631,151 @@ __global__ __launch_bounds__(64, 4) void spread64_kernel(SpreadLaunch a) {
     const int64_t keybase = ((int64_t)wk.band * ntiles + wk.tile) * a.g.nj0max;
     const int qstart = max(0, wk.p0 - WW + 1);
     const size_t plane_sz = (size_t)a.g.gx * a.g.gy;
-    // weight evaluated by this lane for entry lane / 32 of a pair: rows 0-7, columns 0-7, planes
-    const int wi = lane & 31, wsel = wi < 8 ? 0 : (wi < 16 ? 1 : 2);
+    // weight evaluated by this lane for entry lane / LPE of PER: rows 0-7, columns 0-7, planes
+    const int wi = lane & (LPE - 1), wsel = wi < 8 ? 0 : (wi < 16 ? 1 : 2);
     const int crow = lane >> 3, ccol = lane & 7;
 
-    for (int sub = 0; sub < nsub * nsub; ++sub) {
-        const int r0 = (sub / nsub) * 8, c0 = (sub % nsub) * 8;
-        R are[WW], aim[WW];
+    const int r0 = (sub / nsub) * 8, c0 = (sub % nsub) * 8;
+    R are[WW], aim[WW];
 #pragma unroll
-        for (int k = 0; k < WW; ++k) are[k] = aim[k] = R(0);
-        unsigned live = 0;    // bit k: base plane q - k has entries in this bucket
-        for (int q = qstart; q < wk.p1; ++q) {
-            int64_t b0 = 0, n = 0;
-            if (q < bd.nj0) {
-                b0 = a.offsets[keybase + q];
-                n = a.offsets[keybase + q + 1] - b0;
+    for (int k = 0; k < WW; ++k) are[k] = aim[k] = R(0);
+    unsigned live = 0;    // bit k: base plane q - k has entries in this bucket
+    for (int q = qstart; q < wk.p1; ++q) {
+        int64_t b0 = 0, n = 0;
+        if (q < bd.nj0) {
+            b0 = a.offsets[keybase + q];
+            n = a.offsets[keybase + q + 1] - b0;
+        }
+        const int64_t e_beg = b0 + n * wk.share / wk.nshare, e_end = b0 + n * (wk.share + 1) / wk.nshare;
+        const R wbase = wsel == 0 ? R(r0 + wi) : (wsel == 1 ? R(c0 + wi - 8) : R(q + wi - 16));
+        for (int64_t e0 = e_beg; e0 < e_end; e0 += 64) {
+            const int64_t e = min(e0 + lane, e_end - 1);
+            const Rec<R> rec = recs[e];
+            const R om = VMODE == 2 ? R(1) : omega[e];
+            const uint32_t at = VMODE == 2 ? a.home_pos[e] : rec.idx & ~kHomeBit;
+            // entries of the batch whose footprint meets this 8 x 8 block
+            const int i0 = (int)dev_floor(rec.fu - hw) + 1, j0 = (int)dev_floor(rec.fv - hw) + 1;
+            unsigned long long todo = __builtin_amdgcn_ballot_w64(e0 + lane < e_end && i0 < r0 + 8 && i0 + W > r0 &&
+                                                                  j0 < c0 + 8 && j0 + W > c0);
+            if (!todo) continue;
+            const R fw = dev_abs(rec.fw);
+            cplx<R> z;
+            if (VMODE == 0) {
+                z = entry_conj(rec, vis[at]) * om;
+                if (!FLAT) z = z * cis_cycles<R>((bd.w0 + fw * bd.dw) * bd.sc);
+            } else if (VMODE == 1) {
+                z = cplx<R>{om, R(0)};
+            } else {
+                z = vis[at];
             }
-            const int64_t e_beg = b0 + n * wk.share / wk.nshare, e_end = b0 + n * (wk.share + 1) / wk.nshare;
-            const R wbase = wsel == 0 ? R(r0 + wi) : (wsel == 1 ? R(c0 + wi - 8) : R(q + wi - 16));
-            for (int64_t e0 = e_beg; e0 < e_end; e0 += 64) {
-                const int64_t e = min(e0 + lane, e_end - 1);
-                const Rec<R> rec = recs[e];
-                const uint32_t vid = rec.idx & ~kHomeBit;
-                const R fw = dev_abs(rec.fw);
-                cplx<R> z;
-                if (VMODE == 0) {
-                    z = entry_conj(rec, vis[vid]) * omega[e];
-                    if (!FLAT) z = z * cis_cycles<R>((bd.w0 + fw * bd.dw) * bd.sc);
-                } else if (VMODE == 1) {
-                    z = cplx<R>{omega[e], R(0)};
-                } else {
-                    z = vis[a.home_pos[e]];
+            wave_lds_fence();    // the last batch's reads are done
+            ent[lane * ENT] = rec.fu;
+            ent[lane * ENT + 1] = rec.fv;
+            ent[lane * ENT + 2] = fw;
+            ent[lane * ENT + 3] = z.re;
+            ent[lane * ENT + 4] = z.im;
+            wave_lds_fence();
+            while (todo) {
+                int pick[PER], cnt = 0;
+#pragma unroll
+                for (int u = 0; u < PER; ++u) {
+                    pick[u] = todo ? __builtin_ctzll(todo) : pick[0];
+                    cnt += todo ? 1 : 0;
+                    todo &= todo - 1;
                 }
-                // entries of the batch whose footprint meets this 8 x 8 block
-                const int i0 = (int)dev_floor(rec.fu - hw) + 1, j0 = (int)dev_floor(rec.fv - hw) + 1;
-                unsigned long long todo = __builtin_amdgcn_ballot_w64(e0 + lane < e_end && i0 < r0 + 8 && i0 + W > r0 &&
-                                                                      j0 < c0 + 8 && j0 + W > c0);
-                wave_lds_fence();    // the last batch's reads are done
-                ent[lane * ENT] = rec.fu;
-                ent[lane * ENT + 1] = rec.fv;
-                ent[lane * ENT + 2] = fw;
-                ent[lane * ENT + 3] = z.re;
-                ent[lane * ENT + 4] = z.im;
+                int ex = pick[0];
+#pragma unroll
+                for (int u = 1; u < PER; ++u) ex = lane >= u * LPE ? pick[u] : ex;
+                const R w = es_kernel<R>(wbase - ent[ex * ENT + wsel], beta, inv_hw);
                 wave_lds_fence();
-                while (todo) {
-                    const int ea = __builtin_ctzll(todo);
-                    todo &= todo - 1;
-                    const int eb = todo ? __builtin_ctzll(todo) : ea;
-                    const bool two = todo != 0;
-                    todo &= todo - 1;
-                    const int ex = lane < 32 ? ea : eb;
-                    const R w = es_kernel<R>(wbase - ent[ex * ENT + wsel], beta, inv_hw);
-                    wave_lds_fence();
-                    wgt[lane] = w;
-                    wave_lds_fence();
+                wgt[lane] = w;
+                wave_lds_fence();
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        if (h == 1 && !two) break;
-                        const R *const wh = wgt + 32 * h;
-                        const R *const en = ent + (h ? eb : ea) * ENT;
-                        const R uv = wh[crow] * wh[8 + ccol];
-                        const R zr = en[3] * uv, zi = en[4] * uv;
-                        if (FLAT) {
-                            are[0] += zr;
-                            aim[0] += zi;
-                        } else {
+                for (int h = 0; h < PER; ++h) {
+                    if (h > 0 && h >= cnt) break;
+                    const R *const wh = wgt + LPE * h;
+                    const R *const en = ent + pick[h] * ENT;
+                    const R uv = wh[crow] * wh[8 + ccol];
+                    const R zr = en[3] * uv, zi = en[4] * uv;
+                    if (FLAT) {
+                        are[0] += zr;
+                        aim[0] += zi;
+                    } else {
 #pragma unroll
-                            for (int k = 0; k < WW; ++k) {
-                                const R pk = wh[16 + k];
-                                are[k] += zr * pk;
-                                aim[k] += zi * pk;
-                            }
+                        for (int k = 0; k < WW; ++k) {
+                            const R pk = wh[16 + k];
+                            are[k] += zr * pk;
+                            aim[k] += zi * pk;
                         }
                     }
                 }
             }
-            live = ((live << 1) | (n > 0 ? 1u : 0u)) & ((1u << WW) - 1u);
-            // planes that no base plane of their reach touches are zero: not written (the
-            // transforms read only occupied tiles), and their sums are zero already
-            if (!live) continue;
-            cplx<R> v{are[0], aim[0]};
-#pragma unroll
-            for (int k = 0; k + 1 < WW; ++k) {
-                are[k] = are[k + 1];
-                aim[k] = aim[k + 1];
-            }
-            are[WW - 1] = aim[WW - 1] = R(0);
-            if (q < wk.p0) continue;
-            if (wk.nshare > 1)
-                reinterpret_cast<cplx<R> *>(a.scratch)[((size_t)(wk.slot + wk.share) * a.g.nwmax + q) * T * T +
-                                                       (r0 + crow) * T + c0 + ccol] = v;
-            else
-                planes[((size_t)bb * a.g.nwmax + q) * plane_sz + (size_t)(tu * T + r0 + crow) * a.g.gy +
-                       (size_t)(tv * T + c0 + ccol)] = v;
         }
+        live = ((live << 1) | (n > 0 ? 1u : 0u)) & ((1u << WW) - 1u);
+        // planes that no base plane of their reach touches are zero: not written (the
+        // transforms read only occupied tiles), and their sums are zero already
+        if (!live) continue;
+        cplx<R> v{are[0], aim[0]};
+#pragma unroll
+        for (int k = 0; k + 1 < WW; ++k) {
+            are[k] = are[k + 1];
+            aim[k] = aim[k + 1];
+        }
+        are[WW - 1] = aim[WW - 1] = R(0);
+        if (q < wk.p0) continue;
+        if (wk.nshare > 1)
+            reinterpret_cast<cplx<R> *>(a.scratch)[((size_t)(wk.slot + wk.share) * a.g.nwmax + q) * T * T +
+                                                   (r0 + crow) * T + c0 + ccol] = v;
+        else
+            planes[((size_t)bb * a.g.nwmax + q) * plane_sz + (size_t)(tu * T + r0 + crow) * a.g.gy +
+                   (size_t)(tv * T + c0 + ccol)] = v;
     }
 }
 
 // The planes of shared tiles from their scratch tiles: FP32 converts the fixed-point sums
-// and clears them for the next launch, FP64 adds the shares in order.  One block per
-// (shared tile, plane); planes the spread did not touch are left alone.
+// and clears them for the next launch, FP64 adds the shares in a fixed order.  A block
+// takes kSharedCells cells of one (shared tile, plane); FP64 the shares in four runs
+// besides, since few tiles of hundreds of shares each are common (1.4e6 visibilities at
+// 128^2: one thread per cell 56 us, this 28).  Planes the spread did not touch are left
+// alone.
+template <typename R> constexpr int kSharedCells = sizeof(R) == 4 ? kThreads : kThreads / 4;
 template <typename R>
 __global__ __launch_bounds__(kThreads) void shared_tiles_kernel(SpreadLaunch a, float S) {
-    const SharedTile st = a.shared[blockIdx.x / a.g.nwmax];
-    const int p = blockIdx.x % a.g.nwmax;
-    const int T = a.g.T, TT = T * T, lgT = __builtin_ctz(T);
+    constexpr int CELLS = kSharedCells<R>, RUNS = kThreads / CELLS;
+    const int T = a.g.T, TT = T * T, lgT = __builtin_ctz(T), parts = (TT + CELLS - 1) / CELLS;
+    const int tp = blockIdx.x / parts, k = (blockIdx.x - tp * parts) * CELLS + threadIdx.x % CELLS;
+    const SharedTile st = a.shared[tp / a.g.nwmax];
+    const int p = tp % a.g.nwmax;
     const int tu = st.tile / a.g.nty, tv = st.tile - tu * a.g.nty;
     if (!a.occ[((size_t)st.band * a.g.nwmax + p) * a.g.ntx * a.g.nty + st.tile]) return;
-    cplx<R> *dst = reinterpret_cast<cplx<R> *>(a.planes) +
-                   ((size_t)(st.band - a.band0) * a.g.nwmax + p) * a.g.gx * a.g.gy + (size_t)tu * T * a.g.gy + (size_t)tv * T;
-    float fscale = 1.f, finv = 1.f;
-    if constexpr (sizeof(R) == 4) fixed_point_scale(*a.absmax, S, fscale, finv);
-    for (int k = threadIdx.x; k < TT; k += kThreads) {
+    cplx<R> *const dst = reinterpret_cast<cplx<R> *>(a.planes) + ((size_t)(st.band - a.band0) * a.g.nwmax + p) * a.g.gx * a.g.gy +
+                         (size_t)(tu * T + (k >> lgT)) * a.g.gy + (size_t)tv * T + (k & (T - 1));
+    if constexpr (sizeof(R) == 4) {
+        if (k >= TT) return;
+        float fscale = 1.f, finv = 1.f;
+        fixed_point_scale(*a.absmax, S, fscale, finv);
+        long long *const c = reinterpret_cast<long long *>(a.scratch) + 2 * (((size_t)st.slot * a.g.nwmax + p) * TT + k);
+        *dst = cplx<R>{(R)((double)c[0] * (double)finv), (R)((double)c[1] * (double)finv)};
+        c[0] = c[1] = 0;
+    } else {
+        static_assert(CELLS == 64, "every tile's cells fill whole blocks");
+        __shared__ cplx<R> sums[kThreads];
+        const cplx<R> *c = reinterpret_cast<const cplx<R> *>(a.scratch) + ((size_t)st.slot * a.g.nwmax + p) * TT + k;
+        const int run = threadIdx.x / CELLS, i1 = st.nshare * (run + 1) / RUNS;
         cplx<R> v{R(0), R(0)};
-        if constexpr (sizeof(R) == 4) {
-            long long *const c = reinterpret_cast<long long *>(a.scratch) + 2 * (((size_t)st.slot * a.g.nwmax + p) * TT + k);
-            v = cplx<R>{(R)((double)c[0] * (double)finv), (R)((double)c[1] * (double)finv)};
-            c[0] = c[1] = 0;
-        } else {
-            const cplx<R> *c = reinterpret_cast<const cplx<R> *>(a.scratch) + ((size_t)st.slot * a.g.nwmax + p) * TT + k;
-            for (int i = 0; i < st.nshare; ++i) v = v + c[(size_t)i * a.g.nwmax * TT];
-        }
-        dst[(size_t)(k >> lgT) * a.g.gy + (k & (T - 1))] = v;
+        for (int i = st.nshare * run / RUNS; i < i1; ++i) v = v + c[(size_t)i * a.g.nwmax * TT];
+        sums[threadIdx.x] = v;
+        __syncthreads();
+        if (run > 0) return;
+#pragma unroll
+        for (int r = 1; r < RUNS; ++r) v = v + sums[threadIdx.x + r * CELLS];
+        *dst = v;
     }
 }
 template <typename R> static hipError_t sum_shared_tiles(const SpreadLaunch &a, float S, hipStream_t s) {
-    if (a.n_shared > 0) PFB_LAUNCH(shared_tiles_kernel<R>, (unsigned)((int64_t)a.n_shared * a.g.nwmax), 0, s, a, S);
+    const int64_t nb = (int64_t)a.n_shared * a.g.nwmax * ((a.g.T * a.g.T + kSharedCells<R> - 1) / kSharedCells<R>);
+    if (nb > INT_MAX) return hipErrorInvalidValue;
+    if (nb > 0) PFB_LAUNCH(shared_tiles_kernel<R>, (unsigned)nb, 0, s, a, S);
     return hipSuccess;
 }
 
@@ -1549,10 +1574,12 @@ hipError_t launch_absmax(int vmode, const void *vis, const void *weight, const u
 template <int W>
 static hipError_t spread64_w(const SpreadLaunch &a, hipStream_t s) {
     const bool flat = a.g.flat;
+    const int64_t nb = (int64_t)a.n_work * (a.g.T / 8) * (a.g.T / 8);
+    if (nb > INT_MAX) return hipErrorInvalidValue;
 #define SPREAD_CASE(FL, VM)                                                                                       \
     if (flat == FL && a.vmode == VM) {                                                                            \
-        PFB_LAUNCH_NT((spread64_kernel<W, FL, VM>), a.n_work, 64, (Spread64<W, FL>::lds), s, a); \
-        return sum_shared_tiles<double>(a, 1.f, s);                                                                                        \
+        PFB_LAUNCH_NT((spread64_kernel<W, FL, VM>), (unsigned)nb, 64, (Spread64<W, FL>::lds), s, a);              \
+        return sum_shared_tiles<double>(a, 1.f, s);                                                               \
     }
     SPREAD_CASE(false, 0)
     SPREAD_CASE(false, 1)
