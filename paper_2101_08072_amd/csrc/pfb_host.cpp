@@ -235,7 +235,7 @@ struct pfb_plan {
     size_t o_planes = 0, o_t1 = 0, o_vals = 0, o_psfimg = 0;
     size_t o_t1c = 0, o_psfhat = 0, o_vec = 0, o_partials = 0, o_scal = 0, o_ctr = 0, o_absmax = 0;
     size_t planes_bytes = 0, t_bytes = 0, vec_bytes = 0;
-    size_t o_sorttmp = 0;   // scratch for the plan-time sort (aliases the w-plane area when it fits)
+    size_t o_sorttmp = 0;   // scratch for the plan-time sort: from the w-plane area on
     Profiler prof;
     bool prof_on = false;
     void *p(size_t off) const { return ws + off; }
@@ -269,13 +269,28 @@ GeomDev base_geom(const pfb_plan &P, int nx, int ny, bool flat) {
 // plane (equal between 390, where it is 8 % faster, and 1030, where it is 38 % slower)
 constexpr int64_t kStreamPerTile = 400;
 
+// Scratch tiles that sharing at `share` entries takes in the launch of a batch that needs
+// most, one for every share (FP64), from the entries of every (band, tile).
+int64_t share_slots(const std::vector<int64_t> &tile_entries, int n_band, int band_batch, int64_t share) {
+    const size_t ntiles = tile_entries.size() / n_band;
+    int64_t most = 0, slots = 0;
+    for (int b = 0; b < n_band; ++b) {
+        if (b % band_batch == 0) slots = 0;
+        for (size_t t = b * ntiles; t < (b + 1) * ntiles; ++t)
+            if (tile_entries[t] > 2 * share) slots += (tile_entries[t] + share - 1) / share;
+        most = std::max(most, slots);
+    }
+    return most;
+}
+
 // Work lists from the per-(band, tile, base plane) counts: spread items of at most
 // `chunk` entries, interpolation items of at most `ichunk` home entries.  share > 0: tiles
 // of more than two such shares of entries go to several items that share them instead,
-// with one scratch tile each (per_share) or one together.  Tiles of at most `cells`
+// with one scratch tile each (per_share) or one together; the scratch tiles are those of
+// one launch, counted from zero in every batch of bands.  Tiles of at most `cells`
 // entries go to the list of the kernel whose lanes own cells.
 void build_work(GridderHost &G, const std::vector<unsigned> &counts, const std::vector<unsigned> &hcounts, int chunk,
-                int ichunk, int64_t share, bool per_share, int64_t cells) {
+                int ichunk, int64_t share, bool per_share, int64_t cells, int band_batch) {
     const GeomDev &g = G.g;
     const int ntiles = g.ntx * g.nty;
     const int W = g.flat ? 1 : g.W;
@@ -286,6 +301,7 @@ void build_work(GridderHost &G, const std::vector<unsigned> &counts, const std::
     G.shared.clear();
     G.shared_start.assign(g.n_band + 1, 0);
     G.n_scratch = 0;
+    int slot = 0;
     G.gband_start.assign(g.n_band + 1, 0);
     G.iband_start.assign(g.n_band + 1, 0);
     std::vector<std::pair<int64_t, GridWork>> gw, cw;
@@ -300,6 +316,7 @@ void build_work(GridderHost &G, const std::vector<unsigned> &counts, const std::
         gw.clear();
         cw.clear();
         iw.clear();
+        if (b % band_batch == 0) slot = 0;
         for (int t = 0; t < ntiles; ++t) {
             const int64_t kb = ((int64_t)b * ntiles + t) * g.nj0max;
             const unsigned *c = counts.data() + kb;
@@ -326,10 +343,11 @@ void build_work(GridderHost &G, const std::vector<unsigned> &counts, const std::
                 cw.push_back({tot, GridWork{b, t, 0, nw, 0, 1, 0}});
             } else if (share > 0 && tot > 2 * share) {
                 const int ns = (int)((tot + share - 1) / share);
-                G.shared.push_back(SharedTile{b, t, G.n_scratch, ns});
+                G.shared.push_back(SharedTile{b, t, slot, ns});
                 for (int k = 0; k < ns; ++k)
-                    gw.push_back({tot / ns * (int64_t)W + 1, GridWork{b, t, 0, nw, k, ns, G.n_scratch}});
-                G.n_scratch += per_share ? ns : 1;
+                    gw.push_back({tot / ns * (int64_t)W + 1, GridWork{b, t, 0, nw, k, ns, slot}});
+                slot += per_share ? ns : 1;
+                G.n_scratch = std::max(G.n_scratch, slot);
             } else {
                 int p0 = 0;
                 while (p0 < nw) {
@@ -689,7 +707,7 @@ pfb_status count_and_layout(pfb_plan *P, char *tmp, hipStream_t stream) {
     if (ctr[2] || ctr[5]) return fail(PFB_EINVAL, "%llu visibilities fell outside the planned w range", ctr[2] + ctr[5]);
     P->n_active = (int64_t)ctr[0];
     P->n_flagged = (int64_t)ctr[1];
-    // bucket offsets and work lists
+    // bucket offsets
     for (GridderHost *G : {&M, &Q}) {
         const std::vector<unsigned> &cnt = (G == &M) ? cM : cQ;
         G->offsets.resize(cnt.size() + 1);
@@ -713,6 +731,44 @@ pfb_status count_and_layout(pfb_plan *P, char *tmp, hipStream_t stream) {
             fail(PFB_EUNSUPPORTED, "%lld bucket entries exceed 2^31", (long long)acc);
             return PFB_EUNSUPPORTED;
         }
+    }
+
+    // band batch
+    P->band_batch = opt.band_batch > 0 ? std::min(opt.band_batch, pr.n_band) : pr.n_band;
+    const size_t csz = 2 * P->rsz;
+    const size_t per_band_planes = std::max((size_t)M.g.nwmax * M.g.gx * M.g.gy, (size_t)Q.g.gx * Q.g.gy) * csz;
+    if (opt.band_batch == 0) {
+        const size_t budget = (size_t)160 << 30;  // planes + two intermediates (MI355X: 288 GB HBM)
+        while (P->band_batch > 1 && P->band_batch * 2 * per_band_planes > budget) --P->band_batch;
+    }
+    P->opt.band_batch = P->band_batch;
+    P->planes_bytes = (size_t)P->band_batch * per_band_planes;
+    {
+        // cropped row spectra, columns padded to whole groups of plane_group_cols
+        const size_t cg = (size_t)plane_group_cols(dbl);
+        auto padded = [cg](int n) { return ((size_t)n + cg - 1) / cg * cg; };
+        P->t_bytes = (size_t)P->band_batch *
+                     std::max((size_t)M.g.nwmax * M.g.gx * padded(M.g.ny), (size_t)Q.g.gx * padded(Q.g.ny)) * csz;
+    }
+    size_t sort_need = 0;
+    for (GridderHost *G : {&M, &Q}) {
+        const size_t recsz = dbl ? sizeof(Rec<double>) : sizeof(Rec<float>);
+        sort_need = std::max(sort_need, (((size_t)G->n_entries * recsz + 255) & ~size_t(255)) +
+                                            (((size_t)G->n_entries * P->rsz + 255) & ~size_t(255)) +
+                                            sort_scratch_bytes(G->n_entries));
+    }
+    // the plan-time sort's scratch takes the planes' area, the transforms' intermediate
+    // after it, and what it needs beyond them after that; FP64 shares' scratch tiles take
+    // the latter two, which are idle during the spread
+    auto whole = [](size_t bytes) { return (bytes + 255) & ~size_t(255); };
+    const size_t sort_room = whole(P->planes_bytes) + whole(P->t_bytes);
+    const size_t sort_more = sort_need > sort_room ? sort_need - sort_room : 0;
+    const size_t scratch_room = whole(P->t_bytes) + sort_more;
+
+    // work lists
+    for (GridderHost *G : {&M, &Q}) {
+        const std::vector<unsigned> &cnt = (G == &M) ? cM : cQ, &hcnt = (G == &M) ? hM : hQ;
+        const int64_t acc = G->n_entries, hacc = G->n_home;
         // work-item size: a given chunk, else one compute unit's share of all entries
         // (>= 4096): a spread item split by plane range re-reads the entries of the
         // W - 1 base planes its neighbour also covers, so only tiles heavier than a
@@ -729,9 +785,12 @@ pfb_status count_and_layout(pfb_plan *P, char *tmp, hipStream_t stream) {
         // of more than two such shares are shared between items, interpolation items, which
         // only read, are split at a third of a share (>= 1024 entries); a given chunk is kept.
         int64_t tiles = 0, sparse = 0;   // (band, tile)s with entries, with few
+        std::vector<int64_t> tile_entries;
+        tile_entries.reserve(cnt.size() / G->g.nj0max);
         for (size_t k2 = 0; k2 < cnt.size(); k2 += G->g.nj0max) {
             int64_t tot = 0;
             for (int q = 0; q < G->g.nj0max; ++q) tot += cnt[k2 + q];
+            tile_entries.push_back(tot);
             tiles += tot > 0;
             sparse += tot > 0 && tot <= kCellsMax;
         }
@@ -751,10 +810,16 @@ pfb_status count_and_layout(pfb_plan *P, char *tmp, hipStream_t stream) {
         // at least a batch of 64 entries; in a tile of several blocks a wave takes about
         // one entry of n_sub; the FP32 PSF's spread does not share)
         const int64_t n_sub = (int64_t)(G->g.T + G->g.W - 1) * (G->g.T + G->g.W - 1) / ((7 + G->g.W) * (7 + G->g.W));
-        const int64_t share = opt.chunk || (!dbl && G == &Q) ? 0
-                              : dbl     ? n_sub * std::max<int64_t>(64, acc / (32 * (int64_t)n_cu))
-                                        : std::max<int64_t>(256, unit);
-        build_work(*G, cnt, hcnt, chunk, ichunk, share, dbl, cells);
+        int64_t share = opt.chunk || (!dbl && G == &Q) ? 0
+                        : dbl     ? n_sub * std::max<int64_t>(64, acc / (32 * (int64_t)n_cu))
+                                  : std::max<int64_t>(256, unit);
+        // FP64: no more shares than the scratch area holds (every share has a scratch tile
+        // over all planes; in an area of its own that was up to half of the workspace)
+        const size_t tile_bytes = (size_t)G->g.nwmax * G->g.T * G->g.T * 16;
+        if (dbl && share > 0)
+            while (share_slots(tile_entries, pr.n_band, P->band_batch, share) * tile_bytes > scratch_room) share *= 2;
+        build_work(*G, cnt, hcnt, chunk, ichunk, share, dbl, cells, P->band_batch);
+        G->scratch_bytes = G->n_scratch * tile_bytes;
         G->sort_items.clear();
         for (size_t k2 = 0; k2 < cnt.size(); ++k2)
             if (cnt[k2]) {
@@ -794,16 +859,6 @@ pfb_status count_and_layout(pfb_plan *P, char *tmp, hipStream_t stream) {
     P->conv_cgc = conv_group_cols(dbl, P->conv_lx / 2);
     P->ldh = ((P->conv_ly / 2 + 1 + 15) / 16) * 16;
 
-    // band batch
-    P->band_batch = opt.band_batch > 0 ? std::min(opt.band_batch, pr.n_band) : pr.n_band;
-    const size_t csz = 2 * P->rsz;
-    const size_t per_band_planes = std::max((size_t)M.g.nwmax * M.g.gx * M.g.gy, (size_t)Q.g.gx * Q.g.gy) * csz;
-    if (opt.band_batch == 0) {
-        const size_t budget = (size_t)160 << 30;  // planes + two intermediates (MI355X: 288 GB HBM)
-        while (P->band_batch > 1 && P->band_batch * 2 * per_band_planes > budget) --P->band_batch;
-    }
-    P->opt.band_batch = P->band_batch;
-
     // workspace layout
     Layout L;
     const int nb = pr.n_band;
@@ -822,8 +877,7 @@ pfb_status count_and_layout(pfb_plan *P, char *tmp, hipStream_t stream) {
         G->o_iwork = L.take(std::max<size_t>(G->iwork.size(), 1) * sizeof(InterpWork));
         G->o_cwork = L.take(std::max<size_t>(G->cwork.size(), 1) * sizeof(GridWork));
         G->o_shared = L.take(std::max<size_t>(G->shared.size(), 1) * sizeof(SharedTile));
-        G->scratch_bytes = (size_t)G->n_scratch * G->g.nwmax * G->g.T * G->g.T * 16;
-        G->o_scratch = L.take(std::max<size_t>(G->scratch_bytes, 1));
+        if (!dbl) G->o_scratch = L.take(std::max<size_t>(G->scratch_bytes, 1));
         G->o_sortitems = L.take(std::max<size_t>(G->sort_items.size(), 4) * sizeof(int64_t));
         G->o_recs = L.take(std::max<int64_t>(G->n_entries, 1) * (dbl ? sizeof(Rec<double>) : sizeof(Rec<float>)));
         G->o_omega = L.take(std::max<int64_t>(G->n_entries, 1) * P->rsz);
@@ -844,25 +898,12 @@ pfb_status count_and_layout(pfb_plan *P, char *tmp, hipStream_t stream) {
             G->o_corry = L.take((size_t)G->g.ny * P->rsz);
         }
     }
-    P->planes_bytes = (size_t)P->band_batch * per_band_planes;
-    {
-        // cropped row spectra, columns padded to whole groups of plane_group_cols
-        const size_t cg = (size_t)plane_group_cols(dbl);
-        auto padded = [cg](int n) { return ((size_t)n + cg - 1) / cg * cg; };
-        P->t_bytes = (size_t)P->band_batch *
-                     std::max((size_t)M.g.nwmax * M.g.gx * padded(M.g.ny), (size_t)Q.g.gx * padded(Q.g.ny)) * csz;
-    }
     P->o_planes = L.take(P->planes_bytes);
     P->o_t1 = L.take(P->t_bytes);
-    {
-        const size_t recsz = dbl ? sizeof(Rec<double>) : sizeof(Rec<float>);
-        size_t need = 0;
-        for (GridderHost *G : {&M, &Q})
-            need = std::max(need, (((size_t)G->n_entries * recsz + 255) & ~size_t(255)) +
-                                      (((size_t)G->n_entries * P->rsz + 255) & ~size_t(255)) +
-                                      sort_scratch_bytes(G->n_entries));
-        P->o_sorttmp = (L.off - P->o_planes >= need) ? P->o_planes : L.take(need);
-    }
+    P->o_sorttmp = P->o_planes;
+    L.take(sort_more);
+    if (dbl)
+        for (GridderHost *G : {&M, &Q}) G->o_scratch = P->o_t1;
     P->o_vals = L.take((size_t)pr.n_row * pr.n_chan * csz);
     P->o_psfimg = L.take((size_t)nb * 4 * Pimg * P->rsz);
     P->o_t1c = L.take((size_t)nb * P->conv_lx * P->ldh * csz);
@@ -1195,7 +1236,7 @@ pfb_status pfb_plan_set_workspace(pfb_plan *P, void *dev, size_t bytes, hipStrea
         if (!G->shared.empty()) {
             HIP_OK(hipMemcpyAsync(G->d_shared, G->shared.data(), G->shared.size() * sizeof(SharedTile),
                                   hipMemcpyHostToDevice, s));
-            HIP_OK(hipMemsetAsync(G->d_scratch, 0, G->scratch_bytes, s));   // zero between launches
+            if (!d) HIP_OK(hipMemsetAsync(G->d_scratch, 0, G->scratch_bytes, s));   // zero between launches
         }
         G->d_recs = P->p(G->o_recs);
         G->d_omega = P->p(G->o_omega);

@@ -591,7 +591,7 @@ __device__ __forceinline__ void fixed_point_scale(float am, float S, float &fsca
 // complete and is written.  A block is one wave: one 8 x 8 block of an item's tile
 // (larger tiles than the default of 8 have several, whose waves each read the item's
 // entries and skip the batches that do not reach them; one wave going through a tile's
-// blocks took 2960 us for 3.2e5 visibilities at 512^2, flat, T = 64, these 230).  Dense
+// blocks took 2960 us for 3.2e5 visibilities at 512^2, flat, T = 64, these 172).  Dense
 // tiles are shared between items, whose planes are summed in a fixed order (bitwise
 // reproducible).
 template <int W, bool FLAT> struct Spread64 {
