@@ -116,8 +116,12 @@ typedef struct {
     int32_t tile;         /* uv tile side T (power of two, 8..64); default 32 FP32, 8 FP64   */
     int32_t flat;         /* 1: drop the w term and the 1/n factor from R (w = 0, n = 1)     */
     int32_t band_batch;   /* bands whose w-planes are resident at once; default n_band       */
-    int32_t chunk;        /* bucket entries per work item before a tile is split (>= 64);
-                             default max(4096, entries / compute units of the device)       */
+    int32_t chunk;        /* bucket entries per work item (>= 64).  FP32: a tile of more is
+                             split by w-planes for the spread, by entries for the
+                             interpolation.  FP64: more entries of a tile than this are
+                             shared between items (its own choice where that is less, or
+                             where the workspace holds no more shares).  0: by the job's
+                             entries per tile and the device's compute units                */
     double  epsilon;      /* requested relative accuracy of grid / degrid (rel-l2); when
                              support is 0 and epsilon > 0 the support is the smallest W whose
                              tabulated error of the 3-D ES product kernel at sigma = 2 plus

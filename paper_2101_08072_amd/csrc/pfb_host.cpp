@@ -783,7 +783,8 @@ pfb_status count_and_layout(pfb_plan *P, char *tmp, hipStream_t stream) {
         // a unit's share of the work: the entries, and per item about what 1500 entries
         // cost (filling or clearing the plane ring, the steps over its planes).  Spread tiles
         // of more than two such shares are shared between items, interpolation items, which
-        // only read, are split at a third of a share (>= 1024 entries); a given chunk is kept.
+        // only read, are split at a third of a share (>= 1024 entries); in FP32 a given chunk
+        // is kept.
         int64_t tiles = 0, sparse = 0;   // (band, tile)s with entries, with few
         std::vector<int64_t> tile_entries;
         tile_entries.reserve(cnt.size() / G->g.nj0max);
@@ -810,13 +811,19 @@ pfb_status count_and_layout(pfb_plan *P, char *tmp, hipStream_t stream) {
         // at least a batch of 64 entries; in a tile of several blocks a wave takes about
         // one entry of n_sub; the FP32 PSF's spread does not share)
         const int64_t n_sub = (int64_t)(G->g.T + G->g.W - 1) * (G->g.T + G->g.W - 1) / ((7 + G->g.W) * (7 + G->g.W));
-        int64_t share = opt.chunk || (!dbl && G == &Q) ? 0
-                        : dbl     ? n_sub * std::max<int64_t>(64, acc / (32 * (int64_t)n_cu))
-                                  : std::max<int64_t>(256, unit);
+        // FP64 takes a given chunk as a bound of the share: an unshared tile of many entries
+        // would be one wave's work (128^2, 1.4e6 visibilities, chunk 65536: 36 ms, shared 1.2)
+        int64_t share = 0;
+        if (dbl) {
+            share = n_sub * std::max<int64_t>(64, acc / (32 * (int64_t)n_cu));
+            if (opt.chunk) share = std::min<int64_t>(share, opt.chunk);
+        } else if (!opt.chunk && G == &M) {
+            share = std::max<int64_t>(256, unit);
+        }
         // FP64: no more shares than the scratch area holds (every share has a scratch tile
         // over all planes; in an area of its own that was up to half of the workspace)
         const size_t tile_bytes = (size_t)G->g.nwmax * G->g.T * G->g.T * 16;
-        if (dbl && share > 0)
+        if (dbl)
             while (share_slots(tile_entries, pr.n_band, P->band_batch, share) * tile_bytes > scratch_room) share *= 2;
         build_work(*G, cnt, hcnt, chunk, ichunk, share, dbl, cells, P->band_batch);
         G->scratch_bytes = G->n_scratch * tile_bytes;

@@ -22,7 +22,7 @@ class Options:
     tile: int = 0               # uv tile side (0 = default: 32 fp32, 8 fp64)
     flat: bool = False          # drop the w term and 1/n (w = 0, n = 1)
     band_batch: int = 0         # bands whose w-planes are resident together (0 = all that fit)
-    chunk: int = 0              # bucket entries per work item (0 = entries / compute units)
+    chunk: int = 0              # most bucket entries per work item (0 = chosen from the job and the device)
     epsilon: float = 0.0        # requested grid/degrid accuracy: picks the support when support = 0
 
     def to_c(self) -> _lib.PfbOptions:

@@ -59,3 +59,21 @@ def test_large_tiles_keep_up_with_small_ones():
         ms[tile] = min(t)
     say(f"flat FP64 dirty image, tiles of 8 and 64: {ms}")
     assert ms[64] < 8 * ms[8]
+
+
+@pytest.mark.parametrize("flat", [False, True])
+def test_a_given_chunk_keeps_dense_tiles_shared(flat):
+    """chunk bounds the entries of an item: a large one leaves the default's shares (the
+    same bits), a small one makes more of them."""
+    import torch
+    prob = synth.tiny_problem(seed=383, nx=64, ny=64, n_row=20000, freqs=(1.0e9, 1.2e9), cell_arcsec=150.0,
+                              w_frac=0.0 if flat else 0.3)
+    prob.uvw[:, :2] *= 0.15
+    rng = np.random.default_rng(384)
+    vis = to_dev(rng.normal(size=(20000, 2)) + 0.5j, torch.complex128)
+    got = {c: host(make_plan(prob, "fp64", flat=flat, chunk=c).grid(vis)).copy() for c in (0, 64, 300, 1 << 20)}
+    pix = rng.choice(64 * 64, 64, replace=False)
+    ref = oracle.grid(prob, host(vis), pix=pix, flat=flat)
+    for c, g in got.items():
+        assert rel(g.ravel()[pix], ref) < 1e-10, c
+    assert np.array_equal(got[0], got[1 << 20])
