@@ -784,7 +784,9 @@ pfb_status count_and_layout(pfb_plan *P, char *tmp, hipStream_t stream) {
         // cost (filling or clearing the plane ring, the steps over its planes).  Spread tiles
         // of more than two such shares are shared between items, interpolation items, which
         // only read, are split at a third of a share (>= 1024 entries); in FP32 a given chunk
-        // is kept.
+        // is kept.  All of this counts the entries of all bands, however many of them a
+        // launch takes, so that the sums (whose runs end with a share) are the same bits for
+        // every band batch; a launch of fewer bands has fewer, not smaller items.
         int64_t tiles = 0, sparse = 0;   // (band, tile)s with entries, with few
         std::vector<int64_t> tile_entries;
         tile_entries.reserve(cnt.size() / G->g.nj0max);
