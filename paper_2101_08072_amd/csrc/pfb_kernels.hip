@@ -812,7 +812,7 @@ __device__ __forceinline__ float es_kernel_fast(float z, float beta2, float inv_
 // truncation (relative size 2^-26).  The per-visibility quantities (1-D ES weights, value)
 // are computed for 8 visibilities at once, one per 8-lane group, then broadcast with
 // readlane / shuffles.  The values are real, so only real sums are kept: half of the LDS
-// adds that bound the kernel (262 -> 162 us for 2.5e6 entries of a 1024^2 image's PSF).  The matrix-core windows below, with dense tiles shared
+// adds that bound the kernel (258 -> 149 us for 2e6 visibilities' PSF at 1024^2).  The matrix-core windows below, with dense tiles shared
 // between items, are faster still (121 us; the whole PSF 242 us against 285, and 395 before), but they round the PSF differently (by 1.7e-7), and an
 // ill-conditioned CG solve with it amplifies that a thousandfold.
 constexpr int kRunMax = 31;
@@ -853,13 +853,12 @@ __global__ __launch_bounds__(kTileThreads) void spread_run_kernel(SpreadLaunch a
         atomicAdd(sum + row * T + c, f2fix(acc));
     };
     // software pipeline: the records and weights of the batches after this one are loaded
-    // while it is being accumulated
-    auto load_rec = [&](int64_t eb) {
-        Rec<R> r{R(0), R(0), R(0), 0u};
-        if (eb < e_end) r = recs[eb];
-        return r;
-    };
-    auto load_val = [&](int64_t eb) { return eb < e_end ? omega[eb] * fscale : R(0); };
+    // while it is being accumulated; indices are clamped to the wave's last entry (tiles
+    // without entries have no item) and weights scaled at their use, so that no branch or
+    // product waits for the loads in flight
+    const int64_t e_last = max(e_end - 1, b0);
+    auto load_rec = [&](int64_t eb) { return recs[min(eb, e_last)]; };
+    auto load_val = [&](int64_t eb) { return omega[min(eb, e_last)]; };
     Rec<R> rec_c = load_rec(e_beg + ls);
     R val_c = load_val(e_beg + ls);
     Rec<R> rec_n = load_rec(e_beg + 8 + ls);
@@ -879,6 +878,7 @@ __global__ __launch_bounds__(kTileThreads) void spread_run_kernel(SpreadLaunch a
                 pv = es_kernel_fast(R(j0 + lj) - rec_c.fv, beta2, inv_hw);
             }
         }
+        const R val = val_c * fscale;
         // all shuffles of the batch first (one LDS round trip), then accumulate
         R wgt[8];
 #pragma unroll
@@ -894,7 +894,7 @@ __global__ __launch_bounds__(kTileThreads) void spread_run_kernel(SpreadLaunch a
                     run = 0;
                 }
                 ++run;
-                acc = __builtin_fmaf(rdlane(val_c, t * 8), wgt[t], acc);
+                acc = __builtin_fmaf(rdlane(val, t * 8), wgt[t], acc);
             }
         }
         rec_c = rec_n;
