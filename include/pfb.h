@@ -118,10 +118,11 @@ typedef struct {
     int32_t band_batch;   /* bands whose w-planes are resident at once; default n_band       */
     int32_t chunk;        /* bucket entries per work item (>= 64).  FP32: a tile of more is
                              split by w-planes for the spread, by entries for the
-                             interpolation.  FP64: more entries of a tile than this are
-                             shared between items (its own choice where that is less, or
-                             where the workspace holds no more shares).  0: by the job's
-                             entries per tile and the device's compute units                */
+                             interpolation.  FP64, and FP32 flat with tiles of up to 16:
+                             more entries of a tile than this are shared between items (its
+                             own choice where that is less, or where the workspace holds no
+                             more shares).  0: by the job's entries per tile and the
+                             device's compute units                                         */
     double  epsilon;      /* requested relative accuracy of grid / degrid (rel-l2); when
                              support is 0 and epsilon > 0 the support is the smallest W whose
                              tabulated error of the 3-D ES product kernel at sigma = 2 plus

@@ -813,11 +813,15 @@ pfb_status count_and_layout(pfb_plan *P, char *tmp, hipStream_t stream) {
         // at least a batch of 64 entries; in a tile of several blocks a wave takes about
         // one entry of n_sub; the FP32 PSF's spread does not share)
         const int64_t n_sub = (int64_t)(G->g.T + G->g.W - 1) * (G->g.T + G->g.W - 1) / ((7 + G->g.W) * (7 + G->g.W));
-        // FP64 takes a given chunk as a bound of the share: an unshared tile of many entries
-        // would be one wave's work (128^2, 1.4e6 visibilities, chunk 65536: 36 ms, shared 1.2)
+        // FP64, and FP32 flat with small tiles (blocks of four waves, of which a unit holds
+        // eight, with next to no cost but their entries), take a given chunk as a bound of
+        // the share: an unshared tile of many entries would be few waves' work (FP64 128^2,
+        // 1.4e6 visibilities, chunk 65536: 36 ms, shared 1.2)
+        const bool small_flat = !dbl && G->g.flat && G->g.T <= 16;
         int64_t share = 0;
-        if (dbl) {
-            share = n_sub * std::max<int64_t>(64, acc / (32 * (int64_t)n_cu));
+        if (dbl || (small_flat && G == &M)) {
+            share = dbl ? n_sub * std::max<int64_t>(64, acc / (32 * (int64_t)n_cu))
+                        : std::max<int64_t>(256, acc / (16 * (int64_t)n_cu));
             if (opt.chunk) share = std::min<int64_t>(share, opt.chunk);
         } else if (!opt.chunk && G == &M) {
             share = std::max<int64_t>(256, unit);

@@ -941,7 +941,8 @@ __global__ __launch_bounds__(kTileThreads) void spread_run_kernel(SpreadLaunch a
 // (1.6e6 visibilities at 1024^2: dirty image 144 against 134 us).
 template <bool FLAT> constexpr int kMfmaRunMax = FLAT ? 28 : kSumMax;
 template <bool FLAT> constexpr float kMfmaScale = FLAT ? 67108864.0f : 16777216.0f;
-constexpr int kMfmaThreads = 1024;              // 16 waves (at most 128 registers per lane)
+// 16 waves (at most 128 registers per lane); four for tiles of 8 or 16 cells a side (flat)
+constexpr int mfma_threads(int tc) { return tc == 8 || tc == 16 ? 256 : 1024; }
 template <int W, bool FLAT> struct MfmaWin {
     static constexpr int R = FLAT ? 16 : 8;     // window rows
     static constexpr int RB = R - W + 1;        // base rows per window
@@ -975,17 +976,19 @@ __device__ __forceinline__ int64_t rfl64(int64_t v) {
 }
 
 // TC: the tile side as a compile-time constant (LDS offsets become immediates), or
-// 0 to take it from the launch arguments.  SHARES: the work list holds tiles shared
+// 0 to take it from the launch arguments.  8 and 16 (flat): four waves, since so small a
+// tile hardly has work for sixteen, of which a CU holds two blocks only (1.6e5
+// visibilities at 2048^2, T = 8: 766 -> 147 us, T = 16: 265 -> 61).  SHARES: the work list holds tiles shared
 // between items (a kernel of its own: tests of the item's kind inside this one made
 // short buckets of whole tiles take 8 % longer)
 template <int W, int VMODE, int TC, bool FLAT, bool SHARES>
-__global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch a) {
+__global__ __launch_bounds__(mfma_threads(TC)) void spread_mfma_kernel(SpreadLaunch a) {
     using R_ = float;
     using A = unsigned long long;
     using Win = MfmaWin<W, FLAT>;
     constexpr int RB = Win::RB, CB = Win::CB, NT = Win::NT, WR = Win::R;
     constexpr int WW = FLAT ? 1 : W;            // planes of the ring
-    constexpr int NWAVE = kMfmaThreads / 64;
+    constexpr int NTHR = mfma_threads(TC), NWAVE = NTHR / 64;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int T = TC ? TC : a.g.T, TT = T * T, TS = run_slot_stride(T, FLAT);
     A *sre = reinterpret_cast<A *>(smem_raw);
@@ -1008,8 +1011,8 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
     // bucket offsets of those base planes: entries of base plane q are
     // soff[q - qstart] .. soff[q - qstart + 1] - 1
     int64_t *soff = reinterpret_cast<int64_t *>(sim + WW * TS);
-    for (int k = threadIdx.x; k < 2 * WW * TS; k += kMfmaThreads) sre[k] = A(0);
-    for (int k = threadIdx.x; k <= qlast - qstart; k += kMfmaThreads) soff[k] = a.offsets[keybase + qstart + k];
+    for (int k = threadIdx.x; k < 2 * WW * TS; k += NTHR) sre[k] = A(0);
+    for (int k = threadIdx.x; k <= qlast - qstart; k += NTHR) soff[k] = a.offsets[keybase + qstart + k];
     __syncthreads();
 
     const int lane = threadIdx.x & 63;
@@ -1296,16 +1299,16 @@ __global__ __launch_bounds__(kMfmaThreads) void spread_mfma_kernel(SpreadLaunch 
             // this share's sums to the tile's scratch planes: integers, so their order is free
             A *const sc = reinterpret_cast<A *>(a.scratch) + 2 * ((size_t)wk.slot * a.g.nwmax + q) * TT;
             if (q >= wk.p0)
-                for (int k = threadIdx.x; k < TT; k += kMfmaThreads) {
+                for (int k = threadIdx.x; k < TT; k += NTHR) {
                     const A re = sre[slot * TS + k], im = sim[slot * TS + k];
                     if (re) atomicAdd(sc + 2 * k, re);
                     if (im) atomicAdd(sc + 2 * k + 1, im);
                 }
         } else if (q >= wk.p0) {
-            for (int k = threadIdx.x; k < TT; k += kMfmaThreads) write_cell(k / T, k - k / T * T);
+            for (int k = threadIdx.x; k < TT; k += NTHR) write_cell(k / T, k - k / T * T);
         }
         if (q + 1 >= wk.p1) break;   // the last plane's slot is not used again
-        for (int k = threadIdx.x; k < TT; k += kMfmaThreads) clear_cell(k);
+        for (int k = threadIdx.x; k < TT; k += NTHR) clear_cell(k);
         __syncthreads();
     }
 }
@@ -1597,15 +1600,22 @@ static hipError_t spread_mfma_w(const SpreadLaunch &a, hipStream_t s) {
     const size_t lds = 2 * (size_t)(FLAT ? 1 : W) * run_slot_stride(a.g.T, FLAT) * sizeof(unsigned long long) +
                        ((size_t)a.g.nj0max + 1) * sizeof(int64_t);
     if (!FLAT && !a.phase) return hipErrorInvalidValue;
+    constexpr int T8 = FLAT ? 8 : 0, T16 = FLAT ? 16 : 0;   // small tiles with kernels of their own
+#define SPREAD_MFMA_LAUNCH(VM, TC, SHARES) \
+    PFB_LAUNCH_NT((spread_mfma_kernel<W, VM, TC, FLAT, SHARES>), a.n_work, mfma_threads(TC), lds, s, a)
 #define SPREAD_MFMA_CASE(VM)                                                                             \
     if (a.vmode == VM) {                                                                                 \
         if (a.n_shared > 0) {                                                                            \
-            if (a.g.T == 32) PFB_LAUNCH_NT((spread_mfma_kernel<W, VM, 32, FLAT, true>), a.n_work, kMfmaThreads, lds, s, a); \
-            else PFB_LAUNCH_NT((spread_mfma_kernel<W, VM, 0, FLAT, true>), a.n_work, kMfmaThreads, lds, s, a); \
-            return sum_shared_tiles<float>(a, kMfmaScale<FLAT>, s);                                            \
+            if (a.g.T == 32) SPREAD_MFMA_LAUNCH(VM, 32, true);                                           \
+            else if (a.g.T == T8) SPREAD_MFMA_LAUNCH(VM, T8, true);  \
+            else if (a.g.T == T16) SPREAD_MFMA_LAUNCH(VM, T16, true);                                      \
+            else SPREAD_MFMA_LAUNCH(VM, 0, true);                                                        \
+            return sum_shared_tiles<float>(a, kMfmaScale<FLAT>, s);                                      \
         }                                                                                                \
-        if (a.g.T == 32) PFB_LAUNCH_NT((spread_mfma_kernel<W, VM, 32, FLAT, false>), a.n_work, kMfmaThreads, lds, s, a); \
-        else PFB_LAUNCH_NT((spread_mfma_kernel<W, VM, 0, FLAT, false>), a.n_work, kMfmaThreads, lds, s, a); \
+        if (a.g.T == 32) SPREAD_MFMA_LAUNCH(VM, 32, false);                                              \
+        else if (a.g.T == T8) SPREAD_MFMA_LAUNCH(VM, T8, false);  \
+            else if (a.g.T == T16) SPREAD_MFMA_LAUNCH(VM, T16, false);                                         \
+        else SPREAD_MFMA_LAUNCH(VM, 0, false);                                                           \
         return hipSuccess;                                                                               \
     }
     SPREAD_MFMA_CASE(0)
@@ -1614,6 +1624,7 @@ static hipError_t spread_mfma_w(const SpreadLaunch &a, hipStream_t s) {
         SPREAD_MFMA_CASE(1)
     }
 #undef SPREAD_MFMA_CASE
+#undef SPREAD_MFMA_LAUNCH
     return hipErrorInvalidValue;
 }
 

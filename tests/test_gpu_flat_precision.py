@@ -49,3 +49,28 @@ def test_long_runs_of_one_window(n_row):
     vis = np.full((n_row, 1), 1.0 - 1.0j)
     plan = make_plan(prob, "fp32", flat=True)
     assert rel(host(plan.grid(to_dev(vis, torch.complex64))), oracle.grid(prob, vis, flat=True)) < 1e-5
+
+
+@pytest.mark.parametrize("tile", [8, 16])
+@pytest.mark.parametrize("support", [4, 7, 8])
+@pytest.mark.parametrize("n_row,chunk", [(5, 0), (3000, 0), (3000, 64), (60000, 0), (60000, 1 << 20)])
+def test_small_tiles_of_four_waves(tile, support, n_row, chunk):
+    """Flat tiles of 8 and 16 cells, sparse, dense and shared between items, every support
+    class; a given chunk bounds the shares (the default's where it is larger: same bits)."""
+    import torch
+    prob = synth.tiny_problem(seed=363, nx=64, ny=96, n_row=n_row, freqs=(1.0e9, 1.2e9), cell_arcsec=30.0, w_frac=0.0,
+                              flag_frac=0.1)
+    rng = np.random.default_rng(364)
+    prob.uvw[n_row // 4:, :2] *= 0.2
+    vis = rng.normal(size=(n_row, 2)) + 1j * rng.normal(size=(n_row, 2))
+    x = rng.normal(size=(1, 64, 96))
+    plan = make_plan(prob, "fp32", tile=tile, support=support, flat=True, chunk=chunk)
+    got = [host(plan.grid(to_dev(vis, torch.complex64))).copy() for _ in range(2)]
+    pix = rng.choice(64 * 96, 50, replace=False)
+    tol = {4: 5e-3, 7: 1e-5, 8: 1e-5}[support]
+    assert rel(got[0].ravel()[pix], oracle.grid(prob, vis, pix=pix, flat=True)) < tol
+    assert rel(host(plan.hessian(to_dev(x, torch.float32))).ravel()[pix], oracle.hessian(prob, x, pix=pix, flat=True)) < tol
+    assert np.array_equal(got[0], got[1])
+    if chunk == 1 << 20:
+        default = make_plan(prob, "fp32", tile=tile, support=support, flat=True)
+        assert np.array_equal(got[0], host(default.grid(to_dev(vis, torch.complex64))))
