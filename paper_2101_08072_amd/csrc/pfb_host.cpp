@@ -1719,24 +1719,22 @@ WaveletFilter db_filter(int n) {
     return table[n];
 }
 
-// element offsets (in reals) of the prox workspace: v, coef, then six image buffers
+// byte offsets in the prox workspace: v, then six image buffers, two of them at a (the
+// wavelets' low-pass blocks)
 struct ProxLayout {
     int64_t NP;          // n_band * nx * ny
-    size_t v, coef, d, c, u, sv, a, b, z, total;   // bytes
+    size_t v, d, c, u, a, z, total;
 };
 ProxLayout prox_layout(const pfb_plan *P, int nbasis) {
     ProxLayout L{};
     L.NP = (int64_t)P->prob.n_band * P->prob.nx * P->prob.ny;
     const size_t img = (size_t)L.NP * P->rsz;
     L.v = 0;
-    L.coef = L.v + (size_t)nbasis * img;
-    L.d = L.coef + (size_t)(nbasis - 1) * img;
+    L.d = L.v + (size_t)nbasis * img;
     L.c = L.d + img;
     L.u = L.c + img;
-    L.sv = L.u + img;
-    L.a = L.sv + img;
-    L.b = L.a + img;
-    L.z = L.b + img;      // forward-step result of pfb_fb_step_wavelet
+    L.a = L.u + img;
+    L.z = L.a + 2 * img;  // forward-step result of pfb_fb_step_wavelet
     L.total = L.z + img;
     return L;
 }

@@ -34,7 +34,7 @@ struct BandDev {
 
 // Spread work item: tile `tile` of band `band`, storing planes [p0, p1).  nshare > 1: the
 // item takes the share-th of nshare equal runs of every bucket, and its sums go to the
-// scratch tile `slot` (see SpreadLaunch::shares).
+// scratch tile `slot` (see SpreadLaunch::scratch).
 struct GridWork {
     int band, tile, p0, p1, share, nshare, slot;
 };

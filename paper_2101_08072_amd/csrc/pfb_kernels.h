@@ -64,13 +64,13 @@ struct SpreadLaunch {
     const BandDev *bands;
     const GridWork *work;
     int n_work;
+    const GridWork *cwork;  // FP32 w-stacked: tiles of at most kCellsMax entries, whole, for the
+    int n_cwork;            // kernel whose lanes own cells
     // tiles whose entries several items share (a dense tile would hold one compute unit
     // long after the others are done): scratch tile k holds planes [nwmax][T T] of 64-bit
     // fixed-point (re, im) pairs that the items add to (FP32: exact, in any order; zero
     // between launches), or of complex values stored by one share (FP64); a kernel after
     // the spread sums them into the planes
-    const GridWork *cwork;  // FP32 w-stacked: tiles of at most kCellsMax entries, whole, for the
-    int n_cwork;            // kernel whose lanes own cells
     const SharedTile *shared;
     int n_shared;
     void *scratch;
@@ -80,7 +80,7 @@ struct SpreadLaunch {
     const void *vis;      // VMODE 0: caller visibilities; VMODE 2: values in home-list order
     void *planes;         // [band_batch][nwmax][gx][gy]
     int band0;
-    int vmode;            // 0 data, 1 unit visibilities, 2 precomputed values
+    int vmode;            // 0 data, 1 unit visibilities (one plane: the PSF), 2 precomputed values
     const float *absmax;  // FP32 path: device scalar, max |z| over active visibilities
     const void *phase;    // FP32 w-stacked gridder: exp(2 pi i s_c w) per entry
     const uint32_t *home_pos;  // VMODE 2: per entry, the home-list position of its visibility
@@ -88,7 +88,10 @@ struct SpreadLaunch {
 // Window of the MFMA spread for support W (4..8): footprints whose base cells lie
 // in a block of rb rows x cb columns share one accumulator tile.
 void mfma_window(int W, bool flat, int *rb, int *cb);
-// LDS bytes per block of the spread and interpolation kernels (the larger)
+// Bytes that bound the tile a plan may ask for: a ring of W planes (one, flat) of the tile
+// and of its halo.  FP32: the larger is the LDS of the spread or interpolation block.
+// FP64: as if those kernels kept such rings, though they hold less (tiles refused here
+// are not supported)
 size_t gridder_lds_bytes(bool dbl, int W, int T, bool flat);
 constexpr size_t kMaxLdsBytes = 160 * 1024;
 hipError_t launch_spread(bool dbl, const SpreadLaunch &a, hipStream_t s);

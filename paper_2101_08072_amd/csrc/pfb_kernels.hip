@@ -1066,8 +1066,6 @@ __global__ __launch_bounds__(mfma_threads(TC)) void spread_mfma_kernel(SpreadLau
             raw.z = vis[rr.idx & ~kHomeBit];
             if (!FLAT) raw.ph = phase[ec];
             raw.om = omega[ec];
-        } else if (VMODE == 1) {
-            raw.om = omega[ec];
         } else {
             raw.z = vis[hp];
         }
@@ -1076,7 +1074,6 @@ __global__ __launch_bounds__(mfma_threads(TC)) void spread_mfma_kernel(SpreadLau
     auto make_val = [&](const RawVal &raw, const Rec<R_> &rr) {
         if (VMODE == 0 && FLAT) return raw.z * (raw.om * fscale);
         if (VMODE == 0) return entry_conj(rr, raw.z) * raw.ph * (raw.om * fscale);
-        if (VMODE == 1) return cplx<R_>{raw.om * fscale, R_(0)};
         return raw.z * fscale;
     };
     auto load_hp = [&](int64_t ei, int64_t bend) { return VMODE == 2 ? a.home_pos[clampi(ei, bend)] : 0u; };
@@ -1380,7 +1377,6 @@ __global__ __launch_bounds__(1024, 8) void spread_cells_kernel(SpreadLaunch a) {
         const Rec<R> rec = recs[e];
         cplx<R> z;
         if (VMODE == 0) z = entry_conj(rec, vis[rec.idx & ~kHomeBit]) * phase[e] * (omega[e] * fscale);
-        else if (VMODE == 1) z = cplx<R>{omega[e] * fscale, R(0)};
         else z = vis[a.home_pos[e]] * fscale;
         efu[k] = rec.fu;
         efv[k] = rec.fv;
@@ -1468,8 +1464,8 @@ template <int W> static hipError_t spread_cells_w(const SpreadLaunch &a, hipStre
     const size_t lds = (size_t)kCellsMax * 20 + (size_t)nthr * (sizeof(float) + W * sizeof(cplx<float>)) +
                        ((size_t)a.g.nj0max + 1) * sizeof(int);
     if (a.vmode == 0) PFB_LAUNCH_NT((spread_cells_kernel<W, 0>), a.n_cwork, nthr, lds, s, a);
-    else if (a.vmode == 1) PFB_LAUNCH_NT((spread_cells_kernel<W, 1>), a.n_cwork, nthr, lds, s, a);
-    else PFB_LAUNCH_NT((spread_cells_kernel<W, 2>), a.n_cwork, nthr, lds, s, a);
+    else if (a.vmode == 2) PFB_LAUNCH_NT((spread_cells_kernel<W, 2>), a.n_cwork, nthr, lds, s, a);
+    else return hipErrorInvalidValue;
     return hipSuccess;
 }
 
@@ -1585,7 +1581,6 @@ static hipError_t spread64_w(const SpreadLaunch &a, hipStream_t s) {
         return sum_shared_tiles<double>(a, 1.f, s);                                                               \
     }
     SPREAD_CASE(false, 0)
-    SPREAD_CASE(false, 1)
     SPREAD_CASE(false, 2)
     SPREAD_CASE(true, 0)
     SPREAD_CASE(true, 1)
@@ -1620,9 +1615,6 @@ static hipError_t spread_mfma_w(const SpreadLaunch &a, hipStream_t s) {
     }
     SPREAD_MFMA_CASE(0)
     SPREAD_MFMA_CASE(2)
-    if constexpr (!FLAT) {
-        SPREAD_MFMA_CASE(1)
-    }
 #undef SPREAD_MFMA_CASE
 #undef SPREAD_MFMA_LAUNCH
     return hipErrorInvalidValue;
