@@ -552,7 +552,7 @@ pfb_status cg_solve(pfb_plan *P, const void *g, void *y, double sigma, int iters
     const int64_t Pn = (int64_t)P->prob.nx * P->prob.ny;
     char *v = reinterpret_cast<char *>(P->p(P->o_vec));
     void *r = v, *p = v + P->vec_bytes, *ap = v + 2 * P->vec_bytes;
-    const int vparts = vec_partials_per_band(Pn);
+    const int vparts = vec_partials_per_band(Pn, nb);
     const int cparts = conv_partials_per_band(d, ca);
     // few blocks: the kernels reduce their own partials (no reduce launches)
     unsigned *const ctr = reinterpret_cast<unsigned *>(P->p(P->o_ctr));
@@ -930,7 +930,7 @@ pfb_status count_and_layout(pfb_plan *P, char *tmp, hipStream_t stream) {
         ca.ny = pr.ny;
         ca.lx = P->conv_lx;
         ca.ly = P->conv_ly;
-        P->max_partials = std::max(vec_partials_per_band((int64_t)Pimg), conv_partials_per_band(dbl, ca));
+        P->max_partials = std::max(vec_partials_per_band((int64_t)Pimg, nb), conv_partials_per_band(dbl, ca));
     }
     P->o_partials = L.take((size_t)nb * P->max_partials * sizeof(double));
     P->o_scal = L.take((size_t)nb * 8 * sizeof(double));
@@ -1575,7 +1575,7 @@ pfb_status pfb_power_iteration(pfb_plan *P, int op, const void *v0, int iters, d
     const int64_t Pn = (int64_t)P->prob.nx * P->prob.ny;
     char *v = reinterpret_cast<char *>(P->p(P->o_vec));
     void *wa = v + 3 * P->vec_bytes, *wb = v + 4 * P->vec_bytes, *tmp = v + 5 * P->vec_bytes;
-    const int vparts = vec_partials_per_band(Pn);
+    const int vparts = vec_partials_per_band(Pn, nb);
     const int cparts = conv_partials_per_band(d, ca);
     const void *src = v0;
     LAUNCH_OK(launch_vec(d, VEC_NORM, nb, Pn, ca.partials, ca.max_partials, ca.scal, const_cast<void *>(src), nullptr,

@@ -179,9 +179,12 @@ struct ConvArgs {
     unsigned *ctr;             // non-null: the partials' kernel reduces them itself (red_op)
     int red_op;
 };
-// most blocks (over all bands) of a kernel that reduces its own partials: more than the
-// chip holds at once, and the counting at every block's end costs more than a launch
-constexpr int kFuseReduceBlocks = 1024;
+// most blocks (over all bands) of a kernel that reduces its own partials.  Every block then
+// waits for its count, and the last one reads all partials across the XCDs, which soon
+// costs more than a launch.  A step of 10 CG iterations, in the kernels against by
+// launches: 64^2 210 against 223 us, 128^2 234 against 237, but 256^2 247 against 238,
+// 512^2 347 against 303, 4 x 512^2 623 against 478.
+constexpr int kFuseReduceBlocks = 64;
 enum ConvIn { CONV_IN_X = 0, CONV_IN_CG_P = 1, CONV_IN_SCALED = 2 };
 enum ConvOut { CONV_OUT_Y = 0, CONV_OUT_SUB = 1, CONV_OUT_CG = 2, CONV_OUT_NORM = 3, CONV_OUT_DOT = 4 };
 // y = PSF * x with optional fused prologue / epilogue:
@@ -212,7 +215,7 @@ enum VecOp {
 hipError_t launch_vec(bool dbl, int op, int n_band, int64_t P, double *partials, int max_partials,
                       double *scal, void *x, void *y, void *r, void *p, const void *ap,
                       double gamma, double lam, hipStream_t s, unsigned *ctr = nullptr, int red_op = 0);
-int vec_partials_per_band(int64_t P);
+int vec_partials_per_band(int64_t P, int n_band);
 
 // scalar slots in scal[b*8 + k]
 enum Slot { S_RR = 0, S_ALPHA = 1, S_BETA = 2, S_PAP = 3, S_SCALE = 4, S_LAMBDA = 5, S_TMP = 6, S_RR0 = 7 };

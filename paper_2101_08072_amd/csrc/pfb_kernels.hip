@@ -3363,17 +3363,21 @@ hipError_t launch_psfhat(bool dbl, const ConvArgs &a, const void *psf_img, hipSt
 // ---------------------------------------------------------------------------
 // vector kernels and device-side scalar reductions
 // ---------------------------------------------------------------------------
-// Elements per thread of a small image: one 16-byte access per array.  One element at a
-// time, a thread's eight loads each waited for the store before them (the arrays may
-// alias for the compiler): a forward-backward step of 512^2 707 -> 659 us.  Large images
-// keep one element per access, which streams better there (4 x 4096^2: 6.2 against
-// 6.9 ms for 22 updates).
-constexpr int kVecPerThread = 4;
+// Elements per thread and access.  Few blocks (four elements per thread, kVecFewBlocks over
+// all bands): one 16-byte access per array.  One element at a time, a thread's eight
+// loads each waited for the store before them (the arrays may alias for the compiler): a
+// forward-backward step of 512^2 707 -> 659 us.  More blocks: eight elements per
+// thread, one per access, which streams better there (4 x 4096^2: 6.2 against 6.9 ms for
+// 22 updates).
+constexpr int kVecFewBlocks = 1024;
+static int64_t vec_blocks(int64_t P, int per_thread) {
+    const int64_t per = (int64_t)kThreads * per_thread;
+    return std::max<int64_t>((P + per - 1) / per, 1);
+}
+static bool vec_few(int64_t P, int n_band) { return vec_blocks(P, 4) * n_band <= kVecFewBlocks; }
 
-int vec_partials_per_band(int64_t P) {
-    const int64_t per = (int64_t)kThreads * kVecPerThread;
-    int64_t n = (P + per - 1) / per;
-    return (int)std::min<int64_t>(n, 4096);
+int vec_partials_per_band(int64_t P, int n_band) {
+    return (int)std::min<int64_t>(vec_blocks(P, vec_few(P, n_band) ? 4 : 8), 4096);
 }
 
 // V elements at a time: 16-byte accesses where every array and band start on 16 bytes, or one
@@ -3474,13 +3478,13 @@ __global__ __launch_bounds__(kThreads) void vec_kernel(int64_t P, int nblk, doub
 hipError_t launch_vec(bool dbl, int op, int n_band, int64_t P, double *partials, int max_partials,
                       double *scal, void *x, void *y, void *r, void *p, const void *ap, double gamma,
                       double lam, hipStream_t s, unsigned *ctr, int red_op) {
-    const int nblk = vec_partials_per_band(P);
+    const int nblk = vec_partials_per_band(P, n_band);
     const int nb = n_band * nblk;
     // 16-byte accesses: the arrays that the operation has, and every band of them
     const uintptr_t bits = reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(y) |
                            reinterpret_cast<uintptr_t>(r) | reinterpret_cast<uintptr_t>(p) |
                            reinterpret_cast<uintptr_t>(ap) | ((uintptr_t)P * (dbl ? 8 : 4));
-    const bool vec = (bits & 15) == 0 && nb <= kFuseReduceBlocks;
+    const bool vec = (bits & 15) == 0 && vec_few(P, n_band);
 #define VEC_LAUNCH(T, OPV, V, FUSE)                                                                         \
     PFB_LAUNCH((vec_kernel<T, OPV, V, FUSE>), nb, 0, s, P, nblk, partials, max_partials, scal, (T *)x, (T *)y, (T *)r, \
                (T *)p, (const T *)ap, (T)gamma, (T)lam, ctr, red_op)

@@ -46,3 +46,24 @@ def test_interpolation_form(n_row, prec, kernel):
     names = plan.profile_report()
     plan.profile(False)
     assert [k for k in names if k.startswith("interp")] == [kernel], names
+
+
+@pytest.mark.parametrize("nx,ny,n_band,in_kernels", [(32, 32, 1, True), (64, 64, 1, True), (256, 256, 2, False),
+                                                     (512, 512, 4, False)])
+def test_cg_sums_by_launch_where_there_are_many_blocks(nx, ny, n_band, in_kernels):
+    import torch
+    prob = synth.tiny_problem(seed=406, nx=nx, ny=ny, n_row=300, freqs=np.linspace(1.0e9, 1.4e9, n_band), cell_arcsec=20.0,
+                              n_band=n_band)
+    plan = make_plan(prob)
+    psf = host(plan.make_psf()).astype(np.float64)
+    x = np.random.default_rng(407).normal(size=(n_band, nx, ny))
+    conv = oracle.psf_conv_op(psf)
+    sigma = 0.3 * float(np.abs(np.fft.rfft2(psf)).max())
+    plan.profile(True)
+    y = plan.precond_solve(to_dev(x, torch.float32), sigma, 5)
+    names = plan.profile_report()
+    plan.profile(False)
+    assert names.get("reduce_kernel", (0, 0))[0] == (0 if in_kernels else 1 + 2 * 5)
+    for b in range(n_band):
+        want = oracle.cg(lambda v: conv.band(b, v) + sigma * v, x[b], 5)[0]
+        assert rel(host(y)[b], want) < 10 * TOL["fp32"]
