@@ -169,6 +169,7 @@ struct GridderHost {
     std::vector<int> occ_list_start, need_list_start;
     bool mfma = false;                   // FP32 w-stacked gridder: phase table of the entries
     int sort_rb = 1, sort_cb = 1;        // sort blocks of base rows x columns
+    bool wide = false;                   // FP64 flat spread: blocks of four waves
     bool istream = false;                // interpolation items of the kernel for few entries per tile
     std::vector<GridWork> cwork;         // FP32: tiles of few entries, for the spread whose lanes own cells
     std::vector<int> cband_start;        // per band first of them (n_band + 1)
@@ -501,6 +502,7 @@ SpreadLaunch spread_args(const pfb_plan *P, const GridderHost &G, int b0, int nb
     s.shared = G.d_shared + G.shared_start[b0];
     s.n_shared = G.shared_start[b0 + nbb] - G.shared_start[b0];
     s.scratch = G.d_scratch;
+    s.wide = G.wide;
     s.occ = G.d_occ;
     s.offsets = G.d_offsets;
     s.recs = G.d_recs;
@@ -810,17 +812,20 @@ pfb_status count_and_layout(pfb_plan *P, char *tmp, hipStream_t stream) {
         const int ichunk = G->istream ? (dbl ? kStreamEntries<double> : kStreamEntries<float>) : opt.chunk ? opt.chunk : (int)std::min<int64_t>(std::max<int64_t>(1024, unit / 3), chunk);
         // (FP64 items are single waves for each 8 x 8 block of the tile, of which a unit
         // holds sixteen: half their share, so that the densest unshared tile is no tail, and
-        // at least a batch of 64 entries; in a tile of several blocks a wave takes about
-        // one entry of n_sub; the FP32 PSF's spread does not share)
+        // at least a batch of 64 entries, or in blocks of four waves 32 each; in a tile of
+        // several blocks a wave takes about one entry of n_sub; the FP32 PSF's spread does
+        // not share)
         const int64_t n_sub = (int64_t)(G->g.T + G->g.W - 1) * (G->g.T + G->g.W - 1) / ((7 + G->g.W) * (7 + G->g.W));
         // FP64, and FP32 flat with small tiles (blocks of four waves, of which a unit holds
         // eight, with next to no cost but their entries), take a given chunk as a bound of
         // the share: an unshared tile of many entries would be few waves' work (FP64 128^2,
         // 1.4e6 visibilities, chunk 65536: 36 ms, shared 1.2)
         const bool small_flat = !dbl && G->g.flat && G->g.T <= 16;
+        G->wide = dbl && G->g.flat && tiles * (G->g.T / 8) * (G->g.T / 8) <= 8 * (int64_t)n_cu;
         int64_t share = 0;
         if (dbl || (small_flat && G == &M)) {
-            share = dbl ? n_sub * std::max<int64_t>(64, acc / (32 * (int64_t)n_cu))
+            share = dbl ? n_sub * (G->wide ? std::max<int64_t>(128, acc / (8 * (int64_t)n_cu))
+                                           : std::max<int64_t>(64, acc / (32 * (int64_t)n_cu)))
                         : std::max<int64_t>(256, acc / (16 * (int64_t)n_cu));
             if (opt.chunk) share = std::min<int64_t>(share, opt.chunk);
         } else if (!opt.chunk && G == &M) {

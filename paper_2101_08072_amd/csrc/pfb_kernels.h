@@ -74,6 +74,7 @@ struct SpreadLaunch {
     const SharedTile *shared;
     int n_shared;
     void *scratch;
+    int wide;             // FP64 flat: blocks of four waves
     const uint8_t *occ;   // as XformArgs::occ: planes of a tile that the spread writes
     const int64_t *offsets;
     const void *recs, *omega;

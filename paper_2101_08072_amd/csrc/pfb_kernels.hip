@@ -588,18 +588,23 @@ __device__ __forceinline__ void fixed_point_scale(float am, float S, float &fsca
 // at a time (four where there is one plane), 8 + 8 + W lanes each (8 + 8) evaluate one
 // 1-D weight (the ES kernel's FP64 square root and exponential are the costly part: once
 // per weight, not once per lane and weight), and every lane adds z U V P[k] to its planes.  After base plane q, plane q is
-// complete and is written.  A block is one wave: one 8 x 8 block of an item's tile
+// complete and is written.  A block is one wave, or four where there is one plane and few
+// blocks (SpreadLaunch::wide), each with a quarter of the item's entries and their sums
+// added at the end (a PSF of 64^2 with 1000 visibilities 42 -> 31 us, one wave's chain
+// having been most of the kernel; at 1024^2 with 32256 in many tiles 189 -> 241, so not
+// there): one 8 x 8 block of an item's tile
 // (larger tiles than the default of 8 have several, whose waves each read the item's
 // entries and skip the batches that do not reach them; one wave going through a tile's
 // blocks took 2960 us for 3.2e5 visibilities at 512^2, flat, T = 64, these 172).  Dense
 // tiles are shared between items, whose planes are summed in a fixed order (bitwise
 // reproducible).
-template <int W, bool FLAT> struct Spread64 {
+template <int W, bool FLAT, bool WIDE> struct Spread64 {
     static constexpr int WW = FLAT ? 1 : W;
     static constexpr int ENT = 5;                        // fu, fv, fw, Re z, Im z
     static constexpr int PER = FLAT ? 4 : 2;             // entries whose weights the lanes evaluate together
     static constexpr int WAVE = 64 * ENT + 64;           // doubles of a wave: batch, those weights
-    static constexpr size_t lds = (size_t)WAVE * sizeof(double);
+    static constexpr int NWV = WIDE ? 4 : 1;             // waves of a block
+    static constexpr size_t lds = (size_t)NWV * WAVE * sizeof(double);
 };
 // LDS writes of this wave's lanes are seen by its other lanes' later reads
 __device__ __forceinline__ void wave_lds_fence() {
@@ -608,14 +613,14 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <int W, bool FLAT, int VMODE>
-__global__ __launch_bounds__(64, 4) void spread64_kernel(SpreadLaunch a) {
-    using K = Spread64<W, FLAT>;
+template <int W, bool FLAT, int VMODE, bool WIDE>
+__global__ __launch_bounds__((64 * Spread64<W, FLAT, WIDE>::NWV), 4) void spread64_kernel(SpreadLaunch a) {
+    using K = Spread64<W, FLAT, WIDE>;
     using R = double;
-    constexpr int WW = K::WW, ENT = K::ENT, PER = K::PER, LPE = 64 / PER;
+    constexpr int WW = K::WW, ENT = K::ENT, PER = K::PER, LPE = 64 / PER, NWV = K::NWV;
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    const int lane = threadIdx.x;
-    R *const ent = reinterpret_cast<R *>(smem_raw), *const wgt = ent + 64 * ENT;
+    const int lane = threadIdx.x & 63, wv = NWV > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
+    R *const ent = reinterpret_cast<R *>(smem_raw) + wv * K::WAVE, *const wgt = ent + 64 * ENT;
     const int T = a.g.T, nsub = T / 8;                   // 8 x 8 blocks per tile side
     const int sub = blockIdx.x % (nsub * nsub);
     const GridWork wk = a.work[blockIdx.x / (nsub * nsub)];
@@ -646,7 +651,9 @@ __global__ __launch_bounds__(64, 4) void spread64_kernel(SpreadLaunch a) {
             b0 = a.offsets[keybase + q];
             n = a.offsets[keybase + q + 1] - b0;
         }
-        const int64_t e_beg = b0 + n * wk.share / wk.nshare, e_end = b0 + n * (wk.share + 1) / wk.nshare;
+        // this wave's part of the item's run of the bucket
+        const int64_t parts = (int64_t)wk.nshare * NWV, part = (int64_t)wk.share * NWV + wv;
+        const int64_t e_beg = b0 + n * part / parts, e_end = b0 + n * (part + 1) / parts;
         const R wbase = wsel == 0 ? R(r0 + wi) : (wsel == 1 ? R(c0 + wi - 8) : R(q + wi - 16));
         for (int64_t e0 = e_beg; e0 < e_end; e0 += 64) {
             const int64_t e = min(e0 + lane, e_end - 1);
@@ -723,6 +730,16 @@ __global__ __launch_bounds__(64, 4) void spread64_kernel(SpreadLaunch a) {
         }
         are[WW - 1] = aim[WW - 1] = R(0);
         if (q < wk.p0) continue;
+        if constexpr (NWV > 1) {   // (one plane: once per block) the waves' sums, in their order
+            static_assert(FLAT && K::WAVE >= 128, "the sums take the batches' place");
+            __syncthreads();
+            cplx<R> *const sums = reinterpret_cast<cplx<R> *>(ent);
+            if (wv > 0) sums[lane] = v;
+            __syncthreads();
+            if (wv > 0) continue;
+#pragma unroll
+            for (int w = 1; w < NWV; ++w) v = v + sums[w * (K::WAVE / 2) + lane];
+        }
         if (wk.nshare > 1)
             reinterpret_cast<cplx<R> *>(a.scratch)[((size_t)(wk.slot + wk.share) * a.g.nwmax + q) * T * T +
                                                    (r0 + crow) * T + c0 + ccol] = v;
@@ -1575,16 +1592,21 @@ static hipError_t spread64_w(const SpreadLaunch &a, hipStream_t s) {
     const bool flat = a.g.flat;
     const int64_t nb = (int64_t)a.n_work * (a.g.T / 8) * (a.g.T / 8);
     if (nb > INT_MAX) return hipErrorInvalidValue;
-#define SPREAD_CASE(FL, VM)                                                                                       \
-    if (flat == FL && a.vmode == VM) {                                                                            \
-        PFB_LAUNCH_NT((spread64_kernel<W, FL, VM>), (unsigned)nb, 64, (Spread64<W, FL>::lds), s, a);              \
+#define SPREAD_CASE(FL, VM, WIDE)                                                                                 \
+    if (flat == FL && a.vmode == VM && wide == WIDE) {                                                            \
+        using K = Spread64<W, FL, WIDE>;                                                                          \
+        PFB_LAUNCH_NT((spread64_kernel<W, FL, VM, WIDE>), (unsigned)nb, 64 * K::NWV, K::lds, s, a);               \
         return sum_shared_tiles<double>(a, 1.f, s);                                                               \
     }
-    SPREAD_CASE(false, 0)
-    SPREAD_CASE(false, 2)
-    SPREAD_CASE(true, 0)
-    SPREAD_CASE(true, 1)
-    SPREAD_CASE(true, 2)
+    const bool wide = a.wide != 0;
+    SPREAD_CASE(false, 0, false)
+    SPREAD_CASE(false, 2, false)
+    SPREAD_CASE(true, 0, false)
+    SPREAD_CASE(true, 1, false)
+    SPREAD_CASE(true, 2, false)
+    SPREAD_CASE(true, 0, true)
+    SPREAD_CASE(true, 1, true)
+    SPREAD_CASE(true, 2, true)
 #undef SPREAD_CASE
     return hipErrorInvalidValue;
 }
