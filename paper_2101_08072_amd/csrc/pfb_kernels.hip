@@ -3275,10 +3275,12 @@ static hipError_t conv_columns(const ConvArgs &a, int psf, hipStream_t s) {
         const int rounds = ((a.n_band * G + 7) / 8) * 8;   // column groups, padded to the XCDs
         // few columns: the fewest per block that still fill a wave (512^2, one band: 72
         // blocks of 8 columns leave most CUs idle; the convolution 22.7 -> 19.1 us with
-        // one column per block and one row pair per row block)
+        // one column per block and one row pair per row block), up to five such blocks per
+        // CU: each fills its twiddle tables anew (1024^2, one band, 1056 blocks 21.5 ->
+        // 17.4 us, 512^2, two bands, 1088 the same, three bands, 1568 14.2 -> 15.7)
         constexpr int CS = conv_few<R, LG>();
         if constexpr (CS < CB) {
-            if (!psf && rounds * (CG / CB) < kColsFewBlocks) {
+            if (!psf && rounds * (CG / CB) < kColsFewBlocks && rounds * (CG / CS) < 1280) {
                 using K = ConvCols<R, LG, CS>;
                 PFB_LAUNCH_NT((conv_cols_kernel<R, LG, CS, CG, false>), rounds * (CG / CS), K::NT, K::lds, s, a);
                 return hipSuccess;
