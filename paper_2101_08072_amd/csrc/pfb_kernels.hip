@@ -2395,9 +2395,11 @@ __global__ __launch_bounds__(row_threads<LOG2L>(), row_min_waves<LOG2L>()) void 
 // ran on 64 blocks, 128 columns on 16.  There a block takes ONE column and C of its
 // planes at a time (the C vectors of the LDS buffer are planes, not columns); the grid
 // pass sums its C accumulators at the end.  Used below kColsFewBlocks blocks of the
-// column form (two 512-thread blocks for every CU): grid columns of 128^2, 8 planes,
-// 50 -> 12 us, degrid columns of 512^2, 9 planes, 73 -> 29 us; from there on the column
-// form fills the chip and reads whole 64-byte pieces per block.
+// column form (two 512-thread blocks for every CU), less where the last round holds few
+// planes: grid columns of 128^2, 8 planes, 50 -> 12 us, degrid columns of 512^2, 9
+// planes, 73 -> 29 us, of 15 x 256^2, 8 planes, the same; of 7 x 512^2, 9 planes, grid
+// 80 -> 105.  From there on the column form fills the chip and reads whole 64-byte
+// pieces per block.
 constexpr int kColsFewBlocks = 512;
 template <typename R, int LOG2N, int C, bool PL> struct WCols {
     static constexpr int N = 1 << LOG2N;
@@ -2793,7 +2795,9 @@ static hipError_t wcols_launch(const XformArgs &a, hipStream_t s) {
             const int G = (a.g.ny + CG - 1) / CG;
             const int rounds = ((a.n_bb * G + 7) / 8) * 8;   // column groups, padded to the XCDs
             if constexpr (C > 1) {
-                if (!a.g.flat && rounds * (CG / C) < kColsFewBlocks) {
+                // (a last round of fewer planes takes as long as a full one)
+                const int64_t padded = (int64_t)(a.g.nwmax + C - 1) / C * C;
+                if (!a.g.flat && rounds * (CG / C) * padded < (int64_t)kColsFewBlocks * a.g.nwmax) {
                     using K = WCols<R, LG, C, true>;
                     if (GRID) PFB_LAUNCH_NT((wgrid_cols_kernel<R, LG, C, true, KEEP>), rounds * CG, K::NT, K::lds, s, a);
                     else PFB_LAUNCH_NT((wdegrid_cols_kernel<R, LG, C, true>), rounds * CG, K::NT, K::lds, s, a);
