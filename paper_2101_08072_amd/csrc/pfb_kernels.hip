@@ -199,8 +199,11 @@ __device__ __forceinline__ void finish_partial(double t, int k, int n_part, doub
 }
 
 // exp(2 pi i t) of the w-plane phases.  FP32: reduced to |f| <= 1 / 8 of a turn around the
-// nearest quarter turn, exactly, then sin and cos(2 pi f) by polynomials fitted to minimax
-// (errors against 64 bits at most 5.9e-8, as the library's sincospif has); 25
+// nearest quarter turn, exactly, then sin(2 pi f) - 2 pi f and cos(2 pi f) - 1 as odd and
+// even polynomials of least maximum absolute error over |f| <= 1 / 8.  Lawson's iteration
+// (least squares, each weight multiplied by its point's error, 2e4 Chebyshev points) gives
+// these coefficients to 5e-7 of each; they leave 1.8e-9 and 1.1e-10.  In FP32 the errors
+// against 64 bits are at most 5.9e-8, as the library's sincospif has.  25
 // vector instructions where the library call took 41, of about 140 per value in the
 // column passes.
 template <typename R> __device__ __forceinline__ cplx<R> cis_plane(R t) {
@@ -829,8 +832,9 @@ __device__ __forceinline__ float es_kernel_fast(float z, float beta2, float inv_
 // truncation (relative size 2^-26).  The per-visibility quantities (1-D ES weights, value)
 // are computed for 8 visibilities at once, one per 8-lane group, then broadcast with
 // readlane / shuffles.  The values are real, so only real sums are kept: half of the LDS
-// adds that bound the kernel (258 -> 149 us for 2e6 visibilities' PSF at 1024^2).  The matrix-core windows below, with dense tiles shared
-// between items, are faster still (121 us; the whole PSF 242 us against 285, and 395 before), but they round the PSF differently (by 1.7e-7), and an
+// adds that bound the kernel (258 -> 149 us for 2e6 visibilities' PSF at 1024^2, the whole
+// PSF 397 -> 273 us).  The matrix-core windows below, with dense tiles shared between items,
+// are faster still (121 us), but they round the PSF differently (by 1.7e-7), and an
 // ill-conditioned CG solve with it amplifies that a thousandfold.
 constexpr int kRunMax = 31;
 constexpr float kRunScale = 67108864.0f;   // 2^26
@@ -1344,6 +1348,7 @@ __global__ __launch_bounds__(mfma_threads(TC)) void spread_mfma_kernel(SpreadLau
 // (two-sum) stay in the registers as the next sums' start.  Without it a run of 384
 // values rounded up to three times as much.  Rare, and in code of its own for tiles of
 // more than kSumMax entries: in the one loop its tests took 10 % of every tile's time.
+// Small jobs still pay for the larger kernel: 1.2e3 visibilities at 256 x 192 10.4 -> 10.8 us.
 // Its LDS still leaves two blocks per CU.
 template <int W, int VMODE>
 __global__ __launch_bounds__(1024, 8) void spread_cells_kernel(SpreadLaunch a) {
